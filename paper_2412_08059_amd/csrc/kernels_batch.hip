@@ -8,6 +8,7 @@
 // connected component.
 
 #include "batch_internal.hpp"
+#include "wave_ops.hpp"
 
 #include <cmath>
 
@@ -23,11 +24,7 @@ template <typename T> __device__ inline T fma_b(T a, T b, T c);
 template <> __device__ inline float fma_b<float>(float a, float b, float c) { return fmaf(a, b, c); }
 template <> __device__ inline double fma_b<double>(double a, double b, double c) { return fma(a, b, c); }
 
-__device__ inline double wave_sum_d(double v)
-{
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
+__device__ inline double wave_sum_d(double v) { return wave_sum_all(v); }
 
 __device__ inline int wave_max_i32(int v)
 {
@@ -74,11 +71,7 @@ __device__ inline double sys_sum(const BArena &a, const BSys &S, int j, double *
 }
 
 // dot_acc = 1: the FP32 phase's sums in float (partials stored widened, exact).
-__device__ inline float wave_sum_f(float v)
-{
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
+__device__ inline float wave_sum_f(float v) { return wave_sum_all(v); }
 
 __device__ inline double sys_sum_f(const BArena &a, const BSys &S, int j, double *sm)
 {
@@ -110,7 +103,7 @@ __device__ inline double sys_sum_f(const BArena &a, const BSys &S, int j, double
 // the lane's term (exact in FP64, one rounding in FP32) summed over the wave.
 __device__ inline double wave_dot32(bool f32, float x, float y)
 {
-    return f32 ? (double)wave_sum_f(x * y) : wave_sum_d((double)x * (double)y);
+    return f32 ? (double)wave_dot(x, y) : wave_dot((double)x, (double)y);
 }
 
 __device__ inline int64_t rp_at(const void *rp, int i64, int64_t i)
@@ -246,7 +239,7 @@ __device__ inline void adm_rows(const BArena &a, int32_t sys, const void *rp, in
     const int sl = slice0 + (int)(i >> 6);
     if (len > 0) atomicMax(&a.slice_w[sl], len);
     const double pr = wave_dot32(a.acc32, rv, rv);
-    const double pb = wave_sum_d(bv * bv);
+    const double pb = wave_dot(bv, bv);
     for (int o = 32; o > 0; o >>= 1) err |= __shfl_xor(err, o, 64);
     if ((threadIdx.x & 63) == 0) {
         a.pslice[2 * (size_t)sl] = pr;
@@ -597,8 +590,8 @@ __device__ inline double cg_product(const BArena &a, const BSys &S, const T *val
         }
         const T dn = dnew[row];
         q[row] = acc;
-        if (sizeof(T) == 4 && a.acc32) return (double)wave_sum_f((float)dn * (float)acc);
-        return wave_sum_d((double)dn * (double)acc);
+        if (sizeof(T) == 4 && a.acc32) return (double)wave_dot((float)dn, (float)acc);
+        return wave_dot((double)dn, (double)acc);
     }
     T acc = T(0);
     const int W = wave_max_i32(len);
@@ -636,8 +629,8 @@ __device__ inline double cg_product(const BArena &a, const BSys &S, const T *val
     const T dn = first ? r[row] : fma_b<T>(beta, dold[row], r[row]);
     dnew[row] = dn;
     q[row] = acc;
-    if (sizeof(T) == 4 && a.acc32) return (double)wave_sum_f((float)dn * (float)acc);   // already summed
-    return wave_sum_d((double)dn * (double)acc);
+    if (sizeof(T) == 4 && a.acc32) return (double)wave_dot((float)dn, (float)acc);   // already summed
+    return wave_dot((double)dn, (double)acc);
 }
 
 // Restart: r = b - A x with x = float64(x~), x, or 0; x takes that value.
@@ -676,7 +669,7 @@ __device__ inline double residual(const BArena &a, const BSys &S, bool restart, 
         else if (src == kSrcZero) a.x64[row] = 0.0;
         a.r64[row] = res;
     }
-    return res * res;
+    return wave_dot(res, res);
 }
 
 template <bool NT>
@@ -702,7 +695,7 @@ __global__ void __launch_bounds__(kBlock) k_b_product(BArena a)
     double p;
     if (mode == kCg32) p = cg_product<float, NT>(a, S, a.v32, a.r32, a.dA32, a.dB32, a.q32, base, row, len);
     else if (mode == kCg64) p = cg_product<double, NT>(a, S, a.v64, a.r64, a.dA64, a.dB64, a.q64, base, row, len);
-    else p = wave_sum_d(residual<NT>(a, S, mode == kRestart, base, row, len));
+    else p = residual<NT>(a, S, mode == kRestart, base, row, len);
     if (lane == 0) a.pslice[2 * (size_t)sl] = p;
 }
 
@@ -785,8 +778,8 @@ __device__ inline double cg_update(const BArena &a, const BSys &S, T *x, T *r, c
     x[row] = fma_b<T>(alpha, d[row], x[row]);
     const T rv = fma_b<T>(-alpha, q[row], r[row]);
     r[row] = rv;
-    if (sizeof(T) == 4 && a.acc32) return (double)wave_sum_f((float)rv * (float)rv);
-    return wave_sum_d((double)rv * (double)rv);
+    if (sizeof(T) == 4 && a.acc32) return (double)wave_dot((float)rv, (float)rv);
+    return wave_dot((double)rv, (double)rv);
 }
 
 __global__ void __launch_bounds__(kBlock) k_b_update(BArena a)

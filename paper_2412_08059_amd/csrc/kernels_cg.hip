@@ -20,45 +20,13 @@
 // product; the arithmetic of each element is unchanged.
 
 #include "mpcg_internal.hpp"
+#include "sell_common.hpp"
 
 #include <cmath>
 
 namespace mpcg {
 
 // ------------------------------------------------------------ helpers --
-
-__device__ inline double wave_sum(double v)
-{
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
-// Deterministic block sum (kBlock threads): butterfly inside each wave, then
-// wave 0..3 in order.  Valid in thread 0.
-__device__ inline double block_sum(double v, double *sm)
-{
-    v = wave_sum(v);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0) sm[w] = v;
-    __syncthreads();
-    double s = 0.0;
-    if (threadIdx.x == 0) {
-        for (int i = 0; i < kBlock / 64; ++i) s += sm[i];
-    }
-    __syncthreads();
-    return s;
-}
-
-// Block sum delivered to every thread of the block.
-__device__ inline double block_sum_all(double v, double *sm)
-{
-    double s = block_sum(v, sm);
-    if (threadIdx.x == 0) sm[kBlock / 64] = s;
-    __syncthreads();
-    s = sm[kBlock / 64];
-    __syncthreads();
-    return s;
-}
 
 // Sum of component j of cnt partials (stride doubles apart) written by the
 // previous kernel, in a fixed order; every block that calls it gets the same
@@ -79,41 +47,15 @@ __device__ inline double reduce_partials(const double *p, int cnt, int stride, i
         acc += p3;
     }
     for (; i < cnt; i += kBlock) acc += p[(size_t)i * stride + j];
-    return block_sum_all(acc, sm);
+    return block_total(acc, sm);
 }
 
-// FP32 accumulation (dot_acc = 1): the same tree in float.  Partials are
-// stored widened to double (exact) and narrowed back (exact) when reduced.
-__device__ inline float wave_sum_f(float v)
-{
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
-__device__ inline float block_sum_f(float v, double *sm)
-{
-    v = wave_sum_f(v);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0) sm[w] = (double)v;
-    __syncthreads();
-    float s = 0.0f;
-    if (threadIdx.x == 0) {
-        for (int i = 0; i < kBlock / 64; ++i) s += (float)sm[i];
-    }
-    __syncthreads();
-    return s;
-}
-
+// FP32 accumulation (dot_acc = 1): the same tree in float.
 __device__ inline double reduce_partials_f(const double *p, int cnt, int stride, int j, double *sm)
 {
     float acc = 0.0f;
     for (int i = threadIdx.x; i < cnt; i += kBlock) acc += (float)p[(size_t)i * stride + j];
-    float s = block_sum_f(acc, sm);
-    if (threadIdx.x == 0) sm[kBlock / 64] = (double)s;
-    __syncthreads();
-    const double r = sm[kBlock / 64];
-    __syncthreads();
-    return r;
+    return block_total_f(acc, sm);
 }
 
 // FP32-phase reduction in the precision dot_acc asks for.
@@ -130,10 +72,6 @@ __device__ inline int xcd_remap(int b, int nb)
     const int x = b % kNumXcd, i = b / kNumXcd;
     return x * q + (x < rem ? x : rem) + i;
 }
-
-template <typename T> __device__ inline T fmaT(T a, T b, T c);
-template <> __device__ inline float fmaT<float>(float a, float b, float c) { return fmaf(a, b, c); }
-template <> __device__ inline double fmaT<double>(double a, double b, double c) { return fma(a, b, c); }
 
 __global__ void k_cast32(const double *__restrict__ val, float *__restrict__ val32, int64_t nnz)
 {
@@ -262,9 +200,9 @@ k_init32(const double *__restrict__ b, float *__restrict__ x, float *__restrict_
             }
         }
     }
-    s0 = acc32 ? (double)block_sum_f(f0, sm) : block_sum(s0, sm);
-    s1 = block_sum(s1, sm);
-    s2 = dg ? (acc32 ? (double)block_sum_f(f2, sm) : block_sum(s2, sm)) : s0;
+    s0 = acc32 ? (double)sell_block_sum_f(f0, sm) : sell_block_sum(s0, sm);
+    s1 = sell_block_sum(s1, sm);
+    s2 = dg ? (acc32 ? (double)sell_block_sum_f(f2, sm) : sell_block_sum(s2, sm)) : s0;
     if (threadIdx.x == 0) {
         part[3 * blockIdx.x] = s0;
         part[3 * blockIdx.x + 1] = s1;
@@ -276,10 +214,10 @@ __global__ void __launch_bounds__(kBlock)
 k_fin_init32(const double *part, int cnt, double eps, int abs_tol, int32_t maxit, int32_t k0rec,
              DevState *st, int acc32)
 {
-    __shared__ double sm[kBlock / 64 + 1];
-    const double g = reduce_partials_acc(acc32, part, cnt, 3, 0, sm);
-    const double bb = reduce_partials(part, cnt, 3, 1, sm);
-    const double rho = reduce_partials_acc(acc32, part, cnt, 3, 2, sm);
+    __shared__ double sm[3][kBlock / 64];
+    const double g = reduce_partials_acc(acc32, part, cnt, 3, 0, sm[0]);
+    const double bb = reduce_partials(part, cnt, 3, 1, sm[1]);
+    const double rho = reduce_partials_acc(acc32, part, cnt, 3, 2, sm[2]);
     if (threadIdx.x == 0) {
         st->bnorm2 = bb;
         st->k0rec = k0rec;
@@ -423,65 +361,36 @@ __global__ void __launch_bounds__(kBlock) k_spmv(SpmvArgs<T> a)
     bool x_pending = false;   // x += alpha_{it-1} d_{it-1} still to apply in the main loop
     const T *dold = nullptr;
     T *dnew = nullptr;
-    const bool f32acc = MODE == kModeCg && sizeof(T) == 4 && st->acc32;   // dot_acc = 1
+    bool f32acc = false;      // dot_acc = 1
     if (MODE == kModeCg) {
+        __shared__ double sm_rho[kBlock / 64], sm_g[kBlock / 64];
         const int it = a.it;
-        __shared__ int s_skip, s_xdone;
-        if (tid == 0) {
-            s_skip = st->stop_it < it;
-            s_xdone = st->x_it == it;
-        }
-        __syncthreads();
-        if (s_skip) return;
+        const CgHead h = cg_head<T>(st, a.up, a.nup, a.pc, it, a.it0, sm_rho, sm_g);
+        if (h.skip) return;
+        f32acc = h.f32acc;
         dold = (it & 1) ? a.dB : a.dA;
         dnew = (it & 1) ? a.dA : a.dB;
         if (it != a.it0) {
-            const bool xdone = s_xdone;
-            // rho_it (alpha, beta) and gamma_it = r.r (stop test, v); equal without a preconditioner
-            const double rho = reduce_partials_acc(f32acc, a.up, a.nup, 1, 0, sm);
-            const double g = a.pc ? reduce_partials_acc(f32acc, a.up + a.nup, a.nup, 1, 0, sm) : rho;
-            const double gp = st->gr[(it - 1) & 1];
-            const double rhop = st->gam[(it - 1) & 1];
-            alpha_prev = (T)st->alph[(it - 1) & 1];
-            const bool conv = sqrt(g) <= st->thr;
-            const bool cap = !conv && it >= st->maxit;
-            if (blockIdx.x == 0 && tid == 0) {
-                st->gam[it & 1] = rho;
-                st->gr[it & 1] = g;
-                const int k = it - 1;
-                if (k < st->k0rec && k < kK0Max) st->ratios[k] = sqrt(g) / sqrt(gp);
-                if (conv || cap) {
-                    st->gamma = g;
-                    st->iter = it;
-                    st->reason = conv ? kConverged : kMaxit;
-                    st->stop_it = it;
-                    st->live = 0;
-                }
-            }
-            const unsigned cross = a.snap ? spec_crossings(st, it, g) : 0u;
-            if (conv || cap || cross) {
+            alpha_prev = (T)h.alph;
+            const bool stop = cg_head_decide(st, h, it);
+            const unsigned cross = a.snap ? spec_crossings(st, it, h.g) : 0u;
+            if (stop || cross) {
                 // the iterate x_it of this block's rows, then its run-ahead copies
                 const int lb0 = xcd_remap(blockIdx.x, gridDim.x);
                 const int r0 = (int)((int64_t)lb0 * a.ntiles / gridDim.x) * a.R;
                 const int r1 = min((int)((int64_t)(lb0 + 1) * a.ntiles / gridDim.x) * a.R, a.n);
                 for (int i = r0 + tid; i < r1; i += kBlock) {
-                    const T xn = xdone ? a.x[i] : fmaT<T>(alpha_prev, dold[i], a.x[i]);
-                    if (!xdone) a.x[i] = xn;
+                    const T xn = h.xdone ? a.x[i] : fma_t<T>(alpha_prev, dold[i], a.x[i]);
+                    if (!h.xdone) a.x[i] = xn;
                     for (int t = 0; t < kNumEps; ++t)
                         if (cross & (1u << t)) a.snap[(size_t)t * a.n + i] = xn;
                 }
-                if (blockIdx.x == 0 && tid == 0) {
-                    for (int t = 0; t < kNumEps; ++t) {
-                        if (!(cross & (1u << t))) continue;
-                        st->cross_iter[t] = it;
-                        st->cross_gamma[t] = g;
-                    }
-                }
-                if (conv || cap) return;
+                record_crossings(st, cross, it, h.g);
+                if (stop) return;
             } else {
-                x_pending = !xdone;
+                x_pending = !h.xdone;
             }
-            beta = (T)(rho / rhop);
+            beta = (T)(h.rho / h.rhop);
         }
     }
 
@@ -513,7 +422,7 @@ __global__ void __launch_bounds__(kBlock) k_spmv(SpmvArgs<T> a)
                 s_val[j] = a.val[k];
                 T g;
                 if (MODE == kModeCg) {
-                    g = fmaT<T>(beta, dold[c], a.r[c]);
+                    g = fma_t<T>(beta, dold[c], a.r[c]);
                 } else if (MODE == kModeRestart || MODE == kModeResid) {
                     g = a.x32 ? (T)a.x32[c] : (T)a.x64in[c];
                 } else {
@@ -524,7 +433,7 @@ __global__ void __launch_bounds__(kBlock) k_spmv(SpmvArgs<T> a)
             __syncthreads();
             if (has) {
                 const int kb = max(my_lo, c0), ke = min(my_hi, c0 + cn);
-                for (int k = kb; k < ke; ++k) acc = fmaT<T>(s_val[k - c0], s_x[k - c0], acc);
+                for (int k = kb; k < ke; ++k) acc = fma_t<T>(s_val[k - c0], s_x[k - c0], acc);
             }
             __syncthreads();
         }
@@ -533,8 +442,8 @@ __global__ void __launch_bounds__(kBlock) k_spmv(SpmvArgs<T> a)
                 a.yout[my_row] = acc;
             } else if (MODE == kModeCg) {
                 const T dof = dold[my_row];
-                if (x_pending) a.x[my_row] = fmaT<T>(alpha_prev, dof, a.x[my_row]);
-                const T dn = fmaT<T>(beta, dof, a.r[my_row]);
+                if (x_pending) a.x[my_row] = fma_t<T>(alpha_prev, dof, a.x[my_row]);
+                const T dn = fma_t<T>(beta, dof, a.r[my_row]);
                 dnew[my_row] = dn;
                 a.q[my_row] = acc;
                 if (f32acc) sf = fmaf((float)dn, (float)acc, sf);
@@ -561,12 +470,12 @@ __global__ void __launch_bounds__(kBlock) k_spmv(SpmvArgs<T> a)
     }
     if (MODE == kModePlain) return;
     if (f32acc) {
-        const float bs = block_sum_f(sf, sm);
+        const float bs = sell_block_sum_f(sf, sm);
         if (tid == 0) a.part[lb] = (double)bs;
         return;
     }
     for (int j = 0; j < NV; ++j) {
-        const double bs = block_sum(s[j], sm);
+        const double bs = sell_block_sum(s[j], sm);
         if (tid == 0) a.part[(size_t)lb * NV + j] = bs;
     }
 }
@@ -576,10 +485,10 @@ __global__ void __launch_bounds__(kBlock)
 k_fin_restart(const double *part, int cnt, int32_t it0, double eps, int abs_tol, int32_t maxit,
               DevState *st)
 {
-    __shared__ double sm[kBlock / 64 + 1];
-    const double g = reduce_partials(part, cnt, 3, 0, sm);
-    const double bb = reduce_partials(part, cnt, 3, 1, sm);
-    const double rho = reduce_partials(part, cnt, 3, 2, sm);
+    __shared__ double sm[3][kBlock / 64];
+    const double g = reduce_partials(part, cnt, 3, 0, sm[0]);
+    const double bb = reduce_partials(part, cnt, 3, 1, sm[1]);
+    const double rho = reduce_partials(part, cnt, 3, 2, sm[2]);
     if (threadIdx.x == 0) {
         st->bnorm2 = bb;
         st->k0rec = 0;
@@ -675,8 +584,7 @@ __global__ void __launch_bounds__(kBlock)
 k_cg_update(int32_t n, T *__restrict__ r, const T *__restrict__ q, const double *sp, int nsp, double *up,
             int it, const T *__restrict__ dg, T *__restrict__ z, DevState *st)
 {
-    __shared__ double sm[kBlock / 64 + 1];
-    __shared__ int s_skip;
+    __shared__ double sm[kBlock / 64], sm_d[kBlock / 64];
     const int64_t nchunk = ((int64_t)n + kVecTile - 1) / kVecTile;
     T rv[kUpdPre][kVecPerThread], qv[kUpdPre][kVecPerThread], dv[kUpdPre][kVecPerThread];
 #pragma unroll
@@ -694,46 +602,22 @@ k_cg_update(int32_t n, T *__restrict__ r, const T *__restrict__ q, const double 
             }
         }
     }
-    if (threadIdx.x == 0) s_skip = st->stop_it <= it;
+    const int32_t stop = st->stop_it;
     const double g = st->gam[it & 1];
     const bool f32acc = sizeof(T) == 4 && st->acc32;   // dot_acc = 1
     // delta: the product's partials in a fixed order (the same bits in every
-    // block).  nsp <= kMaxGrid, so every thread's share is issued at once;
-    // a share past nsp adds +0.0, which leaves the sum's bits unchanged (the
-    // running sum starts at +0.0 and so is never -0.0).
+    // block), one barrier
     double acc = 0.0;
     float accf = 0.0f;
-    if (f32acc) {
-        for (int i = threadIdx.x; i < nsp; i += kBlock) accf += (float)sp[i];
-    } else {
-        double pv[kMaxGrid / kBlock];
-#pragma unroll
-        for (int k = 0; k < kMaxGrid / kBlock; ++k) {
-            const int i = threadIdx.x + k * kBlock;
-            pv[k] = i < nsp ? sp[i] : 0.0;
-        }
-#pragma unroll
-        for (int k = 0; k < kMaxGrid / kBlock; ++k) acc += pv[k];
-    }
-    __syncthreads();
-    if (s_skip) return;
-    double delta;
-    if (f32acc) {
-        const float df = block_sum_f(accf, sm);
-        if (threadIdx.x == 0) sm[kBlock / 64] = (double)df;
-        __syncthreads();
-        delta = sm[kBlock / 64];
-        __syncthreads();
-    } else {
-        // butterfly in each wave, then waves 0..3 in order by every thread:
-        // block_sum's bits with one barrier (sm_d is written once)
-        __shared__ double sm_d[kBlock / 64];
-        const double v = wave_sum(acc);
-        if ((threadIdx.x & 63) == 0) sm_d[threadIdx.x >> 6] = v;
-        __syncthreads();
-        delta = 0.0;
-        for (int w = 0; w < kBlock / 64; ++w) delta += sm_d[w];
-    }
+    if (f32acc) accf = partials_share_f(sp, nsp);
+    else acc = partials_share(sp, nsp);
+    // A stop before this iteration is final.  A stop in it may be the product's
+    // or, while this launch runs, block 0's breakdown below, which the waves of
+    // a block can see or miss: they all take the barrier, and a breakdown is
+    // in every block's delta.
+    if (stop < it) return;
+    const double delta = f32acc ? block_total_f(accf, sm_d) : block_total(acc, sm_d);
+    if (stop == it) return;
     if (!isfinite(delta) || !(delta > 0.0)) {
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             st->delta = delta;
@@ -754,7 +638,7 @@ k_cg_update(int32_t n, T *__restrict__ r, const T *__restrict__ q, const double 
     double s = 0.0, s2 = 0.0;
     float sf = 0.0f, s2f = 0.0f;
     auto elem = [&](int64_t i, T r0, T q0, T d0) {
-        const T rn = fmaT<T>(-alpha, q0, r0);
+        const T rn = fma_t<T>(-alpha, q0, r0);
         r[i] = rn;
         if (f32acc) s2f = fmaf((float)rn, (float)rn, s2f);
         else s2 = fma((double)rn, (double)rn, s2);
@@ -781,14 +665,14 @@ k_cg_update(int32_t n, T *__restrict__ r, const T *__restrict__ q, const double 
         }
     }
     if (PC) {
-        s = f32acc ? (double)block_sum_f(sf, sm) : block_sum(s, sm);
-        s2 = f32acc ? (double)block_sum_f(s2f, sm) : block_sum(s2, sm);
+        s = f32acc ? (double)sell_block_sum_f(sf, sm) : sell_block_sum(s, sm);
+        s2 = f32acc ? (double)sell_block_sum_f(s2f, sm) : sell_block_sum(s2, sm);
         if (threadIdx.x == 0) {
             up[blockIdx.x] = s;
             up[gridDim.x + blockIdx.x] = s2;
         }
     } else {
-        s2 = f32acc ? (double)block_sum_f(s2f, sm) : block_sum(s2, sm);
+        s2 = f32acc ? (double)sell_block_sum_f(s2f, sm) : sell_block_sum(s2, sm);
         if (threadIdx.x == 0) up[blockIdx.x] = s2;
     }
 }

@@ -45,23 +45,23 @@ struct JacArgs {
 template <typename T>
 __device__ inline bool jac_prologue(const JacArgs<T> &a, double *sm)
 {
-    __shared__ int s_skip;
     DevState *st = a.st;
     const int k = a.k;
-    if (threadIdx.x == 0) s_skip = st->stop_it < k;
-    __syncthreads();
-    if (s_skip) return true;
+    const double thr = st->thr;
+    // stop_it = k - 1 is block 0's decision in this launch, which the waves of
+    // a block can see or miss: only an earlier stop skips the barrier below
+    if (st->stop_it < k - 1) return true;
     if (k == 0) {
-        const double bb = sell_reduce_partials(a.part + a.np, a.np, sm);
+        const double bb = partials_total(false, a.part + a.np, a.np, sm);
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             st->bnorm2 = bb;
             st->thr = a.abs_tol ? a.eps : a.eps * sqrt(bb);
         }
         return false;
     }
-    const double g = sell_reduce_partials(a.part + (size_t)((k - 1) & 1) * a.np, a.np, sm);
+    const double g = partials_total(false, a.part + (size_t)((k - 1) & 1) * a.np, a.np, sm);
     const bool bad = !(g == g) || isinf(g);
-    const bool conv = !bad && sqrt(g) <= st->thr;
+    const bool conv = !bad && sqrt(g) <= thr;
     const bool cap = !conv && !bad && k - 1 >= a.maxit;
     if (!(conv || cap || bad)) return false;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -84,8 +84,8 @@ template <bool NT, typename P> __device__ inline P jac_ld(const P *p)
 template <typename T, typename IDX, int B, bool NT>
 __global__ void __launch_bounds__(kBlock) k_jac_sell(JacArgs<T> a)
 {
-    __shared__ double sm[kBlock / 64 + 1];
-    if (jac_prologue<T>(a, sm)) return;
+    __shared__ double sm[kBlock / 64], sm_head[kBlock / 64];
+    if (jac_prologue<T>(a, sm_head)) return;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const T *x = (a.k & 1) ? a.x1 : a.x0;
     T *xn = (a.k & 1) ? a.x0 : a.x1;
@@ -153,8 +153,8 @@ __global__ void __launch_bounds__(kBlock) k_jac_sell(JacArgs<T> a)
 template <typename T>
 __global__ void __launch_bounds__(kBlock) k_jac_csr(JacArgs<T> a)
 {
-    __shared__ double sm[kBlock / 64 + 1];
-    if (jac_prologue<T>(a, sm)) return;
+    __shared__ double sm[kBlock / 64], sm_head[kBlock / 64];
+    if (jac_prologue<T>(a, sm_head)) return;
     const T *x = (a.k & 1) ? a.x1 : a.x0;
     T *xn = (a.k & 1) ? a.x0 : a.x1;
     double s2 = 0.0;

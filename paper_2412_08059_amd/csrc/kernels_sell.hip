@@ -276,86 +276,58 @@ template <bool NT, typename P> __device__ inline P sell_ld(const P *p)
 // entry past the row's length is the slice's padding (past W, its last
 // column; both inside the slice), its gather reads the row itself and its
 // product is skipped.  Without BF each entry's loads sit behind its own guard.
+//
+// The grid is sized for every wave slot (8 blocks per CU), so a wave must fit
+// eight times on a SIMD: kSgprCap keeps the compiler within 80 scalar
+// registers.  With 85 the hardware fits seven waves (the trap handler's
+// registers come on top) and the last eighth of the blocks forms a tail: the
+// 128^3 FP64 product took 59 us instead of 42.
 template <int MODE, typename T, typename IDX, int B, bool BF, bool NT>
-__global__ void __launch_bounds__(kBlock) k_sell(SellArgs<T> a)
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(kSgprCap))) k_sell(SellArgs<T> a)
 {
     constexpr int NV = (MODE == kSellRestart) ? 3 : 1;
-    __shared__ double sm[kBlock / 64 + 1];
+    __shared__ double sm[kBlock / 64];
     DevState *st = a.st;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
 
     T beta = T(0), alpha_prev = T(0);
     bool x_pending = false;   // x += alpha_{it-1} d_{it-1} still to apply in the main loop
+    bool f32acc = false;      // dot_acc = 1: the FP32 phase's dot products accumulate in FP32
     const T *dold = nullptr;
     T *dnew = nullptr;
-    // dot_acc = 1: the FP32 phase's dot products accumulate in FP32
-    const bool f32acc = (MODE == kSellCg || MODE == kSellDir || MODE == kSellCgD) && sizeof(T) == 4 && st->acc32;
     if (MODE == kSellCgD) {   // the direction is formed: skip only after a stop
-        __shared__ int s_skip2;
-        if (tid == 0) s_skip2 = st->stop_it <= a.it;
-        __syncthreads();
-        if (s_skip2) return;
+        f32acc = sizeof(T) == 4 && st->acc32;
+        if (st->stop_it <= a.it) return;
         dold = (a.it & 1) ? a.dA : a.dB;   // the d formed by kSellDir of this iteration
     }
     if (MODE == kSellCg || MODE == kSellDir) {
+        __shared__ double sm_rho[kBlock / 64], sm_g[kBlock / 64];
         const int it = a.it;
-        __shared__ int s_skip, s_xdone;
-        if (tid == 0) {
-            s_skip = st->stop_it < it;
-            s_xdone = st->x_it == it;
-        }
-        __syncthreads();
-        if (s_skip) return;
+        const CgHead h = cg_head<T>(st, a.up, a.nup, a.pc, it, a.it0, sm_rho, sm_g);
+        if (h.skip) return;
+        f32acc = h.f32acc;
         dold = (it & 1) ? a.dB : a.dA;
         dnew = (it & 1) ? a.dA : a.dB;
         if (it != a.it0) {
-            const bool xdone = s_xdone;
-            // rho_it (alpha, beta) and gamma_it = r.r (stop test, v); equal without a preconditioner
-            const double rho = f32acc ? sell_reduce_partials_f(a.up, a.nup, sm) : sell_reduce_partials(a.up, a.nup, sm);
-            const double g = !a.pc ? rho
-                             : f32acc ? sell_reduce_partials_f(a.up + a.nup, a.nup, sm)
-                                      : sell_reduce_partials(a.up + a.nup, a.nup, sm);
-            const double gp = st->gr[(it - 1) & 1];
-            const double rhop = st->gam[(it - 1) & 1];
-            alpha_prev = (T)st->alph[(it - 1) & 1];
-            const bool conv = sqrt(g) <= st->thr;
-            const bool cap = !conv && it >= st->maxit;
-            if (blockIdx.x == 0 && tid == 0) {
-                st->gam[it & 1] = rho;
-                st->gr[it & 1] = g;
-                const int k = it - 1;
-                if (k < st->k0rec && k < kK0Max) st->ratios[k] = sqrt(g) / sqrt(gp);
-                if (conv || cap) {
-                    st->gamma = g;
-                    st->iter = it;
-                    st->reason = conv ? kConverged : kMaxit;
-                    st->stop_it = it;
-                    st->live = 0;
-                }
-            }
-            const unsigned cross = a.snap ? spec_crossings(st, it, g) : 0u;
-            if (conv || cap || cross) {
+            alpha_prev = (T)h.alph;
+            const bool stop = cg_head_decide(st, h, it);
+            const unsigned cross = a.snap ? spec_crossings(st, it, h.g) : 0u;
+            if (stop || cross) {
                 // the iterate x_it of this block's rows, then its run-ahead copies
                 for (SliceWalk w = slice_walk(a.nslices); w.g < w.g_end; w.g += w.step) {
                     const int i = w.g * kBlock + tid;
                     if (i >= a.n) continue;
-                    const T xn = xdone ? a.x[i] : fma_t<T>(alpha_prev, dold[i], a.x[i]);
-                    if (!xdone) a.x[i] = xn;
+                    const T xn = h.xdone ? a.x[i] : fma_t<T>(alpha_prev, dold[i], a.x[i]);
+                    if (!h.xdone) a.x[i] = xn;
                     for (int t = 0; t < kNumEps; ++t)
                         if (cross & (1u << t)) a.snap[(size_t)t * a.n + i] = xn;
                 }
-                if (blockIdx.x == 0 && tid == 0) {
-                    for (int t = 0; t < kNumEps; ++t) {
-                        if (!(cross & (1u << t))) continue;
-                        st->cross_iter[t] = it;
-                        st->cross_gamma[t] = g;
-                    }
-                }
-                if (conv || cap) return;
+                record_crossings(st, cross, it, h.g);
+                if (stop) return;
             } else {
-                x_pending = !xdone;
+                x_pending = !h.xdone;
             }
-            beta = (T)(rho / rhop);
+            beta = (T)(h.rho / h.rhop);
         }
     }
     if (MODE == kSellDir) {   // d = r + beta d_old and the deferred x update, row by row

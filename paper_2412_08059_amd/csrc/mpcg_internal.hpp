@@ -37,6 +37,7 @@ constexpr int64_t kInfinityCacheBytes = 256ll << 20;   // MI355X last-level (Inf
 constexpr int kNumXcd = 8;            // MI355X: blocks are dispatched round-robin over 8 XCDs
 constexpr int kMaxGrid = 2048;        // largest grid of a kernel that writes reduction partials
 constexpr int kUpdateGrid = 1024;     // blocks of a CG update launch: fewer partials for the next product
+constexpr int kSgprCap = 80;          // scalar registers with which eight waves fit on a SIMD
 constexpr int kSpmvBlocksPerCu = 5;   // 32 KB of LDS per block, 160 KB per CU
 
 enum StopReason : int32_t { kRunning = 0, kConverged = 1, kMaxit = 2, kNotSpd = 3, kNonFinite = 4 };
