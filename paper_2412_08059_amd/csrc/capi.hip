@@ -200,6 +200,20 @@ Layout plan_layout(int64_t n, int64_t nnz)
     return L;
 }
 
+WalkTab walk_tab(int32_t nslices, int32_t grid)
+{
+    WalkTab t{};
+    const int64_t ngroups = ((int64_t)nslices + kBlock / 64 - 1) / (kBlock / 64);
+    int64_t before = 0;   // blocks on the XCDs before x
+    for (int x = 0; x < kNumXcd; ++x) {
+        t.blocks[x] = grid / kNumXcd + (x < grid % kNumXcd ? 1 : 0);
+        t.first[x] = (int32_t)(before * ngroups / grid);
+        before += t.blocks[x];
+    }
+    t.first[kNumXcd] = (int32_t)ngroups;
+    return t;
+}
+
 SpmvShape spmv_shape(int64_t n, int64_t nnz, int value_bytes, int num_cu)
 {
     // rows per tile so that a tile's entries fill one LDS chunk on average
@@ -241,7 +255,8 @@ struct Plan {
     double *z64 = nullptr, *dg64 = nullptr;
     SpmvShape sh32{}, sh64{};
     SellMat sell{};
-    bool use_sell = false;
+    DsMat ds{};
+    bool use_sell = false, use_ds = false;   // at most one; neither: CSR
     int nup = 1;
     mpcg_tuning tune{};   // scheduling parameters resolved for this matrix
     char *ws = nullptr;
@@ -297,19 +312,43 @@ mpcg_status ingest(mpcg_ctx *c, const mpcg_csr *A, const double *b, bool need_va
     int32_t *rp32 = A->row_ptr_is_i64 ? p->at<int32_t>(p->L.rp32) : nullptr;
     p->rp = A->row_ptr_is_i64 ? rp32 : static_cast<const int32_t *>(A->row_ptr);
     HIPCHK(hipMemsetAsync(p->st, 0, sizeof(DevState), c->stream));
-    int64_t *soff = p->at<int64_t>(p->L.sell_off);
+    int64_t *soff = p->at<int64_t>(p->L.sell_off), *wid = p->at<int64_t>(p->L.sell_wid);
     const int nsl = (p->n + 63) / 64;
-    launch_ingest_sell(c->stream, A->row_ptr, A->row_ptr_is_i64 ? 1 : 0, p->rp, rp32, A->col_idx, A->val, b,
-                       p->n, A->nnz, p->at<int64_t>(p->L.sell_wid), soff, p->at<int32_t>(p->L.ingest_blk),
-                       p->L.sell_cap, c->force_csr ? 0 : 1,
-                       p->ws + p->L.sell_col, p->at<double>(p->L.sell_v64),
-                       need_val32 ? p->at<float>(p->L.sell_v32) : nullptr, p->st);
-    if (want_diag) launch_diag(c->stream, p->rp, A->col_idx, A->val, p->n, p->dg64, p->dg32, p->st);
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(&c->hst[2].spare_i64, soff + nsl, sizeof(int64_t), hipMemcpyDeviceToHost,
-                          c->stream));
-    HIPCHK(hipMemcpyAsync(&c->hst[1], p->st, sizeof(DevState), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
+    double *v64 = p->at<double>(p->L.sell_v64);
+    float *v32 = need_val32 ? p->at<float>(p->L.sell_v32) : nullptr;
+    launch_ingest_rows(c->stream, A->row_ptr, A->row_ptr_is_i64 ? 1 : 0, rp32, A->col_idx, b, p->n, A->nnz, wid,
+                       p->at<int32_t>(p->L.ingest_blk), p->st);
+    // symmetric matrices on few diagonals: diagonal storage, in the SELL value
+    // arrays; what its passes find unfit (or an explicit variant) goes to SELL
+    const bool try_ds = c->opt.spmv_variant == 0;
+    if (try_ds)
+        launch_ds_ingest(c->stream, p->rp, A->col_idx, A->val, p->n, A->nnz, p->L.sell_cap, v64, v32,
+                         want_diag ? p->dg64 : nullptr, want_diag ? p->dg32 : nullptr, p->st);
+    auto general = [&]() {
+        launch_ingest_sell(c->stream, p->rp, A->col_idx, A->val, p->n, wid, soff, p->L.sell_cap,
+                           c->force_csr ? 0 : 1, p->ws + p->L.sell_col, v64, v32, p->st);
+        if (want_diag) launch_diag(c->stream, p->rp, A->col_idx, A->val, p->n, p->dg64, p->dg32, p->st);
+    };
+    auto verdict = [&]() -> mpcg_status {
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipMemcpyAsync(&c->hst[2].spare_i64, soff + nsl, sizeof(int64_t), hipMemcpyDeviceToHost,
+                              c->stream));
+        HIPCHK(hipMemcpyAsync(&c->hst[1], p->st, sizeof(DevState), hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(hipStreamSynchronize(c->stream));
+        return MPCG_OK;
+    };
+    general();
+    mpcg_status rc = verdict();
+    if (rc != MPCG_OK) return rc;
+    if (c->hst[1].ds_cand && c->hst[1].ds_miss) {   // other diagonals, not symmetric, or malformed
+        HIPCHK(hipMemsetAsync(&p->st->ds_cand, 0, sizeof(int32_t), c->stream));
+        HIPCHK(hipMemsetAsync(&p->st->ing_err, 0, sizeof(int32_t), c->stream));
+        launch_ingest_rows(c->stream, A->row_ptr, A->row_ptr_is_i64 ? 1 : 0, rp32, A->col_idx, b, p->n, A->nnz, wid,
+                           p->at<int32_t>(p->L.ingest_blk), p->st);
+        general();
+        rc = verdict();
+        if (rc != MPCG_OK) return rc;
+    }
     const DevState s = c->hst[1];
     const int64_t padded = c->hst[2].spare_i64;
     p->band = s.max_band;
@@ -317,13 +356,24 @@ mpcg_status ingest(mpcg_ctx *c, const mpcg_csr *A, const double *b, bool need_va
     if (s.ing_err & (kErrNonFiniteA | kErrNonFiniteB)) return MPCG_ENONFINITE;
     if (s.ing_err & kErrDiag) return MPCG_ENOTSPD;   // Jacobi needs a positive diagonal (any SPD A has one)
     // the entry kernel filled the SELL copy under exactly this condition
-    p->use_sell = !c->force_csr && padded <= p->L.sell_cap;
+    p->use_ds = s.ds_cand != 0;
+    p->use_sell = !p->use_ds && !c->force_csr && padded <= p->L.sell_cap;
     p->sh64 = spmv_shape(A->n, A->nnz, 8, c->num_cu);
     p->sh32 = spmv_shape(A->n, A->nnz, 4, c->num_cu);
     p->nup = vec_grid(A->n);
     if (p->nup > kUpdateGrid) p->nup = kUpdateGrid;
     p->tune = resolve_tuning(c, A->n, A->nnz, s.max_band);
-    if (p->use_sell) {
+    int64_t pg = ((int64_t)nsl + kBlock / 64 - 1) / (kBlock / 64);   // blocks of a product launch
+    if (pg > kMaxGrid) pg = kMaxGrid;
+    p->sell.grid = (int32_t)(pg < 1 ? 1 : pg);
+    if (p->use_ds) {
+        DsMat &m = p->ds;
+        m.p64 = v64;
+        m.p32 = v32;
+        m.n = p->n;
+        m.nh = s.ds_nh;
+        for (int t = 0; t < kDsMax; ++t) m.d[t] = s.ds_d[t];
+    } else if (p->use_sell) {
         SellMat &m = p->sell;
         m.rp = p->rp;
         m.off = soff;
@@ -340,12 +390,9 @@ mpcg_status ingest(mpcg_ctx *c, const mpcg_csr *A, const double *b, bool need_va
         m.nt_mask = p->tune.sell_stream < 0 ? nt_auto : (p->tune.sell_stream ? 3 : 0);
         // scattered gathers (columns beyond 16-bit offsets): one gathered vector, not two
         m.split = p->tune.sell_split >= 0 ? p->tune.sell_split : (m.idx16 ? 0 : 1);
-        int64_t g = ((int64_t)nsl + kBlock / 64 - 1) / (kBlock / 64);
-        if (g > kMaxGrid) g = kMaxGrid;
-        m.grid = (int32_t)(g < 1 ? 1 : g);
         m.scol = p->ws + p->L.sell_col;
-        m.v64 = p->at<double>(p->L.sell_v64);
-        m.v32 = need_val32 ? p->at<float>(p->L.sell_v32) : nullptr;
+        m.v64 = v64;
+        m.v32 = v32;
     } else if (need_val32) {
         launch_cast32(c->stream, A->val, p->at<float>(p->L.val32), A->nnz);
     }
@@ -353,9 +400,13 @@ mpcg_status ingest(mpcg_ctx *c, const mpcg_csr *A, const double *b, bool need_va
     return MPCG_OK;
 }
 
-// ---- dispatch: SELL-64 kernels when the padded copy fits, CSR-stream otherwise
+// ---- dispatch: diagonal storage where it holds the matrix, else SELL-64
+// kernels when the padded copy fits, CSR-stream otherwise
 
-int prod_grid(const Plan &p, bool f32) { return p.use_sell ? p.sell.grid : (f32 ? p.sh32.grid : p.sh64.grid); }
+int prod_grid(const Plan &p, bool f32)
+{
+    return p.use_ds || p.use_sell ? p.sell.grid : (f32 ? p.sh32.grid : p.sh64.grid);
+}
 
 template <typename T> const T *csr_vals(const Plan &p);
 template <> const float *csr_vals<float>(const Plan &p) { return p.at<float>(p.L.val32); }
@@ -382,7 +433,9 @@ void run_cg_spmv(hipStream_t s, const Plan &p, const T *r, T *dA, T *dB, T *q, i
                  T *snap = nullptr)
 {
     const T *src = p.pc ? zbuf<T>(p) : r;
-    if (p.use_sell)
+    if (p.use_ds)
+        launch_ds_cg_spmv<T>(s, p.ds, p.sell.grid, src, dA, dB, q, p.up, p.nup, p.sp, it, it0, x, snap, p.pc, p.st);
+    else if (p.use_sell)
         launch_sell_cg_spmv<T>(s, p.sell, src, dA, dB, q, p.up, p.nup, p.sp, it, it0, x, snap, p.pc, p.st);
     else
         launch_cg_spmv<T>(s, csr_shape<T>(p), p.rp, p.col, csr_vals<T>(p), src, dA, dB, q, p.up, p.nup, p.sp,
@@ -401,7 +454,10 @@ void run_restart(hipStream_t s, const Plan &p, const float *x32, double *x, cons
 {
     const double *dg = p.pc ? p.dg64 : nullptr;
     double *z = p.pc ? p.z64 : nullptr;
-    if (p.use_sell) {
+    if (p.use_ds) {
+        launch_ds_restart(s, p.ds, p.sell.grid, x32, x, b, r, dA, dB, it0, dg, z, p.sp, p.st);
+        launch_fin_restart(s, p.sp, p.sell.grid, it0, eps, abs_tol, maxit, p.st);
+    } else if (p.use_sell) {
         launch_sell_restart(s, p.sell, x32, x, b, r, dA, dB, it0, dg, z, p.sp, p.st);
         launch_fin_restart(s, p.sp, p.sell.grid, it0, eps, abs_tol, maxit, p.st);
     } else {
@@ -412,7 +468,10 @@ void run_restart(hipStream_t s, const Plan &p, const float *x32, double *x, cons
 
 void run_resid(hipStream_t s, const Plan &p, const double *x, const double *b)
 {
-    if (p.use_sell) {
+    if (p.use_ds) {
+        launch_ds_resid(s, p.ds, p.sell.grid, x, b, p.sp, p.st);
+        launch_fin_resid(s, p.sp, p.sell.grid, p.st);
+    } else if (p.use_sell) {
         launch_sell_resid(s, p.sell, x, b, p.sp, p.st);
         launch_fin_resid(s, p.sp, p.sell.grid, p.st);
     } else {
@@ -423,7 +482,8 @@ void run_resid(hipStream_t s, const Plan &p, const double *x, const double *b)
 template <typename T>
 void run_plain(hipStream_t s, const Plan &p, const T *x, T *y)
 {
-    if (p.use_sell) launch_sell_plain<T>(s, p.sell, x, y);
+    if (p.use_ds) launch_ds_plain<T>(s, p.ds, p.sell.grid, x, y);
+    else if (p.use_sell) launch_sell_plain<T>(s, p.sell, x, y);
     else launch_spmv_plain<T>(s, csr_shape<T>(p), p.rp, p.col, csr_vals<T>(p), x, y);
 }
 
@@ -471,7 +531,9 @@ JacMat jac_mat(const Plan &p)
     m.col = p.col;
     m.n = p.n;
     m.use_sell = p.use_sell;
+    m.use_ds = p.use_ds;
     m.sell = p.sell;
+    m.ds = p.ds;
     return m;
 }
 
@@ -735,7 +797,7 @@ mpcg_status pseudo_diameter(const mpcg_ctx *c, const Chan &ch, const Plan &p, mp
 Plan shared_plan(const mpcg_ctx *c, const Plan &p)
 {
     Plan q = p;
-    if (p.use_sell && p.sell.grid >= 8 * c->num_cu) {
+    if ((p.use_ds || p.use_sell) && p.sell.grid >= 8 * c->num_cu) {
         const int g = 7 * c->num_cu;
         if (g < q.sell.grid) q.sell.grid = g;
     }

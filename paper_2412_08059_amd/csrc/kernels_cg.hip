@@ -695,6 +695,7 @@ k_diag(const int32_t *__restrict__ rp, const int32_t *__restrict__ col, const do
        int32_t n, double *dg64, float *dg32, DevState *st)
 {
     int bad = 0;
+    if (st->ds_cand) return;   // the diagonal storage's pass writes both
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
         double d = 0.0;
         const int e = rp[i + 1];

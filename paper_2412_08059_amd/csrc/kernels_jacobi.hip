@@ -17,62 +17,9 @@
 // reduces instead the partials of ||b||^2 (part[1], from k_jac_bnorm) and
 // sets the threshold.
 
-#include "mpcg_internal.hpp"
-#include "sell_common.hpp"
+#include "jacobi_common.hpp"
 
 namespace mpcg {
-
-template <typename T>
-struct JacArgs {
-    // SELL-64 copy (SELL kernel) or CSR (CSR kernel)
-    const int32_t *rp;
-    const void *scol;
-    const T *sval;
-    const int64_t *off;
-    const int32_t *col;
-    const T *val;
-    int32_t n, nslices;
-    int32_t k, maxit, abs_tol, np;
-    double eps;
-    const T *b;
-    const T *dg;
-    T *x0, *x1;       // xs[0], xs[1]
-    double *part;     // 2 * np partials
-    DevState *st;
-};
-
-// Stop decision of launch k (block-uniform); returns true when the block exits.
-template <typename T>
-__device__ inline bool jac_prologue(const JacArgs<T> &a, double *sm)
-{
-    DevState *st = a.st;
-    const int k = a.k;
-    const double thr = st->thr;
-    // stop_it = k - 1 is block 0's decision in this launch, which the waves of
-    // a block can see or miss: only an earlier stop skips the barrier below
-    if (st->stop_it < k - 1) return true;
-    if (k == 0) {
-        const double bb = partials_total(false, a.part + a.np, a.np, sm);
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            st->bnorm2 = bb;
-            st->thr = a.abs_tol ? a.eps : a.eps * sqrt(bb);
-        }
-        return false;
-    }
-    const double g = partials_total(false, a.part + (size_t)((k - 1) & 1) * a.np, a.np, sm);
-    const bool bad = !(g == g) || isinf(g);
-    const bool conv = !bad && sqrt(g) <= thr;
-    const bool cap = !conv && !bad && k - 1 >= a.maxit;
-    if (!(conv || cap || bad)) return false;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        st->gamma = g;
-        st->iter = k - 1;
-        st->reason = conv ? kConverged : (bad ? kNonFinite : kMaxit);
-        st->stop_it = k - 1;
-        st->live = 0;
-    }
-    return true;
-}
 
 // NT: nontemporal loads of the matrix stream (see the SELL products)
 template <bool NT, typename P> __device__ inline P jac_ld(const P *p)
@@ -91,7 +38,7 @@ __global__ void __launch_bounds__(kBlock) k_jac_sell(JacArgs<T> a)
     T *xn = (a.k & 1) ? a.x0 : a.x1;
     const IDX *scol = static_cast<const IDX *>(a.scol);
     double s2 = 0.0;
-    for (SliceWalk w = slice_walk(a.nslices); w.g < w.g_end; w.g += w.step) {
+    for (SliceWalk w = slice_walk(a.walk); w.g < w.g_end; w.g += w.step) {
         const int sl = w.g * (kBlock / 64) + wv;
         if (sl >= a.nslices) continue;
         const int row = sl * 64 + lane;
@@ -204,7 +151,7 @@ __global__ void k_jac_widen(const float *x32, double *x64, int32_t n)
 
 int jacobi_grid(const JacMat &m)
 {
-    if (m.use_sell) return m.sell.grid;
+    if (m.use_ds || m.use_sell) return m.sell.grid;
     int g = (m.n + kBlock - 1) / kBlock;
     if (g > kMaxGrid) g = kMaxGrid;
     return g < 1 ? 1 : g;
@@ -235,11 +182,16 @@ void launch_jacobi_iter(hipStream_t s, const JacMat &m, const T *val_csr, const 
     a.x1 = x1;
     a.part = part;
     a.st = st;
-    if (m.use_sell) {
+    if (m.use_ds) {
+        a.nslices = (m.n + 63) / 64;
+        a.walk = walk_tab(a.nslices, a.np);
+        launch_ds_jacobi<T>(s, m.ds, a);
+    } else if (m.use_sell) {
         a.scol = m.sell.scol;
         a.sval = sizeof(T) == 8 ? reinterpret_cast<const T *>(m.sell.v64) : reinterpret_cast<const T *>(m.sell.v32);
         a.off = m.sell.off;
         a.nslices = m.sell.nslices;
+        a.walk = walk_tab(a.nslices, a.np);
         const bool nt = (m.sell.nt_mask >> (sizeof(T) == 8 ? 1 : 0)) & 1;
         if (m.sell.idx16) {
             if (nt) hipLaunchKernelGGL((k_jac_sell<T, int16_t, 4, true>), dim3(a.np), dim3(kBlock), 0, s, a);

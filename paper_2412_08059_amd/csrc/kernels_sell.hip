@@ -24,10 +24,12 @@ namespace mpcg {
 
 // ------------------------------------------------------------- ingest --
 //
-// Ingest is three launches and one host read-back:
+// Ingest is four launches and one host read-back (the diagonal storage's
+// passes come between the first two and the last two, see kernels_ds.hip):
 //   k_ingest_rows     thread per row: row-pointer checks (and int64 -> int32
 //                     conversion), b finite, row length, bandwidth from the
 //                     first and last column of the row, slice width;
+//   k_ingest_fold     the blocks' statistics into the device state;
 //   k_sell_scan       padded slice offsets;
 //   k_ingest_entries  wave per slice, entries read in coalesced 64-wide
 //                     strides: column range, strictly increasing columns,
@@ -99,40 +101,43 @@ k_ingest_rows(const void *rp_in, int rp_is_i64, const int32_t *__restrict__ col,
     }
 }
 
-// exclusive scan of the padded slice sizes (one block), off[nslices] = total;
-// also folds the per-block ingest statistics into the device state
-__global__ void __launch_bounds__(1024)
-k_sell_scan(const int64_t *wid, int32_t nslices, int64_t *off, const int32_t *blk, int32_t nblk,
-            DevState *st)
+// folds the per-block ingest statistics into the device state (one block)
+__global__ void __launch_bounds__(1024) k_ingest_fold(const int32_t *blk, int32_t nblk, DevState *st)
 {
-    __shared__ int64_t part[1024];
     __shared__ int fold[3][1024];
     const int t = threadIdx.x;
-    {
-        int e = 0, l = 0, bd = 0;
-        for (int i = t; i < nblk; i += 1024) {
-            e |= blk[3 * i];
-            l = l > blk[3 * i + 1] ? l : blk[3 * i + 1];
-            bd = bd > blk[3 * i + 2] ? bd : blk[3 * i + 2];
-        }
-        fold[0][t] = e;
-        fold[1][t] = l;
-        fold[2][t] = bd;
-        __syncthreads();
-        for (int d = 512; d > 0; d >>= 1) {
-            if (t < d) {
-                fold[0][t] |= fold[0][t + d];
-                fold[1][t] = fold[1][t] > fold[1][t + d] ? fold[1][t] : fold[1][t + d];
-                fold[2][t] = fold[2][t] > fold[2][t + d] ? fold[2][t] : fold[2][t + d];
-            }
-            __syncthreads();
-        }
-        if (t == 0) {
-            st->ing_err |= fold[0][0];
-            st->max_row = fold[1][0];
-            st->max_band = fold[2][0];
-        }
+    int e = 0, l = 0, bd = 0;
+    for (int i = t; i < nblk; i += 1024) {
+        e |= blk[3 * i];
+        l = l > blk[3 * i + 1] ? l : blk[3 * i + 1];
+        bd = bd > blk[3 * i + 2] ? bd : blk[3 * i + 2];
     }
+    fold[0][t] = e;
+    fold[1][t] = l;
+    fold[2][t] = bd;
+    __syncthreads();
+    for (int d = 512; d > 0; d >>= 1) {
+        if (t < d) {
+            fold[0][t] |= fold[0][t + d];
+            fold[1][t] = fold[1][t] > fold[1][t + d] ? fold[1][t] : fold[1][t + d];
+            fold[2][t] = fold[2][t] > fold[2][t + d] ? fold[2][t] : fold[2][t + d];
+        }
+        __syncthreads();
+    }
+    if (t == 0) {
+        st->ing_err |= fold[0][0];
+        st->max_row = fold[1][0];
+        st->max_band = fold[2][0];
+    }
+}
+
+// exclusive scan of the padded slice sizes (one block), off[nslices] = total
+__global__ void __launch_bounds__(1024)
+k_sell_scan(const int64_t *wid, int32_t nslices, int64_t *off, const DevState *st)
+{
+    __shared__ int64_t part[1024];
+    if (st->ds_cand) return;
+    const int t = threadIdx.x;
     const int per = (nslices + 1023) / 1024;
     const int a = min(t * per, nslices), b = min(a + per, nslices);
     int64_t sum = 0;
@@ -160,9 +165,9 @@ k_ingest_entries(const int32_t *__restrict__ rp, const int32_t *__restrict__ col
                  double *__restrict__ sv64, float *__restrict__ sv32, DevState *st)
 {
     __shared__ int s_ok;
-    if (threadIdx.x == 0) s_ok = !(st->ing_err & kErrRowPtr);
+    if (threadIdx.x == 0) s_ok = !(st->ing_err & kErrRowPtr) && !st->ds_cand;
     __syncthreads();
-    if (!s_ok) return;   // row pointers are not usable
+    if (!s_ok) return;   // row pointers are not usable, or the diagonal storage takes the entries
     const bool fill = allow_fill && off[nslices] <= cap;
     const bool idx16 = st->max_band < 32768;
     const int lane = threadIdx.x & 63;
@@ -206,16 +211,22 @@ k_ingest_entries(const int32_t *__restrict__ rp, const int32_t *__restrict__ col
     if (lane == 0 && err) atomicOr(&st->ing_err, err);
 }
 
-void launch_ingest_sell(hipStream_t s, const void *rp_in, int rp_is_i64, const int32_t *rp32,
-                        int32_t *rp32_out, const int32_t *col, const double *val, const double *b,
-                        int32_t n, int64_t nnz, int64_t *wid, int64_t *off, int32_t *blk, int64_t cap,
-                        int allow_fill, void *scol, double *sv64, float *sv32, DevState *st)
+void launch_ingest_rows(hipStream_t s, const void *rp_in, int rp_is_i64, int32_t *rp32_out, const int32_t *col,
+                        const double *b, int32_t n, int64_t nnz, int64_t *wid, int32_t *blk, DevState *st)
 {
     const int nslices = (n + 63) / 64;
     const int nblk = (n + kBlock - 1) / kBlock;
     hipLaunchKernelGGL(k_ingest_rows, dim3(nblk), dim3(kBlock), 0, s, rp_in, rp_is_i64, col, b, n, nnz,
                        nslices, rp32_out, wid, blk);
-    hipLaunchKernelGGL(k_sell_scan, dim3(1), dim3(1024), 0, s, wid, nslices, off, blk, nblk, st);
+    hipLaunchKernelGGL(k_ingest_fold, dim3(1), dim3(1024), 0, s, blk, nblk, st);
+}
+
+void launch_ingest_sell(hipStream_t s, const int32_t *rp32, const int32_t *col, const double *val, int32_t n,
+                        const int64_t *wid, int64_t *off, int64_t cap, int allow_fill, void *scol, double *sv64,
+                        float *sv32, DevState *st)
+{
+    const int nslices = (n + 63) / 64;
+    hipLaunchKernelGGL(k_sell_scan, dim3(1), dim3(1024), 0, s, wid, nslices, off, st);
     int g = (nslices + 3) / 4;
     if (g > 8192) g = 8192;
     hipLaunchKernelGGL(k_ingest_entries, dim3(g), dim3(kBlock), 0, s, rp32, col, val, n, nslices, off, cap,
@@ -239,6 +250,7 @@ struct SellArgs {
     const int64_t *off;
     int32_t n, nslices;
     int32_t it, it0;
+    WalkTab walk;
     const T *r;
     T *dA, *dB, *q;
     const double *up;
@@ -314,7 +326,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(kSgprCa
             const unsigned cross = a.snap ? spec_crossings(st, it, h.g) : 0u;
             if (stop || cross) {
                 // the iterate x_it of this block's rows, then its run-ahead copies
-                for (SliceWalk w = slice_walk(a.nslices); w.g < w.g_end; w.g += w.step) {
+                for (SliceWalk w = slice_walk(a.walk); w.g < w.g_end; w.g += w.step) {
                     const int i = w.g * kBlock + tid;
                     if (i >= a.n) continue;
                     const T xn = h.xdone ? a.x[i] : fma_t<T>(alpha_prev, dold[i], a.x[i]);
@@ -331,7 +343,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(kSgprCa
         }
     }
     if (MODE == kSellDir) {   // d = r + beta d_old and the deferred x update, row by row
-        for (SliceWalk w = slice_walk(a.nslices); w.g < w.g_end; w.g += w.step) {
+        for (SliceWalk w = slice_walk(a.walk); w.g < w.g_end; w.g += w.step) {
             const int i = w.g * kBlock + tid;
             if (i >= a.n) continue;
             const T dof = dold[i];
@@ -347,7 +359,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(kSgprCa
     for (int j = 0; j < NV; ++j) s[j] = 0.0;
     float sf = 0.0f;   // d.q in FP32 (dot_acc = 1)
 
-    for (SliceWalk w = slice_walk(a.nslices); w.g < w.g_end; w.g += w.step) {
+    for (SliceWalk w = slice_walk(a.walk); w.g < w.g_end; w.g += w.step) {
         const int sl = w.g * (kBlock / 64) + wv;
         if (sl >= a.nslices) continue;
         const int row = sl * 64 + lane;
@@ -484,6 +496,7 @@ static SellArgs<T> sell_args(const SellMat &m, const T *sval)
 {
     SellArgs<T> a{};
     a.rp = m.rp; a.scol = m.scol; a.sval = sval; a.off = m.off; a.n = m.n; a.nslices = m.nslices;
+    a.walk = walk_tab(m.nslices, m.grid);
     return a;
 }
 

@@ -37,6 +37,7 @@ constexpr int64_t kInfinityCacheBytes = 256ll << 20;   // MI355X last-level (Inf
 constexpr int kNumXcd = 8;            // MI355X: blocks are dispatched round-robin over 8 XCDs
 constexpr int kMaxGrid = 2048;        // largest grid of a kernel that writes reduction partials
 constexpr int kUpdateGrid = 1024;     // blocks of a CG update launch: fewer partials for the next product
+constexpr int kDsMax = 8;             // distances |i - j| > 0 that diagonal storage handles
 constexpr int kSgprCap = 80;          // scalar registers with which eight waves fit on a SIMD
 constexpr int kSpmvBlocksPerCu = 5;   // 32 KB of LDS per block, 160 KB per CU
 
@@ -106,6 +107,10 @@ struct alignas(256) DevState {
     int32_t dia_base;     // first level of the current round of bit-parallel level launches
     int32_t dia_over;
     int32_t dia_off[16];
+    // Diagonal storage (kernels_ds.hip): the sampled distances, ascending, and
+    // whether the entries' pass found others or an unsymmetric pair.
+    int32_t ds_cand, ds_miss, ds_nh;
+    int32_t ds_d[8];
 };
 
 // Byte offsets of every region inside the caller's arena.
@@ -131,6 +136,13 @@ struct SpmvShape {
 SpmvShape spmv_shape(int64_t n, int64_t nnz, int value_bytes, int num_cu);
 int vec_grid(int64_t n);
 
+// The slice groups that each XCD's blocks walk (sell_common.hpp): groups
+// first[x] .. first[x + 1] - 1 for the blocks[x] blocks of a launch on XCD x.
+struct WalkTab {
+    int32_t first[kNumXcd + 1], blocks[kNumXcd];
+};
+WalkTab walk_tab(int32_t nslices, int32_t grid);
+
 // SELL-64 copy of A (kernels_sell.hip): slices of 64 rows, entries of a slice
 // stored column-major, 16-bit column offsets when the bandwidth allows.
 struct SellMat {
@@ -146,6 +158,18 @@ struct SellMat {
     int32_t split;   // CG product in two launches (direction, then a one-vector gather)
 };
 
+// Diagonal storage of a symmetric matrix on few diagonals (kernels_ds.hip):
+// plane 0 the main diagonal, plane j the entries at distance d[j - 1] above it.
+struct DsMat {
+    const double *p64;
+    const float *p32;
+    int32_t n, nh;
+    int32_t d[kDsMax];
+};
+// elements from one plane to the next; the odd multiple of 256 bytes keeps
+// planes of a power-of-two n off the same memory channels
+__host__ __device__ inline int64_t ds_stride(int64_t n) { return (n + 63) / 64 * 64 + 5 * 64; }
+
 Layout plan_layout(int64_t n, int64_t nnz);
 
 // The matrix as the Jacobi-iteration kernels see it: the SELL-64 copy when the
@@ -154,8 +178,9 @@ struct JacMat {
     const int32_t *rp;
     const int32_t *col;
     int32_t n;
-    bool use_sell;
+    bool use_sell, use_ds;
     SellMat sell;
+    DsMat ds;
 };
 int jacobi_grid(const JacMat &m);   // blocks (= partial slots) of one iteration launch
 // partials of ||b||^2 into part[np ..], stop markers reset
@@ -186,10 +211,14 @@ __device__ inline unsigned spec_crossings(DevState *st, int it, double g)
 // ----- launch wrappers (kernels_cg.hip) -----
 // Validate A (and b), convert int64 row pointers, and build the SELL-64 copy
 // when its padded size fits in `cap` entries (see kernels_sell.hip).
-void launch_ingest_sell(hipStream_t s, const void *rp_in, int rp_is_i64, const int32_t *rp32,
-                        int32_t *rp32_out, const int32_t *col, const double *val, const double *b,
-                        int32_t n, int64_t nnz, int64_t *wid, int64_t *off, int32_t *blk, int64_t cap,
-                        int allow_fill, void *scol, double *sv64, float *sv32, DevState *st);
+// launch_ingest_rows: row pointers, b, row lengths, slice widths, statistics
+// folded into st.  launch_ingest_sell, after it: slice offsets and entries
+// (nothing while st->ds_cand says that the diagonal storage takes them).
+void launch_ingest_rows(hipStream_t s, const void *rp_in, int rp_is_i64, int32_t *rp32_out, const int32_t *col,
+                        const double *b, int32_t n, int64_t nnz, int64_t *wid, int32_t *blk, DevState *st);
+void launch_ingest_sell(hipStream_t s, const int32_t *rp32, const int32_t *col, const double *val, int32_t n,
+                        const int64_t *wid, int64_t *off, int64_t cap, int allow_fill, void *scol, double *sv64,
+                        float *sv32, DevState *st);
 void launch_cast32(hipStream_t s, const double *val, float *val32, int64_t nnz);
 void launch_fill_f64(hipStream_t s, double *p, int64_t n, double v);
 void launch_fill_f32(hipStream_t s, float *p, int64_t n, float v);
@@ -205,6 +234,7 @@ void launch_init32(hipStream_t s, const double *b, float *x, float *r, float *dA
                    double *part, DevState *st, int acc32);
 // Jacobi: dg64 = diag(A), dg32 = float32(dg64); a row without a positive,
 // finite diagonal entry sets kErrDiag.
+// (nothing while st->ds_cand: the diagonal storage's pass writes them)
 void launch_diag(hipStream_t s, const int32_t *rp, const int32_t *col, const double *val, int32_t n,
                  double *dg64, float *dg32, DevState *st);
 void launch_set_phase(hipStream_t s, DevState *st, double thr, int32_t maxit, int32_t k0rec);
@@ -258,6 +288,22 @@ void launch_sell_resid(hipStream_t s, const SellMat &m, const double *x64, const
                        double *part, DevState *st);
 template <typename T>
 void launch_sell_plain(hipStream_t s, const SellMat &m, const T *x, T *y);
+
+// ----- diagonal storage (kernels_ds.hip) -----
+// After k_ingest_rows: distances sampled, planes (and diag(A) if dg64) filled
+// and the symmetry checked, all on the device; st->ds_cand && !st->ds_miss
+// says that the planes hold the matrix.  cap: elements of p64 / p32.
+void launch_ds_ingest(hipStream_t s, const int32_t *rp, const int32_t *col, const double *val, int32_t n, int64_t nnz,
+                      int64_t cap, double *p64, float *p32, double *dg64, float *dg32, DevState *st);
+template <typename T>
+void launch_ds_cg_spmv(hipStream_t s, const DsMat &m, int grid, const T *r, T *dA, T *dB, T *q, const double *up,
+                       int nup, double *part, int it, int it0, T *x, T *snap, int pc, DevState *st);
+void launch_ds_restart(hipStream_t s, const DsMat &m, int grid, const float *x32, double *x64, const double *b,
+                       double *r, double *dA, double *dB, int it0, const double *dg, double *z, double *part,
+                       DevState *st);
+void launch_ds_resid(hipStream_t s, const DsMat &m, int grid, const double *x64, const double *b, double *part,
+                     DevState *st);
+template <typename T> void launch_ds_plain(hipStream_t s, const DsMat &m, int grid, const T *x, T *y);
 
 // ----- BFS (kernels_bfs.hip) -----
 // A queued BFS vertex is stored as its CSR row range: the level that expands

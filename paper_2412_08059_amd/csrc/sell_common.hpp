@@ -174,25 +174,20 @@ __device__ inline void record_crossings(DevState *st, unsigned cross, int it, do
 // Slice groups (kBlock / 64 slices, one per wave) of an XCD's contiguous
 // range are dealt round-robin to that XCD's blocks: at any moment the blocks
 // of one XCD work on a narrow window of consecutive rows, so the rows that a
-// stencil's neighbour planes gather are still in that XCD's L2.
+// stencil's neighbour planes gather are still in that XCD's L2.  The ranges
+// (in proportion to each XCD's blocks) come from the host with the launch: two
+// 64-bit divisions per wave are several hundred scalar instructions.
 struct SliceWalk {
     int g, g_end, step;   // group index, end, stride
 };
 
-__device__ inline SliceWalk slice_walk(int nslices)
+__device__ inline SliceWalk slice_walk(const WalkTab &t)
 {
-    constexpr int per = kBlock / 64;
-    const int ngroups = (nslices + per - 1) / per;
-    const int nb = gridDim.x, b = blockIdx.x;
-    const int nx = nb < kNumXcd ? nb : kNumXcd;           // XCDs that hold blocks
-    const int q = nb / nx, rem = nb % nx;
-    const int x = b % nx, i = b / nx;
-    const int bx = q + (x < rem ? 1 : 0);                 // blocks on this XCD (>= 1)
-    const int64_t before = (int64_t)x * q + (x < rem ? x : rem);
-    SliceWalk w;                                          // groups in proportion to blocks
-    w.g = (int)(before * ngroups / nb) + i;
-    w.g_end = (int)((before + bx) * ngroups / nb);
-    w.step = bx;
+    const int x = blockIdx.x % kNumXcd, i = blockIdx.x / kNumXcd;
+    SliceWalk w;
+    w.g = t.first[x] + i;
+    w.g_end = t.first[x + 1];
+    w.step = t.blocks[x];
     return w;
 }
 
