@@ -789,11 +789,13 @@ mpcg_status pseudo_diameter(const mpcg_ctx *c, const Chan &ch, const Plan &p, mp
     return rc;
 }
 
-// The plan of the FP32 launches that run beside the 2BFS: when the SELL
+// The plan of the launches that run, or may run, beside the 2BFS: when the
 // product grid fills every CU (8 blocks of 256 threads each), one block per CU
-// fewer.  Both kernels of an iteration take their partial counts from the
-// same plan, and the first product after the switch reduces the update's
-// partials, whose grid does not change.
+// fewer.  A phase keeps the plan it may have started with beside the 2BFS to
+// its end: the grid fixes which rows share a partial sum, so Algorithm II's
+// bits then do not depend on when the 2BFS ends.  (With diagonal storage the
+// smaller grid is no slower alone either: 1M band FP64 product 25.5 us at
+// 1,792 blocks and 26.0 at 2,048, 128^3 35.6 and 35.3.)
 Plan shared_plan(const mpcg_ctx *c, const Plan &p)
 {
     Plan q = p;
@@ -1050,6 +1052,10 @@ mpcg_status mpcg_solve(mpcg_ctx *c, const mpcg_csr *A, const double *b, double *
     DevState s;
     bool feat_timed = false;
     double bnorm = 0.0;
+    const Plan ps = autoe ? shared_plan(c, p) : p;   // launches that may run beside the 2BFS
+    // the FP64 phase: on ps where it may have started beside the 2BFS, i.e.
+    // from the tightest candidate's state
+    const Plan *pd = &p;
     bool spec_final = false;      // the FP64 phase is the speculative one (its restart residual below)
     double spec_rr_final = 0.0;
 
@@ -1086,7 +1092,6 @@ mpcg_status mpcg_solve(mpcg_ctx *c, const mpcg_csr *A, const double *b, double *
                 (void)hipEventSynchronize(c->tm[2]);
                 bfs_done.store(1);
             });
-            const Plan ps = shared_plan(c, p);   // FP32 launches beside the BFS
             DevState sp0;
             rc = fp32_prefix(c, ps, b, c->opt.k0, &sp0);
             s = sp0;
@@ -1133,6 +1138,7 @@ mpcg_status mpcg_solve(mpcg_ctx *c, const mpcg_csr *A, const double *b, double *
             if (exact) S.flags |= MPCG_FLAG_KNN_EXACT;
             if (bfs_dia) S.flags |= MPCG_FLAG_BFS_DIA;
             spec_keep = spec64 && cls - 2 == kNumEps - 1;
+            if (cls - 2 == kNumEps - 1) pd = &ps;
             if (!broke) {
                 const int ci = cls - 2;
                 if (s.cross_iter[ci] >= 0) {
@@ -1146,7 +1152,7 @@ mpcg_status mpcg_solve(mpcg_ctx *c, const mpcg_csr *A, const double *b, double *
                     const double thr1 = abs_tol ? e1 : e1 * std::sqrt(sp0.bnorm2);
                     launch_set_phase(c->stream, p.st, thr1, maxit1, c->opt.k0);
                     HIPCHK(hipGetLastError());
-                    rc = cg_loop<float>(c, p, x32, r32, q32, dA32, dB32, it_next, 0, &s);
+                    rc = cg_loop<float>(c, ps, x32, r32, q32, dA32, dB32, it_next, 0, &s);
                     if (rc != MPCG_OK) return rc;
                 }
                 // otherwise the run-ahead stopped (breakdown or maxit1) before
@@ -1172,13 +1178,13 @@ mpcg_status mpcg_solve(mpcg_ctx *c, const mpcg_csr *A, const double *b, double *
         if (spec_keep) {
             // the speculative FP64 phase is the chosen one: it continues
             if (s64.live) {
-                rc = cg_loop<double>(c, p, x, r64, q64, dA64, dB64, it64_next, 0, &s64);
+                rc = cg_loop<double>(c, *pd, x, r64, q64, dA64, dB64, it64_next, 0, &s64);
                 if (rc != MPCG_OK) return rc;
             }
         } else {
             HIPCHK(hipEventRecord(c->tm[3], c->stream));
             // restart in FP64 from float64(x~) with a freshly computed residual
-            run_restart(c->stream, p, x32_src, x, b, r64, dA64, dB64, 0, eps2, abs_tol, maxit2);
+            run_restart(c->stream, *pd, x32_src, x, b, r64, dA64, dB64, 0, eps2, abs_tol, maxit2);
             HIPCHK(hipGetLastError());
         }
     } else {
@@ -1199,13 +1205,13 @@ mpcg_status mpcg_solve(mpcg_ctx *c, const mpcg_csr *A, const double *b, double *
         const double thr2 = abs_tol ? eps2 : eps2 * bnorm;
         for (;;) {
             if (s.live) {
-                rc = cg_loop<double>(c, p, x, r64, q64, dA64, dB64, s.iter, s.iter, &s);
+                rc = cg_loop<double>(c, *pd, x, r64, q64, dA64, dB64, s.iter, s.iter, &s);
                 if (rc != MPCG_OK) return rc;
             }
             if (s.reason == kMaxit) { rc = MPCG_ENOCONV; break; }
             if (s.reason == kNotSpd) { rc = MPCG_ENOTSPD; break; }
             if (s.reason == kNonFinite) { rc = MPCG_ENONFINITE; break; }
-            run_resid(c->stream, p, x, b);
+            run_resid(c->stream, *pd, x, b);
             HIPCHK(hipGetLastError());
             rc = read_state(c, p, &s);
             if (rc != MPCG_OK) return rc;
@@ -1215,13 +1221,13 @@ mpcg_status mpcg_solve(mpcg_ctx *c, const mpcg_csr *A, const double *b, double *
             if (S.restarts >= c->opt.max_restarts) { rc = MPCG_ENOCONV; break; }
             S.restarts++;
             S.flags |= MPCG_FLAG_FINAL_RESTARTED;
-            run_restart(c->stream, p, nullptr, x, b, r64, dA64, dB64, s.iter, eps2, abs_tol, maxit2);
+            run_restart(c->stream, *pd, nullptr, x, b, r64, dA64, dB64, s.iter, eps2, abs_tol, maxit2);
             HIPCHK(hipGetLastError());
             rc = read_state(c, p, &s);
             if (rc != MPCG_OK) return rc;
         }
         if (rc != MPCG_OK && S.relres_final_true == 0.0) {
-            run_resid(c->stream, p, x, b);
+            run_resid(c->stream, *pd, x, b);
             DevState s2;
             if (read_state(c, p, &s2) == MPCG_OK) S.relres_final_true = std::sqrt(s2.resid2) / bnorm;
         }
