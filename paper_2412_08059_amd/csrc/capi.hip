@@ -239,6 +239,11 @@ SpmvShape spmv_shape(int64_t n, int64_t nnz, int value_bytes, int num_cu)
 
 namespace {
 
+// segmented sweeps of narrow bands from here on (us, queue kernels against
+// segments: one BFS 253 / 322 at 4,096 rows, 398 / 324 at 8,192; features 748 /
+// 683 and 1,035 / 684)
+constexpr int64_t kSegMinRows = 6144;
+
 struct Plan {
     Layout L;
     int32_t n = 0;
@@ -602,6 +607,10 @@ BfsBufs bfs_bufs(const Plan &p, bool shared = false)
     }
     b.dia_h = 0;
     b.dia_two = 0;
+    // a band of half-width 8 or less: its levels hold a few vertices each, and
+    // the segmented sweeps cost a few passes over the segments instead of n / 8
+    // dependent levels
+    b.seg = p.band <= kSegBand && p.n >= kSegMinRows;
     b.dist = p.at<int32_t>(p.L.dist);
     b.q0 = p.at<QEnt>(p.L.q0);
     b.q1 = p.at<QEnt>(p.L.q1);
@@ -665,6 +674,25 @@ mpcg_status dia_prepare(const Chan &ch, const Plan &p, BfsBufs *bb)
     return MPCG_OK;
 }
 
+// A sweep of a narrow band in segments; *ok = 0 when it gave up (its guard is
+// cleared: the queue kernels take the sweep).
+mpcg_status seg_sweep(const Chan &ch, const Plan &p, const BfsBufs &bb, int32_t src, bool want_dist, DevState *out,
+                      bool *ok)
+{
+    launch_seg_sweep(ch.s, bb, src, want_dist);
+    HIPCHK(hipGetLastError());
+    const mpcg_status rc = read_state(ch, p, out);
+    if (rc != MPCG_OK) return rc;
+    *ok = out->guard == 0;
+    if (!*ok) {
+        out->guard = 0;
+        HIPCHK(hipMemsetAsync(&p.st->guard, 0, sizeof(int32_t), ch.s));
+    }
+    out->bfs_ecc = (int32_t)(out->comp_best >> 32);
+    out->bfs_far = (int32_t)(0xffffffffu - (uint32_t)(out->comp_best & 0xffffffffull));
+    return MPCG_OK;
+}
+
 mpcg_status bfs_run(const Chan &ch, const Plan &p, const BfsBufs &bb, DevState *out)
 {
     if (bb.dia && bb.dia_h > 0) {   // temporal tiles: dia_h levels per launch
@@ -709,6 +737,26 @@ mpcg_status bfs_run(const Chan &ch, const Plan &p, const BfsBufs &bb, DevState *
     return read_state(ch, p, out);
 }
 
+// One single-source sweep (launch_seg_prepare done if bb->seg): out's
+// bfs_visited, bfs_ecc and bfs_far, and the distances in bb->dist unless they
+// are not wanted and the sweep runs in segments.
+mpcg_status sweep_from(const Chan &ch, const Plan &p, BfsBufs *bb, int32_t src, bool want_dist, DevState *out)
+{
+    if (bb->seg) {
+        bool ok = false;
+        const mpcg_status rc = seg_sweep(ch, p, *bb, src, want_dist, out, &ok);
+        if (rc != MPCG_OK || ok) return rc;
+        bb->seg = 0;   // its segments' data is overwritten from here on
+    }
+    if (bb->dia) {
+        launch_dia_seed(ch.s, *bb, src);
+        launch_dia_ring_seed(ch.s, *bb, src);
+    } else {
+        launch_bfs_seed_single(ch.s, *bb, src);
+    }
+    return bfs_run(ch, p, *bb, out);
+}
+
 // 2BFS per component; fills pdiam, bfs_t, bfs_u, n_components.
 mpcg_status pseudo_diameter_with(const Chan &ch, const Plan &p, BfsBufs bb, mpcg_features_t *f, int *dia_used)
 {
@@ -716,22 +764,14 @@ mpcg_status pseudo_diameter_with(const Chan &ch, const Plan &p, BfsBufs bb, mpcg
     *dia_used = 0;
     mpcg_status rc = dia_prepare(ch, p, &bb);
     if (rc != MPCG_OK) return rc;
-    auto seed = [&](int32_t v) {
-        if (bb.dia) {
-            launch_dia_seed(ch.s, bb, v);
-            launch_dia_ring_seed(ch.s, bb, v);
-        } else {
-            launch_bfs_seed_single(ch.s, bb, v);
-        }
-    };
-    seed(0);
-    rc = bfs_run(ch, p, bb, &s);
+    if (bb.dia) bb.seg = 0;
+    if (bb.seg) launch_seg_prepare(ch.s, bb);
+    rc = sweep_from(ch, p, &bb, 0, false, &s);
     if (rc != MPCG_OK) return rc;
     if (s.guard) return MPCG_EDEVICE;
     if (s.bfs_visited == p.n) {
         const int32_t t = s.bfs_far;
-        seed(t);
-        rc = bfs_run(ch, p, bb, &s);
+        rc = sweep_from(ch, p, &bb, t, false, &s);
         if (rc != MPCG_OK) return rc;
         f->pdiam = s.bfs_ecc;
         f->bfs_t = t;
@@ -1311,23 +1351,15 @@ mpcg_status mpcg_bfs(mpcg_ctx *c, const mpcg_csr *A, int64_t src, int32_t *dist,
     BfsBufs bb = bfs_bufs(p);
     rc = dia_prepare(c->main, p, &bb);
     if (rc != MPCG_OK) return rc;
-    auto seed = [&]() {
-        if (bb.dia) {
-            launch_dia_seed(c->stream, bb, (int32_t)src);
-            launch_dia_ring_seed(c->stream, bb, (int32_t)src);
-        } else {
-            launch_bfs_seed_single(c->stream, bb, (int32_t)src);
-        }
-    };
-    seed();
+    if (bb.dia) bb.seg = 0;
+    if (bb.seg) launch_seg_prepare(c->stream, bb);
     DevState s;
-    rc = bfs_run(c->main, p, bb, &s);
+    rc = sweep_from(c->main, p, &bb, (int32_t)src, true, &s);
     if (rc == MPCG_EDEVICE && bb.persist) {   // see pseudo_diameter
         HIPCHK(hipStreamSynchronize(c->stream));
         HIPCHK(hipMemsetAsync(&p.st->guard, 0, sizeof(int32_t), c->stream));
         bb.persist = 0;
-        seed();
-        rc = bfs_run(c->main, p, bb, &s);
+        rc = sweep_from(c->main, p, &bb, (int32_t)src, true, &s);
     }
     if (rc != MPCG_OK) return rc;
     HIPCHK(hipMemcpyAsync(dist, bb.dist, sizeof(int32_t) * (size_t)p.n, hipMemcpyDeviceToDevice,
@@ -1417,19 +1449,18 @@ mpcg_status mpcg_diameter_multi(mpcg_ctx *c, const mpcg_csr *A, const int32_t *s
     d.best_start = -1;
     BfsBufs bb = bfs_bufs(p);
     bb.persist = 0;   // one launch per level: needs no co-residency
+    if (bb.seg) launch_seg_prepare(c->stream, bb);
     // the per-component key array is not used by single-source sweeps
     unsigned long long *hist = bb.best;
     launch_fill_f64(c->stream, reinterpret_cast<double *>(hist), p.n, 0.0);
     int64_t max_ecc = 0;
     for (int32_t i = 0; i < count; ++i) {
         DevState s1, s2;
-        launch_bfs_seed_single(c->stream, bb, starts[i]);
-        rc = bfs_run(c->main, p, bb, &s1);
+        rc = sweep_from(c->main, p, &bb, starts[i], true, &s1);
         if (rc != MPCG_OK) return rc;
         launch_dist_hist(c->stream, bb.dist, p.n, hist);
         if (s1.bfs_ecc > max_ecc) max_ecc = s1.bfs_ecc;
-        launch_bfs_seed_single(c->stream, bb, s1.bfs_far);
-        rc = bfs_run(c->main, p, bb, &s2);
+        rc = sweep_from(c->main, p, &bb, s1.bfs_far, false, &s2);
         if (rc != MPCG_OK) return rc;
         if (s2.bfs_ecc > d.pdiam_multi) {
             d.pdiam_multi = s2.bfs_ecc;

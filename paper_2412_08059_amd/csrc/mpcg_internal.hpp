@@ -37,6 +37,7 @@ constexpr int64_t kInfinityCacheBytes = 256ll << 20;   // MI355X last-level (Inf
 constexpr int kNumXcd = 8;            // MI355X: blocks are dispatched round-robin over 8 XCDs
 constexpr int kMaxGrid = 2048;        // largest grid of a kernel that writes reduction partials
 constexpr int kUpdateGrid = 1024;     // blocks of a CG update launch: fewer partials for the next product
+constexpr int kSegBand = 8;           // widest band of the segmented BFS (kernels_bseg.hip)
 constexpr int kDsMax = 8;             // distances |i - j| > 0 that diagonal storage handles
 constexpr int kSgprCap = 80;          // scalar registers with which eight waves fit on a SIMD
 constexpr int kSpmvBlocksPerCu = 5;   // 32 KB of LDS per block, 160 KB per CU
@@ -346,7 +347,14 @@ struct BfsBufs {
     int32_t *ring_cnt, *ring_min;   // kDiaRing slots each
     int32_t *part_cnt, *part_min;   // level kernels: 2 parities x 2 levels x kDiaPartMax per-block partials each
     int32_t dia_two;                // two levels per launch (k_dia_level2)
+    int32_t seg;                    // narrow band: sweeps in segments (kernels_bseg.hip)
 };
+// Segmented BFS of a narrow band (band <= kSegBand): the segments' own
+// distances once per matrix, then a sweep from src.  A sweep leaves
+// bfs_visited, comp_best = (ecc << 32) | ~far (of the farthest vertex, ties to
+// the smallest index), the distances if asked for, and guard = 1 if it gave up.
+void launch_seg_prepare(hipStream_t s, const BfsBufs &b);
+void launch_seg_sweep(hipStream_t s, const BfsBufs &b, int32_t src, bool want_dist);
 // Diagonal structure: st->dia_over / dia_off from the CSR pattern (cleared
 // first); then, with b.doff filled from them, the masks.  Columns outside
 // [0, n) are ignored.
