@@ -205,7 +205,9 @@ mpcg_status mpcg_solve(mpcg_ctx *ctx, const mpcg_csr *A, const double *b, double
 mpcg_status mpcg_solve_noalloc(mpcg_ctx *ctx, const mpcg_csr *A, const double *b, double *x, double eps1,
                                double eps2, mpcg_stats *stats);
 
-/* y = A x with the solver's SpMV kernel (one fma chain per row in CSR order).
+/* y = A x (one fma chain per row in CSR order, the bits of the solver's
+ * products).  spmv_variant 0 checks A and forms the product in one pass over
+ * the CSR arrays; the explicit variants build their storage and use it.
  * precision 64: x, y float64; precision 32: x, y float32 and A rounded to
  * float32 (round to nearest even).  For parity tests and bandwidth timing. */
 mpcg_status mpcg_spmv(mpcg_ctx *ctx, const mpcg_csr *A, int32_t precision, const void *x, void *y);

@@ -291,14 +291,29 @@ mpcg_status read_state(const Chan &ch, const Plan &p, DevState *out)
 
 mpcg_status read_state(mpcg_ctx *c, const Plan &p, DevState *out) { return read_state(c->main, p, out); }
 
+// What can be said of A without reading it.
+bool csr_args_ok(const mpcg_ctx *c, const mpcg_csr *A)
+{
+    return c && A && A->n > 0 && A->n < 0x7fffffff && A->nnz >= 0 && A->nnz < 0x7fffffff && A->row_ptr &&
+           (A->nnz == 0 || (A->col_idx && A->val));
+}
+
+// The checks' verdict on the entries.
+mpcg_status ingest_status(int32_t err)
+{
+    if (err & (kErrRowPtr | kErrCol | kErrUnsorted)) return MPCG_EINVAL;
+    if (err & (kErrNonFiniteA | kErrNonFiniteB)) return MPCG_ENONFINITE;
+    if (err & kErrDiag) return MPCG_ENOTSPD;   // Jacobi needs a positive diagonal (any SPD A has one)
+    return MPCG_OK;
+}
+
 // Validate A (and b) on the device, convert row pointers / cast values when
 // asked, and read back the verdict before any result buffer is touched.
+// want_copy = false: the checks alone (the caller reads the CSR pattern).
 mpcg_status ingest(mpcg_ctx *c, const mpcg_csr *A, const double *b, bool need_val32, Plan *p,
-                   bool want_diag = false)
+                   bool want_diag = false, bool want_copy = true)
 {
-    if (!c || !A || A->n <= 0 || A->n >= 0x7fffffff || A->nnz < 0 || A->nnz >= 0x7fffffff ||
-        !A->row_ptr || (A->nnz > 0 && (!A->col_idx || !A->val)))
-        return MPCG_EINVAL;
+    if (!csr_args_ok(c, A)) return MPCG_EINVAL;
     p->L = plan_layout(A->n, A->nnz);
     if (!c->ws || c->ws_bytes < p->L.total) return MPCG_ENOMEM;
     p->ws = c->ws;
@@ -325,13 +340,13 @@ mpcg_status ingest(mpcg_ctx *c, const mpcg_csr *A, const double *b, bool need_va
                        p->at<int32_t>(p->L.ingest_blk), p->st);
     // symmetric matrices on few diagonals: diagonal storage, in the SELL value
     // arrays; what its passes find unfit (or an explicit variant) goes to SELL
-    const bool try_ds = c->opt.spmv_variant == 0;
+    const bool try_ds = want_copy && c->opt.spmv_variant == 0;
     if (try_ds)
         launch_ds_ingest(c->stream, p->rp, A->col_idx, A->val, p->n, A->nnz, p->L.sell_cap, v64, v32,
                          want_diag ? p->dg64 : nullptr, want_diag ? p->dg32 : nullptr, p->st);
     auto general = [&]() {
         launch_ingest_sell(c->stream, p->rp, A->col_idx, A->val, p->n, wid, soff, p->L.sell_cap,
-                           c->force_csr ? 0 : 1, p->ws + p->L.sell_col, v64, v32, p->st);
+                           want_copy && !c->force_csr ? 1 : 0, p->ws + p->L.sell_col, v64, v32, p->st);
         if (want_diag) launch_diag(c->stream, p->rp, A->col_idx, A->val, p->n, p->dg64, p->dg32, p->st);
     };
     auto verdict = [&]() -> mpcg_status {
@@ -357,12 +372,11 @@ mpcg_status ingest(mpcg_ctx *c, const mpcg_csr *A, const double *b, bool need_va
     const DevState s = c->hst[1];
     const int64_t padded = c->hst[2].spare_i64;
     p->band = s.max_band;
-    if (s.ing_err & (kErrRowPtr | kErrCol | kErrUnsorted)) return MPCG_EINVAL;
-    if (s.ing_err & (kErrNonFiniteA | kErrNonFiniteB)) return MPCG_ENONFINITE;
-    if (s.ing_err & kErrDiag) return MPCG_ENOTSPD;   // Jacobi needs a positive diagonal (any SPD A has one)
+    rc = ingest_status(s.ing_err);
+    if (rc != MPCG_OK) return rc;
     // the entry kernel filled the SELL copy under exactly this condition
     p->use_ds = s.ds_cand != 0;
-    p->use_sell = !p->use_ds && !c->force_csr && padded <= p->L.sell_cap;
+    p->use_sell = want_copy && !p->use_ds && !c->force_csr && padded <= p->L.sell_cap;
     p->sh64 = spmv_shape(A->n, A->nnz, 8, c->num_cu);
     p->sh32 = spmv_shape(A->n, A->nnz, 4, c->num_cu);
     p->nup = vec_grid(A->n);
@@ -1326,6 +1340,29 @@ mpcg_status mpcg_solve_noalloc(mpcg_ctx *c, const mpcg_csr *A, const double *b, 
 mpcg_status mpcg_spmv(mpcg_ctx *c, const mpcg_csr *A, int32_t precision, const void *x, void *y)
 {
     if (!c || !x || !y || (precision != 32 && precision != 64)) return MPCG_EINVAL;
+    if (c->opt.spmv_variant == 0) {   // no storage format asked for: one pass over the CSR arrays
+        if (!csr_args_ok(c, A)) return MPCG_EINVAL;
+        const Layout L = plan_layout(A->n, A->nnz);
+        if (!c->ws || c->ws_bytes < L.total) return MPCG_ENOMEM;
+        DevState *st = reinterpret_cast<DevState *>(c->ws + L.state);
+        HIPCHK(hipMemsetAsync(st, 0, sizeof(DevState), c->stream));
+        HIPCHK(hipEventRecord(c->tm[5], c->stream));
+        if (precision == 64)
+            launch_spmv_checked<double>(c->stream, A->row_ptr, A->row_ptr_is_i64 ? 1 : 0, A->col_idx, A->val,
+                                        (int32_t)A->n, A->nnz, static_cast<const double *>(x),
+                                        reinterpret_cast<double *>(c->ws + L.q64), static_cast<double *>(y), st);
+        else
+            launch_spmv_checked<float>(c->stream, A->row_ptr, A->row_ptr_is_i64 ? 1 : 0, A->col_idx, A->val,
+                                       (int32_t)A->n, A->nnz, static_cast<const float *>(x),
+                                       reinterpret_cast<float *>(c->ws + L.q32), static_cast<float *>(y), st);
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipEventRecord(c->tm[6], c->stream));
+        HIPCHK(hipMemcpyAsync(&c->hst[2].ing_err, &st->ing_err, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(hipStreamSynchronize(c->stream));
+        const mpcg_status rc1 = ingest_status(c->hst[2].ing_err);
+        if (rc1 == MPCG_OK) c->last_kernel_ms = elapsed(c->tm[5], c->tm[6]);
+        return rc1;
+    }
     Plan p;
     mpcg_status rc = ingest(c, A, nullptr, precision == 32, &p);
     if (rc != MPCG_OK) return rc;
@@ -1346,7 +1383,7 @@ mpcg_status mpcg_bfs(mpcg_ctx *c, const mpcg_csr *A, int64_t src, int32_t *dist,
 {
     if (!c || !A || !dist || src < 0 || src >= A->n) return MPCG_EINVAL;
     Plan p;
-    mpcg_status rc = ingest(c, A, nullptr, false, &p);
+    mpcg_status rc = ingest(c, A, nullptr, false, &p, false, false);
     if (rc != MPCG_OK) return rc;
     BfsBufs bb = bfs_bufs(p);
     rc = dia_prepare(c->main, p, &bb);
@@ -1438,7 +1475,7 @@ mpcg_status mpcg_diameter_multi(mpcg_ctx *c, const mpcg_csr *A, const int32_t *s
     for (int32_t i = 0; i < count; ++i)
         if (starts[i] < 0 || (int64_t)starts[i] >= A->n) return MPCG_EINVAL;
     Plan p;
-    mpcg_status rc = ingest(c, A, nullptr, false, &p);
+    mpcg_status rc = ingest(c, A, nullptr, false, &p, false, false);
     if (rc != MPCG_OK) return rc;
     mpcg_features_t f{};
     rc = pseudo_diameter(c, c->main, p, &f);

@@ -233,6 +233,132 @@ void launch_ingest_sell(hipStream_t s, const int32_t *rp32, const int32_t *col, 
                        allow_fill, scol, sv64, sv32, st);
 }
 
+// ------------------------------------------------------ checked product --
+//
+// One product with no storage to keep (mpcg_spmv): checking the CSR arrays,
+// writing a copy and reading it back is three passes over the matrix for a
+// product that needs one.  Here one pass checks the rows and forms the product
+// in scratch; a second kernel hands it over if every check passed.  What bounds
+// it: the 12 bytes an entry (4M-row band, 68 M entries, FP64: the call 1,113 ->
+// 257 us, of which the pass is 3.6 TB/s; 128^3 stencil 275 -> 86 us; 1,000 rows
+// 66 -> 34 us, the launches and one read-back).
+//
+// Wave per 64 rows: the row pointers are checked before anything is read
+// through them; the entries come in chunks of kChkEntries with coalesced
+// loads, each checked and its vector element gathered as it arrives, and each
+// lane runs its row's fma chain over the chunk from LDS in CSR order, starting
+// from 0 (the bits of the other products), checking the order on the way.
+constexpr int kChkBatch = 5;                    // loads of a lane issued together
+constexpr int kChkEntries = 2 * 64 * kChkBatch;
+
+template <typename T>
+__global__ void __launch_bounds__(kBlock)
+k_spmv_checked(const void *rp_in, int rp_is_i64, const int32_t *__restrict__ col, const double *__restrict__ val,
+               int32_t n, int64_t nnz, const T *__restrict__ x, T *__restrict__ y, DevState *st)
+{
+    __shared__ T s_v[kBlock / 64][kChkEntries], s_g[kBlock / 64][kChkEntries];
+    __shared__ int32_t s_c[kBlock / 64][kChkEntries];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    T *sv = s_v[w], *sg = s_g[w];
+    int32_t *sc = s_c[w];
+    const int nslices = (n + 63) / 64;
+    int err = 0;
+    for (int s = blockIdx.x * (kBlock / 64) + w; s < nslices; s += gridDim.x * (kBlock / 64)) {
+        const int64_t row = (int64_t)s * 64 + lane;
+        int64_t lo = 0, hi = 0;
+        bool bad = false;
+        if (row < n) {
+            if (rp_is_i64) {
+                lo = static_cast<const int64_t *>(rp_in)[row];
+                hi = static_cast<const int64_t *>(rp_in)[row + 1];
+            } else {
+                lo = static_cast<const int32_t *>(rp_in)[row];
+                hi = static_cast<const int32_t *>(rp_in)[row + 1];
+            }
+            bad = (row == 0 && lo != 0) || (row == n - 1 && hi != nnz) || lo < 0 || hi < lo || hi > nnz;
+        }
+        if (__ballot(bad) != 0ull) {   // nothing is read through them
+            err |= kErrRowPtr;
+            continue;
+        }
+        const int last = min(63, n - 1 - s * 64);
+        const int b0 = __builtin_amdgcn_readfirstlane((int)lo), b1 = __builtin_amdgcn_readlane((int)hi, last);
+        const int rlo = (int)lo, rhi = (int)hi;
+        T acc = T(0);
+        int prev = -1;
+        for (int c0 = b0; c0 < b1; c0 += kChkEntries) {
+            const int cn = min(kChkEntries, b1 - c0);
+            for (int j0 = 0; j0 < cn; j0 += 64 * kChkBatch) {
+                int c[kChkBatch];
+                double v[kChkBatch];
+                T g[kChkBatch];
+#pragma unroll
+                for (int j = 0; j < kChkBatch; ++j) {
+                    const int k = j0 + j * 64 + lane;
+                    c[j] = 0;
+                    v[j] = 0.0;
+                    if (k < cn) {
+                        c[j] = col[c0 + k];
+                        v[j] = val[c0 + k];
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < kChkBatch; ++j) {
+                    const bool in = c[j] >= 0 && c[j] < n;
+                    if (!in) err |= kErrCol;
+                    if (!isfinite(v[j])) err |= kErrNonFiniteA;
+                    g[j] = x[in ? c[j] : 0];
+                }
+#pragma unroll
+                for (int j = 0; j < kChkBatch; ++j) {
+                    const int k = j0 + j * 64 + lane;
+                    sc[k] = c[j];
+                    sv[k] = (T)v[j];
+                    sg[k] = g[j];
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (row < n) {
+                const int ke = min(rhi, c0 + cn) - c0;
+#pragma unroll 4
+                for (int k = max(rlo, c0) - c0; k < ke; ++k) {
+                    const int c = sc[k];
+                    if (c <= prev) err |= kErrUnsorted;
+                    prev = c;
+                    acc = fma_t<T>(sv[k], sg[k], acc);
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+        if (row < n) y[row] = acc;
+    }
+    for (int o = 32; o > 0; o >>= 1) err |= __shfl_xor(err, o, 64);
+    if (lane == 0 && err) atomicOr(&st->ing_err, err);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kBlock) k_commit(const T *__restrict__ from, T *__restrict__ to, int32_t n, const DevState *st)
+{
+    if (st->ing_err) return;
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock)
+        to[i] = from[i];
+}
+
+template <typename T>
+void launch_spmv_checked(hipStream_t s, const void *rp, int rp_is_i64, const int32_t *col, const double *val, int32_t n,
+                         int64_t nnz, const T *x, T *scratch, T *y, DevState *st)
+{
+    const int ngroups = ((n + 63) / 64 + kBlock / 64 - 1) / (kBlock / 64);
+    hipLaunchKernelGGL((k_spmv_checked<T>), dim3(ngroups), dim3(kBlock), 0, s, rp, rp_is_i64, col, val, n, nnz, x, scratch, st);
+    hipLaunchKernelGGL((k_commit<T>), dim3(ngroups < 4096 ? ngroups : 4096), dim3(kBlock), 0, s, scratch, y, n, st);
+}
+
+template void launch_spmv_checked<float>(hipStream_t, const void *, int, const int32_t *, const double *, int32_t,
+                                         int64_t, const float *, float *, float *, DevState *);
+template void launch_spmv_checked<double>(hipStream_t, const void *, int, const int32_t *, const double *, int32_t,
+                                          int64_t, const double *, double *, double *, DevState *);
+
 // -------------------------------------------------------------- kernels --
 
 // kSellDir + kSellCgD: the CG product split in two launches for matrices

@@ -290,6 +290,12 @@ void launch_sell_resid(hipStream_t s, const SellMat &m, const double *x64, const
 template <typename T>
 void launch_sell_plain(hipStream_t s, const SellMat &m, const T *x, T *y);
 
+// y = A x in one pass over the CSR arrays, checks included (mpcg_spmv): errors
+// into st->ing_err, y written only if there are none.
+template <typename T>
+void launch_spmv_checked(hipStream_t s, const void *rp, int rp_is_i64, const int32_t *col, const double *val, int32_t n,
+                         int64_t nnz, const T *x, T *scratch, T *y, DevState *st);
+
 // ----- diagonal storage (kernels_ds.hip) -----
 // After k_ingest_rows: distances sampled, planes (and diag(A) if dg64) filled
 // and the symmetry checked, all on the device; st->ds_cand && !st->ds_miss

@@ -73,6 +73,7 @@ CASES = [
     ("lap2d", lambda: W.poisson2d(67)),
     ("lap3d", lambda: W.varcoef3d(17, seed=3)),
     ("band_600k", lambda: W.banded(600_001, 3, seed=4)),              # several slice groups per block
+    ("star", lambda: W.star(3000)),                                   # a row of several chunks
     ("unsymmetric", lambda: _unsymmetric(1500)),
     ("one_sided", lambda: _one_sided(1500)),
     ("rare_diagonal", lambda: _rare_diagonal(40_000)),
@@ -137,5 +138,19 @@ def test_malformed_entries_are_reported(bad):
     for variant in (0, 1):
         s = Solver(a.n, a.nnz, spmv_variant=variant)
         st, _, _ = s.solve(A, torch.from_numpy(b).cuda(), 1e-3, 1e-8)
-        s.close()
         assert st == want, (bad, variant, st)
+        for prec, dt in ((64, torch.float64), (32, torch.float32)):
+            st, _ = s.spmv(A, torch.ones(a.n, dtype=dt, device="cuda"), prec)
+            assert st == (want if bad != "inf_b" else 0), (bad, variant, prec, st)
+        s.close()
+    if bad == "column":   # row pointers: nothing is read through them, y stays as it was
+        from paper_2412_08059_amd import capi
+        rp = a.row_ptr.copy()
+        rp[2000] = a.nnz + 10_000_000
+        bad_a = DeviceCSR.from_host(W.CSR(a.n, rp, a.col, a.val))
+        s = Solver(a.n, a.nnz)
+        x = torch.ones(a.n, dtype=torch.float64, device="cuda")
+        y = torch.full_like(x, 7.0)
+        assert capi.mpcg_spmv(s.ctx, bad_a.desc, 64, x.data_ptr(), y.data_ptr()) == -1
+        assert bool((y == 7.0).all())
+        s.close()
