@@ -243,6 +243,7 @@ namespace {
 // segments: one BFS 253 / 322 at 4,096 rows, 398 / 324 at 8,192; features 748 /
 // 683 and 1,035 / 684)
 constexpr int64_t kSegMinRows = 6144;
+constexpr int32_t kDiaBlockMinRows = 64;
 
 struct Plan {
     Layout L;
@@ -637,54 +638,88 @@ BfsBufs bfs_bufs(const Plan &p, bool shared = false)
 
 // The bit-parallel levels over diagonals replace the queue kernels for a
 // sweep when the tuning asks for them (bfs_dia: 1 on patterns wider than the
-// one-workgroup kernel's narrow-band window, above 2^16 rows; 2 whenever it
-// qualifies) and the pattern lies on at most kDiaMax diagonals.  Returns
-// MPCG_OK whether or not it qualifies (bb->dia says which).
+// narrow bands that the segmented sweeps and the one-workgroup kernel take; 2
+// whenever it qualifies) and the pattern lies on at most kDiaMax diagonals.
+// Returns MPCG_OK whether or not it qualifies (bb->dia says which).
 mpcg_status dia_prepare(const Chan &ch, const Plan &p, BfsBufs *bb)
 {
     bb->dia = 0;
-    const int mode = p.tune.bfs_dia;
+    const int mode = p.tune.bfs_dia, tiles = p.tune.bfs_dia_tiles;
+    // one block holds all bit vectors (see below): worth it from small grids on
+    const bool small = tiles && bb->nwords <= kDiaBlockWords;
     // launch k expands level k: at most n levels, kept below the launch index wrap
-    if (mode == 0 || p.n >= (1 << 30) - 64 || (mode == 1 && (p.band <= 8 || p.n < (1 << 16)))) return MPCG_OK;
-    launch_dia_detect(ch.s, *bb);
-    HIPCHK(hipGetLastError());
-    DevState s;
-    mpcg_status rc = read_state(ch, p, &s);
-    if (rc != MPCG_OK) return rc;
-    if (s.dia_over || s.dia_off[0] == 0) return MPCG_OK;
-    bb->doff.nd = 0;
-    for (int t = 0; t < kDiaMax && s.dia_off[t] != 0; ++t) bb->doff.d[bb->doff.nd++] = s.dia_off[t];
+    if (mode == 0 || p.n >= (1 << 30) - 64 ||
+        (mode == 1 && (p.band <= 8 || p.n < (small ? kDiaBlockMinRows : 1 << 16))))
+        return MPCG_OK;
+    DiaOffs &o = bb->doff;
+    o.nd = 0;
+    if (p.use_ds) {   // diagonal storage knows the distances
+        for (int t = p.ds.nh - 1; t >= 0; --t) o.d[o.nd++] = -p.ds.d[t];
+        for (int t = 0; t < p.ds.nh; ++t) o.d[o.nd++] = p.ds.d[t];
+    } else {
+        launch_dia_detect(ch.s, *bb);
+        HIPCHK(hipGetLastError());
+        DevState s;
+        mpcg_status rc = read_state(ch, p, &s);
+        if (rc != MPCG_OK) return rc;
+        if (s.dia_over || s.dia_off[0] == 0) return MPCG_OK;
+        for (int t = 0; t < kDiaMax && s.dia_off[t] != 0; ++t) o.d[o.nd++] = s.dia_off[t];
+    }
     for (int t = 0; t < kDiaMax; ++t) {
-        if (t >= bb->doff.nd) bb->doff.d[t] = 0;
-        const int64_t m = -(int64_t)bb->doff.d[t];
-        bb->doff.q[t] = (int32_t)(m >= 0 ? m / 32 : -((-m + 31) / 32));   // floor(-d / 32)
-        bb->doff.r[t] = (int32_t)(m - 32 * (int64_t)bb->doff.q[t]);
+        if (t >= o.nd) o.d[t] = 0;
+        const int64_t m = -(int64_t)o.d[t];
+        o.q[t] = (int32_t)(m >= 0 ? m / 32 : -((-m + 31) / 32));   // floor(-d / 32)
+        o.r[t] = (int32_t)(m - 32 * (int64_t)o.q[t]);
     }
     launch_dia_masks(ch.s, *bb);
     HIPCHK(hipGetLastError());
     bb->dia = 1;
-    // temporal tiles: a tile's loaded range (kDiaTileWords) holds its own
-    // words and a halo of h R words on each side; h as large as keeps the
-    // own words at least half the range
-    int R = 1;
-    for (int t = 0; t < bb->doff.nd; ++t) {
-        const int d = bb->doff.d[t] < 0 ? -bb->doff.d[t] : bb->doff.d[t];
+    int R = 1;   // the most words a window reaches
+    for (int t = 0; t < o.nd; ++t) {
+        const int d = o.d[t] < 0 ? -o.d[t] : o.d[t];
         if (d / 32 + 1 > R) R = d / 32 + 1;
     }
     bb->dia_R = R;
     bb->dia_h = 0;
-    // Tiles pay when a launch forms many levels over several tiles: a tile's
-    // level runs on one CU, the per-level kernel's on the whole grid.
-    if (p.tune.bfs_dia_tiles && bb->doff.nd <= kDiaTileDiags && R <= kDiaPad && bb->nwords > kDiaTileWords) {
-        int h = kDiaTileWords / (4 * R);
+    bb->dia_blk = 0;
+    bb->dia_two = 0;
+    if (!tiles || o.nd > kDiaTileDiags) return MPCG_OK;   // one launch per level
+    // Several levels per launch, on words and masks that stay in a block: a
+    // level costs about 0.5 + 0.23 P us with P words for each of the block's
+    // 1,024 threads.
+    //   One block holds everything (up to kDiaBlockWords): no launch per level.
+    //   Temporal tiles: a tile's loaded range holds its own words and a halo of
+    //   h R words on each side, h as large as keeps the own words at least half
+    //   the range; a launch of h levels adds about 8 us (side 1,001: P = 2,
+    //   h = 15).  With h below kDiaTileMinLevels two levels per launch (chunks
+    //   with a 2R-word halo in LDS) are faster.
+    // The one with the least time per level is taken (us per level, one block
+    // against tiles: side 512 2.1 and 1.8, side 200 0.47 and 1.0).
+    float best = 0.0f;
+    if (small && R <= kDiaPad) {
+        int P = 1;
+        while (P * kDiaTileThreads < bb->nwords) P *= 2;
+        bb->dia_blk = 1;
+        best = 0.23f * (float)P;
+    }
+    for (int P = 2; P <= 8; P *= 2) {
+        int h = P * kDiaTileThreads / (4 * R);
         if (h > kDiaMaxLevels) h = kDiaMaxLevels;
-        if (h >= kDiaTileMinLevels) {
+        if (R > kDiaPad || h < kDiaTileMinLevels || P * kDiaTileThreads >= bb->nwords) continue;
+        const float cost = 8.0f / (float)h + 0.23f * (float)P;
+        if (best == 0.0f || cost < best) {
+            best = cost;
+            bb->dia_blk = 0;
+            bb->dia_P = P;
             bb->dia_h = h;
-            bb->dia_T = kDiaTileWords - 2 * h * R;
+            bb->dia_T = P * kDiaTileThreads - 2 * h * R;
         }
     }
-    // otherwise two levels per launch (chunks with a 2R-word halo in LDS)
-    bb->dia_two = p.tune.bfs_dia_tiles && bb->dia_h == 0 && bb->doff.nd <= kDiaTileDiags && R <= kDia2MaxReach;
+    if (bb->dia_blk) {
+        bb->dia_h = 0;
+        return MPCG_OK;
+    }
+    bb->dia_two = bb->dia_h == 0 && R <= kDia2MaxReach;
     return MPCG_OK;
 }
 
@@ -709,6 +744,15 @@ mpcg_status seg_sweep(const Chan &ch, const Plan &p, const BfsBufs &bb, int32_t 
 
 mpcg_status bfs_run(const Chan &ch, const Plan &p, const BfsBufs &bb, DevState *out)
 {
+    if (bb.dia && bb.dia_blk) {   // one block, one launch (more only beyond kDiaBlockLevels levels)
+        for (int k = 0;; ++k) {
+            launch_dia_block(ch.s, bb, k);
+            HIPCHK(hipGetLastError());
+            const mpcg_status rc = read_state(ch, p, out);
+            if (rc != MPCG_OK || out->bfs_done) return rc;
+            if ((int64_t)k * kDiaBlockLevels > (int64_t)p.n) return MPCG_EDEVICE;
+        }
+    }
     if (bb.dia && bb.dia_h > 0) {   // temporal tiles: dia_h levels per launch
         const int launches = 64 / bb.dia_h > 1 ? 64 / bb.dia_h : 1;
         int k = 0;
@@ -752,8 +796,8 @@ mpcg_status bfs_run(const Chan &ch, const Plan &p, const BfsBufs &bb, DevState *
 }
 
 // One single-source sweep (launch_seg_prepare done if bb->seg): out's
-// bfs_visited, bfs_ecc and bfs_far, and the distances in bb->dist unless they
-// are not wanted and the sweep runs in segments.
+// bfs_visited, bfs_ecc and bfs_far, and the distances in bb->dist (unless they
+// are not wanted and the sweep runs on bits).
 mpcg_status sweep_from(const Chan &ch, const Plan &p, BfsBufs *bb, int32_t src, bool want_dist, DevState *out)
 {
     if (bb->seg) {
@@ -762,13 +806,15 @@ mpcg_status sweep_from(const Chan &ch, const Plan &p, BfsBufs *bb, int32_t src, 
         if (rc != MPCG_OK || ok) return rc;
         bb->seg = 0;   // its segments' data is overwritten from here on
     }
-    if (bb->dia) {
-        launch_dia_seed(ch.s, *bb, src);
-        launch_dia_ring_seed(ch.s, *bb, src);
-    } else {
+    if (!bb->dia) {
         launch_bfs_seed_single(ch.s, *bb, src);
+        return bfs_run(ch, p, *bb, out);
     }
-    return bfs_run(ch, p, *bb, out);
+    BfsBufs b = *bb;
+    if (!want_dist) b.dist = nullptr;
+    launch_dia_seed(ch.s, b, src);
+    launch_dia_ring_seed(ch.s, b, src);
+    return bfs_run(ch, p, b, out);
 }
 
 // 2BFS per component; fills pdiam, bfs_t, bfs_u, n_components.

@@ -13,6 +13,7 @@
 // enqueue rounds without waiting for every level.
 
 #include "mpcg_internal.hpp"
+#include "wave_ops.hpp"
 
 namespace mpcg {
 
@@ -97,19 +98,11 @@ __device__ inline void astore_i32(int32_t *p, int v)
 
 __device__ inline int wave_max_i(int v)
 {
-    for (int off = 32; off > 0; off >>= 1) {
-        const int o = __shfl_xor(v, off, 64);
-        v = v > o ? v : o;
-    }
-    return v;
+    return wave_fold(v, [](int x, int y) { return x > y ? x : y; });
 }
 __device__ inline int wave_min_i(int v)
 {
-    for (int off = 32; off > 0; off >>= 1) {
-        const int o = __shfl_xor(v, off, 64);
-        v = v < o ? v : o;
-    }
-    return v;
+    return wave_fold(v, [](int x, int y) { return x < y ? x : y; });
 }
 
 // Where the window goes for a frontier with vertices in [fmin, fmax]
@@ -160,8 +153,7 @@ constexpr int kBitDone = 0, kBitMove = 1, kBitFlush = 2;
 
 __device__ inline int wave_sum_i(int v)
 {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    return wave_fold(v, [](int x, int y) { return x + y; });
 }
 
 __global__ void __launch_bounds__(kBfsSmallThreads)
@@ -1406,7 +1398,7 @@ __global__ void k_dia_seed(uint32_t *f0, uint32_t *v, int32_t *dist, int32_t src
     if (threadIdx.x == 0 && blockIdx.x == 0) {
         f0[src >> 5] = 1u << (src & 31);
         v[src >> 5] = 1u << (src & 31);
-        dist[src] = 0;
+        if (dist) dist[src] = 0;
         bfs_start(st, 1, src);
         st->dia_base = 0;
     }
@@ -1421,7 +1413,7 @@ void launch_dia_seed(hipStream_t s, const BfsBufs &b, int32_t src)
 {
     int g = (b.nwords + kBlock - 1) / kBlock;
     if (g > 1024) g = 1024;
-    launch_fill_i32(s, b.dist, b.n, -1);
+    if (b.dist) launch_fill_i32(s, b.dist, b.n, -1);
     hipLaunchKernelGGL(k_dia_clear, dim3(g), dim3(kBlock), 0, s, b.df0, b.df1, b.dv, b.nwords);
     hipLaunchKernelGGL(k_dia_seed, dim3(1), dim3(kBlock), 0, s, b.df0, b.dv, b.dist, src, b.part_cnt, b.part_min,
                        b.st);
@@ -1487,7 +1479,8 @@ k_dia_level(const uint32_t *__restrict__ fc, uint32_t *__restrict__ fn, uint32_t
             cnt += __popc(nb);
             const int v0 = 32 * w + __ffs(nb) - 1;
             mn = mn < v0 ? mn : v0;
-            for (uint32_t bb = nb; bb; bb &= bb - 1u) dist[32 * w + __ffs(bb) - 1] = L + 1;
+            if (dist)
+                for (uint32_t bb = nb; bb; bb &= bb - 1u) dist[32 * w + __ffs(bb) - 1] = L + 1;
         }
     }
     cnt = wave_sum_i(cnt);
@@ -1617,13 +1610,15 @@ k_dia_level2(const uint32_t *__restrict__ fc, uint32_t *__restrict__ fn, uint32_
                 c1 += __popc(own1);
                 const int v0 = 32 * w + __ffs(own1) - 1;
                 m1 = m1 < v0 ? m1 : v0;
-                for (uint32_t bb = own1; bb; bb &= bb - 1u) dist[32 * w + __ffs(bb) - 1] = L0 + 1;
+                if (dist)
+                    for (uint32_t bb = own1; bb; bb &= bb - 1u) dist[32 * w + __ffs(bb) - 1] = L0 + 1;
             }
             if (nb2) {
                 c2 += __popc(nb2);
                 const int v0 = 32 * w + __ffs(nb2) - 1;
                 m2 = m2 < v0 ? m2 : v0;
-                for (uint32_t bb = nb2; bb; bb &= bb - 1u) dist[32 * w + __ffs(bb) - 1] = L0 + 2;
+                if (dist)
+                    for (uint32_t bb = nb2; bb; bb &= bb - 1u) dist[32 * w + __ffs(bb) - 1] = L0 + 2;
             }
         }
         __syncthreads();   // LDS reused by the next chunk
@@ -1712,7 +1707,7 @@ void launch_dia_round(hipStream_t s, const BfsBufs &b)
 // eccentricity and the farthest vertex are the per-level kernels' integers.
 
 
-template <int ND>
+template <int ND, int P>
 __global__ void __launch_bounds__(kDiaTileThreads)
 k_dia_multi(const uint32_t *__restrict__ fin, uint32_t *__restrict__ fout, uint32_t *dv,
             const uint32_t *__restrict__ dm, int32_t *dist, int32_t nw, int32_t L0, int32_t h, int32_t T, int32_t R,
@@ -1721,9 +1716,8 @@ k_dia_multi(const uint32_t *__restrict__ fin, uint32_t *__restrict__ fout, uint3
     // F: frontier bits of the loaded range at LDS index kDiaPad + (w - lo),
     // zero outside it, so that a window needs no bounds test (words outside
     // [0, nw) fall in the zero parts; R <= kDiaPad)
-    constexpr int kF = kDiaTileWords + 2 * kDiaPad;
+    constexpr int kF = P * kDiaTileThreads + 2 * kDiaPad;
     __shared__ uint32_t F[2][kF];
-    __shared__ uint32_t V[kDiaTileWords];
     __shared__ int s_cnt[kDiaMaxLevels], s_min[kDiaMaxLevels];
     const int tid = threadIdx.x;
     if (blockIdx.x == 0 && tid < 64) {
@@ -1768,17 +1762,16 @@ k_dia_multi(const uint32_t *__restrict__ fin, uint32_t *__restrict__ fout, uint3
     }
     // thread-owned words w = lo + tid + j kDiaTileThreads; their masks stay in
     // registers for the launch (all loads issued together)
-    uint32_t mr[kDiaPerThread][ND];
+    uint32_t mr[P][ND], V[P], V0[P];
 #pragma unroll
-    for (int j = 0; j < kDiaPerThread; ++j) {
+    for (int j = 0; j < P; ++j) {
         const int w = lo + tid + j * kDiaTileThreads;
         const int wc = w < hi ? w : hi - 1;
 #pragma unroll
         for (int t = 0; t < ND; ++t) mr[j][t] = dm[(size_t)t * nw + wc];
-        if (w < hi) {
-            F[0][kDiaPad + w - lo] = fin[w];
-            V[w - lo] = dv[w];
-        }
+        V[j] = dv[wc];
+        V0[j] = V[j];
+        if (w < hi) F[0][kDiaPad + w - lo] = fin[w];
     }
     __syncthreads();
     for (int l = 0; l < h; ++l) {
@@ -1789,7 +1782,7 @@ k_dia_multi(const uint32_t *__restrict__ fin, uint32_t *__restrict__ fout, uint3
         const int vh = e + shrink < hi ? e + shrink : hi;
         int cnt = 0, mn = kIntMax;
 #pragma unroll
-        for (int j = 0; j < kDiaPerThread; ++j) {
+        for (int j = 0; j < P; ++j) {
             int w = lo + tid + j * kDiaTileThreads;
             // opaque per level: the window indices derived from w are formed
             // here, not hoisted out of the level loop (96 live registers)
@@ -1804,33 +1797,36 @@ k_dia_multi(const uint32_t *__restrict__ fin, uint32_t *__restrict__ fout, uint3
                     if (o.r[t]) win = __builtin_amdgcn_alignbit(cur[i0 + 1], win, o.r[t]);
                     nb |= win & mr[j][t];
                 }
-                const uint32_t vis = V[w - lo];
-                nb &= ~vis;
+                nb &= ~V[j];
                 nxt[iw] = nb;
-                if (nb) {
-                    V[w - lo] = vis | nb;
-                    if (w >= a && w < e) {
-                        cnt += __popc(nb);
-                        const int v0 = 32 * w + __ffs(nb) - 1;
-                        mn = mn < v0 ? mn : v0;
+                V[j] |= nb;
+                if (nb && w >= a && w < e) {
+                    cnt += __popc(nb);
+                    const int v0 = 32 * w + __ffs(nb) - 1;
+                    mn = mn < v0 ? mn : v0;
+                    if (dist)
                         for (uint32_t bb = nb; bb; bb &= bb - 1u) dist[32 * w + __ffs(bb) - 1] = L0 + l + 1;
-                    }
                 }
             }
         }
-        cnt = wave_sum_i(cnt);
-        mn = wave_min_i(mn);
-        if ((tid & 63) == 0 && cnt) {
-            atomicAdd(&s_cnt[l], cnt);
-            atomicMin(&s_min[l], mn);
+        if (__ballot(cnt != 0) != 0ull) {
+            cnt = wave_sum_i(cnt);
+            mn = wave_min_i(mn);
+            if ((tid & 63) == 0) {
+                atomicAdd(&s_cnt[l], cnt);
+                atomicMin(&s_min[l], mn);
+            }
         }
         __syncthreads();
     }
     const uint32_t *fl = F[h & 1];
-    for (int w = a + tid; w < e; w += kDiaTileThreads) {   // changed words only: see k_dia_clear
-        const uint32_t fw = fl[kDiaPad + w - lo], vw = V[w - lo];
+#pragma unroll
+    for (int j = 0; j < P; ++j) {   // changed words only: see k_dia_clear
+        const int w = lo + tid + j * kDiaTileThreads;
+        if (w < a || w >= e) continue;
+        const uint32_t fw = fl[kDiaPad + w - lo];
         if (fw) fout[w] = fw;
-        if (vw != dv[w]) dv[w] = vw;   // only this block writes its own words
+        if (V[j] != V0[j]) dv[w] = V[j];   // only this block writes its own words
     }
     if (tid < h && s_cnt[tid]) {
         atomicAdd(&ring_cnt[(L0 + tid + 1) % kDiaRing], s_cnt[tid]);
@@ -1852,24 +1848,162 @@ void launch_dia_ring_seed(hipStream_t s, const BfsBufs &b, int32_t src)
     hipLaunchKernelGGL(k_dia_ring_seed, dim3(1), dim3(kDiaRing), 0, s, b.ring_cnt, b.ring_min, src);
 }
 
+#define MPCG_DIA_TILE_CASES(X)                                                                                         \
+    X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8)
+
+template <int P>
+static void dia_multi_launch(hipStream_t s, const BfsBufs &b, int g, const uint32_t *fin, uint32_t *fout, int32_t L0)
+{
+    switch (b.doff.nd) {
+#define X(N)                                                                                                        \
+    case N:                                                                                                         \
+        hipLaunchKernelGGL((k_dia_multi<N, P>), dim3(g), dim3(kDiaTileThreads), 0, s, fin, fout, b.dv, b.dm, b.dist, \
+                           b.nwords, L0, b.dia_h, b.dia_T, b.dia_R, b.doff, b.ring_cnt, b.ring_min, b.st);          \
+        break;
+        MPCG_DIA_TILE_CASES(X)
+#undef X
+    default: break;
+    }
+}
+
 int launch_dia_multi_round(hipStream_t s, const BfsBufs &b, int launches, int k)
 {
     const int g = (b.nwords + b.dia_T - 1) / b.dia_T;
     for (int l = 0; l < launches; ++l, ++k) {
         const uint32_t *fin = (k & 1) ? b.df1 : b.df0;
         uint32_t *fout = (k & 1) ? b.df0 : b.df1;
-        switch (b.doff.nd) {
-#define X(N)                                                                                                        \
-    case N:                                                                                                         \
-        hipLaunchKernelGGL(k_dia_multi<N>, dim3(g), dim3(kDiaTileThreads), 0, s, fin, fout, b.dv, b.dm, b.dist,     \
-                           b.nwords, k * b.dia_h, b.dia_h, b.dia_T, b.dia_R, b.doff, b.ring_cnt, b.ring_min, b.st); \
-        break;
-            X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8)
-#undef X
-        default: break;
-        }
+        if (b.dia_P == 2) dia_multi_launch<2>(s, b, g, fin, fout, k * b.dia_h);
+        else if (b.dia_P == 4) dia_multi_launch<4>(s, b, g, fin, fout, k * b.dia_h);
+        else dia_multi_launch<8>(s, b, g, fin, fout, k * b.dia_h);
     }
     return k;
+}
+
+// ------------------------------------------------- one block, all levels --
+//
+// A pattern whose bit vectors fit one block's LDS (nwords <= kDiaBlockWords,
+// n <= 262,144) needs no launch per level at all: the block keeps the frontier
+// in LDS, the visited bits and the masks of a thread's P words in registers,
+// and a level is ND windows per word and one barrier.  The levels' sizes are
+// not counted: whether a level is empty is one flag (three slots in turn: a
+// slot is cleared while nobody reads or writes it), the visited vertices and
+// the last level's smallest vertex are formed at the end.  A launch runs at
+// most kDiaBlockLevels levels and hands its state on.  49^3 grid: 144 levels in
+// 0.16 ms (1.1 us a level; queue kernels 5.9).
+template <int ND, int P>
+__global__ void __launch_bounds__(kDiaTileThreads)
+k_dia_block(const uint32_t *__restrict__ fin, uint32_t *__restrict__ fout, uint32_t *dv,
+            const uint32_t *__restrict__ dm, int32_t *dist, int32_t nw, int32_t L0, DiaOffs o, DevState *st)
+{
+    constexpr int kF = P * kDiaTileThreads + 2 * kDiaPad;
+    __shared__ uint32_t F[2][kF];
+    __shared__ int s_any[3], s_min, s_vis;
+    if (st->bfs_done) return;   // set by an earlier launch
+    const int tid = threadIdx.x;
+    uint32_t mr[P][ND], V[P];
+    for (int i = tid; i < kF; i += kDiaTileThreads) {
+        F[0][i] = 0u;
+        F[1][i] = 0u;
+    }
+    if (tid < 3) s_any[tid] = 0;
+    if (tid == 0) {
+        s_min = kIntMax;
+        s_vis = 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+        const int w = tid + j * kDiaTileThreads;
+        const bool in = w < nw;
+#pragma unroll
+        for (int t = 0; t < ND; ++t) mr[j][t] = in ? dm[(size_t)t * nw + w] : 0u;
+        V[j] = in ? dv[w] : 0u;
+        if (in) F[0][kDiaPad + w] = fin[w];
+    }
+    __syncthreads();
+    int l = 0;
+    bool ended = false;
+    for (; l < kDiaBlockLevels; ++l) {
+        const uint32_t *cur = F[l & 1];
+        uint32_t *nxt = F[(l + 1) & 1];
+        uint32_t any = 0u;
+#pragma unroll
+        for (int j = 0; j < P; ++j) {
+            int w = tid + j * kDiaTileThreads;
+            asm volatile("" : "+v"(w));   // window indices formed here, not kept for every word
+            uint32_t nb = 0u;
+#pragma unroll
+            for (int t = 0; t < ND; ++t) {
+                const int i0 = kDiaPad + w + o.q[t];
+                uint32_t win = cur[i0];
+                if (o.r[t]) win = __builtin_amdgcn_alignbit(cur[i0 + 1], win, o.r[t]);
+                nb |= win & mr[j][t];
+            }
+            nb &= ~V[j];
+            nxt[kDiaPad + w] = nb;
+            V[j] |= nb;
+            any |= nb;
+            if (dist)
+                for (uint32_t bb = nb; bb; bb &= bb - 1u) dist[32 * w + __ffs(bb) - 1] = L0 + l + 1;
+        }
+        if (any) s_any[l % 3] = 1;
+        if (tid == 0) s_any[(l + 1) % 3] = 0;
+        __syncthreads();
+        if (!s_any[l % 3]) {
+            ended = true;
+            break;
+        }
+    }
+    const uint32_t *last = F[l & 1];   // level L0 + l's vertices
+    int vis = 0;
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+        const int w = tid + j * kDiaTileThreads;
+        if (w >= nw) continue;
+        const uint32_t fw = last[kDiaPad + w];
+        if (ended) {
+            if (fw) atomicMin(&s_min, 32 * w + __ffs(fw) - 1);
+            vis += __popc(V[j]);
+        } else {
+            fout[w] = fw;
+            dv[w] = V[j];
+        }
+    }
+    if (!ended) return;
+    vis = wave_sum_i(vis);
+    if ((tid & 63) == 0) atomicAdd(&s_vis, vis);
+    __syncthreads();
+    if (tid == 0) {
+        st->bfs_visited = s_vis;
+        st->bfs_ecc = L0 + l;
+        st->bfs_far = s_min;
+        st->bfs_done = 1;
+    }
+}
+
+template <int P>
+static void dia_block_launch(hipStream_t s, const BfsBufs &b, const uint32_t *fin, uint32_t *fout, int32_t L0)
+{
+    switch (b.doff.nd) {
+#define X(N)                                                                                                        \
+    case N:                                                                                                         \
+        hipLaunchKernelGGL((k_dia_block<N, P>), dim3(1), dim3(kDiaTileThreads), 0, s, fin, fout, b.dv, b.dm, b.dist, \
+                           b.nwords, L0, b.doff, b.st);                                                             \
+        break;
+        MPCG_DIA_TILE_CASES(X)
+#undef X
+    default: break;
+    }
+}
+
+void launch_dia_block(hipStream_t s, const BfsBufs &b, int k)
+{
+    const uint32_t *fin = (k & 1) ? b.df1 : b.df0;
+    uint32_t *fout = (k & 1) ? b.df0 : b.df1;
+    if (b.nwords <= kDiaTileThreads) dia_block_launch<1>(s, b, fin, fout, k * kDiaBlockLevels);
+    else if (b.nwords <= 2 * kDiaTileThreads) dia_block_launch<2>(s, b, fin, fout, k * kDiaBlockLevels);
+    else if (b.nwords <= 4 * kDiaTileThreads) dia_block_launch<4>(s, b, fin, fout, k * kDiaBlockLevels);
+    else dia_block_launch<8>(s, b, fin, fout, k * kDiaBlockLevels);
 }
 
 }  // namespace mpcg

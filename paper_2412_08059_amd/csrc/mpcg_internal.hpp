@@ -25,8 +25,8 @@ constexpr int kDiaMax = 16;           // largest number of diagonals the bit-par
 constexpr int kDiaRound = 16;         // level launches per round (a multiple of 4: the level rings)
 constexpr int kDiaPartMax = 2048;     // largest grid of the level kernels (per-block partials)
 constexpr int kDiaTileThreads = 1024; // threads of a temporal-tile block
-constexpr int kDiaPerThread = 8;      // words of a tile's loaded range per thread
-constexpr int kDiaTileWords = kDiaTileThreads * kDiaPerThread;   // loaded range (LDS: 2 padded copies + visited)
+constexpr int kDiaBlockWords = 8 * kDiaTileThreads;   // bit vectors that one block holds (k_dia_block)
+constexpr int kDiaBlockLevels = 1024; // levels per launch there (even: the frontier's parity)
 constexpr int kDiaTileDiags = 8;      // most diagonals of a temporal-tile pattern (masks in registers)
 constexpr int kDiaPad = 1024;         // zero words beside a tile's LDS range: largest halo per level R
 constexpr int kDia2MaxReach = 2048;   // largest R of the two-level kernel (LDS: 2 kBlock + 6 R words)
@@ -349,7 +349,8 @@ struct BfsBufs {
     uint32_t *df0, *df1, *dv, *dm, *draw;   // dm, draw: kDiaMax masks of nwords words each
     // temporal tiles: dia_h levels per launch, dia_T words per block, halo
     // dia_R words per level (dia_h = 0: one level per launch)
-    int32_t dia_h, dia_T, dia_R;
+    int32_t dia_h, dia_T, dia_R, dia_P;   // dia_P: words of a tile's loaded range per thread
+    int32_t dia_blk;                // 1: one block runs all levels (k_dia_block)
     int32_t *ring_cnt, *ring_min;   // kDiaRing slots each
     int32_t *part_cnt, *part_min;   // level kernels: 2 parities x 2 levels x kDiaPartMax per-block partials each
     int32_t dia_two;                // two levels per launch (k_dia_level2)
@@ -377,6 +378,8 @@ void launch_dia_round(hipStream_t s, const BfsBufs &b);
 // k dia_h .. (k + 1) dia_h - 1.
 void launch_dia_ring_seed(hipStream_t s, const BfsBufs &b, int32_t src);
 int launch_dia_multi_round(hipStream_t s, const BfsBufs &b, int launches, int k);
+// One block, launch k: levels k kDiaBlockLevels and on.
+void launch_dia_block(hipStream_t s, const BfsBufs &b, int k);
 void launch_bfs_seed_single(hipStream_t s, const BfsBufs &b, int32_t src);
 // Enqueues one round (the one-workgroup kernel, then `levels` level kernels)
 // with launch indices k, k + 1, ...; returns the next launch index.

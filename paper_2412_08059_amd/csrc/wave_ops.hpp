@@ -70,6 +70,22 @@ template <typename T> __device__ inline T wave_sum_all(T v)
     return lane_add<1>(v);
 }
 
+// Integer sum and extremes over the wave by the same exchanges.
+template <int STEP, typename F> __device__ inline int lane_fold(int v, const F &f)
+{
+    const LanePair p = lane_pair<STEP>((uint32_t)v);
+    return f((int)p.a, (int)p.b);
+}
+template <typename F> __device__ inline int wave_fold(int v, const F &f)
+{
+    v = lane_fold<32>(v, f);
+    v = lane_fold<16>(v, f);
+    v = lane_fold<8>(v, f);
+    v = lane_fold<4>(v, f);
+    v = lane_fold<2>(v, f);
+    return lane_fold<1>(v, f);
+}
+
 // Sum over the wave of x * y, valid in lane 0: the products are rounded once
 // except lane l's own (l < 32), which enters its first addition unrounded
 // (one fma with the rounded product of lane l + 32).
