@@ -332,28 +332,26 @@ mpcg_status ingest(mpcg_ctx *c, const mpcg_csr *A, const double *b, bool need_va
     p->dg64 = p->at<double>(p->L.dg64);
     int32_t *rp32 = A->row_ptr_is_i64 ? p->at<int32_t>(p->L.rp32) : nullptr;
     p->rp = A->row_ptr_is_i64 ? rp32 : static_cast<const int32_t *>(A->row_ptr);
-    HIPCHK(hipMemsetAsync(p->st, 0, sizeof(DevState), c->stream));
     int64_t *soff = p->at<int64_t>(p->L.sell_off), *wid = p->at<int64_t>(p->L.sell_wid);
     const int nsl = (p->n + 63) / 64;
     double *v64 = p->at<double>(p->L.sell_v64);
     float *v32 = need_val32 ? p->at<float>(p->L.sell_v32) : nullptr;
-    launch_ingest_rows(c->stream, A->row_ptr, A->row_ptr_is_i64 ? 1 : 0, rp32, A->col_idx, b, p->n, A->nnz, wid,
-                       p->at<int32_t>(p->L.ingest_blk), p->st);
     // symmetric matrices on few diagonals: diagonal storage, in the SELL value
     // arrays; what its passes find unfit (or an explicit variant) goes to SELL
-    const bool try_ds = want_copy && c->opt.spmv_variant == 0;
+    const bool try_ds = want_copy && c->opt.spmv_variant == 0 && A->nnz <= (2 * kDsMax + 1) * A->n;
+    int32_t *blk = p->at<int32_t>(p->L.ingest_blk);
+    launch_ingest_rows(c->stream, A->row_ptr, A->row_ptr_is_i64 ? 1 : 0, rp32, A->col_idx, b, p->n, A->nnz, wid, blk);
+    launch_ingest_fold(c->stream, blk, p->rp, A->col_idx, p->n, A->nnz, wid, soff, p->L.sell_cap, try_ds, p->st);
     if (try_ds)
-        launch_ds_ingest(c->stream, p->rp, A->col_idx, A->val, p->n, A->nnz, p->L.sell_cap, v64, v32,
-                         want_diag ? p->dg64 : nullptr, want_diag ? p->dg32 : nullptr, p->st);
+        launch_ds_ingest(c->stream, p->rp, A->col_idx, A->val, p->n, v64, v32, want_diag ? p->dg64 : nullptr,
+                         want_diag ? p->dg32 : nullptr, p->st);
     auto general = [&]() {
-        launch_ingest_sell(c->stream, p->rp, A->col_idx, A->val, p->n, wid, soff, p->L.sell_cap,
+        launch_ingest_sell(c->stream, p->rp, A->col_idx, A->val, p->n, soff, p->L.sell_cap,
                            want_copy && !c->force_csr ? 1 : 0, p->ws + p->L.sell_col, v64, v32, p->st);
         if (want_diag) launch_diag(c->stream, p->rp, A->col_idx, A->val, p->n, p->dg64, p->dg32, p->st);
     };
     auto verdict = [&]() -> mpcg_status {
         HIPCHK(hipGetLastError());
-        HIPCHK(hipMemcpyAsync(&c->hst[2].spare_i64, soff + nsl, sizeof(int64_t), hipMemcpyDeviceToHost,
-                              c->stream));
         HIPCHK(hipMemcpyAsync(&c->hst[1], p->st, sizeof(DevState), hipMemcpyDeviceToHost, c->stream));
         HIPCHK(hipStreamSynchronize(c->stream));
         return MPCG_OK;
@@ -362,16 +360,13 @@ mpcg_status ingest(mpcg_ctx *c, const mpcg_csr *A, const double *b, bool need_va
     mpcg_status rc = verdict();
     if (rc != MPCG_OK) return rc;
     if (c->hst[1].ds_cand && c->hst[1].ds_miss) {   // other diagonals, not symmetric, or malformed
-        HIPCHK(hipMemsetAsync(&p->st->ds_cand, 0, sizeof(int32_t), c->stream));
-        HIPCHK(hipMemsetAsync(&p->st->ing_err, 0, sizeof(int32_t), c->stream));
-        launch_ingest_rows(c->stream, A->row_ptr, A->row_ptr_is_i64 ? 1 : 0, rp32, A->col_idx, b, p->n, A->nnz, wid,
-                           p->at<int32_t>(p->L.ingest_blk), p->st);
+        launch_ingest_fold(c->stream, blk, p->rp, A->col_idx, p->n, A->nnz, wid, soff, p->L.sell_cap, 0, p->st);
         general();
         rc = verdict();
         if (rc != MPCG_OK) return rc;
     }
     const DevState s = c->hst[1];
-    const int64_t padded = c->hst[2].spare_i64;
+    const int64_t padded = s.sell_total;
     p->band = s.max_band;
     rc = ingest_status(s.ing_err);
     if (rc != MPCG_OK) return rc;

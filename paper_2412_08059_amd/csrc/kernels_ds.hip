@@ -33,67 +33,147 @@ namespace mpcg {
 
 // ------------------------------------------------------------- ingest --
 
-// Sampled rows' offsets (one block): the distances |i - j| > 0 of up to 1024
-// rows spread over the matrix.  A pattern with others than these is found out
-// by k_ds_rows, which costs a second ingest but no result.
-__device__ inline void ds_sample(const int32_t *rp, const int32_t *col, int32_t n, int64_t nnz, int64_t cap,
-                                 DevState *st, int32_t *slot)
+// Sampled offsets (one block): the distances |i - j| > 0 of kDsSample rows
+// spread over the matrix, a thread per entry.  Up to 63 they are bits of a
+// mask, beyond that slots claimed by compare-and-swap.  A pattern with others
+// than these is found out by k_ds_rows, which costs a second ingest but no
+// result.
+constexpr int kDsRowMax = 2 * kDsMax + 1;          // entries of the longest row that can match
+constexpr int kDsSample = 1024 / kDsRowMax;        // rows
+struct DsSample {
+    unsigned long long near;      // bit d: distance d
+    int32_t far[kDsMax], misfit;
+};
+__device__ inline void ds_sample(int lo, int hi, int64_t i, const int32_t *col, int32_t n, int64_t nnz, int64_t cap,
+                                 DevState *st, DsSample *sm)
 {
-    // slot: kDsMax + 1 ints of LDS, the last one counts misfits
-    if (threadIdx.x <= kDsMax) slot[threadIdx.x] = 0;
-    __syncthreads();
-    const int64_t step = ((int64_t)n + blockDim.x - 1) / blockDim.x;
-    const int64_t i = (int64_t)threadIdx.x * step + (threadIdx.x * 2654435761u >> 7) % (uint64_t)step;
-    if (i < n) {
-        const int lo = rp[i], hi = rp[i + 1];
-        if (hi - lo > 2 * kDsMax + 1) {
-            atomicOr(&slot[kDsMax], 1);
-        } else {
-            for (int k = lo; k < hi; ++k) {
-                const int64_t diff = (int64_t)col[k] - i;
-                const int64_t d = diff < 0 ? -diff : diff;
-                if (d == 0 || d >= n) continue;   // a column out of range is found by the entries' pass
-                int t = 0;
-                for (; t < kDsMax; ++t) {
-                    const int old = atomicCAS(&slot[t], 0, (int)d);
-                    if (old == 0 || old == (int)d) break;
-                }
-                if (t == kDsMax) atomicOr(&slot[kDsMax], 1);
+    // (lo, hi): the sampled row's entries, none for a thread without a row
+    const int j = threadIdx.x % kDsRowMax;
+    if (hi - lo > kDsRowMax) sm->misfit = 1;
+    if (lo + j < hi) {
+        const int64_t diff = (int64_t)col[lo + j] - i;
+        const int64_t d = diff < 0 ? -diff : diff;
+        if (d > 0 && d < 64) {
+            atomicOr(&sm->near, 1ull << d);
+        } else if (d >= 64 && d < n) {   // a column out of range is found by the entries' pass
+            int t = 0;
+            for (; t < kDsMax; ++t) {
+                const int old = atomicCAS(&sm->far[t], 0, (int)d);
+                if (old == 0 || old == (int)d) break;
             }
+            if (t == kDsMax) sm->misfit = 1;
         }
     }
     __syncthreads();
     if (threadIdx.x != 0) return;
-    int nh = 0;
-    while (nh < kDsMax && slot[nh]) ++nh;
-    st->ds_cand = 0;
-    if (slot[kDsMax] || nh == 0) return;
-    for (int a = 1; a < nh; ++a) {   // ascending
-        const int v = slot[a];
-        int b = a;
-        for (; b > 0 && slot[b - 1] > v; --b) slot[b] = slot[b - 1];
-        slot[b] = v;
-    }
+    const int nnear = __popcll(sm->near);
+    int nh = nnear, nfar = 0;
+    while (nfar < kDsMax && sm->far[nfar]) ++nfar;
+    nh += nfar;
+    if (sm->misfit || nh == 0 || nh > kDsMax) return;
     // Worth it when at least two thirds of the diagonals' places hold an
     // entry: each place costs a gather whether or not it does.
     if ((int64_t)(2 * nh + 1) * n * 2 > 3 * nnz || (int64_t)(nh + 1) * ds_stride(n) > cap) return;
     if (n >= (1 << 28) || (int64_t)(nh + 1) * ds_stride(n) * 8 >= (1ll << 32)) return;   // 32-bit byte offsets
-    for (int t = 0; t < kDsMax; ++t) st->ds_d[t] = t < nh ? slot[t] : 0;
+    unsigned long long m = sm->near;
+    for (int t = 0; t < nnear; ++t, m &= m - 1) st->ds_d[t] = __builtin_ctzll(m);
+    int prev = 0;
+    for (int t = nnear; t < nh; ++t) {   // the far ones, ascending
+        int next = kNoStop;
+        for (int k = 0; k < nfar; ++k)
+            if (sm->far[k] > prev && sm->far[k] < next) next = sm->far[k];
+        st->ds_d[t] = next;
+        prev = next;
+    }
     st->ds_nh = nh;
     st->ds_cand = 1;
 }
 
+// One block after k_ingest_rows: clears the device state, folds the blocks'
+// statistics into it, samples the distances if ds (and the row pointers are
+// usable), and unless diagonal storage takes the matrix forms the SELL slice
+// offsets (exclusive scan of the padded slice sizes).
 __global__ void __launch_bounds__(1024)
-k_ds_sample(const int32_t *rp, const int32_t *col, int32_t n, int64_t nnz, int64_t cap, DevState *st)
+k_ingest_fold(const int32_t *blk, int32_t nblk, const int32_t *rp, const int32_t *col, int32_t n, int64_t nnz,
+              const int64_t *wid, int64_t *off, int64_t cap, int ds, DevState *st)
 {
-    __shared__ int32_t slot[kDsMax + 1];
-    if (st->ing_err & kErrRowPtr) return;   // ds_cand stays 0
-    ds_sample(rp, col, n, nnz, cap, st, slot);
+    __shared__ int32_t fold[3][1024 / 64];
+    __shared__ int64_t part[1024 / 64];
+    __shared__ DsSample smp;
+    __shared__ int32_t cand;
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    for (int i = t; i < (int)(sizeof(DevState) / sizeof(int32_t)); i += 1024) reinterpret_cast<int32_t *>(st)[i] = 0;
+    // the sampled row's pointers, loaded beside the statistics
+    const int64_t step = ((int64_t)n + kDsSample - 1) / kDsSample;
+    const int r = t / kDsRowMax;
+    const int64_t row = (int64_t)r * step + (r * 2654435761u >> 7) % (uint64_t)step;
+    const bool has = ds && r < kDsSample && row < n;
+    const int rlo = has ? rp[row] : 0, rhi = has ? rp[row + 1] : 0;
+    int e = 0, l = 0, bd = 0;
+    for (int i = t; i < nblk; i += 1024) {
+        e |= blk[3 * i];
+        l = l > blk[3 * i + 1] ? l : blk[3 * i + 1];
+        bd = bd > blk[3 * i + 2] ? bd : blk[3 * i + 2];
+    }
+    auto larger = [](int x, int y) { return x > y ? x : y; };
+    e = wave_fold(e, [](int x, int y) { return x | y; });
+    l = wave_fold(l, larger);
+    bd = wave_fold(bd, larger);
+    if (lane == 0) {
+        fold[0][w] = e;
+        fold[1][w] = l;
+        fold[2][w] = bd;
+    }
+    if (t == 0) smp.near = 0;
+    if (t < kDsMax) smp.far[t] = 0;
+    if (t == kDsMax) smp.misfit = 0;
+    __syncthreads();
+    for (int k = 0; k < 1024 / 64; ++k) {
+        e |= fold[0][k];
+        l = larger(l, fold[1][k]);
+        bd = larger(bd, fold[2][k]);
+    }
+    if (t == 0) {
+        st->ing_err = e;
+        st->max_row = l;
+        st->max_band = bd;
+    }
+    if (ds && !(e & kErrRowPtr)) ds_sample(rlo, rhi, row, col, n, nnz, cap, st, &smp);   // ds_cand is 0 otherwise
+    if (t == 0) cand = st->ds_cand;
+    __syncthreads();
+    if (cand) return;
+    // per thread a run of slices; the runs' sums scanned in the waves and over them
+    const int nsl = (n + 63) / 64, per = (nsl + 1023) / 1024;
+    const int a = min(t * per, nsl), b = min(a + per, nsl);
+    int64_t sum = 0;
+    for (int i = a; i < b; ++i) sum += wid[i];
+    int64_t inc = sum;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int64_t v = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += v;
+    }
+    if (lane == 63) part[w] = inc;
+    __syncthreads();
+    int64_t run = inc - sum;
+    for (int k = 0; k < w; ++k) run += part[k];
+    for (int i = a; i < b; ++i) {
+        off[i] = run;
+        run += wid[i];
+    }
+    if (t == 1023) {
+        off[nsl] = run;
+        st->sell_total = run;
+    }
+}
+
+void launch_ingest_fold(hipStream_t s, const int32_t *blk, const int32_t *rp, const int32_t *col, int32_t n,
+                        int64_t nnz, const int64_t *wid, int64_t *off, int64_t cap, int ds, DevState *st)
+{
+    hipLaunchKernelGGL(k_ingest_fold, dim3(1), dim3(1024), 0, s, blk, (n + kBlock - 1) / kBlock, rp, col, n, nnz, wid,
+                       off, cap, ds, st);
 }
 
 constexpr int kDsNear = 32;   // largest distance of the kernels that keep a slice's vector elements in LDS
-
-constexpr int kDsRowMax = 2 * kDsMax + 1;   // entries of the longest row that can match
 
 // Wave per 64 rows: the rows' entries are staged in LDS with coalesced loads,
 // then each lane walks its row along the diagonals.  VERIFY 0: the planes (and
@@ -192,13 +272,12 @@ k_ds_rows(const int32_t *__restrict__ rp, const int32_t *__restrict__ col, const
     if (lane == 0 && miss) atomicOr(&st->ds_miss, 1);
 }
 
-void launch_ds_ingest(hipStream_t s, const int32_t *rp, const int32_t *col, const double *val, int32_t n, int64_t nnz,
-                      int64_t cap, double *p64, float *p32, double *dg64, float *dg32, DevState *st)
+void launch_ds_ingest(hipStream_t s, const int32_t *rp, const int32_t *col, const double *val, int32_t n, double *p64,
+                      float *p32, double *dg64, float *dg32, DevState *st)
 {
     const int nslices = (n + 63) / 64;
     int g = (nslices + kBlock / 64 - 1) / (kBlock / 64);
     if (g > 4096) g = 4096;
-    hipLaunchKernelGGL(k_ds_sample, dim3(1), dim3(1024), 0, s, rp, col, n, nnz, cap, st);
     hipLaunchKernelGGL((k_ds_rows<0>), dim3(g), dim3(kBlock), 0, s, rp, col, val, n, nslices, p64, p32, dg64, dg32, st);
     hipLaunchKernelGGL((k_ds_rows<1>), dim3(g), dim3(kBlock), 0, s, rp, col, val, n, nslices, p64, p32, dg64, dg32, st);
 }

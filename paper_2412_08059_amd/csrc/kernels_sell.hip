@@ -24,13 +24,13 @@ namespace mpcg {
 
 // ------------------------------------------------------------- ingest --
 //
-// Ingest is four launches and one host read-back (the diagonal storage's
-// passes come between the first two and the last two, see kernels_ds.hip):
+// Ingest is three launches and one host read-back (the diagonal storage's
+// passes come before the last, see kernels_ds.hip):
 //   k_ingest_rows     thread per row: row-pointer checks (and int64 -> int32
 //                     conversion), b finite, row length, bandwidth from the
 //                     first and last column of the row, slice width;
-//   k_ingest_fold     the blocks' statistics into the device state;
-//   k_sell_scan       padded slice offsets;
+//   k_ingest_fold     one block: the blocks' statistics into the device state,
+//                     padded slice offsets (kernels_ds.hip);
 //   k_ingest_entries  wave per slice, entries read in coalesced 64-wide
 //                     strides: column range, strictly increasing columns,
 //                     finite values, and the SELL-64 copy when it fits.
@@ -101,63 +101,6 @@ k_ingest_rows(const void *rp_in, int rp_is_i64, const int32_t *__restrict__ col,
     }
 }
 
-// folds the per-block ingest statistics into the device state (one block)
-__global__ void __launch_bounds__(1024) k_ingest_fold(const int32_t *blk, int32_t nblk, DevState *st)
-{
-    __shared__ int fold[3][1024];
-    const int t = threadIdx.x;
-    int e = 0, l = 0, bd = 0;
-    for (int i = t; i < nblk; i += 1024) {
-        e |= blk[3 * i];
-        l = l > blk[3 * i + 1] ? l : blk[3 * i + 1];
-        bd = bd > blk[3 * i + 2] ? bd : blk[3 * i + 2];
-    }
-    fold[0][t] = e;
-    fold[1][t] = l;
-    fold[2][t] = bd;
-    __syncthreads();
-    for (int d = 512; d > 0; d >>= 1) {
-        if (t < d) {
-            fold[0][t] |= fold[0][t + d];
-            fold[1][t] = fold[1][t] > fold[1][t + d] ? fold[1][t] : fold[1][t + d];
-            fold[2][t] = fold[2][t] > fold[2][t + d] ? fold[2][t] : fold[2][t + d];
-        }
-        __syncthreads();
-    }
-    if (t == 0) {
-        st->ing_err |= fold[0][0];
-        st->max_row = fold[1][0];
-        st->max_band = fold[2][0];
-    }
-}
-
-// exclusive scan of the padded slice sizes (one block), off[nslices] = total
-__global__ void __launch_bounds__(1024)
-k_sell_scan(const int64_t *wid, int32_t nslices, int64_t *off, const DevState *st)
-{
-    __shared__ int64_t part[1024];
-    if (st->ds_cand) return;
-    const int t = threadIdx.x;
-    const int per = (nslices + 1023) / 1024;
-    const int a = min(t * per, nslices), b = min(a + per, nslices);
-    int64_t sum = 0;
-    for (int i = a; i < b; ++i) sum += wid[i];
-    part[t] = sum;
-    __syncthreads();
-    for (int d = 1; d < 1024; d <<= 1) {
-        const int64_t v = t >= d ? part[t - d] : 0;
-        __syncthreads();
-        part[t] += v;
-        __syncthreads();
-    }
-    int64_t run = part[t] - sum;
-    for (int i = a; i < b; ++i) {
-        off[i] = run;
-        run += wid[i];
-    }
-    if (t == 1023) off[nslices] = part[1023];
-}
-
 __global__ void __launch_bounds__(kBlock)
 k_ingest_entries(const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
                  const double *__restrict__ val, int32_t n, int32_t nslices,
@@ -212,21 +155,18 @@ k_ingest_entries(const int32_t *__restrict__ rp, const int32_t *__restrict__ col
 }
 
 void launch_ingest_rows(hipStream_t s, const void *rp_in, int rp_is_i64, int32_t *rp32_out, const int32_t *col,
-                        const double *b, int32_t n, int64_t nnz, int64_t *wid, int32_t *blk, DevState *st)
+                        const double *b, int32_t n, int64_t nnz, int64_t *wid, int32_t *blk)
 {
-    const int nslices = (n + 63) / 64;
     const int nblk = (n + kBlock - 1) / kBlock;
     hipLaunchKernelGGL(k_ingest_rows, dim3(nblk), dim3(kBlock), 0, s, rp_in, rp_is_i64, col, b, n, nnz,
-                       nslices, rp32_out, wid, blk);
-    hipLaunchKernelGGL(k_ingest_fold, dim3(1), dim3(1024), 0, s, blk, nblk, st);
+                       (n + 63) / 64, rp32_out, wid, blk);
 }
 
 void launch_ingest_sell(hipStream_t s, const int32_t *rp32, const int32_t *col, const double *val, int32_t n,
-                        const int64_t *wid, int64_t *off, int64_t cap, int allow_fill, void *scol, double *sv64,
-                        float *sv32, DevState *st)
+                        const int64_t *off, int64_t cap, int allow_fill, void *scol, double *sv64, float *sv32,
+                        DevState *st)
 {
     const int nslices = (n + 63) / 64;
-    hipLaunchKernelGGL(k_sell_scan, dim3(1), dim3(1024), 0, s, wid, nslices, off, st);
     int g = (nslices + 3) / 4;
     if (g > 8192) g = 8192;
     hipLaunchKernelGGL(k_ingest_entries, dim3(g), dim3(kBlock), 0, s, rp32, col, val, n, nslices, off, cap,

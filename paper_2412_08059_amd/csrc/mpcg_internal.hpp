@@ -101,7 +101,6 @@ struct alignas(256) DevState {
     int32_t cross_iter[6];
     double spec_thr[6];
     double cross_gamma[6];
-    int64_t spare_i64;    // host-side scratch in the pinned mirror
     // Diagonal structure of the pattern (k_dia_offsets): the distinct nonzero
     // offsets j - i of the stored entries, if there are at most kDiaMax
     // (slots filled from 0, 0 = empty; dia_over: more than kDiaMax).
@@ -112,6 +111,7 @@ struct alignas(256) DevState {
     // whether the entries' pass found others or an unsymmetric pair.
     int32_t ds_cand, ds_miss, ds_nh;
     int32_t ds_d[8];
+    int64_t sell_total;   // padded SELL entries (if the offsets were formed)
 };
 
 // Byte offsets of every region inside the caller's arena.
@@ -213,13 +213,17 @@ __device__ inline unsigned spec_crossings(DevState *st, int it, double g)
 // Validate A (and b), convert int64 row pointers, and build the SELL-64 copy
 // when its padded size fits in `cap` entries (see kernels_sell.hip).
 // launch_ingest_rows: row pointers, b, row lengths, slice widths, statistics
-// folded into st.  launch_ingest_sell, after it: slice offsets and entries
-// (nothing while st->ds_cand says that the diagonal storage takes them).
+// per block.  launch_ingest_fold, after it: clears st, the statistics into it,
+// with ds the sampled distances, and unless st->ds_cand says that the diagonal
+// storage takes the matrix the slice offsets.  launch_ingest_sell, after that:
+// the entries (nothing while st->ds_cand).
 void launch_ingest_rows(hipStream_t s, const void *rp_in, int rp_is_i64, int32_t *rp32_out, const int32_t *col,
-                        const double *b, int32_t n, int64_t nnz, int64_t *wid, int32_t *blk, DevState *st);
+                        const double *b, int32_t n, int64_t nnz, int64_t *wid, int32_t *blk);
+void launch_ingest_fold(hipStream_t s, const int32_t *blk, const int32_t *rp, const int32_t *col, int32_t n,
+                        int64_t nnz, const int64_t *wid, int64_t *off, int64_t cap, int ds, DevState *st);
 void launch_ingest_sell(hipStream_t s, const int32_t *rp32, const int32_t *col, const double *val, int32_t n,
-                        const int64_t *wid, int64_t *off, int64_t cap, int allow_fill, void *scol, double *sv64,
-                        float *sv32, DevState *st);
+                        const int64_t *off, int64_t cap, int allow_fill, void *scol, double *sv64, float *sv32,
+                        DevState *st);
 void launch_cast32(hipStream_t s, const double *val, float *val32, int64_t nnz);
 void launch_fill_f64(hipStream_t s, double *p, int64_t n, double v);
 void launch_fill_f32(hipStream_t s, float *p, int64_t n, float v);
@@ -297,11 +301,11 @@ void launch_spmv_checked(hipStream_t s, const void *rp, int rp_is_i64, const int
                          int64_t nnz, const T *x, T *scratch, T *y, DevState *st);
 
 // ----- diagonal storage (kernels_ds.hip) -----
-// After k_ingest_rows: distances sampled, planes (and diag(A) if dg64) filled
-// and the symmetry checked, all on the device; st->ds_cand && !st->ds_miss
-// says that the planes hold the matrix.  cap: elements of p64 / p32.
-void launch_ds_ingest(hipStream_t s, const int32_t *rp, const int32_t *col, const double *val, int32_t n, int64_t nnz,
-                      int64_t cap, double *p64, float *p32, double *dg64, float *dg32, DevState *st);
+// After launch_ingest_fold: planes (and diag(A) if dg64) filled and the
+// symmetry checked; st->ds_cand && !st->ds_miss then says that the planes hold
+// the matrix.
+void launch_ds_ingest(hipStream_t s, const int32_t *rp, const int32_t *col, const double *val, int32_t n, double *p64,
+                      float *p32, double *dg64, float *dg32, DevState *st);
 template <typename T>
 void launch_ds_cg_spmv(hipStream_t s, const DsMat &m, int grid, const T *r, T *dA, T *dB, T *q, const double *up,
                        int nup, double *part, int it, int it0, T *x, T *snap, int pc, DevState *st);
