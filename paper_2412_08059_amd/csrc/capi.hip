@@ -263,6 +263,8 @@ struct Plan {
     SellMat sell{};
     DsMat ds{};
     bool use_sell = false, use_ds = false;   // at most one; neither: CSR
+    bool use_wg = false;                     // CG iterations in one workgroup
+    int32_t max_row = 0;                     // longest row
     int nup = 1;
     mpcg_tuning tune{};   // scheduling parameters resolved for this matrix
     char *ws = nullptr;
@@ -375,6 +377,10 @@ mpcg_status ingest(mpcg_ctx *c, const mpcg_csr *A, const double *b, bool need_va
     p->use_sell = want_copy && !p->use_ds && !c->force_csr && padded <= p->L.sell_cap;
     p->sh64 = spmv_shape(A->n, A->nnz, 8, c->num_cu);
     p->sh32 = spmv_shape(A->n, A->nnz, 4, c->num_cu);
+    // small systems: unpreconditioned, FP64-accumulated dots, no explicit variant
+    p->max_row = s.max_row;
+    p->use_wg = (p->use_ds || p->use_sell) && wg_fits(A->n, s.max_row) && !want_diag && c->opt.dot_acc == 0 &&
+                c->opt.spmv_variant == 0;
     p->nup = vec_grid(A->n);
     if (p->nup > kUpdateGrid) p->nup = kUpdateGrid;
     p->tune = resolve_tuning(c, A->n, A->nnz, s.max_band);
@@ -503,6 +509,8 @@ void run_plain(hipStream_t s, const Plan &p, const T *x, T *y)
 }
 
 int poll_iters(const mpcg_ctx *c) { return c->opt.graph_iters > 0 ? c->opt.graph_iters : 8; }
+// one launch between polls there: long enough to hide the next one's enqueueing
+int poll_iters_wg(const mpcg_ctx *c) { return c->opt.graph_iters > 0 ? c->opt.graph_iters : 32; }
 
 // Run CG iterations in precision T from iteration `it` (phase started at
 // `it0`) until the device says stop, or until *stop_flag is set (Algorithm II
@@ -513,12 +521,17 @@ template <typename T>
 mpcg_status cg_loop(mpcg_ctx *c, const Plan &p, T *x, T *r, T *q, T *dA, T *dB, int it, int it0,
                     DevState *out, const std::atomic<int> *stop_flag = nullptr, int *it_next = nullptr)
 {
-    const int G = poll_iters(c);
+    const int G = p.use_wg ? poll_iters_wg(c) : poll_iters(c);
     const Chan &ch = c->main;
     T *snap = stop_flag ? snap_buf<T>(p) : nullptr;
     int64_t k = 0;
     for (;;) {
-        for (int g = 0; g < G; ++g, ++it) {
+        if (p.use_wg) {
+            launch_wg_cg<T>(ch.s, p.rp, p.col, p.val, p.n, p.max_row, p.sell.grid, x, r, dA, dB, snap, p.up, it, it0,
+                            G, p.st);
+            it += G;
+        }
+        for (int g = 0; g < G && !p.use_wg; ++g, ++it) {
             run_cg_spmv<T>(ch.s, p, r, dA, dB, q, it, it0, x, snap);
             run_cg_update<T>(ch.s, p, r, q, it);
         }

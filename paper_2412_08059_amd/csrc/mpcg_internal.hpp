@@ -316,6 +316,16 @@ void launch_ds_resid(hipStream_t s, const DsMat &m, int grid, const double *x64,
                      DevState *st);
 template <typename T> void launch_ds_plain(hipStream_t s, const DsMat &m, int grid, const T *x, T *y);
 
+// ----- small systems (kernels_wg.hip) -----
+// `iters` CG iterations from iteration it (phase started at it0) in one
+// workgroup, A from the CSR arrays; up[0] carries the update's sum from launch
+// to launch.  wg_fits: whether a system of n rows of at most max_row entries
+// is one of them.
+bool wg_fits(int64_t n, int32_t max_row);
+template <typename T>
+void launch_wg_cg(hipStream_t s, const int32_t *rp, const int32_t *col, const double *val, int32_t n, int32_t max_row,
+                  int grid, T *x, T *r, T *dA, T *dB, T *snap, double *up, int it, int it0, int iters, DevState *st);
+
 // ----- BFS (kernels_bfs.hip) -----
 // A queued BFS vertex is stored as its CSR row range: the level that expands
 // it needs no further load to find its neighbours.
