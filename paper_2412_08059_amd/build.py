@@ -23,7 +23,7 @@ LIB = os.path.join(HERE, "libmpcg.so")
 BUILD_DIR = os.path.join(HERE, "_build")
 
 HIP_SOURCES = ["kernels_cg.hip", "kernels_sell.hip", "kernels_ds.hip", "kernels_bseg.hip", "kernels_wg.hip", "kernels_bfs.hip", "kernels_jacobi.hip", "kernels_batch.hip",
-               "batch_engine.hip", "capi.hip"]
+               "kernels_bwg.hip", "batch_engine.hip", "capi.hip"]
 HOST_SOURCES = ["knn.cpp", "tune.cpp"]
 
 

@@ -167,6 +167,7 @@ struct Engine {
     // the step's work list: the admitted systems that are not retiring
     bool list_dirty = true;
     int32_t list_slices = 0, list_sys = 0;
+    int32_t list_max = 0;               // slices of the largest listed system
     // step groups captured as graphs, by (product grid, per-system grid)
     hipStream_t cap = nullptr;
     std::map<std::tuple<int32_t, int32_t, int32_t, int32_t>, hipGraphExec_t> graphs;   // (grids, steps, dir)
@@ -210,6 +211,9 @@ struct Engine {
     void admit();
     void process(const BSys *m, int32_t cnt, int64_t gi);
     void process_slots(const BSys *m, int32_t cnt, int64_t gi, AdmitList &l2);
+    void retire(RetireList &l, int32_t slot, const Slot &sl, double *x);
+    void flush_retired();
+    RetireList results{}, releases{};   // systems whose x / whose slot goes back, launched by list
     bool bfs_pump();
     bool process_bfs(const BSys *m, int32_t cnt);
     void fail_all(int status);
@@ -370,7 +374,26 @@ void Engine::process(const BSys *m, int32_t cnt, int64_t gi)
 {
     AdmitList l2{};   // stage 2 of the systems whose scan this copy shows: one launch per kernel
     process_slots(m, cnt, gi, l2);
+    flush_retired();
     if (!failed) launch_admit_stage2(s, a, l2);
+}
+
+void Engine::flush_retired()
+{
+    if (!failed) {
+        launch_results(s, a, results);
+        launch_releases(s, a, releases);
+    }
+    results.cnt = releases.cnt = 0;
+}
+
+void Engine::retire(RetireList &l, int32_t slot, const Slot &sl, double *x)
+{
+    const int k = l.cnt++;
+    l.sys[k] = slot;
+    l.nsl[k] = sl.nslices;
+    l.x[k] = x;
+    if (l.cnt == kRetireList) flush_retired();
 }
 
 void Engine::process_slots(const BSys *m, int32_t cnt, int64_t gi, AdmitList &l2)
@@ -391,7 +414,7 @@ void Engine::process_slots(const BSys *m, int32_t cnt, int64_t gi, AdmitList &l2
                     n_queued += 1;
                     n_active -= 1;
                 }
-                launch_release(s, a, i, sl.slice0, sl.nslices);
+                retire(releases, i, sl, nullptr);
                 slices.release(sl.slice0, sl.nslices);
                 sl.used = false;
                 recompute_hi();
@@ -421,7 +444,7 @@ void Engine::process_slots(const BSys *m, int32_t cnt, int64_t gi, AdmitList &l2
         if (sl.retiring) {
             if (gi >= sl.retire_group) {
                 finish(sl, &finals[i], 0);
-                launch_release(s, a, i, sl.slice0, sl.nslices);
+                retire(releases, i, sl, nullptr);
                 slices.release(sl.slice0, sl.nslices);
                 entries.release(sl.entry0, sl.padded);
                 sl.used = false;
@@ -468,10 +491,18 @@ void Engine::process_slots(const BSys *m, int32_t cnt, int64_t gi, AdmitList &l2
         if (M.mode == kDone && (!sl.autoe || sl.feat == 4)) {
             const int st = M.status;
             if (st != MPCG_EINVAL && st != MPCG_ECANCELED && sl.req.x) {
-                if (hipMemcpyAsync(sl.req.x, a.x64 + M.row0, sizeof(double) * (size_t)M.n, hipMemcpyDeviceToDevice,
-                                   s) != hipSuccess) {
-                    failed = true;
-                    return;
+                // device memory: written by the list's kernel; anything else a copy takes, by a copy
+                hipPointerAttribute_t at{};
+                if (hipPointerGetAttributes(&at, sl.req.x) == hipSuccess && at.type == hipMemoryTypeDevice &&
+                    at.device == device) {
+                    retire(results, i, sl, sl.req.x);
+                } else {
+                    (void)hipGetLastError();
+                    if (hipMemcpyAsync(sl.req.x, a.x64 + M.row0, sizeof(double) * (size_t)M.n,
+                                       hipMemcpyDeviceToDevice, s) != hipSuccess) {
+                        failed = true;
+                        return;
+                    }
                 }
             }
             // the statistics are final in this copy; x is complete once the state copy of
@@ -673,7 +704,11 @@ bool Engine::rebuild_list()
     std::vector<int32_t> ids;
     for (int32_t i = 0; i < (int32_t)slots.size(); ++i)
         if (slots[i].used && slots[i].adm == 2 && !slots[i].retiring) ids.push_back(i);
-    for (int32_t i : ids) total += slots[i].nslices;
+    int32_t most = 0;
+    for (int32_t i : ids) {
+        total += slots[i].nslices;
+        most = std::max(most, slots[i].nslices);
+    }
     nsys = (int32_t)ids.size();
     int32_t pre = 0;
     size_t k = 0;
@@ -696,6 +731,7 @@ bool Engine::rebuild_list()
     if (hipGetLastError() != hipSuccess) return false;
     list_slices = total;
     list_sys = nsys;
+    list_max = most;
     list_dirty = false;
     return true;
 }
@@ -710,6 +746,10 @@ void Engine::drop_graphs()
 // pair of grid sizes), else plain launches.
 bool Engine::launch_group(int len)
 {
+    if (list_max <= kWgMaxSlices) {   // small systems only: each advances in a workgroup of its own
+        launch_wg_steps(s, a, list_sys, list_max, kWgSteps);
+        return hipGetLastError() == hipSuccess;
+    }
     const int32_t gsl = coarse_grid((list_slices + kSlicesPerBlock - 1) / kSlicesPerBlock);
     const int32_t gsys = coarse_grid(list_sys);
     if (graphs_ok) {
@@ -806,7 +846,7 @@ bool Engine::step_once()
     const int k = (int)(group & 1);
     if (list_dirty && !rebuild_list()) return false;
     const int len = group_len();
-    len_k[k] = any_live && list_sys > 0 ? len : 0;
+    len_k[k] = any_live && list_sys > 0 && list_max > kWgMaxSlices ? len : 0;   // one-workgroup steps are not timed
     if (any_live && list_sys > 0 && !launch_group(len)) return false;
     if (hipGetLastError() != hipSuccess) return false;
     mirror_n[k] = hi_sys;

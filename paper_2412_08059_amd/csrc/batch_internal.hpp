@@ -14,6 +14,8 @@
 //                 restart and final-check decisions
 //   k_b_update    per slice: r -= alpha q, x += alpha d, partial of r.r
 //   k_b_scalar2   one block per system: gamma, stop tests, beta, v ratios
+//   k_b_wg        instead of the four while every listed system has at most
+//                 4,096 rows: a workgroup per system, many steps a launch
 //   k_b_bfs_*     2BFS levels of the systems whose features are pending, on a
 //                 stream of their own beside the steps
 //
@@ -165,7 +167,16 @@ struct AdmitList {
 };
 void launch_admit_stage1(hipStream_t s, const BArena &a, const AdmitList &l);
 void launch_admit_stage2(hipStream_t s, const BArena &a, const AdmitList &l);
-void launch_release(hipStream_t s, const BArena &a, int32_t sys, int32_t slice0, int32_t nslices);
+// Retirement of a list of systems: x to the caller (x[k] null: none), and the
+// slots' release.
+constexpr int kRetireList = 150;
+struct RetireList {
+    int32_t cnt, pad_;
+    int32_t sys[kRetireList], nsl[kRetireList];
+    double *x[kRetireList];
+};
+void launch_results(hipStream_t s, const BArena &a, const RetireList &l);
+void launch_releases(hipStream_t s, const BArena &a, const RetireList &l);
 void launch_cancel(hipStream_t s, const BArena &a, int32_t sys);       // the solve (step stream)
 void launch_bfs_cancel(hipStream_t s, const BArena &a, int32_t sys);   // its 2BFS (BFS stream)
 // Algorithm II: eps1 chosen by the host, of candidate class ci (0: 1e-2 ... 5: 1e-7)
@@ -179,6 +190,14 @@ void launch_fill_slices(hipStream_t s, const BArena &a);   // every slice unowne
 void launch_worklist(hipStream_t s, const BArena &a, const ListChunk &c);
 // dir: some listed system gathers a stored direction (k_b_dir first)
 void launch_step(hipStream_t s, const BArena &a, int32_t grid_slices, int32_t grid_sys, bool dir);
+
+// The steps of a list whose systems have at most kWgMaxSlices slices each, one
+// workgroup per system and `steps` steps a launch (max_slices: the largest).
+// Beside a larger system the small ones ride in its steps instead, where they
+// cost little; a launch lasts 0.1 to 0.3 ms, the latency the host sees.
+constexpr int kWgMaxSlices = 64;
+constexpr int kWgSteps = 64;
+void launch_wg_steps(hipStream_t s, const BArena &a, int32_t nsys, int32_t max_slices, int32_t steps);
 
 // ---- 2BFS (BFS stream) ----
 // Kernels on the BFS stream write only the BFS fields of a system's state

@@ -7,8 +7,7 @@
 // 2BFS of the section "Computing Pseudo-Diameter of the Graph Matrix" per
 // connected component.
 
-#include "batch_internal.hpp"
-#include "wave_ops.hpp"
+#include "batch_step.hpp"
 
 #include <cmath>
 
@@ -19,10 +18,6 @@ namespace {
 
 constexpr int kIntMax = 0x7fffffff;
 constexpr int kLoadBatch = 4;
-
-template <typename T> __device__ inline T fma_b(T a, T b, T c);
-template <> __device__ inline float fma_b<float>(float a, float b, float c) { return fmaf(a, b, c); }
-template <> __device__ inline double fma_b<double>(double a, double b, double c) { return fma(a, b, c); }
 
 __device__ inline double wave_sum_d(double v) { return wave_sum_all(v); }
 
@@ -97,13 +92,6 @@ __device__ inline double sys_sum_f(const BArena &a, const BSys &S, int j, double
         for (int i = 0; i < kBlock / 64; ++i) s += (float)sm[i];
     __syncthreads();
     return (double)s;
-}
-
-// A partial of an FP32-phase dot product in the precision dot_acc asks for:
-// the lane's term (exact in FP64, one rounding in FP32) summed over the wave.
-__device__ inline double wave_dot32(bool f32, float x, float y)
-{
-    return f32 ? (double)wave_dot(x, y) : wave_dot((double)x, (double)y);
 }
 
 __device__ inline int64_t rp_at(const void *rp, int i64, int64_t i)
@@ -393,7 +381,8 @@ __device__ inline void adm_publish(const BArena &a, int32_t sys, int blk)
 // The blocks of a launch are dealt to the listed systems in order, each
 // system taking as many as its slices need (spb slices per block); a block
 // finds its system by walking the list (at most kAdmitList entries).
-__device__ inline bool adm_block(const AdmitList &L, int spb, int &j, int &blk)
+template <typename LIST>
+__device__ inline bool adm_block(const LIST &L, int spb, int &j, int &blk)
 {
     int b = (int)blockIdx.x;
     for (j = 0; j < L.cnt; ++j) {
@@ -454,13 +443,28 @@ __global__ void __launch_bounds__(kBlock) k_admit_publish_l(BArena a, AdmitList 
     adm_publish(a, L.sys[j], blk);
 }
 
-__global__ void k_release(BArena a, int32_t sys, int32_t slice0, int32_t nslices)
+// Retirement of a list of systems, a launch for all their solutions and one for
+// their slots (512 systems of 1,000 rows: a copy and a launch per system took
+// the stream 2.4 ms)
+__global__ void __launch_bounds__(kBlock) k_results_l(BArena a, RetireList L)
 {
-    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < nslices; j += gridDim.x * blockDim.x)
-        a.sys_of_slice[slice0 + j] = -1;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        a.sys[sys].mode = kFree;
-        a.sys[sys].bfs_mode = kBfsNone;
+    int j, blk;
+    if (!adm_block(L, kSlicesPerBlock, j, blk)) return;
+    const BSys &S = a.sys[L.sys[j]];
+    const int i = blk * kBlock + (int)threadIdx.x;
+    if (L.x[j] && i < S.n) L.x[j][i] = a.x64[S.row0 + i];
+}
+
+__global__ void __launch_bounds__(kBlock) k_release_l(BArena a, RetireList L)
+{
+    int j, blk;
+    if (!adm_block(L, kBlock, j, blk)) return;
+    BSys &S = a.sys[L.sys[j]];
+    const int i = blk * kBlock + (int)threadIdx.x;
+    if (i < L.nsl[j]) a.sys_of_slice[S.slice0 + i] = -1;
+    if (i == 0) {
+        S.mode = kFree;
+        S.bfs_mode = kBfsNone;
     }
 }
 
@@ -709,64 +713,7 @@ __global__ void __launch_bounds__(kBlock) k_b_scalar1(BArena a)
     if (threadIdx.x == 0 && S.snap_mask) S.snap_mask = 0;   // the product of this step took the copies
     if (mode != kCg32 && mode != kCg64 && mode != kRestart && mode != kResid) return;
     const double v = (mode == kCg32 && a.acc32) ? sys_sum_f(a, S, 0, sm) : sys_sum(a, S, 0, sm);
-    if (threadIdx.x != 0) return;
-    const double sb = sqrt(S.bb);
-    if (mode == kCg32 || mode == kCg64) {
-        const double delta = v;
-        S.delta = delta;
-        if (!isfinite(delta) || !(delta > 0.0)) {
-            if (mode == kCg32 && S.auto_eps && !S.eps_set && S.k0_used != 0) {
-                // run-ahead: where the FP32 phase stops depends on eps1
-                S.ra_stop = kRaBreakdown;
-                S.mode = kHold;
-                return;
-            }
-            if (mode == kCg32) {
-                S.flags |= MPCG_FLAG_FP32_BREAKDOWN;
-                if (S.auto_eps && !S.eps_set && S.k0_used == 0) S.k0_used = S.n1 < S.k0 ? S.n1 : S.k0;
-                S.relres_sp = sqrt(S.gamma) / sb;
-                S.src = kSrcX32;
-                S.ph_it = 0;
-                S.mode = kRestart;
-            } else {
-                S.pend = isfinite(delta) ? MPCG_ENOTSPD : MPCG_ENONFINITE;
-                S.mode = kResid;
-            }
-            return;
-        }
-        S.alpha = mode == kCg32 ? (double)(float)(S.gamma / delta) : S.gamma / delta;
-        S.upd = 1;
-    } else if (mode == kRestart) {
-        S.gamma = v;
-        S.relres_restart = sqrt(v) / sb;
-        S.ph_it = 0;
-        if (sqrt(v) <= S.thr2) {
-            S.mode = kResid;
-        } else if (S.n2 >= S.maxit2) {
-            S.pend = MPCG_ENOCONV;
-            S.mode = kResid;
-        } else {
-            S.mode = kCg64;
-        }
-    } else {   // final check
-        const double rho = sqrt(v);
-        S.relres_final = rho / sb;
-        if (S.pend) {
-            S.status = S.pend;
-            S.mode = kDone;
-        } else if (rho <= S.thr2) {
-            S.status = MPCG_OK;
-            S.mode = kDone;
-        } else if (S.restarts < S.max_restarts) {
-            S.restarts += 1;
-            S.flags |= MPCG_FLAG_FINAL_RESTARTED;
-            S.src = kSrcX64;
-            S.mode = kRestart;
-        } else {
-            S.status = MPCG_ENOCONV;
-            S.mode = kDone;
-        }
-    }
+    if (threadIdx.x == 0) step_product_done(S, mode, v);
 }
 
 template <typename T>
@@ -806,88 +753,7 @@ __global__ void __launch_bounds__(kBlock) k_b_scalar2(BArena a)
     BSys &S = a.sys[a.step_sys[blockIdx.x]];
     if (!S.upd) return;
     const double g = (S.mode == kCg32 && a.acc32) ? sys_sum_f(a, S, 0, sm) : sys_sum(a, S, 0, sm);
-    if (threadIdx.x != 0) return;
-    S.upd = 0;
-    const double gp = S.gamma;
-    S.gamma_prev = gp;
-    S.gamma = g;
-    S.ph_it += 1;
-    const double sb = sqrt(S.bb);
-    if (S.mode == kCg32) {
-        S.n1 += 1;
-        const bool prefix = S.auto_eps && S.k0_used == 0;
-        if (prefix && S.n1 <= S.k0 && S.n1 <= kK0Max) S.ratios[S.n1 - 1] = sqrt(g) / sqrt(gp);
-        S.beta = (double)(float)(g / gp);
-        if (prefix && (S.n1 >= S.k0 || g == 0.0)) S.k0_used = S.n1;
-        if (prefix && S.n1 < S.k0 && g != 0.0) return;   // Algorithm II: k0 iterations first
-        if (S.auto_eps && !S.eps_set) {
-            // until eps1 is known: record the first crossing of each
-            // candidate (x~ is copied by the next product); then either hold
-            // (many systems listed: a.hold_above) or run ahead
-            const double rg = sqrt(g);
-            int due = 0, left = 0;
-            for (int t = 0; t < kNumEps; ++t) {
-                if (S.cross_iter[t] >= 0) continue;
-                if (rg <= S.spec_thr[t]) {
-                    S.cross_iter[t] = S.n1;
-                    S.cross_gamma[t] = g;
-                    due |= 1 << t;
-                } else {
-                    ++left;
-                }
-            }
-            S.snap_mask = due;
-            if (a.step_cnt[1] > a.hold_above) {
-                // Until the loosest candidate is crossed every choice of eps1
-                // needs these iterations; from the first crossing on they may
-                // be wasted, so the system waits there for eps1 without taking
-                // bandwidth from the others (no iteration past the chosen
-                // eps1, no speculative FP64 phase that the choice may
-                // discard).  k_set_eps resumes it from the state the
-                // sequential method stops in, as after a run-ahead.
-                if (due) {
-                    S.ra_stop = left == 0 ? kRaAllCrossed : kRaWait;
-                    S.mode = kHold;
-                } else if (S.n1 >= S.maxit1) {
-                    S.ra_stop = kRaMaxit;
-                    S.mode = kHold;
-                }
-            } else if (left == 0) {
-                // every candidate crossed before eps1 is known: the FP64 phase
-                // starts now from the tightest candidate's state (x~ of this
-                // iteration); k_set_eps keeps it when the chosen candidate
-                // crossed at this same iteration, else restarts the FP64 phase
-                // from the chosen candidate's copy -- the sequential method's
-                // state either way
-                S.ra_stop = kRaAllCrossed;
-                S.spec = 1;
-                S.relres_sp = sqrt(g) / sb;
-                S.src = kSrcX32;
-                S.ph_it = 0;
-                S.mode = kRestart;
-            } else if (S.n1 >= S.maxit1) {
-                S.ra_stop = kRaMaxit;
-                S.mode = kHold;
-            }
-            return;
-        }
-        if (sqrt(g) <= S.thr1 || S.n1 >= S.maxit1) {
-            if (!(sqrt(g) <= S.thr1)) S.flags |= MPCG_FLAG_FP32_MAXIT;
-            S.relres_sp = sqrt(g) / sb;
-            S.src = kSrcX32;
-            S.ph_it = 0;
-            S.mode = kRestart;
-        }
-    } else {
-        S.n2 += 1;
-        S.beta = g / gp;
-        if (sqrt(g) <= S.thr2) {
-            S.mode = kResid;
-        } else if (S.n2 >= S.maxit2) {
-            S.pend = MPCG_ENOCONV;
-            S.mode = kResid;
-        }
-    }
+    if (threadIdx.x == 0) step_update_done(S, a.step_cnt[1] > a.hold_above, g);
 }
 
 // ----------------------------------------------------------------- 2BFS --
@@ -1739,7 +1605,8 @@ void launch_bfs_band(hipStream_t s, const BArena &a, const BandList &l)
 
 // ------------------------------------------------------- admission (host) --
 
-static int adm_grid(const AdmitList &l, int spb)
+template <typename LIST>
+static int adm_grid(const LIST &l, int spb)
 {
     int g = 0;
     for (int j = 0; j < l.cnt; ++j) g += (l.nsl[j] + spb - 1) / spb;
@@ -1762,9 +1629,14 @@ void launch_admit_stage2(hipStream_t s, const BArena &a, const AdmitList &l)
     hipLaunchKernelGGL(k_admit_publish_l, dim3(adm_grid(l, kBlock)), dim3(kBlock), 0, s, a, l);
 }
 
-void launch_release(hipStream_t s, const BArena &a, int32_t sys, int32_t slice0, int32_t nslices)
+void launch_results(hipStream_t s, const BArena &a, const RetireList &l)
 {
-    hipLaunchKernelGGL(k_release, dim3(rows_grid(nslices)), dim3(kBlock), 0, s, a, sys, slice0, nslices);
+    if (l.cnt > 0) hipLaunchKernelGGL(k_results_l, dim3(adm_grid(l, kSlicesPerBlock)), dim3(kBlock), 0, s, a, l);
+}
+
+void launch_releases(hipStream_t s, const BArena &a, const RetireList &l)
+{
+    if (l.cnt > 0) hipLaunchKernelGGL(k_release_l, dim3(adm_grid(l, kBlock)), dim3(kBlock), 0, s, a, l);
 }
 
 void launch_cancel(hipStream_t s, const BArena &a, int32_t sys)
