@@ -93,6 +93,7 @@ struct alignas(256) BSys {
     unsigned long long doffs;              // bit d + 32: some entry at j - i = d, 0 < |d| <= 31 (admission)
     int32_t band_fail;                     // band 2BFS: 1 frontier too wide for its window, 2 not connected
     int32_t split;                         // CG product in two launches (scattered columns, set at admission)
+    int32_t ds, ds_bad;                    // diagonal storage: distances (0: SELL-64); no symmetric band (admission)
     int64_t padded;                        // SELL-64 entries of the system (admission scan)
     unsigned long long comp_best;
     int64_t item0;                         // first BFS work item of this system in the current level
@@ -223,6 +224,9 @@ constexpr int kBandMaxBw = 31;          // offsets d + 32 fit bits 1..63 of a 64
 // scattered columns: their CG product runs in two launches (k_b_dir forms
 // d, the product gathers it alone instead of r and d_old).
 constexpr int kSplitBw = 4096;
+// Diagonal storage of bands (batch_ds.hpp): at most this many distances, and
+// at least two thirds of the diagonals' places filled.
+constexpr int kBdsMax = 8;
 // batch_runahead = 0: systems wait for their features (at their first
 // crossing) only while more than this many systems share the steps; with
 // fewer, the run-ahead takes bandwidth that would otherwise go unused.

@@ -7,7 +7,7 @@
 // 2BFS of the section "Computing Pseudo-Diameter of the Graph Matrix" per
 // connected component.
 
-#include "batch_step.hpp"
+#include "batch_ds.hpp"
 
 #include <cmath>
 
@@ -327,6 +327,7 @@ __device__ inline void adm_finish(const BArena &a, int32_t sys, double eps1, int
     if (threadIdx.x == 0) {
         S.entry0 = entry0;
         S.split = S.bw > kSplitBw ? 1 : 0;   // the entries' pass has recorded the bandwidth
+        S.ds = S.ds_bad ? 0 : bds_candidate(S);
         S.bb = bb;
         S.gamma = g0;
         S.ph_it = 0;
@@ -421,12 +422,31 @@ __global__ void __launch_bounds__(1024) k_admit_scan_l(BArena a, AdmitList L)
     adm_scan(a, L.sys[blockIdx.x], part);
 }
 
-// stage 2: entries, start state (block per system), publication
+// stage 2: entries, whether they are a symmetric band, start state (block per
+// system), diagonal storage, publication
 __global__ void __launch_bounds__(kBlock) k_admit_entries_l(BArena a, AdmitList L)
 {
     int j, blk;
     if (!adm_block(L, kSlicesPerBlock, j, blk)) return;
     adm_entries(a, L.sys[j], L.rp[j], L.rp_i64[j], L.col[j], L.val[j], L.entry0[j], blk);
+}
+
+__global__ void __launch_bounds__(kBlock) k_admit_verify_l(BArena a, AdmitList L)
+{
+    int j, blk;
+    if (!adm_block(L, kSlicesPerBlock, j, blk)) return;
+    const int k = blk * kSlicesPerBlock + (int)(threadIdx.x >> 6);
+    const BSys &S = a.sys[L.sys[j]];
+    if (k < S.nslices) bds_verify(a, S, L.entry0[j], L.sys[j], S.slice0 + k);
+}
+
+__global__ void __launch_bounds__(kBlock) k_admit_diagonals_l(BArena a, AdmitList L)
+{
+    int j, blk;
+    if (!adm_block(L, kSlicesPerBlock, j, blk)) return;
+    const int k = blk * kSlicesPerBlock + (int)(threadIdx.x >> 6);
+    const BSys &S = a.sys[L.sys[j]];
+    if (k < S.nslices) bds_convert(a, S, S.slice0 + k);
 }
 
 __global__ void __launch_bounds__(kBlock) k_admit_finish_l(BArena a, AdmitList L)
@@ -677,9 +697,12 @@ __device__ inline double residual(const BArena &a, const BSys &S, bool restart, 
 }
 
 template <bool NT>
-__global__ void __launch_bounds__(kBlock) k_b_product(BArena a)
+__global__ void __launch_bounds__(kBlock, 8) __attribute__((amdgpu_num_sgpr(kSgprCap))) k_b_product(BArena a)
 {
-    const int k = blockIdx.x * kSlicesPerBlock + (threadIdx.x >> 6);
+    __shared__ double lu[kSlicesPerBlock][kBdsLds];
+    // scalar: the wave's slice, its system and the system's state
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int k = blockIdx.x * kSlicesPerBlock + wv;
     if (k >= a.step_cnt[0]) return;
     const int2 e = a.step_map[k];   // slice and its system: no dependent lookup of the owner
     const int sl = e.x, s = e.y;
@@ -694,9 +717,17 @@ __global__ void __launch_bounds__(kBlock) k_b_product(BArena a)
     }
     const int mode = S.mode;
     if (mode != kCg32 && mode != kCg64 && mode != kRestart && mode != kResid) return;
+    double p;
+    if (S.ds) {
+        if (mode == kCg32)
+            p = bds_product<float>(a, S, a.v32, a.r32, a.dA32, a.dB32, a.q32, sl, reinterpret_cast<float *>(lu[wv]));
+        else if (mode == kCg64) p = bds_product<double>(a, S, a.v64, a.r64, a.dA64, a.dB64, a.q64, sl, lu[wv]);
+        else p = bds_residual(a, S, mode == kRestart, sl, lu[wv]);
+        if (lane == 0) a.pslice[2 * (size_t)sl] = p;
+        return;
+    }
     const int len = a.rowlen[row];
     const int64_t base = S.entry0 + a.slice_off[sl] + lane;
-    double p;
     if (mode == kCg32) p = cg_product<float, NT>(a, S, a.v32, a.r32, a.dA32, a.dB32, a.q32, base, row, len);
     else if (mode == kCg64) p = cg_product<double, NT>(a, S, a.v64, a.r64, a.dA64, a.dB64, a.q64, base, row, len);
     else p = residual<NT>(a, S, mode == kRestart, base, row, len);
@@ -1625,7 +1656,10 @@ void launch_admit_stage2(hipStream_t s, const BArena &a, const AdmitList &l)
 {
     if (l.cnt <= 0) return;
     hipLaunchKernelGGL(k_admit_entries_l, dim3(adm_grid(l, kSlicesPerBlock)), dim3(kBlock), 0, s, a, l);
+    const int g = adm_grid(l, kSlicesPerBlock);
+    hipLaunchKernelGGL(k_admit_verify_l, dim3(g), dim3(kBlock), 0, s, a, l);
     hipLaunchKernelGGL(k_admit_finish_l, dim3(l.cnt), dim3(kBlock), 0, s, a, l);
+    hipLaunchKernelGGL(k_admit_diagonals_l, dim3(g), dim3(kBlock), 0, s, a, l);
     hipLaunchKernelGGL(k_admit_publish_l, dim3(adm_grid(l, kBlock)), dim3(kBlock), 0, s, a, l);
 }
 
