@@ -131,7 +131,7 @@ struct BArena {
     int64_t *items;                        // total items of the large level
     // the step's work list, rebuilt when a system joins or leaves it
     int2 *step_map;                        // [k] = (slice, slot) of the k-th listed slice (systems in list order)
-    int32_t *step_sys;                     // [k] = slot of the k-th listed system
+    int4 *step_sys;                        // [k] = (slot, first slice, slices, 0) of the k-th listed system
     int32_t *step_cnt;                     // [0] = listed slices, [1] = listed systems
     int32_t acc32;                         // dot_acc = 1: FP32-phase dot products accumulate in FP32
     int32_t nt;                            // the step product reads the matrices with nontemporal loads

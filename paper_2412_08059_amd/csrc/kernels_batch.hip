@@ -10,6 +10,7 @@
 #include "batch_ds.hpp"
 
 #include <cmath>
+#include <cstddef>
 
 namespace mpcg {
 namespace batch {
@@ -44,25 +45,28 @@ __device__ inline double block_sum_d(double v, double *sm)
     return s;
 }
 
+// The thread's chain of a system's slice partials (component j): every kBlock-th
+// in order, kSumAhead loads in flight.
+constexpr int kSumAhead = 8;
+template <typename A> __device__ inline A slice_sum(const BArena &a, int slice0, int cnt, int j)
+{
+    const double *p = a.pslice + 2 * (size_t)slice0 + j;
+    A acc = A(0);
+    for (int i = threadIdx.x; i < cnt; i += kSumAhead * kBlock) {
+        double v[kSumAhead];
+#pragma unroll
+        for (int t = 0; t < kSumAhead; ++t) v[t] = i + t * kBlock < cnt ? p[2 * (size_t)(i + t * kBlock)] : 0.0;
+#pragma unroll
+        for (int t = 0; t < kSumAhead; ++t)
+            if (i + t * kBlock < cnt) acc += (A)v[t];
+    }
+    return acc;
+}
+
 // Sum of component j of the slice partials of system S, fixed order.
 __device__ inline double sys_sum(const BArena &a, const BSys &S, int j, double *sm)
 {
-    // four loads in flight per thread, added in index order (the same bits
-    // as one at a time)
-    const double *p = a.pslice + 2 * (size_t)S.slice0 + j;
-    const int cnt = S.nslices;
-    double acc = 0.0;
-    int i = threadIdx.x;
-    for (; i + 3 * kBlock < cnt; i += 4 * kBlock) {
-        const double p0 = p[2 * (size_t)i], p1 = p[2 * (size_t)(i + kBlock)];
-        const double p2 = p[2 * (size_t)(i + 2 * kBlock)], p3 = p[2 * (size_t)(i + 3 * kBlock)];
-        acc += p0;
-        acc += p1;
-        acc += p2;
-        acc += p3;
-    }
-    for (; i < cnt; i += kBlock) acc += p[2 * (size_t)i];
-    return block_sum_d(acc, sm);
+    return block_sum_d(slice_sum<double>(a, S.slice0, S.nslices, j), sm);
 }
 
 // dot_acc = 1: the FP32 phase's sums in float (partials stored widened, exact).
@@ -70,19 +74,7 @@ __device__ inline float wave_sum_f(float v) { return wave_sum_all(v); }
 
 __device__ inline double sys_sum_f(const BArena &a, const BSys &S, int j, double *sm)
 {
-    const double *p = a.pslice + 2 * (size_t)S.slice0 + j;
-    const int cnt = S.nslices;
-    float acc = 0.0f;
-    int i = threadIdx.x;
-    for (; i + 3 * kBlock < cnt; i += 4 * kBlock) {
-        const double p0 = p[2 * (size_t)i], p1 = p[2 * (size_t)(i + kBlock)];
-        const double p2 = p[2 * (size_t)(i + 2 * kBlock)], p3 = p[2 * (size_t)(i + 3 * kBlock)];
-        acc += (float)p0;
-        acc += (float)p1;
-        acc += (float)p2;
-        acc += (float)p3;
-    }
-    for (; i < cnt; i += kBlock) acc += (float)p[2 * (size_t)i];
+    float acc = slice_sum<float>(a, S.slice0, S.nslices, j);
     acc = wave_sum_f(acc);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     if (lane == 0) sm[w] = (double)acc;
@@ -118,7 +110,7 @@ size_t arena_bytes(int32_t max_sys, int32_t max_slices, int64_t max_entries)
     t += up256(8 * rows);                                             // band 2BFS masks
     t += up256(4 * e) + up256(8 * e) + up256(4 * e);                  // col, v64, v32
     t += up256(4 * (size_t)max_sys) * 2 + up256(8 * (size_t)max_sys) + 256 + 256;
-    t += up256(8 * sl) + up256(4 * (size_t)max_sys) + 256;            // step work list
+    t += up256(8 * sl) + up256(16 * (size_t)max_sys) + 256;           // step work list
     return t;
 }
 
@@ -166,7 +158,7 @@ BArena carve(void *base, int32_t max_sys, int32_t max_slices, int64_t max_entrie
     a.counts = reinterpret_cast<int32_t *>(take(256));
     a.items = reinterpret_cast<int64_t *>(take(256));
     a.step_map = reinterpret_cast<int2 *>(take(8 * sl));
-    a.step_sys = reinterpret_cast<int32_t *>(take(4 * (size_t)max_sys));
+    a.step_sys = reinterpret_cast<int4 *>(take(16 * (size_t)max_sys));
     a.step_cnt = reinterpret_cast<int32_t *>(take(256));
     return a;
 }
@@ -529,7 +521,7 @@ __global__ void k_set_eps(BArena a, int32_t sys, double eps1, int32_t ci)
         S.mode = kRestart;
         return;
     }
-    if (S.spec) {   // the speculative FP64 phase (see k_b_scalar2)
+    if (S.spec) {   // the speculative FP64 phase (see step_update_done)
         S.spec = 0;
         if (ci >= 0 && ci < kNumEps && S.cross_iter[ci] == S.cross_iter[kNumEps - 1]) return;   // same state: kept
         // discarded: the FP64 stage starts again from the chosen candidate's copy
@@ -696,15 +688,27 @@ __device__ inline double residual(const BArena &a, const BSys &S, bool restart, 
     return wave_dot(res, res);
 }
 
+// Entry of the list at position `at`, and whether it is listed: both loaded at
+// once (a position past the list reads an entry of the array that is not used;
+// a dependent load costs 0.8 us, the caches being cold at a launch's start).
+template <typename E>
+__device__ inline bool listed(const E *list, int32_t cap, const int32_t *cnt, int32_t at, E &e, int32_t &n)
+{
+    e = list[min(at, cap - 1)];
+    n = *cnt;
+    asm volatile("" : "+s"(e.x), "+s"(n));
+    return at < n;
+}
+
 template <bool NT>
 __global__ void __launch_bounds__(kBlock, 8) __attribute__((amdgpu_num_sgpr(kSgprCap))) k_b_product(BArena a)
 {
     __shared__ double lu[kSlicesPerBlock][kBdsLds];
     // scalar: the wave's slice, its system and the system's state
     const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int k = blockIdx.x * kSlicesPerBlock + wv;
-    if (k >= a.step_cnt[0]) return;
-    const int2 e = a.step_map[k];   // slice and its system: no dependent lookup of the owner
+    int2 e;   // slice and its system: no dependent lookup of the owner
+    int32_t total;
+    if (!listed(a.step_map, a.max_slices, a.step_cnt, (int)blockIdx.x * kSlicesPerBlock + wv, e, total)) return;
     const int sl = e.x, s = e.y;
     if (s < 0) return;
     const BSys &S = a.sys[s];
@@ -734,19 +738,6 @@ __global__ void __launch_bounds__(kBlock, 8) __attribute__((amdgpu_num_sgpr(kSgp
     if (lane == 0) a.pslice[2 * (size_t)sl] = p;
 }
 
-// Block per system: finish the product's reduction and take its decision.
-__global__ void __launch_bounds__(kBlock) k_b_scalar1(BArena a)
-{
-    __shared__ double sm[kBlock / 64 + 1];
-    if ((int)blockIdx.x >= a.step_cnt[1]) return;
-    BSys &S = a.sys[a.step_sys[blockIdx.x]];
-    const int mode = S.mode;
-    if (threadIdx.x == 0 && S.snap_mask) S.snap_mask = 0;   // the product of this step took the copies
-    if (mode != kCg32 && mode != kCg64 && mode != kRestart && mode != kResid) return;
-    const double v = (mode == kCg32 && a.acc32) ? sys_sum_f(a, S, 0, sm) : sys_sum(a, S, 0, sm);
-    if (threadIdx.x == 0) step_product_done(S, mode, v);
-}
-
 template <typename T>
 __device__ inline double cg_update(const BArena &a, const BSys &S, T *x, T *r, const T *q, const T *dA, const T *dB,
                                    int row)
@@ -762,9 +753,10 @@ __device__ inline double cg_update(const BArena &a, const BSys &S, T *x, T *r, c
 
 __global__ void __launch_bounds__(kBlock) k_b_update(BArena a)
 {
-    const int k = blockIdx.x * kSlicesPerBlock + (threadIdx.x >> 6);
-    if (k >= a.step_cnt[0]) return;
-    const int2 e = a.step_map[k];   // slice and its system: no dependent lookup of the owner
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    int2 e;
+    int32_t total;
+    if (!listed(a.step_map, a.max_slices, a.step_cnt, (int)blockIdx.x * kSlicesPerBlock + wv, e, total)) return;
     const int sl = e.x, s = e.y;
     if (s < 0) return;
     const BSys &S = a.sys[s];
@@ -776,15 +768,59 @@ __global__ void __launch_bounds__(kBlock) k_b_update(BArena a)
     if (lane == 0) a.pslice[2 * (size_t)sl] = p;
 }
 
-// Block per system: gamma of the new residual, v ratios, stop tests, beta.
-__global__ void __launch_bounds__(kBlock) k_b_scalar2(BArena a)
+// Block per system, after the product (UPDATE false: delta and alpha, or the
+// restart and final-check decisions) or after the update (true: gamma of the
+// new residual, v ratios, stop tests, beta).  The state and the partials are
+// loaded together, from the list entry, and one thread decides on the state's
+// copy in LDS: what is left is two memory latencies, one reduction and the
+// store (4.8 us a launch when the list, the state, the partials and the
+// state's other fields followed one another).
+template <bool UPDATE> __global__ void __launch_bounds__(kBlock) k_b_scalar(BArena a)
 {
-    __shared__ double sm[kBlock / 64 + 1];
-    if ((int)blockIdx.x >= a.step_cnt[1]) return;
-    BSys &S = a.sys[a.step_sys[blockIdx.x]];
-    if (!S.upd) return;
-    const double g = (S.mode == kCg32 && a.acc32) ? sys_sum_f(a, S, 0, sm) : sys_sum(a, S, 0, sm);
-    if (threadIdx.x == 0) step_update_done(S, a.step_cnt[1] > a.hold_above, g);
+    __shared__ BSys S;
+    __shared__ double sm[kBlock / 64];
+    constexpr int kWords = (int)(sizeof(BSys) / 4);
+    static_assert(kWords <= kBlock, "one word a thread");
+    const int tid = threadIdx.x;
+    int4 e;
+    int32_t nsys;
+    if (!listed(a.step_sys, a.max_sys, a.step_cnt + 1, (int)blockIdx.x, e, nsys)) return;
+    uint32_t *g = reinterpret_cast<uint32_t *>(a.sys + e.x);
+    uint32_t *l = reinterpret_cast<uint32_t *>(&S);
+    const uint32_t word = tid < kWords ? g[tid] : 0u;
+    const double part = slice_sum<double>(a, e.y, e.z, 0);
+    float part32 = 0.0f;
+    if (a.acc32) part32 = slice_sum<float>(a, e.y, e.z, 0);
+    if (tid < kWords) l[tid] = word;
+    const double ws = wave_sum_all(part);
+    float ws32 = 0.0f;
+    if (a.acc32) ws32 = wave_sum_all(part32);
+    __syncthreads();
+    const int mode = S.mode;
+    const bool f32 = a.acc32 && mode == kCg32;
+    if (UPDATE ? !S.upd : mode != kCg32 && mode != kCg64 && mode != kRestart && mode != kResid && !S.snap_mask) return;
+    if ((tid & 63) == 0) sm[tid >> 6] = f32 ? (double)ws32 : ws;
+    __syncthreads();
+    if (tid == 0) {
+        double v = 0.0;
+        if (f32) {
+            float s = 0.0f;
+            for (int i = 0; i < kBlock / 64; ++i) s += (float)sm[i];
+            v = (double)s;
+        } else {
+            for (int i = 0; i < kBlock / 64; ++i) v += sm[i];
+        }
+        if (UPDATE) {
+            step_update_done(S, nsys > a.hold_above, v);
+        } else {
+            S.snap_mask = 0;   // the product of this step took the copies
+            if (mode == kCg32 || mode == kCg64 || mode == kRestart || mode == kResid) step_product_done(S, mode, v);
+        }
+    }
+    __syncthreads();
+    // the fields of the recurrence only: those of the 2BFS belong to another stream
+    constexpr int kFrom = (int)(offsetof(BSys, mode) / 4), kTo = (int)(offsetof(BSys, bfs_mode) / 4);
+    if (tid >= kFrom && tid < kTo) g[tid] = l[tid];
 }
 
 // ----------------------------------------------------------------- 2BFS --
@@ -1108,7 +1144,7 @@ __global__ void __launch_bounds__(kBlock) k_worklist(BArena a, ListChunk c)
     if (j >= c.n) return;
     const int32_t s0 = c.slice0[j], pre = c.pre[j];
     for (int i = threadIdx.x; i < c.nslices[j]; i += kBlock) a.step_map[pre + i] = make_int2(s0 + i, c.slot[j]);
-    if (threadIdx.x == 0) a.step_sys[c.first + j] = c.slot[j];
+    if (threadIdx.x == 0) a.step_sys[c.first + j] = make_int4(c.slot[j], s0, c.nslices[j], 0);
 }
 
 void launch_worklist(hipStream_t s, const BArena &a, const ListChunk &c)
@@ -1149,9 +1185,9 @@ void launch_step(hipStream_t s, const BArena &a, int32_t grid_slices, int32_t gr
     if (dir) hipLaunchKernelGGL(k_b_dir, dim3(grid_slices), dim3(kBlock), 0, s, a);
     if (a.nt) hipLaunchKernelGGL(k_b_product<true>, dim3(grid_slices), dim3(kBlock), 0, s, a);
     else hipLaunchKernelGGL(k_b_product<false>, dim3(grid_slices), dim3(kBlock), 0, s, a);
-    hipLaunchKernelGGL(k_b_scalar1, dim3(grid_sys), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_b_scalar<false>, dim3(grid_sys), dim3(kBlock), 0, s, a);
     hipLaunchKernelGGL(k_b_update, dim3(grid_slices), dim3(kBlock), 0, s, a);
-    hipLaunchKernelGGL(k_b_scalar2, dim3(grid_sys), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(k_b_scalar<true>, dim3(grid_sys), dim3(kBlock), 0, s, a);
 }
 
 void launch_bfs_round(hipStream_t s, const BArena &a, int32_t hi_sys, int small_levels, int small_cap,
