@@ -21,8 +21,9 @@
 // groups as there and leave partials of the same rows.
 //
 // What bounds it: the bytes above plus the vectors (gathers of r and d hit
-// the L2).  One FP64 CG product on the 128^3 stencil moves 168 MB instead of
-// 255 MB.
+// the L2).  One FP64 CG product on the 128^3 stencil needs 168 MB instead of
+// 255 MB (counted: 188 MB read and 50 MB written; neighbouring rows a plane of
+// the grid apart fall to other XCDs' L2s).
 
 #include "jacobi_common.hpp"
 
@@ -385,9 +386,80 @@ __device__ inline T ds_sum(const T *p, uint32_t S, const int32_t *d, int32_t n, 
     return ds_row<NH, true, NEAR, SKIP_MAIN, T>(p, S, d, n, rb + lane, lane, lu, g);
 }
 
-template <int MODE, typename T, int NH, bool NEAR>
-__global__ void __launch_bounds__(kBlock, 8) __attribute__((amdgpu_num_sgpr(kSgprCap))) k_ds(DsArgs<T> a)
+// A slice's operands for a CG product, all loaded at once: the matrix, d_old
+// and r of the columns (NEAR: of the slice and of its halo, else one per
+// diagonal), x of the rows.  LOOP: a wave takes several slices in turn.
+template <int NH, bool NEAR, bool LOOP, typename T> struct DsSlice {
+    static constexpr int K = 2 * NH + 1, C = NEAR ? 2 : K, OWN = NEAR ? 0 : NH;
+    T v[K], d[C], r[C], x;
+
+    __device__ inline void load(const DsArgs<T> &a, const T *dold, int rb, int lane)
+    {
+        constexpr int W = (int)sizeof(T);
+        int32_t row = rb + lane;
+        if (LOOP) asm("" : "+v"(row));   // opaque: see ds_row
+        const int32_t last = a.n - 1, rc = min(row, last);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int t = k - NH;
+            const int32_t c = row + (t < 0 ? -a.d[-t - 1] : (t > 0 ? a.d[t - 1] : 0));
+            v[k] = T(NAN);   // no entry
+            if (!NEAR) d[k] = r[k] = T(0);
+            if (c >= 0 && c <= last) {
+                v[k] = ds_at(a.p, (uint32_t)((t < 0 ? c : rc) * W) + (uint32_t)(t < 0 ? -t : t) * a.S);
+                if (!NEAR) {
+                    d[k] = ds_at(dold, (uint32_t)(c * W));
+                    r[k] = ds_at(a.r, (uint32_t)(c * W));
+                }
+            }
+        }
+        if (NEAR) {
+            const int reach = a.d[NH - 1], h = lane < reach ? lane - reach : lane + reach;
+            const uint32_t o = (uint32_t)(rc * W), ho = (uint32_t)(max(0, min(rb + h, last)) * W);
+            d[0] = ds_at(dold, o);
+            r[0] = ds_at(a.r, o);
+            d[C - 1] = ds_at(dold, ho);
+            r[C - 1] = ds_at(a.r, ho);
+        }
+        x = ds_at(a.x, (uint32_t)(rc * W));
+    }
+
+    // The row's sum of v * (r + beta d_old).
+    __device__ inline T sum(const DsArgs<T> &a, T beta, int lane, T *lu) const
+    {
+        int at = a.d[NH - 1] + lane;
+        if (LOOP) asm("" : "+v"(at));
+        if (NEAR) {
+            const int reach = a.d[NH - 1], h = lane < reach ? lane - reach : lane + reach;
+            if (LOOP) __builtin_amdgcn_wave_barrier();   // the previous slice's reads are done
+            lu[reach + lane] = fma_t<T>(beta, d[0], r[0]);
+            if (lane < reach || lane >= 64 - reach) lu[reach + h] = fma_t<T>(beta, d[C - 1], r[C - 1]);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+        T acc = T(0);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int t = k - NH;
+            const int32_t off = t < 0 ? -a.d[-t - 1] : (t > 0 ? a.d[t - 1] : 0);
+            const T u = NEAR ? lu[at + off] : fma_t<T>(beta, d[NEAR ? 0 : k], r[NEAR ? 0 : k]);
+            const T f = fma_t<T>(v[k], u, acc);
+            acc = v[k] == v[k] ? f : acc;
+        }
+        return acc;
+    }
+};
+
+// How a wave takes its slices: one after the other, their diagonals loaded as
+// they are walked (kDsWalk); or each loaded whole, the first before the
+// iteration's scalars are known: its only slice (kDsOne), or several (kDsLoop).
+enum DsPre { kDsWalk = 0, kDsOne = 1, kDsLoop = 2 };
+
+template <int MODE, typename T, int NH, bool NEAR, int PRE>
+__global__ void __launch_bounds__(kBlock, PRE == kDsWalk ? 8 : PRE == kDsOne ? 4 : 5)
+__attribute__((amdgpu_num_sgpr(kSgprCap))) k_ds(DsArgs<T> a)
 {
+    static_assert(PRE == kDsWalk || MODE == kDsCg, "the products of a phase");
     constexpr int NV = MODE == kDsRestart ? 3 : 1;
     __shared__ double sm[kBlock / 64];
     __shared__ T s_u[kBlock / 64][NEAR ? 64 + 2 * kDsNear : 1];
@@ -400,6 +472,10 @@ __global__ void __launch_bounds__(kBlock, 8) __attribute__((amdgpu_num_sgpr(kSgp
     bool x_pending = false, f32acc = false;
     const T *dold = nullptr;
     T *dnew = nullptr;
+    DsSlice<NH, NEAR, PRE == kDsLoop, T> one;
+    SliceWalk ow = slice_walk(a.walk);
+    int osl = ow.g < ow.g_end ? ow.g * (kBlock / 64) + wv : a.nslices;
+    if (PRE && osl < a.nslices) one.load(a, (a.it & 1) ? a.dB : a.dA, osl * 64, lane);
     if (MODE == kDsCg) {
         __shared__ double sm_rho[kBlock / 64], sm_g[kBlock / 64];
         const int it = a.it;
@@ -434,51 +510,73 @@ __global__ void __launch_bounds__(kBlock, 8) __attribute__((amdgpu_num_sgpr(kSgp
     double s[NV];
     for (int j = 0; j < NV; ++j) s[j] = 0.0;
     float sf = 0.0f;   // d.q in FP32 (dot_acc = 1)
-    for (SliceWalk w = slice_walk(a.walk); w.g < w.g_end; w.g += w.step) {
-        const int sl = w.g * (kBlock / 64) + wv;
-        if (sl >= a.nslices) continue;
-        const int rb = sl * 64;
-        const int row = rb + lane;
-        const bool has = row < a.n;
-        T acc;
-        if (MODE == kDsCg)
-            acc = ds_sum<NH, NEAR, false, T>(a.p, a.S, a.d, a.n, rb, lane, lu,
-                                       [&](uint32_t c) { return fma_t<T>(beta, ds_at(dold, c), ds_at(a.r, c)); });
-        else if (MODE == kDsPlain)
-            acc = ds_sum<NH, NEAR, false, T>(a.p, a.S, a.d, a.n, rb, lane, lu, [&](uint32_t c) { return ds_at(a.xin, c); });
-        else if (a.x32)
-            acc = ds_sum<NH, NEAR, false, T>(a.p, a.S, a.d, a.n, rb, lane, lu,
-                                       [&](uint32_t c) { return (T)ds_at(a.x32, c / 2); });
-        else
-            acc = ds_sum<NH, NEAR, false, T>(a.p, a.S, a.d, a.n, rb, lane, lu,
-                                       [&](uint32_t c) { return (T)ds_at(a.x64in, c); });
-        if (!has) continue;
-        if (MODE == kDsPlain) {
-            a.yout[row] = acc;
-        } else if (MODE == kDsCg) {
-            const T dof = dold[row];
-            if (x_pending) a.x[row] = fma_t<T>(alpha_prev, dof, a.x[row]);
-            const T dn = fma_t<T>(beta, dof, a.r[row]);
-            dnew[row] = dn;
-            a.q[row] = acc;
-            if (f32acc) sf = fmaf((float)dn, (float)acc, sf);
-            else s[0] = fma((double)dn, (double)acc, s[0]);
-        } else {
-            const double bv = a.b[row];
-            const double res = bv - (double)acc;
-            if (MODE == kDsRestart) {
-                if (a.x32) a.x64out[row] = (double)a.x32[row];
-                a.rout[row] = res;
-                a.dz[row] = 0.0;
-                s[1 % NV] = fma(bv, bv, s[1 % NV]);
-                double zv = res;
-                if (a.dg) {
-                    zv = res / a.dg[row];
-                    a.z[row] = zv;
-                }
-                s[2 % NV] = fma(res, zv, s[2 % NV]);
+    if (PRE) {
+        while (osl < a.nslices) {
+            const int row = osl * 64 + lane;
+            const T acc = one.sum(a, beta, lane, lu);
+            if (row < a.n) {
+                const T dof = one.d[one.OWN];
+                if (x_pending) a.x[row] = fma_t<T>(alpha_prev, dof, one.x);
+                const T dn = fma_t<T>(beta, dof, one.r[one.OWN]);
+                dnew[row] = dn;
+                a.q[row] = acc;
+                if (f32acc) sf = fmaf((float)dn, (float)acc, sf);
+                else s[0] = fma((double)dn, (double)acc, s[0]);
             }
-            s[0] = fma(res, res, s[0]);
+            if (PRE == kDsOne) break;
+            ow.g += ow.step;
+            if (ow.g >= ow.g_end) break;
+            osl = ow.g * (kBlock / 64) + wv;
+            if (osl >= a.nslices) break;
+            one.load(a, dold, osl * 64, lane);
+        }
+    } else {
+        for (SliceWalk w = slice_walk(a.walk); w.g < w.g_end; w.g += w.step) {
+            const int sl = w.g * (kBlock / 64) + wv;
+            if (sl >= a.nslices) continue;
+            const int rb = sl * 64;
+            const int row = rb + lane;
+            const bool has = row < a.n;
+            T acc;
+            if (MODE == kDsCg)
+                acc = ds_sum<NH, NEAR, false, T>(a.p, a.S, a.d, a.n, rb, lane, lu,
+                                           [&](uint32_t c) { return fma_t<T>(beta, ds_at(dold, c), ds_at(a.r, c)); });
+            else if (MODE == kDsPlain)
+                acc = ds_sum<NH, NEAR, false, T>(a.p, a.S, a.d, a.n, rb, lane, lu, [&](uint32_t c) { return ds_at(a.xin, c); });
+            else if (a.x32)
+                acc = ds_sum<NH, NEAR, false, T>(a.p, a.S, a.d, a.n, rb, lane, lu,
+                                           [&](uint32_t c) { return (T)ds_at(a.x32, c / 2); });
+            else
+                acc = ds_sum<NH, NEAR, false, T>(a.p, a.S, a.d, a.n, rb, lane, lu,
+                                           [&](uint32_t c) { return (T)ds_at(a.x64in, c); });
+            if (!has) continue;
+            if (MODE == kDsPlain) {
+                a.yout[row] = acc;
+            } else if (MODE == kDsCg) {
+                const T dof = dold[row];
+                if (x_pending) a.x[row] = fma_t<T>(alpha_prev, dof, a.x[row]);
+                const T dn = fma_t<T>(beta, dof, a.r[row]);
+                dnew[row] = dn;
+                a.q[row] = acc;
+                if (f32acc) sf = fmaf((float)dn, (float)acc, sf);
+                else s[0] = fma((double)dn, (double)acc, s[0]);
+            } else {
+                const double bv = a.b[row];
+                const double res = bv - (double)acc;
+                if (MODE == kDsRestart) {
+                    if (a.x32) a.x64out[row] = (double)a.x32[row];
+                    a.rout[row] = res;
+                    a.dz[row] = 0.0;
+                    s[1 % NV] = fma(bv, bv, s[1 % NV]);
+                    double zv = res;
+                    if (a.dg) {
+                        zv = res / a.dg[row];
+                        a.z[row] = zv;
+                    }
+                    s[2 % NV] = fma(res, zv, s[2 % NV]);
+                }
+                s[0] = fma(res, res, s[0]);
+            }
         }
     }
     if (MODE == kDsPlain) return;
@@ -560,10 +658,30 @@ template <typename T> static DsArgs<T> ds_args(const DsMat &m, int grid)
     return a;
 }
 
+// Slices are loaded whole in FP64 where their registers leave at least four
+// waves on a SIMD: every near matrix, far ones up to three distances.  The
+// first slice's loads run beside the partials' and all of a slice's loads are
+// in flight at once, which is worth more than the other four waves.  FP64 CG
+// product, us before and after: band of half-width 8, n = 100,000 5.9 -> 4.9,
+// 500,000 15.8 -> 11.9, 2 M 45.1 -> 34.2; 7-point 49^3 5.1 -> 4.8, 128^3
+// 34.9 -> 32.4; 5-point 300^2 4.5 -> 4.0, 1001^2 14.9 -> 14.2.  With eight
+// waves (64 registers) the same kernels spill: the band at 2 M took 302.  In
+// FP32, half the registers in flight either way, the walk is as fast or
+// faster (128^3 15.6 against 15.8, 1001^2 8.0 against 8.5).
+template <typename T, int NH, bool NEAR> constexpr bool ds_pre = sizeof(T) == 8 && (NEAR || NH <= 3);
+
 template <int MODE, typename T> static void ds_launch(hipStream_t s, const DsMat &m, int grid, const DsArgs<T> &a)
 {
     ds_dispatch(m, [&](auto nh, auto near) {
-        hipLaunchKernelGGL((k_ds<MODE, T, decltype(nh)::value, decltype(near)::value>), dim3(grid), dim3(kBlock), 0, s, a);
+        constexpr int NH = decltype(nh)::value;
+        constexpr bool NEAR = decltype(near)::value;
+        if constexpr (MODE == kDsCg && ds_pre<T, NH, NEAR>) {
+            if (a.nslices <= grid * (kBlock / 64))   // then no wave has two
+                hipLaunchKernelGGL((k_ds<MODE, T, NH, NEAR, kDsOne>), dim3(grid), dim3(kBlock), 0, s, a);
+            else hipLaunchKernelGGL((k_ds<MODE, T, NH, NEAR, kDsLoop>), dim3(grid), dim3(kBlock), 0, s, a);
+        } else {
+            hipLaunchKernelGGL((k_ds<MODE, T, NH, NEAR, kDsWalk>), dim3(grid), dim3(kBlock), 0, s, a);
+        }
     });
 }
 
