@@ -31,7 +31,7 @@ constexpr int kBdsHalo = kBandMaxBw;
 constexpr int kBdsLds = 64 + 2 * kBdsHalo;   // vector elements a wave keeps
 
 // The distances d > 0 of the system's entries: bit d.
-__device__ inline uint32_t bds_dist(const BSys &S) { return (uint32_t)(S.doffs >> 32) & ~1u; }
+__device__ inline uint32_t bds_dist(unsigned long long doffs) { return (uint32_t)(doffs >> 32) & ~1u; }
 
 // Whether the system's distances allow diagonal storage.  Worth it where two
 // thirds of the diagonals' places hold an entry; systems that may advance in
@@ -39,7 +39,7 @@ __device__ inline uint32_t bds_dist(const BSys &S) { return (uint32_t)(S.doffs >
 __device__ inline int bds_candidate(const BSys &S)
 {
     if (S.err || S.bw > kBandMaxBw || S.nslices <= kWgMaxSlices) return 0;
-    const uint32_t up = bds_dist(S), low = (uint32_t)S.doffs;   // low: distance d at bit 32 - d
+    const uint32_t up = bds_dist(S.doffs), low = (uint32_t)S.doffs;   // low: distance d at bit 32 - d
     const int nh = __popc(up);
     if (nh < 1 || nh > kBdsMax || (__brev(up) << 1) != low) return 0;
     if ((int64_t)(2 * nh + 1) * S.n * 2 > 3 * S.nnz) return 0;
@@ -83,7 +83,7 @@ __device__ inline void bds_convert(const BArena &a, const BSys &S, int sl)
     int k = 0;
     while (k < len && a.col[base + (int64_t)k * 64] < row) ++k;
     double v[kBdsMax + 1];
-    uint32_t m = bds_dist(S) | 1u;   // the main diagonal first
+    uint32_t m = bds_dist(S.doffs) | 1u;   // the main diagonal first
 #pragma unroll
     for (int t = 0; t <= kBdsMax; ++t) {
         v[t] = NAN;
@@ -102,11 +102,11 @@ __device__ inline void bds_convert(const BArena &a, const BSys &S, int sl)
 // Row sums of slice sl with the vector elements g(row); lu: the wave's LDS.
 // own: the row's element.
 template <typename T, typename G>
-__device__ inline T bds_sum(const BArena &a, const BSys &S, const T *val, int sl, T *lu, const G &g, T &own)
+__device__ inline T bds_sum(const BArena &a, const StepSys &S, const T *val, int sl, T *lu, const G &g, T &own)
 {
     const int lane = threadIdx.x & 63, row = sl * 64 + lane;
     const int nh = S.ds;
-    const uint32_t dist = bds_dist(S);
+    const uint32_t dist = bds_dist(S.doffs);
     const bool top = sl == S.slice0;
     // one scalar base, the previous slice's places first
     const int64_t off0 = a.slice_off[top ? sl : sl - 1];
@@ -167,7 +167,7 @@ __device__ inline T bds_sum(const BArena &a, const BSys &S, const T *val, int sl
 
 // As cg_product and residual for a system in diagonal storage.
 template <typename T>
-__device__ inline double bds_product(const BArena &a, const BSys &S, const T *val, const T *r, T *dA, T *dB, T *q,
+__device__ inline double bds_product(const BArena &a, const StepSys &S, const T *val, const T *r, T *dA, T *dB, T *q,
                                      int sl, T *lu)
 {
     const int row = sl * 64 + (int)(threadIdx.x & 63);
@@ -184,7 +184,7 @@ __device__ inline double bds_product(const BArena &a, const BSys &S, const T *va
     return wave_dot((double)dn, (double)acc);
 }
 
-__device__ inline double bds_residual(const BArena &a, const BSys &S, bool restart, int sl, double *lu)
+__device__ inline double bds_residual(const BArena &a, const StepSys &S, bool restart, int sl, double *lu)
 {
     const int row = sl * 64 + (int)(threadIdx.x & 63);
     const int src = restart ? S.src : (int)kSrcX64;

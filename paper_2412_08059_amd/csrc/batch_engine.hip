@@ -166,7 +166,7 @@ struct Engine {
     int64_t group = 0;
     // the step's work list: the admitted systems that are not retiring
     bool list_dirty = true;
-    int32_t list_slices = 0, list_sys = 0;
+    int32_t list_blocks = 0, list_sys = 0;
     int32_t list_max = 0;               // slices of the largest listed system
     // step groups captured as graphs, by (product grid, per-system grid)
     hipStream_t cap = nullptr;
@@ -704,9 +704,10 @@ bool Engine::rebuild_list()
     std::vector<int32_t> ids;
     for (int32_t i = 0; i < (int32_t)slots.size(); ++i)
         if (slots[i].used && slots[i].adm == 2 && !slots[i].retiring) ids.push_back(i);
+    auto blocks = [](const Slot &sl) { return (sl.nslices + kSlicesPerBlock - 1) / kSlicesPerBlock; };
     int32_t most = 0;
     for (int32_t i : ids) {
-        total += slots[i].nslices;
+        total += blocks(slots[i]);
         most = std::max(most, slots[i].nslices);
     }
     nsys = (int32_t)ids.size();
@@ -721,15 +722,15 @@ bool Engine::rebuild_list()
             c.slice0[c.n] = sl.slice0;
             c.nslices[c.n] = sl.nslices;
             c.pre[c.n] = pre;
-            pre += sl.nslices;
+            pre += blocks(sl);
         }
         c.last = k == ids.size() ? 1 : 0;
-        c.total_slices = total;
+        c.total_blocks = total;
         c.total_sys = nsys;
         launch_worklist(s, a, c);
     } while (k < ids.size());
     if (hipGetLastError() != hipSuccess) return false;
-    list_slices = total;
+    list_blocks = total;
     list_sys = nsys;
     list_max = most;
     list_dirty = false;
@@ -750,11 +751,11 @@ bool Engine::launch_group(int len)
         launch_wg_steps(s, a, list_sys, list_max, kWgSteps);
         return hipGetLastError() == hipSuccess;
     }
-    const int32_t gsl = coarse_grid((list_slices + kSlicesPerBlock - 1) / kSlicesPerBlock);
+    const int32_t gblk = coarse_grid(list_blocks);
     const int32_t gsys = coarse_grid(list_sys);
     if (graphs_ok) {
         const bool dir = dir_needed();
-        const auto key = std::make_tuple(gsl, gsys, (int32_t)len, (int32_t)dir);
+        const auto key = std::make_tuple(gblk, gsys, (int32_t)len, (int32_t)dir);
         auto it = graphs.find(key);
         if (it == graphs.end()) {
             if (graphs.size() >= 64) drop_graphs();
@@ -762,7 +763,7 @@ bool Engine::launch_group(int len)
             hipGraphExec_t ex = nullptr;
             bool ok = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal) == hipSuccess;
             if (ok) {
-                for (int j = 0; j < len; ++j) launch_step(cap, a, gsl, gsys, dir);
+                launch_steps(cap, a, len, gblk, gsys, dir);
                 ok = hipStreamEndCapture(cap, &g) == hipSuccess && g != nullptr;
             }
             ok = ok && hipGraphInstantiate(&ex, g, nullptr, nullptr, 0) == hipSuccess;
@@ -777,7 +778,7 @@ bool Engine::launch_group(int len)
         if (graphs_ok) return hipGraphLaunch(it->second, s) == hipSuccess;
     }
     const bool dir = dir_needed();
-    for (int j = 0; j < len; ++j) launch_step(s, a, gsl, gsys, dir);
+    launch_steps(s, a, len, gblk, gsys, dir);
     return hipGetLastError() == hipSuccess;
 }
 

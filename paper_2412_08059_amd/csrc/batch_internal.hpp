@@ -10,11 +10,13 @@
 //   k_b_product   per slice: the CG product, the restart residual or the
 //                 final-check residual of the slice's system, as its mode says;
 //                 one partial per slice
-//   k_b_scalar1   one block per system: its partials -> delta / alpha, or the
-//                 restart and final-check decisions
-//   k_b_update    per slice: r -= alpha q, x += alpha d, partial of r.r
-//   k_b_scalar2   one block per system: gamma, stop tests, beta, v ratios
-//   k_b_wg        instead of the four while every listed system has at most
+//   k_b_update    the products' partials -> delta / alpha, or the restart and
+//                 final-check decisions; per slice: r -= alpha q, x += alpha d,
+//                 partial of r.r
+//   the updates' partials -> gamma, stop tests, beta, v ratios: at the head of
+//                 the next step's k_b_product, after a group's last step in
+//                 k_b_close
+//   k_b_wg        instead of these while every listed system has at most
 //                 4,096 rows: a workgroup per system, many steps a launch
 //   k_b_bfs_*     2BFS levels of the systems whose features are pending, on a
 //                 stream of their own beside the steps
@@ -107,7 +109,7 @@ struct BArena {
     // per slice
     int32_t *slice_w, *sys_of_slice;
     int64_t *slice_off;                    // local to the system's entry range
-    double *pslice;                        // 2 per slice
+    double *pslice;                        // 2 per slice: of the product, of the update (admission: r~.r~ and b.b)
     // per row
     int32_t *rowlen;
     double *b64, *x64, *r64, *q64, *dA64, *dB64;
@@ -130,9 +132,11 @@ struct BArena {
     int32_t *counts;                       // [0] = #act, [1] = #small, [2] = admission error (unused)
     int64_t *items;                        // total items of the large level
     // the step's work list, rebuilt when a system joins or leaves it
-    int2 *step_map;                        // [k] = (slice, slot) of the k-th listed slice (systems in list order)
-    int4 *step_sys;                        // [k] = (slot, first slice, slices, 0) of the k-th listed system
-    int32_t *step_cnt;                     // [0] = listed slices, [1] = listed systems
+    BSys *after;                           // the systems' states between a step's product and its update
+    int2 *step_map;                        // [k] = (first slice, 4 slot + slices - 1) of the k-th listed block
+    int2 *step_of;                         // [k] = (first slice, slices) of that block's system
+    int32_t *step_sys;                     // [k] = slot of the k-th listed system
+    int32_t *step_cnt;                     // [0] = listed blocks, [1] = listed systems
     int32_t acc32;                         // dot_acc = 1: FP32-phase dot products accumulate in FP32
     int32_t nt;                            // the step product reads the matrices with nontemporal loads
     int32_t hold_above;                    // Algorithm II: a system waits for eps1 at its first crossing when
@@ -141,10 +145,10 @@ struct BArena {
 
 // One launch's share of a work-list rebuild: entries first .. first + n - 1
 // of the list (slot, its first slice and slice count, and the list position
-// of its first slice); the last share also writes the totals.
+// of its first block); the last share also writes the totals.
 constexpr int kListChunk = 200;   // keeps the launch argument under 4 KB
 struct ListChunk {
-    int32_t first, n, last, total_slices, total_sys, pad_;
+    int32_t first, n, last, total_blocks, total_sys, pad_;
     int32_t slot[kListChunk], slice0[kListChunk], nslices[kListChunk], pre[kListChunk];
 };
 
@@ -185,12 +189,13 @@ void launch_set_eps(hipStream_t s, const BArena &a, int32_t sys, double eps1, in
 void launch_fill_slices(hipStream_t s, const BArena &a);   // every slice unowned
 
 // ---- one step over the systems of the work list ----
-// A rebuild of the work list (chunks in order); then steps launch grid_slices
-// blocks of four slices and grid_sys blocks of one system, at least the
-// listed counts (blocks past them return at once).
+// A rebuild of the work list (chunks in order); then a group of steps launches
+// grid_blocks blocks (of up to four slices of one system) and at its end
+// grid_sys blocks of one system, at least the listed counts (blocks past them
+// return at once).
 void launch_worklist(hipStream_t s, const BArena &a, const ListChunk &c);
 // dir: some listed system gathers a stored direction (k_b_dir first)
-void launch_step(hipStream_t s, const BArena &a, int32_t grid_slices, int32_t grid_sys, bool dir);
+void launch_steps(hipStream_t s, const BArena &a, int32_t steps, int32_t grid_blocks, int32_t grid_sys, bool dir);
 
 // The steps of a list whose systems have at most kWgMaxSlices slices each, one
 // workgroup per system and `steps` steps a launch (max_slices: the largest).

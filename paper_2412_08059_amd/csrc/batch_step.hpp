@@ -22,6 +22,36 @@ __device__ inline double wave_dot32(bool f32, float x, float y)
     return f32 ? (double)wave_dot(x, y) : wave_dot((double)x, (double)y);
 }
 
+// What a wave of a step needs of its system, in scalar registers.
+struct StepSys {
+    int32_t mode, ph_it, src, snap_ci, snap_mask;
+    double alpha, beta;
+    int32_t split, ds, row0, slice0, nslices;
+    int64_t entry0;
+    unsigned long long doffs;
+};
+// live: the fields of the recurrence; at: those set at admission.
+__device__ inline StepSys step_sys_of(const BSys &live, const BSys &at)
+{
+    auto sc = [](int32_t v) { return (int32_t)__builtin_amdgcn_readfirstlane(v); };
+    StepSys s;
+    s.mode = sc(live.mode);
+    s.ph_it = sc(live.ph_it);
+    s.src = sc(live.src);
+    s.snap_ci = sc(live.snap_ci);
+    s.snap_mask = sc(live.snap_mask);
+    s.alpha = live.alpha;
+    s.beta = live.beta;
+    s.split = at.split;
+    s.ds = at.ds;
+    s.row0 = at.row0;
+    s.slice0 = at.slice0;
+    s.nslices = at.nslices;
+    s.entry0 = at.entry0;
+    s.doffs = at.doffs;
+    return s;
+}
+
 // One thread, v: the sum of the product's partials (d.q, or the squared
 // residual of a restart or final check).
 __device__ inline void step_product_done(BSys &S, int mode, double v)

@@ -110,7 +110,8 @@ size_t arena_bytes(int32_t max_sys, int32_t max_slices, int64_t max_entries)
     t += up256(8 * rows);                                             // band 2BFS masks
     t += up256(4 * e) + up256(8 * e) + up256(4 * e);                  // col, v64, v32
     t += up256(4 * (size_t)max_sys) * 2 + up256(8 * (size_t)max_sys) + 256 + 256;
-    t += up256(8 * sl) + up256(16 * (size_t)max_sys) + 256;           // step work list
+    t += up256(8 * sl) * 2 + up256(4 * (size_t)max_sys) + 256;        // step work list
+    t += up256(sizeof(BSys) * (size_t)max_sys);                       // states between product and update
     return t;
 }
 
@@ -158,8 +159,10 @@ BArena carve(void *base, int32_t max_sys, int32_t max_slices, int64_t max_entrie
     a.counts = reinterpret_cast<int32_t *>(take(256));
     a.items = reinterpret_cast<int64_t *>(take(256));
     a.step_map = reinterpret_cast<int2 *>(take(8 * sl));
-    a.step_sys = reinterpret_cast<int4 *>(take(16 * (size_t)max_sys));
+    a.step_of = reinterpret_cast<int2 *>(take(8 * sl));
+    a.step_sys = reinterpret_cast<int32_t *>(take(4 * (size_t)max_sys));
     a.step_cnt = reinterpret_cast<int32_t *>(take(256));
+    a.after = reinterpret_cast<BSys *>(take(sizeof(BSys) * (size_t)max_sys));
     return a;
 }
 
@@ -577,7 +580,7 @@ template <bool NT, typename P> __device__ inline P b_ld(const P *p)
 // Wave per slice.  CG product of iteration j of the phase:
 // d_j = r_j + beta_j d_{j-1} (d_0 = r_0), q = A d_j, partial of d_j.q (FP64).
 template <typename T, bool NT>
-__device__ inline double cg_product(const BArena &a, const BSys &S, const T *val, const T *r, T *dA, T *dB,
+__device__ inline double cg_product(const BArena &a, const StepSys &S, const T *val, const T *r, T *dA, T *dB,
                                     T *q, int64_t base, int row, int len)
 {
     const int j = S.ph_it;
@@ -652,7 +655,7 @@ __device__ inline double cg_product(const BArena &a, const BSys &S, const T *val
 // Restart: r = b - A x with x = float64(x~), x, or 0; x takes that value.
 // Final check: partial of ||b - A x||^2.
 template <bool NT>
-__device__ inline double residual(const BArena &a, const BSys &S, bool restart, int64_t base, int row, int len)
+__device__ inline double residual(const BArena &a, const StepSys &S, bool restart, int64_t base, int row, int len)
 {
     const int src = restart ? S.src : kSrcX64;
     const float *xs = a.snap32 + (size_t)S.snap_ci * ((size_t)a.max_slices * 64);   // src == kSrcSnap
@@ -688,30 +691,108 @@ __device__ inline double residual(const BArena &a, const BSys &S, bool restart, 
     return wave_dot(res, res);
 }
 
-// Entry of the list at position `at`, and whether it is listed: both loaded at
-// once (a position past the list reads an entry of the array that is not used;
-// a dependent load costs 0.8 us, the caches being cold at a launch's start).
-template <typename E>
-__device__ inline bool listed(const E *list, int32_t cap, const int32_t *cnt, int32_t at, E &e, int32_t &n)
+// ---- heads of the step's kernels ----
+//
+// A block serves up to four slices of one system.  Each block adds the partials
+// of the launch before and takes the system's decision itself, on a copy of its
+// state in LDS: every block of the system comes to the same bits, and the
+// system's first block hands the state on.  The list entries, the listed count
+// and then state and partials are loaded together (a dependent load costs 0.8
+// us, the caches being cold at a launch's start).  A launch of one block per
+// system for each decision took 4.7 us.
+struct StepBlock {
+    int32_t slice, cnt;      // first slice, slices
+    int32_t slot, slice0, nslices;
+};
+
+__device__ inline bool step_block(const BArena &a, StepBlock &b)
 {
-    e = list[min(at, cap - 1)];
-    n = *cnt;
-    asm volatile("" : "+s"(e.x), "+s"(n));
-    return at < n;
+    const int32_t k = min((int)blockIdx.x, a.max_slices - 1);   // past the list: an entry that is not used
+    const int2 m = a.step_map[k], o = a.step_of[k];
+    const int32_t n = a.step_cnt[0];
+    asm volatile("" ::"s"(m.x), "s"(o.x), "s"(n));
+    b.slice = m.x;
+    b.slot = m.y >> 2;
+    b.cnt = (m.y & 3) + 1;
+    b.slice0 = o.x;
+    b.nslices = o.y;
+    return (int)blockIdx.x < n;
+}
+
+constexpr int kSysWords = (int)(sizeof(BSys) / 4);
+static_assert(kSysWords <= kBlock, "one word a thread");
+// the fields of the recurrence: those of the 2BFS belong to another stream
+constexpr int kStepFrom = (int)(offsetof(BSys, mode) / 4), kStepTo = (int)(offsetof(BSys, bfs_mode) / 4);
+
+__device__ inline bool step_active(int mode)
+{
+    return mode == kCg32 || mode == kCg64 || mode == kRestart || mode == kResid;
+}
+
+// Loads the state `from` into S and, if sum, the system's sum of component j of
+// the partials, valid in thread 0.  Every thread may read S afterwards.
+__device__ inline double step_load(const BArena &a, const StepBlock &b, const BSys *from, BSys &S, bool sum, int j,
+                                   double *sm)
+{
+    const int tid = threadIdx.x;
+    uint32_t *l = reinterpret_cast<uint32_t *>(&S);
+    const uint32_t word = tid < kSysWords ? reinterpret_cast<const uint32_t *>(from + b.slot)[tid] : 0u;
+    double part = 0.0;
+    float part32 = 0.0f;
+    if (sum) part = slice_sum<double>(a, b.slice0, b.nslices, j);
+    if (sum && a.acc32) part32 = slice_sum<float>(a, b.slice0, b.nslices, j);
+    if (tid < kSysWords) l[tid] = word;
+    if (!sum) {
+        __syncthreads();
+        return 0.0;
+    }
+    part = wave_sum_all(part);
+    if (a.acc32) part32 = wave_sum_all(part32);
+    if ((tid & 63) == 0) {
+        sm[tid >> 6] = part;
+        sm[kBlock / 64 + (tid >> 6)] = (double)part32;
+    }
+    __syncthreads();
+    double v = 0.0;
+    if (tid == 0) {
+        if (a.acc32 && S.mode == kCg32) {
+            float s = 0.0f;
+            for (int i = 0; i < kBlock / 64; ++i) s += (float)sm[kBlock / 64 + i];
+            v = (double)s;
+        } else {
+            for (int i = 0; i < kBlock / 64; ++i) v += sm[i];
+        }
+    }
+    return v;
+}
+
+// State at the head of a product: as the update before left it, its sum taken
+// (head), or complete.
+__device__ inline void step_begin(const BArena &a, const StepBlock &b, bool head, BSys &S, double *sm)
+{
+    const int32_t nsys = a.step_cnt[1];
+    const double g = step_load(a, b, a.sys, S, head, 1, sm);
+    if (!head) return;
+    if (threadIdx.x == 0 && S.upd) step_update_done(S, nsys > a.hold_above, g);
+    __syncthreads();
 }
 
 template <bool NT>
-__global__ void __launch_bounds__(kBlock, 8) __attribute__((amdgpu_num_sgpr(kSgprCap))) k_b_product(BArena a)
+__global__ void __launch_bounds__(kBlock, 8) __attribute__((amdgpu_num_sgpr(kSgprCap)))
+k_b_product(BArena a, int32_t head)
 {
     __shared__ double lu[kSlicesPerBlock][kBdsLds];
-    // scalar: the wave's slice, its system and the system's state
+    __shared__ BSys state;
+    __shared__ double sm[2 * kBlock / 64];
+    StepBlock b;
+    if (!step_block(a, b)) return;
+    step_begin(a, b, head != 0, state, sm);
+    if (b.slice == b.slice0 && threadIdx.x < kSysWords)
+        reinterpret_cast<uint32_t *>(a.after + b.slot)[threadIdx.x] = reinterpret_cast<uint32_t *>(&state)[threadIdx.x];
     const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    int2 e;   // slice and its system: no dependent lookup of the owner
-    int32_t total;
-    if (!listed(a.step_map, a.max_slices, a.step_cnt, (int)blockIdx.x * kSlicesPerBlock + wv, e, total)) return;
-    const int sl = e.x, s = e.y;
-    if (s < 0) return;
-    const BSys &S = a.sys[s];
+    if (wv >= b.cnt) return;
+    const StepSys S = step_sys_of(state, a.sys[b.slot]);
+    const int sl = b.slice + wv;
     const int lane = threadIdx.x & 63;
     const int row = sl * 64 + lane;
     const int due = S.snap_mask;
@@ -720,26 +801,25 @@ __global__ void __launch_bounds__(kBlock, 8) __attribute__((amdgpu_num_sgpr(kSgp
             if ((due >> t) & 1) a.snap32[(size_t)t * ((size_t)a.max_slices * 64) + row] = a.x32[row];
     }
     const int mode = S.mode;
-    if (mode != kCg32 && mode != kCg64 && mode != kRestart && mode != kResid) return;
+    if (!step_active(mode)) return;
     double p;
     if (S.ds) {
         if (mode == kCg32)
             p = bds_product<float>(a, S, a.v32, a.r32, a.dA32, a.dB32, a.q32, sl, reinterpret_cast<float *>(lu[wv]));
         else if (mode == kCg64) p = bds_product<double>(a, S, a.v64, a.r64, a.dA64, a.dB64, a.q64, sl, lu[wv]);
         else p = bds_residual(a, S, mode == kRestart, sl, lu[wv]);
-        if (lane == 0) a.pslice[2 * (size_t)sl] = p;
-        return;
+    } else {
+        const int len = a.rowlen[row];
+        const int64_t base = S.entry0 + a.slice_off[sl] + lane;
+        if (mode == kCg32) p = cg_product<float, NT>(a, S, a.v32, a.r32, a.dA32, a.dB32, a.q32, base, row, len);
+        else if (mode == kCg64) p = cg_product<double, NT>(a, S, a.v64, a.r64, a.dA64, a.dB64, a.q64, base, row, len);
+        else p = residual<NT>(a, S, mode == kRestart, base, row, len);
     }
-    const int len = a.rowlen[row];
-    const int64_t base = S.entry0 + a.slice_off[sl] + lane;
-    if (mode == kCg32) p = cg_product<float, NT>(a, S, a.v32, a.r32, a.dA32, a.dB32, a.q32, base, row, len);
-    else if (mode == kCg64) p = cg_product<double, NT>(a, S, a.v64, a.r64, a.dA64, a.dB64, a.q64, base, row, len);
-    else p = residual<NT>(a, S, mode == kRestart, base, row, len);
     if (lane == 0) a.pslice[2 * (size_t)sl] = p;
 }
 
 template <typename T>
-__device__ inline double cg_update(const BArena &a, const BSys &S, T *x, T *r, const T *q, const T *dA, const T *dB,
+__device__ inline double cg_update(const BArena &a, const StepSys &S, T *x, T *r, const T *q, const T *dA, const T *dB,
                                    int row)
 {
     const T alpha = (T)S.alpha;
@@ -753,74 +833,45 @@ __device__ inline double cg_update(const BArena &a, const BSys &S, T *x, T *r, c
 
 __global__ void __launch_bounds__(kBlock) k_b_update(BArena a)
 {
-    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    int2 e;
-    int32_t total;
-    if (!listed(a.step_map, a.max_slices, a.step_cnt, (int)blockIdx.x * kSlicesPerBlock + wv, e, total)) return;
-    const int sl = e.x, s = e.y;
-    if (s < 0) return;
-    const BSys &S = a.sys[s];
-    if (!S.upd) return;
-    const int lane = threadIdx.x & 63;
+    __shared__ BSys state;
+    __shared__ double sm[2 * kBlock / 64];
+    StepBlock b;
+    if (!step_block(a, b)) return;
+    const double v = step_load(a, b, a.after, state, true, 0, sm);
+    if (threadIdx.x == 0) {
+        state.snap_mask = 0;   // the product of this step took the copies
+        const int mode = state.mode;
+        if (step_active(mode)) step_product_done(state, mode, v);
+    }
+    __syncthreads();
+    const int t = threadIdx.x;
+    if (b.slice == b.slice0 && t >= kStepFrom && t < kStepTo)
+        reinterpret_cast<uint32_t *>(a.sys + b.slot)[t] = reinterpret_cast<uint32_t *>(&state)[t];
+    const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    if (!state.upd || wv >= b.cnt) return;
+    const StepSys S = step_sys_of(state, a.sys[b.slot]);
+    const int sl = b.slice + wv, lane = t & 63;
     const int row = sl * 64 + lane;
     const double p = S.mode == kCg32 ? cg_update<float>(a, S, a.x32, a.r32, a.q32, a.dA32, a.dB32, row)
                                      : cg_update<double>(a, S, a.x64, a.r64, a.q64, a.dA64, a.dB64, row);
-    if (lane == 0) a.pslice[2 * (size_t)sl] = p;
+    if (lane == 0) a.pslice[2 * (size_t)sl + 1] = p;
 }
 
-// Block per system, after the product (UPDATE false: delta and alpha, or the
-// restart and final-check decisions) or after the update (true: gamma of the
-// new residual, v ratios, stop tests, beta).  The state and the partials are
-// loaded together, from the list entry, and one thread decides on the state's
-// copy in LDS: what is left is two memory latencies, one reduction and the
-// store (4.8 us a launch when the list, the state, the partials and the
-// state's other fields followed one another).
-template <bool UPDATE> __global__ void __launch_bounds__(kBlock) k_b_scalar(BArena a)
+// Block per system, after a group's last step: the update's sum and decision,
+// so that the state is complete for the host's copy.
+__global__ void __launch_bounds__(kBlock) k_b_close(BArena a)
 {
     __shared__ BSys S;
-    __shared__ double sm[kBlock / 64];
-    constexpr int kWords = (int)(sizeof(BSys) / 4);
-    static_assert(kWords <= kBlock, "one word a thread");
-    const int tid = threadIdx.x;
-    int4 e;
-    int32_t nsys;
-    if (!listed(a.step_sys, a.max_sys, a.step_cnt + 1, (int)blockIdx.x, e, nsys)) return;
-    uint32_t *g = reinterpret_cast<uint32_t *>(a.sys + e.x);
-    uint32_t *l = reinterpret_cast<uint32_t *>(&S);
-    const uint32_t word = tid < kWords ? g[tid] : 0u;
-    const double part = slice_sum<double>(a, e.y, e.z, 0);
-    float part32 = 0.0f;
-    if (a.acc32) part32 = slice_sum<float>(a, e.y, e.z, 0);
-    if (tid < kWords) l[tid] = word;
-    const double ws = wave_sum_all(part);
-    float ws32 = 0.0f;
-    if (a.acc32) ws32 = wave_sum_all(part32);
-    __syncthreads();
-    const int mode = S.mode;
-    const bool f32 = a.acc32 && mode == kCg32;
-    if (UPDATE ? !S.upd : mode != kCg32 && mode != kCg64 && mode != kRestart && mode != kResid && !S.snap_mask) return;
-    if ((tid & 63) == 0) sm[tid >> 6] = f32 ? (double)ws32 : ws;
-    __syncthreads();
-    if (tid == 0) {
-        double v = 0.0;
-        if (f32) {
-            float s = 0.0f;
-            for (int i = 0; i < kBlock / 64; ++i) s += (float)sm[i];
-            v = (double)s;
-        } else {
-            for (int i = 0; i < kBlock / 64; ++i) v += sm[i];
-        }
-        if (UPDATE) {
-            step_update_done(S, nsys > a.hold_above, v);
-        } else {
-            S.snap_mask = 0;   // the product of this step took the copies
-            if (mode == kCg32 || mode == kCg64 || mode == kRestart || mode == kResid) step_product_done(S, mode, v);
-        }
-    }
-    __syncthreads();
-    // the fields of the recurrence only: those of the 2BFS belong to another stream
-    constexpr int kFrom = (int)(offsetof(BSys, mode) / 4), kTo = (int)(offsetof(BSys, bfs_mode) / 4);
-    if (tid >= kFrom && tid < kTo) g[tid] = l[tid];
+    __shared__ double sm[2 * kBlock / 64];
+    if ((int)blockIdx.x >= a.step_cnt[1]) return;
+    StepBlock b;
+    b.slot = a.step_sys[blockIdx.x];
+    b.slice0 = a.sys[b.slot].slice0;
+    b.nslices = a.sys[b.slot].nslices;
+    step_begin(a, b, true, S, sm);
+    const int t = threadIdx.x;
+    if (t >= kStepFrom && t < kStepTo)
+        reinterpret_cast<uint32_t *>(a.sys + b.slot)[t] = reinterpret_cast<uint32_t *>(&S)[t];
 }
 
 // ----------------------------------------------------------------- 2BFS --
@@ -1132,19 +1183,23 @@ __global__ void __launch_bounds__(kBlock) k_bfs_small_batch(BArena a, int32_t ma
     }
 }
 
-// Block j writes the list entries of the chunk's system j: its slot, and the
-// slices of its range at their list positions.
+// Block j writes the list entries of the chunk's system j: its slot, and its
+// blocks of slices at their list positions.
 __global__ void __launch_bounds__(kBlock) k_worklist(BArena a, ListChunk c)
 {
     const int j = blockIdx.x;
     if (c.last && j == 0 && threadIdx.x == 0) {
-        a.step_cnt[0] = c.total_slices;
+        a.step_cnt[0] = c.total_blocks;
         a.step_cnt[1] = c.total_sys;
     }
     if (j >= c.n) return;
-    const int32_t s0 = c.slice0[j], pre = c.pre[j];
-    for (int i = threadIdx.x; i < c.nslices[j]; i += kBlock) a.step_map[pre + i] = make_int2(s0 + i, c.slot[j]);
-    if (threadIdx.x == 0) a.step_sys[c.first + j] = make_int4(c.slot[j], s0, c.nslices[j], 0);
+    const int32_t s0 = c.slice0[j], ns = c.nslices[j], pre = c.pre[j];
+    for (int i = threadIdx.x; i * kSlicesPerBlock < ns; i += kBlock) {
+        const int first = i * kSlicesPerBlock;
+        a.step_map[pre + i] = make_int2(s0 + first, 4 * c.slot[j] + min(kSlicesPerBlock, ns - first) - 1);
+        a.step_of[pre + i] = make_int2(s0, ns);
+    }
+    if (threadIdx.x == 0) a.step_sys[c.first + j] = c.slot[j];
 }
 
 void launch_worklist(hipStream_t s, const BArena &a, const ListChunk &c)
@@ -1156,7 +1211,7 @@ void launch_worklist(hipStream_t s, const BArena &a, const ListChunk &c)
 // (d_0 = r_0), the value the fused product forms per gathered entry, stored
 // once for the product to gather (the same fma, so the same bits).
 template <typename T>
-__device__ inline void dir_rows(const BSys &S, const T *r, T *dA, T *dB, int row)
+__device__ inline void dir_rows(const StepSys &S, const T *r, T *dA, T *dB, int row)
 {
     const int j = S.ph_it;
     T *dnew = (j & 1) ? dB : dA;
@@ -1164,30 +1219,34 @@ __device__ inline void dir_rows(const BSys &S, const T *r, T *dA, T *dB, int row
     dnew[row] = j == 0 ? r[row] : fma_b<T>((T)S.beta, dold[row], r[row]);
 }
 
-__global__ void __launch_bounds__(kBlock) k_b_dir(BArena a)
+__global__ void __launch_bounds__(kBlock) k_b_dir(BArena a, int32_t head)
 {
-    const int k = blockIdx.x * kSlicesPerBlock + (threadIdx.x >> 6);
-    if (k >= a.step_cnt[0]) return;
-    const int2 e = a.step_map[k];
-    const int sl = e.x, s = e.y;
-    if (s < 0) return;
-    const BSys &S = a.sys[s];
-    if (!S.split) return;
+    __shared__ BSys state;
+    __shared__ double sm[2 * kBlock / 64];
+    StepBlock b;
+    if (!step_block(a, b)) return;
+    if (!a.sys[b.slot].split) return;
+    step_begin(a, b, head != 0, state, sm);
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (wv >= b.cnt) return;
+    const StepSys S = step_sys_of(state, a.sys[b.slot]);
     const int mode = S.mode;
-    const int row = sl * 64 + (threadIdx.x & 63);
+    const int row = (b.slice + wv) * 64 + (int)(threadIdx.x & 63);
     if (mode == kCg32) dir_rows<float>(S, a.r32, a.dA32, a.dB32, row);
     else if (mode == kCg64) dir_rows<double>(S, a.r64, a.dA64, a.dB64, row);
 }
 
-void launch_step(hipStream_t s, const BArena &a, int32_t grid_slices, int32_t grid_sys, bool dir)
+void launch_steps(hipStream_t s, const BArena &a, int32_t steps, int32_t grid_blocks, int32_t grid_sys, bool dir)
 {
-    if (grid_slices <= 0 || grid_sys <= 0) return;
-    if (dir) hipLaunchKernelGGL(k_b_dir, dim3(grid_slices), dim3(kBlock), 0, s, a);
-    if (a.nt) hipLaunchKernelGGL(k_b_product<true>, dim3(grid_slices), dim3(kBlock), 0, s, a);
-    else hipLaunchKernelGGL(k_b_product<false>, dim3(grid_slices), dim3(kBlock), 0, s, a);
-    hipLaunchKernelGGL(k_b_scalar<false>, dim3(grid_sys), dim3(kBlock), 0, s, a);
-    hipLaunchKernelGGL(k_b_update, dim3(grid_slices), dim3(kBlock), 0, s, a);
-    hipLaunchKernelGGL(k_b_scalar<true>, dim3(grid_sys), dim3(kBlock), 0, s, a);
+    if (steps <= 0 || grid_blocks <= 0 || grid_sys <= 0) return;
+    for (int32_t j = 0; j < steps; ++j) {
+        const int32_t head = j > 0;
+        if (dir) hipLaunchKernelGGL(k_b_dir, dim3(grid_blocks), dim3(kBlock), 0, s, a, head);
+        if (a.nt) hipLaunchKernelGGL(k_b_product<true>, dim3(grid_blocks), dim3(kBlock), 0, s, a, head);
+        else hipLaunchKernelGGL(k_b_product<false>, dim3(grid_blocks), dim3(kBlock), 0, s, a, head);
+        hipLaunchKernelGGL(k_b_update, dim3(grid_blocks), dim3(kBlock), 0, s, a);
+    }
+    hipLaunchKernelGGL(k_b_close, dim3(grid_sys), dim3(kBlock), 0, s, a);
 }
 
 void launch_bfs_round(hipStream_t s, const BArena &a, int32_t hi_sys, int small_levels, int small_cap,

@@ -228,7 +228,7 @@ __global__ void __launch_bounds__(kWgThreads, WAVES) k_b_wg(BArena a, int32_t st
     if ((int)blockIdx.x >= a.step_cnt[1]) return;
     constexpr int kWords = (int)(sizeof(BSys) / 4);
     static_assert(kWords <= kWgThreads, "one word a thread");
-    uint32_t *g = reinterpret_cast<uint32_t *>(a.sys + a.step_sys[blockIdx.x].x);
+    uint32_t *g = reinterpret_cast<uint32_t *>(a.sys + a.step_sys[blockIdx.x]);
     uint32_t *l = reinterpret_cast<uint32_t *>(&S);
     const int tid = threadIdx.x, W = tid >> 6;
     if (tid < kWords) l[tid] = g[tid];
