@@ -180,16 +180,19 @@ void launch_ingest_sell(hipStream_t s, const int32_t *rp32, const int32_t *col, 
 // product that needs one.  Here one pass checks the rows and forms the product
 // in scratch; a second kernel hands it over if every check passed.  What bounds
 // it: the 12 bytes an entry (4M-row band, 68 M entries, FP64: the call 1,113 ->
-// 257 us, of which the pass is 3.6 TB/s; 128^3 stencil 275 -> 86 us; 1,000 rows
-// 66 -> 34 us, the launches and one read-back).
+// 231 us, of which the pass is 4.2 TB/s; 128^3 stencil 275 -> 73 us; 1,000 rows
+// 66 -> 34 us, the launches and one read-back).  With chunks of two batches,
+// twelve waves a CU, 262 and 88 us; of 4, 6 or 8 loads instead of 5, 231, 227
+// and 245, 70, 77 and 76.
 //
 // Wave per 64 rows: the row pointers are checked before anything is read
 // through them; the entries come in chunks of kChkEntries with coalesced
 // loads, each checked and its vector element gathered as it arrives, and each
 // lane runs its row's fma chain over the chunk from LDS in CSR order, starting
 // from 0 (the bits of the other products), checking the order on the way.
+// A chunk is one batch of loads: its LDS lets 24 waves share a CU.
 constexpr int kChkBatch = 5;                    // loads of a lane issued together
-constexpr int kChkEntries = 2 * 64 * kChkBatch;
+constexpr int kChkEntries = 64 * kChkBatch;
 
 template <typename T>
 __global__ void __launch_bounds__(kBlock)
@@ -228,34 +231,32 @@ k_spmv_checked(const void *rp_in, int rp_is_i64, const int32_t *__restrict__ col
         int prev = -1;
         for (int c0 = b0; c0 < b1; c0 += kChkEntries) {
             const int cn = min(kChkEntries, b1 - c0);
-            for (int j0 = 0; j0 < cn; j0 += 64 * kChkBatch) {
-                int c[kChkBatch];
-                double v[kChkBatch];
-                T g[kChkBatch];
+            int c[kChkBatch];
+            double v[kChkBatch];
+            T g[kChkBatch];
 #pragma unroll
-                for (int j = 0; j < kChkBatch; ++j) {
-                    const int k = j0 + j * 64 + lane;
-                    c[j] = 0;
-                    v[j] = 0.0;
-                    if (k < cn) {
-                        c[j] = col[c0 + k];
-                        v[j] = val[c0 + k];
-                    }
+            for (int j = 0; j < kChkBatch; ++j) {
+                const int k = j * 64 + lane;
+                c[j] = 0;
+                v[j] = 0.0;
+                if (k < cn) {
+                    c[j] = col[c0 + k];
+                    v[j] = val[c0 + k];
                 }
+            }
 #pragma unroll
-                for (int j = 0; j < kChkBatch; ++j) {
-                    const bool in = c[j] >= 0 && c[j] < n;
-                    if (!in) err |= kErrCol;
-                    if (!isfinite(v[j])) err |= kErrNonFiniteA;
-                    g[j] = x[in ? c[j] : 0];
-                }
+            for (int j = 0; j < kChkBatch; ++j) {
+                const bool in = c[j] >= 0 && c[j] < n;
+                if (!in) err |= kErrCol;
+                if (!isfinite(v[j])) err |= kErrNonFiniteA;
+                g[j] = x[in ? c[j] : 0];
+            }
 #pragma unroll
-                for (int j = 0; j < kChkBatch; ++j) {
-                    const int k = j0 + j * 64 + lane;
-                    sc[k] = c[j];
-                    sv[k] = (T)v[j];
-                    sg[k] = g[j];
-                }
+            for (int j = 0; j < kChkBatch; ++j) {
+                const int k = j * 64 + lane;
+                sc[k] = c[j];
+                sv[k] = (T)v[j];
+                sg[k] = g[j];
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
