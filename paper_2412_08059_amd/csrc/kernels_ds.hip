@@ -176,12 +176,129 @@ void launch_ingest_fold(hipStream_t s, const int32_t *blk, const int32_t *rp, co
 
 constexpr int kDsNear = 32;   // largest distance of the kernels that keep a slice's vector elements in LDS
 
+// The entries of rows r .. r + nrows - 1 (cnt of them, from lo) into a wave's LDS.
+__device__ inline void ds_stage(const int32_t *__restrict__ col, const double *__restrict__ val, int lo, int cnt,
+                                int32_t *sc, double *sv)
+{
+    const int lane = threadIdx.x & 63;
+    for (int k0 = 0; k0 < cnt; k0 += 256) {
+        int c[4];
+        double v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int k = k0 + j * 64 + lane;
+            if (k < cnt) {
+                c[j] = col[lo + k];
+                v[j] = val[lo + k];
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int k = k0 + j * 64 + lane;
+            if (k < cnt) {
+                sc[k] = c[j];
+                sv[k] = v[j];
+            }
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// One slice of a near matrix: the planes and the check of its lower entries in
+// one pass.  A lower entry's partner row is in the slice or one of the `reach`
+// rows before it, whose upper entries the first lanes pick up beforehand (the
+// slice before reads the same lines); the slice's and these rows' upper entries
+// then meet in LDS.
+__device__ inline void ds_near_slice(const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
+                                     const double *__restrict__ val, int32_t n, int r0, const int32_t (&d)[kDsMax],
+                                     int nh, int64_t S, double *p64, float *p32, double *dg64, float *dg32, int32_t *sc,
+                                     double *sv, int &miss, int &err)
+{
+    const int lane = threadIdx.x & 63;
+    const int reach = d[nh - 1], nrows = min(64, n - r0), row = r0 + lane;
+    // slice 0 has no rows before it
+    const int nbefore = r0 ? reach : 0, h0 = r0 - nbefore;
+    const int hs = rp[h0 + min(lane, nbefore)], he = rp[h0 + min(lane + 1, nbefore)];
+    const int ps = rp[r0 + min(lane, nrows)], pe = rp[r0 + min(lane + 1, nrows)];
+    const int hlo = rp[h0], lo = rp[r0], hi = rp[r0 + nrows];
+    if (lo - hlo > 64 * kDsRowMax || hi - lo > 64 * kDsRowMax) {   // a row too long to match
+        miss = 1;
+        return;
+    }
+    double before[kDsMax], low[kDsMax], up[kDsMax];
+    ds_stage(col, val, hlo, lo - hlo, sc, sv);
+    {
+        const int hr = h0 + lane;
+        int k = hs - hlo;
+        const int ke = he - hlo;
+        while (k < ke && sc[k] <= hr) ++k;
+#pragma unroll
+        for (int t = 0; t < kDsMax; ++t) {
+            before[t] = NAN;
+            if (t < nh && k < ke && sc[k] == hr + d[t]) before[t] = sv[k++];
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+    ds_stage(col, val, lo, hi - lo, sc, sv);
+    int k = ps - lo;
+    const int ke = pe - lo;
+    auto take = [&](int c) {   // the next entry if it is column c
+        if (k >= ke || sc[k] != c) return (double)NAN;
+        const double v = sv[k++];
+        if (!isfinite(v)) err |= kErrNonFiniteA;
+        return v;
+    };
+#pragma unroll
+    for (int t = kDsMax - 1; t >= 0; --t) low[t] = t < nh ? take(row - d[t]) : NAN;
+    const double mid = take(row);
+#pragma unroll
+    for (int t = 0; t < kDsMax; ++t) up[t] = t < nh ? take(row + d[t]) : NAN;
+    if (k != ke) miss = 1;
+    if (row < n) {
+        p64[row] = mid;
+        if (p32) p32[row] = (float)mid;
+        if (dg64) {
+            const double dv = mid == mid ? mid : 0.0;
+            dg64[row] = dv;
+            dg32[row] = (float)dv;
+            if (!(dv > 0.0) || !isfinite(dv) || !((float)dv > 0.0f) || !isfinite((float)dv)) err |= kErrDiag;
+        }
+#pragma unroll
+        for (int t = 0; t < kDsMax; ++t)
+            if (t < nh) {
+                p64[(t + 1) * S + row] = up[t];
+                if (p32) p32[(t + 1) * S + row] = (float)up[t];
+            }
+    }
+    __builtin_amdgcn_wave_barrier();
+    constexpr int kMeet = 64 + kDsNear;
+    static_assert(kDsMax * kMeet <= 64 * kDsRowMax, "the upper entries take the staged entries' place");
+#pragma unroll
+    for (int t = 0; t < kDsMax; ++t) {
+        if (lane < reach) sv[t * kMeet + lane] = r0 ? before[t] : NAN;
+        sv[t * kMeet + reach + lane] = up[t];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int t = 0; t < kDsMax; ++t) {
+        if (t >= nh) continue;
+        const double u = sv[t * kMeet + reach + lane - d[t]];
+        const bool here = low[t] == low[t], there = u == u;
+        if (here != there || (here && __double_as_longlong(u) != __double_as_longlong(low[t]))) miss = 1;
+    }
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Wave per 64 rows: the rows' entries are staged in LDS with coalesced loads,
 // then each lane walks its row along the diagonals.  VERIFY 0: the planes (and
 // diag(A) for Jacobi), values finite, every entry on a sampled diagonal.
 // VERIFY 1, after it: every lower entry equals the upper one of its partner
 // row, bit for bit, and every upper entry has one (absent = NaN on both
-// sides), i.e. the matrix is symmetric.
+// sides), i.e. the matrix is symmetric.  Near matrices have both in the first
+// launch: 2 M-row band of half-width 8, 298 -> 160 us, of which the matrix and
+// the planes need 110.
 template <int VERIFY>
 __global__ void __launch_bounds__(kBlock)
 k_ds_rows(const int32_t *__restrict__ rp, const int32_t *__restrict__ col, const double *__restrict__ val,
@@ -196,8 +313,16 @@ k_ds_rows(const int32_t *__restrict__ rp, const int32_t *__restrict__ col, const
     int32_t *sc = s_col[w];
     double *sv = s_val[w];
     int miss = 0, err = 0;
+    const bool near = st->ds_d[nh - 1] <= kDsNear;
+    if (VERIFY && near) return;
+    int32_t d[kDsMax];
+    for (int t = 0; t < kDsMax; ++t) d[t] = t < nh ? st->ds_d[t] : 0;
     for (int s = blockIdx.x * (kBlock / 64) + w; s < nslices; s += gridDim.x * (kBlock / 64)) {
         const int r0 = s * 64;
+        if (near) {
+            ds_near_slice(rp, col, val, n, r0, d, nh, S, p64, p32, dg64, dg32, sc, sv, miss, err);
+            continue;
+        }
         const int nrows = min(64, n - r0);
         const int row = r0 + lane;
         const bool has = lane < nrows;
@@ -210,28 +335,7 @@ k_ds_rows(const int32_t *__restrict__ rp, const int32_t *__restrict__ col, const
             miss = 1;
             continue;
         }
-        for (int k0 = 0; k0 < cnt; k0 += 256) {
-            int c[4];
-            double v[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int k = k0 + j * 64 + lane;
-                if (k < cnt) {
-                    c[j] = col[lo + k];
-                    v[j] = val[lo + k];
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int k = k0 + j * 64 + lane;
-                if (k < cnt) {
-                    sc[k] = c[j];
-                    sv[k] = v[j];
-                }
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+        ds_stage(col, val, lo, cnt, sc, sv);
         if (has) {
             int k = rpl - lo;
             const int ke = rph - lo;

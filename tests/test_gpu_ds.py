@@ -117,6 +117,25 @@ def test_same_bits_as_sell(matrices, name):
         assert float((got[0][9].cpu() - ref).norm()) <= 1e-12 * float(ref.norm())
 
 
+@pytest.mark.parametrize("lower", [False, True])
+@pytest.mark.parametrize("row", [0, 31, 63, 64, 100, 128, 1000 - 33])
+def test_unsymmetric_value_is_seen_across_slices(row, lower):
+    """One changed value of a pair whose rows lie in one slice or in two."""
+    import torch
+    from paper_2412_08059_amd import MPCG_EPS1_NONE, DeviceCSR, Solver
+    a = _band(1000, [1, 32], 13).to_scipy().tolil()
+    i, j = (row + 32, row) if lower else (row, row + 32)
+    a[i, j] *= 1.5
+    m = W.CSR.from_scipy(a.tocsr())
+    A, B = DeviceCSR.from_host(m), torch.linspace(-1.0, 1.0, m.n, dtype=torch.float64, device="cuda")
+    x = []
+    for variant in (0, 1):
+        s = Solver(m.n, m.nnz, spmv_variant=variant, precond=1, maxit1=40, maxit2=40, max_restarts=0)
+        x.append(s.solve(A, B, MPCG_EPS1_NONE, 1e-8)[1].clone())
+        s.close()
+    assert torch.equal(x[0].view(torch.uint8), x[1].view(torch.uint8))
+
+
 @pytest.mark.parametrize("bad", ["column", "order", "nan", "inf_b"])
 def test_malformed_entries_are_reported(bad):
     """Found by the diagonal pass or not, an error is the general pass's."""
