@@ -213,6 +213,10 @@ struct Engine {
     void process_slots(const BSys *m, int32_t cnt, int64_t gi, AdmitList &l2);
     void retire(RetireList &l, int32_t slot, const Slot &sl, double *x);
     void flush_retired();
+    EpsList eps{};                        // systems whose eps1 has been chosen
+    BfsList starts{}, nexts{}, finishes{};   // transitions of the level kernels' 2BFS
+    void bfs_add(BfsList &l, int32_t slot, const Slot &sl);
+    void flush_bfs();
     RetireList results{}, releases{};   // systems whose x / whose slot goes back, launched by list
     bool bfs_pump();
     bool process_bfs(const BSys *m, int32_t cnt);
@@ -383,8 +387,25 @@ void Engine::flush_retired()
     if (!failed) {
         launch_results(s, a, results);
         launch_releases(s, a, releases);
+        launch_set_eps(s, a, eps);
     }
-    results.cnt = releases.cnt = 0;
+    results.cnt = releases.cnt = eps.cnt = 0;
+}
+
+void Engine::bfs_add(BfsList &l, int32_t slot, const Slot &sl)
+{
+    const int k = l.cnt++;
+    l.sys[k] = slot;
+    l.nsl[k] = sl.nslices;
+    if (l.cnt == kBfsList) flush_bfs();
+}
+
+void Engine::flush_bfs()
+{
+    launch_bfs_fast_start(sb, a, starts);
+    launch_bfs_next_sweep(sb, a, nexts);
+    launch_bfs_finish(sb, a, finishes);
+    starts.cnt = nexts.cnt = finishes.cnt = 0;
 }
 
 void Engine::retire(RetireList &l, int32_t slot, const Slot &sl, double *x)
@@ -481,7 +502,11 @@ void Engine::process_slots(const BSys *m, int32_t cnt, int64_t gi, AdmitList &l2
                 const int cls = knn_select(*model, chi, opt.knn_k, &sl.exact);
                 sl.cls = (cls >= 2 && cls <= 7) ? cls : 4;
                 sl.eps1 = kEpsClass[sl.cls];
-                launch_set_eps(s, a, i, sl.eps1, sl.cls - 2);
+                const int k = eps.cnt++;
+                eps.sys[k] = i;
+                eps.ci[k] = sl.cls - 2;
+                eps.eps1[k] = sl.eps1;
+                if (eps.cnt == kEpsList) flush_retired();
                 sl.t_feat = now_ms();
                 sl.feat = 4;
                 sl.guard = group + 1;
@@ -538,7 +563,7 @@ bool Engine::process_bfs(const BSys *m, int32_t cnt)
             continue;
         }
         if (sl.feat == 1 && M.bfs_mode == kBfsSwept) {
-            launch_bfs_next_sweep(sb, a, i, (int32_t)sl.f.n);
+            bfs_add(nexts, i, sl);
             sl.feat = 2;
             enq = true;
         } else if (sl.feat == 2 && M.bfs_mode == kBfsSwept) {
@@ -548,7 +573,7 @@ bool Engine::process_bfs(const BSys *m, int32_t cnt)
                 sl.fast = false;
                 sl.feat = 1;
             } else {
-                launch_bfs_finish(sb, a, i, (int32_t)sl.f.n);
+                bfs_add(finishes, i, sl);
                 sl.feat = 3;
             }
             enq = true;
@@ -601,16 +626,25 @@ bool Engine::band_pump()
         process_band(bandmirror, bandmirror_n);
     }
     BandList bl[4] = {};
+    BfsList masks{};
     bool any = false;
     for (int32_t i = 0; i < (int32_t)slots.size(); ++i) {
         Slot &sl = slots[i];
         if (!sl.used || !sl.autoe || !sl.want_start || !sl.band) continue;
-        launch_band_masks(sband, a, i, sl.nslices);
+        const int k = masks.cnt++;
+        masks.sys[k] = i;
+        masks.nsl[k] = sl.nslices;
+        if (masks.cnt == kBfsList) {
+            launch_band_masks(sband, a, masks);
+            masks.cnt = 0;
+        }
         const int c = sl.nh <= 4 ? 0 : sl.nh <= 8 ? 1 : sl.nh <= 16 ? 2 : 3;
         BandList &l = bl[c];
         l.slot[l.cnt++] = i;
         l.nh_max = std::max(l.nh_max, sl.nh);
         if (l.cnt == kBandList) {
+            launch_band_masks(sband, a, masks);   // before the sweeps that read them
+            masks.cnt = 0;
             launch_bfs_band(sband, a, l);
             l = BandList{};
         }
@@ -619,6 +653,7 @@ bool Engine::band_pump()
         any = true;
     }
     if (!any) return true;
+    launch_band_masks(sband, a, masks);
     for (const BandList &l : bl) launch_bfs_band(sband, a, l);   // nothing for an empty list
     if (hipGetLastError() != hipSuccess) return false;
     bandmirror_n = hi_sys;
@@ -654,7 +689,7 @@ bool Engine::bfs_pump()
             enq = true;
         }
         if (sl.want_start && !sl.band) {
-            launch_bfs_fast_start(sb, a, i, (int32_t)sl.f.n);
+            bfs_add(starts, i, sl);
             sl.fast = true;
             sl.want_start = false;
             sl.feat = 1;
@@ -662,7 +697,7 @@ bool Engine::bfs_pump()
         }
         if (sl.feat == 7) {   // the band sweeps gave up: the level kernels
             if (sl.fall_cc) launch_bfs_start(sb, a, i, (int32_t)sl.f.n);
-            else launch_bfs_fast_start(sb, a, i, (int32_t)sl.f.n);
+            else bfs_add(starts, i, sl);
             sl.fast = !sl.fall_cc;
             sl.feat = 1;
             enq = true;
@@ -670,6 +705,7 @@ bool Engine::bfs_pump()
         if (sl.feat == 1 || sl.feat == 2) run = true;
         if ((sl.feat == 3 && !sl.bfs_ready) || sl.feat == 5) enq = true;   // waiting for a copy that shows the result
     }
+    flush_bfs();
     if (run)
         for (int r = 0; r < bfs_rounds; ++r) launch_bfs_round(sb, a, hi_sys, small_levels, small_cap, small_work, level_grid);
     if (hipGetLastError() != hipSuccess) return false;

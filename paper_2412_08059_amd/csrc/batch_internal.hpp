@@ -184,8 +184,15 @@ void launch_results(hipStream_t s, const BArena &a, const RetireList &l);
 void launch_releases(hipStream_t s, const BArena &a, const RetireList &l);
 void launch_cancel(hipStream_t s, const BArena &a, int32_t sys);       // the solve (step stream)
 void launch_bfs_cancel(hipStream_t s, const BArena &a, int32_t sys);   // its 2BFS (BFS stream)
-// Algorithm II: eps1 chosen by the host, of candidate class ci (0: 1e-2 ... 5: 1e-7)
-void launch_set_eps(hipStream_t s, const BArena &a, int32_t sys, double eps1, int32_t ci);
+// Algorithm II: eps1 chosen by the host, of candidate class ci (0: 1e-2 ... 5:
+// 1e-7), for a list of systems
+constexpr int kEpsList = 200;
+struct EpsList {
+    int32_t cnt, pad_;
+    int32_t sys[kEpsList], ci[kEpsList];
+    double eps1[kEpsList];
+};
+void launch_set_eps(hipStream_t s, const BArena &a, const EpsList &l);
 void launch_fill_slices(hipStream_t s, const BArena &a);   // every slice unowned
 
 // ---- one step over the systems of the work list ----
@@ -236,20 +243,26 @@ constexpr int kBdsMax = 8;
 // crossing) only while more than this many systems share the steps; with
 // fewer, the run-ahead takes bandwidth that would otherwise go unused.
 constexpr int kHoldAboveSystems = 8;
+// Systems and their slices, for one launch per kernel.
+constexpr int kBfsList = 200;
+struct BfsList {
+    int32_t cnt, pad_;
+    int32_t sys[kBfsList], nsl[kBfsList];
+};
 struct BandList {
     int32_t cnt, nh_max;                // nh_max: the most offsets of one sign among the listed systems
     int32_t slot[kBandList];
 };
-void launch_band_masks(hipStream_t s, const BArena &a, int32_t sys, int32_t nslices);
+void launch_band_masks(hipStream_t s, const BArena &a, const BfsList &l);
 void launch_bfs_band(hipStream_t s, const BArena &a, const BandList &l);
-// host-driven transitions of one system of n rows
+// host-driven transitions: of one system of n rows
 void launch_bfs_start(hipStream_t s, const BArena &a, int32_t sys, int32_t n);        // CC + sweep-1 seeds
-// first sweep from vertex 0 alone, every vertex labelled with it (no
-// components): right when the graph is connected, which its end shows
+// and of a list.  First sweep from vertex 0 alone, every vertex labelled with it
+// (no components): right when the graph is connected, which its end shows
 // (reached == n); otherwise the host starts over with launch_bfs_start
-void launch_bfs_fast_start(hipStream_t s, const BArena &a, int32_t sys, int32_t n);
-void launch_bfs_next_sweep(hipStream_t s, const BArena &a, int32_t sys, int32_t n);   // argmax + sweep-2 seeds
-void launch_bfs_finish(hipStream_t s, const BArena &a, int32_t sys, int32_t n);       // argmax + per-system result
+void launch_bfs_fast_start(hipStream_t s, const BArena &a, const BfsList &l);
+void launch_bfs_next_sweep(hipStream_t s, const BArena &a, const BfsList &l);   // argmax + sweep-2 seeds
+void launch_bfs_finish(hipStream_t s, const BArena &a, const BfsList &l);       // argmax + per-system result
 
 // ---- host engine (batch_engine.hip) ----
 struct Engine;

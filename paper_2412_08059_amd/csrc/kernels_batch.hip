@@ -392,6 +392,15 @@ __device__ inline bool adm_block(const LIST &L, int spb, int &j, int &blk)
     return false;
 }
 
+// Blocks of spb slices that a list takes.
+template <typename LIST>
+static int adm_grid(const LIST &l, int spb)
+{
+    int g = 0;
+    for (int j = 0; j < l.cnt; ++j) g += (l.nsl[j] + spb - 1) / spb;
+    return g;
+}
+
 // stage 1: slice widths zeroed (a launch of its own: the rows' pass takes
 // their maximum), then the rows' pass, then the padded-size scan
 __global__ void __launch_bounds__(kBlock) k_admit_fill_l(BArena a, AdmitList L)
@@ -510,10 +519,13 @@ __global__ void k_bfs_cancel(BArena a, int32_t sys)
 // stopped (breakdown, maxit1) before reaching eps1, from x~ at the stop;
 // otherwise the FP32 phase continues with the eps1 test (Remark 3).  Each
 // case is the state the sequential method stops in.
-__global__ void k_set_eps(BArena a, int32_t sys, double eps1, int32_t ci)
+// Thread per listed system.
+__global__ void __launch_bounds__(kBlock) k_set_eps(BArena a, EpsList L)
 {
-    if (threadIdx.x != 0) return;
-    BSys &S = a.sys[sys];
+    if ((int)threadIdx.x >= L.cnt) return;
+    BSys &S = a.sys[L.sys[threadIdx.x]];
+    const double eps1 = L.eps1[threadIdx.x];
+    const int32_t ci = L.ci[threadIdx.x];
     const double sb = sqrt(S.bb);
     S.thr1 = S.tol_abs ? eps1 : eps1 * sb;
     S.eps_set = 1;
@@ -1329,38 +1341,44 @@ __global__ void __launch_bounds__(kBlock) k_b_cc_seed(BArena a, int32_t sys)
     if (guard) atomicOr(&S.bfs_err, kErrGuard);
 }
 
-// First sweep without components: every vertex labelled with vertex 0, which
-// seeds the sweep alone (k_b_seed_root, after this kernel).
-__global__ void __launch_bounds__(kBlock) k_b_fast_init(BArena a, int32_t sys)
+// ---- transitions of a list of systems ----
+//
+// Blocks are dealt to the listed systems as at admission, a thread per row.  A
+// launch or more per system and kernel had the host thread, which also feeds
+// the steps, enqueue a thousand launches while 72 systems took their two sweeps.
+
+// The fields of a sweep that is about to run.
+__device__ inline void bfs_arm(BSys &S, int32_t sweep)
 {
-    const BSys &S = a.sys[sys];
-    for (int i = blockIdx.x * kBlock + threadIdx.x; i < S.n; i += gridDim.x * kBlock) {
-        a.label[S.row0 + i] = S.row0;
-        a.dist[S.row0 + i] = -1;
-    }
+    S.bfs_level = -1;
+    S.bfs_sweep = sweep;
+    S.vis_lvl = INT32_MIN;   // the stored visited bits belong to an earlier sweep
+    S.bfs_mode = kBfsRun;
+    S.comp_best = 0ull;
 }
 
-__global__ void k_b_seed_root(BArena a, int32_t sys)
+// First sweep without components: every vertex labelled with vertex 0, which
+// seeds the sweep alone.
+__global__ void __launch_bounds__(kBlock) k_b_fast_start_l(BArena a, BfsList L)
 {
-    if (threadIdx.x != 0) return;
-    BSys &S = a.sys[sys];
-    a.dist[S.row0] = 0;
+    int j, blk;
+    if (!adm_block(L, kSlicesPerBlock, j, blk)) return;
+    BSys &S = a.sys[L.sys[j]];
+    const int i = blk * kBlock + (int)threadIdx.x;
+    if (i >= S.n) return;
+    a.label[S.row0 + i] = S.row0;
+    a.dist[S.row0 + i] = i ? -1 : 0;
+    if (i) return;
     a.best[S.row0] = 0ull;
     a.q0[S.row0] = S.row0;
     S.bfs_nxt = 1;
     S.reached = 0;
+    bfs_arm(S, 1);
 }
 
 __global__ void k_b_bfs_arm(BArena a, int32_t sys, int32_t sweep)
 {
-    if (threadIdx.x == 0) {
-        BSys &S = a.sys[sys];
-        S.bfs_level = -1;
-        S.bfs_sweep = sweep;
-        S.vis_lvl = INT32_MIN;   // the stored visited bits belong to an earlier sweep
-        S.bfs_mode = kBfsRun;
-        S.comp_best = 0ull;
-    }
+    if (threadIdx.x == 0) bfs_arm(a.sys[sys], sweep);
 }
 
 __global__ void k_b_zero_nxt(BArena a, int32_t sys)
@@ -1372,80 +1390,86 @@ __global__ void k_b_zero_nxt(BArena a, int32_t sys)
 // connected system sends every vertex to the same key slot, and same-address
 // atomics serialise: a wave whose reached vertices share one component takes
 // the maximum over its lanes first and issues one atomic.
-__global__ void __launch_bounds__(kBlock) k_b_argmax(BArena a, int32_t sys, int32_t count)
+__global__ void __launch_bounds__(kBlock) k_b_argmax_l(BArena a, BfsList L, int32_t count)
 {
-    BSys &S = a.sys[sys];
+    int j, blk;
+    if (!adm_block(L, kSlicesPerBlock, j, blk)) return;
+    BSys &S = a.sys[L.sys[j]];
     const int lane = threadIdx.x & 63;
-    // wave-uniform loop: every lane of a wave walks the same bases
-    for (int base = blockIdx.x * kBlock + (threadIdx.x & ~63); base < S.n; base += gridDim.x * kBlock) {
-        const int i = base + lane;
-        int lab = -1;
-        unsigned long long key = 0ull;
-        if (i < S.n) {
-            const int v = S.row0 + i;
-            const int d = a.dist[v];
-            if (d >= 0) {
-                key = ((unsigned long long)(unsigned)d << 32) | (unsigned long long)(0xffffffffu - (unsigned)v);
-                lab = a.label[v];
-            }
+    const int i = blk * kBlock + (int)threadIdx.x;
+    int lab = -1;
+    unsigned long long key = 0ull;
+    if (i < S.n) {
+        const int v = S.row0 + i;
+        const int d = a.dist[v];
+        if (d >= 0) {
+            key = ((unsigned long long)(unsigned)d << 32) | (unsigned long long)(0xffffffffu - (unsigned)v);
+            lab = a.label[v];
         }
-        const unsigned long long m = __ballot(lab >= 0);
-        if (m == 0ull) continue;
-        if (count && lane == 0) atomicAdd(&S.reached, (int)__popcll(m));   // the first sweep's reach
-        const int l0 = __ffsll((unsigned long long)m) - 1;
-        const int L = __shfl(lab, l0, 64);
-        if (__all(lab < 0 || lab == L)) {
-            unsigned long long kmax = key;   // lanes without a vertex hold 0, below every key
-            for (int off = 32; off > 0; off >>= 1) {
-                const unsigned long long o = __shfl_xor(kmax, off, 64);
-                kmax = kmax > o ? kmax : o;
-            }
-            if (lane == l0) atomicMax(&a.best[L], kmax);
-        } else if (lab >= 0) {
-            atomicMax(&a.best[lab], key);
+    }
+    const unsigned long long m = __ballot(lab >= 0);
+    if (m == 0ull) return;
+    if (count && lane == 0) atomicAdd(&S.reached, (int)__popcll(m));   // the first sweep's reach
+    const int l0 = __ffsll((unsigned long long)m) - 1;
+    const int lab0 = __shfl(lab, l0, 64);
+    if (__all(lab < 0 || lab == lab0)) {
+        unsigned long long kmax = key;   // lanes without a vertex hold 0, below every key
+        for (int off = 32; off > 0; off >>= 1) {
+            const unsigned long long o = __shfl_xor(kmax, off, 64);
+            kmax = kmax > o ? kmax : o;
         }
+        if (lane == l0) atomicMax(&a.best[lab0], kmax);
+    } else if (lab >= 0) {
+        atomicMax(&a.best[lab], key);
     }
 }
 
-__global__ void __launch_bounds__(kBlock) k_b_fill_dist(BArena a, int32_t sys)
+__global__ void __launch_bounds__(kBlock) k_b_unvisit_l(BArena a, BfsList L)
 {
-    const BSys &S = a.sys[sys];
-    for (int i = blockIdx.x * kBlock + threadIdx.x; i < S.n; i += gridDim.x * kBlock) a.dist[S.row0 + i] = -1;
+    int j, blk;
+    if (!adm_block(L, kSlicesPerBlock, j, blk)) return;
+    BSys &S = a.sys[L.sys[j]];
+    const int i = blk * kBlock + (int)threadIdx.x;
+    if (i < S.n) a.dist[S.row0 + i] = -1;
+    if (i == 0) S.bfs_nxt = 0;
 }
 
 // Second sweep from t_c of every component c.
-__global__ void __launch_bounds__(kBlock) k_b_seed_far(BArena a, int32_t sys)
+__global__ void __launch_bounds__(kBlock) k_b_seed_far_l(BArena a, BfsList L)
 {
-    BSys &S = a.sys[sys];
-    for (int i = blockIdx.x * kBlock + threadIdx.x; i < S.n; i += gridDim.x * kBlock) {
-        const int v = S.row0 + i;
-        if (a.label[v] != v) continue;
-        const int t = (int)(0xffffffffu - (unsigned)(a.best[v] & 0xffffffffull));
-        if (t < S.row0 || t >= S.row0 + S.n) continue;   // cannot happen: the root itself has a key
-        a.tarr[v] = t;
-        a.best[v] = 0ull;
-        a.dist[t] = 0;
-        const int pos = atomicAdd(&S.bfs_nxt, 1);
-        a.q0[S.row0 + pos] = t;
-    }
+    int j, blk;
+    if (!adm_block(L, kSlicesPerBlock, j, blk)) return;
+    BSys &S = a.sys[L.sys[j]];
+    const int i = blk * kBlock + (int)threadIdx.x;
+    if (i == 0) bfs_arm(S, 2);
+    const int v = S.row0 + i;
+    if (i >= S.n || a.label[v] != v) return;
+    const int t = (int)(0xffffffffu - (unsigned)(a.best[v] & 0xffffffffull));
+    if (t < S.row0 || t >= S.row0 + S.n) return;   // cannot happen: the root itself has a key
+    a.tarr[v] = t;
+    a.best[v] = 0ull;
+    a.dist[t] = 0;
+    const int pos = atomicAdd(&S.bfs_nxt, 1);
+    a.q0[S.row0 + pos] = t;
 }
 
 // Best component: largest eccentricity, first (smallest root) on ties.
-__global__ void __launch_bounds__(kBlock) k_b_comp_best(BArena a, int32_t sys)
+__global__ void __launch_bounds__(kBlock) k_b_comp_best_l(BArena a, BfsList L)
 {
-    BSys &S = a.sys[sys];
-    for (int i = blockIdx.x * kBlock + threadIdx.x; i < S.n; i += gridDim.x * kBlock) {
-        const int c = S.row0 + i;
-        if (a.label[c] != c) continue;
-        const unsigned long long ecc = a.best[c] >> 32;
-        atomicMax(&S.comp_best, (ecc << 32) | (unsigned long long)(0xffffffffu - (unsigned)c));
-    }
+    int j, blk;
+    if (!adm_block(L, kSlicesPerBlock, j, blk)) return;
+    BSys &S = a.sys[L.sys[j]];
+    const int i = blk * kBlock + (int)threadIdx.x, c = S.row0 + i;
+    if (i >= S.n || a.label[c] != c) return;
+    const unsigned long long ecc = a.best[c] >> 32;
+    atomicMax(&S.comp_best, (ecc << 32) | (unsigned long long)(0xffffffffu - (unsigned)c));
 }
 
-__global__ void k_b_feat_final(BArena a, int32_t sys)
+// Thread per system.
+__global__ void __launch_bounds__(kBlock) k_b_feat_final_l(BArena a, BfsList L)
 {
-    if (threadIdx.x != 0) return;
-    BSys &S = a.sys[sys];
+    if ((int)threadIdx.x >= L.cnt) return;
+    BSys &S = a.sys[L.sys[threadIdx.x]];
     const unsigned long long key = S.comp_best;
     const int comp = (int)(0xffffffffu - (unsigned)(key & 0xffffffffull));
     if (key == 0ull || comp < S.row0 || comp >= S.row0 + S.n) {
@@ -1477,30 +1501,27 @@ void launch_bfs_start(hipStream_t s, const BArena &a, int32_t sys, int32_t n)
     hipLaunchKernelGGL(k_b_bfs_arm, dim3(1), dim3(64), 0, s, a, sys, 1);
 }
 
-void launch_bfs_fast_start(hipStream_t s, const BArena &a, int32_t sys, int32_t n)
+void launch_bfs_fast_start(hipStream_t s, const BArena &a, const BfsList &l)
 {
-    const int g = rows_grid(n);
-    hipLaunchKernelGGL(k_b_fast_init, dim3(g), dim3(kBlock), 0, s, a, sys);
-    hipLaunchKernelGGL(k_b_seed_root, dim3(1), dim3(64), 0, s, a, sys);
-    hipLaunchKernelGGL(k_b_bfs_arm, dim3(1), dim3(64), 0, s, a, sys, 1);
+    if (l.cnt > 0) hipLaunchKernelGGL(k_b_fast_start_l, dim3(adm_grid(l, kSlicesPerBlock)), dim3(kBlock), 0, s, a, l);
 }
 
-void launch_bfs_next_sweep(hipStream_t s, const BArena &a, int32_t sys, int32_t n)
+void launch_bfs_next_sweep(hipStream_t s, const BArena &a, const BfsList &l)
 {
-    const int g = rows_grid(n);
-    hipLaunchKernelGGL(k_b_argmax, dim3(g), dim3(kBlock), 0, s, a, sys, 1);
-    hipLaunchKernelGGL(k_b_fill_dist, dim3(g), dim3(kBlock), 0, s, a, sys);
-    hipLaunchKernelGGL(k_b_zero_nxt, dim3(1), dim3(64), 0, s, a, sys);
-    hipLaunchKernelGGL(k_b_seed_far, dim3(g), dim3(kBlock), 0, s, a, sys);
-    hipLaunchKernelGGL(k_b_bfs_arm, dim3(1), dim3(64), 0, s, a, sys, 2);
+    if (l.cnt <= 0) return;
+    const int g = adm_grid(l, kSlicesPerBlock);
+    hipLaunchKernelGGL(k_b_argmax_l, dim3(g), dim3(kBlock), 0, s, a, l, 1);
+    hipLaunchKernelGGL(k_b_unvisit_l, dim3(g), dim3(kBlock), 0, s, a, l);
+    hipLaunchKernelGGL(k_b_seed_far_l, dim3(g), dim3(kBlock), 0, s, a, l);
 }
 
-void launch_bfs_finish(hipStream_t s, const BArena &a, int32_t sys, int32_t n)
+void launch_bfs_finish(hipStream_t s, const BArena &a, const BfsList &l)
 {
-    const int g = rows_grid(n);
-    hipLaunchKernelGGL(k_b_argmax, dim3(g), dim3(kBlock), 0, s, a, sys, 0);
-    hipLaunchKernelGGL(k_b_comp_best, dim3(g), dim3(kBlock), 0, s, a, sys);
-    hipLaunchKernelGGL(k_b_feat_final, dim3(1), dim3(64), 0, s, a, sys);
+    if (l.cnt <= 0) return;
+    const int g = adm_grid(l, kSlicesPerBlock);
+    hipLaunchKernelGGL(k_b_argmax_l, dim3(g), dim3(kBlock), 0, s, a, l, 0);
+    hipLaunchKernelGGL(k_b_comp_best_l, dim3(g), dim3(kBlock), 0, s, a, l);
+    hipLaunchKernelGGL(k_b_feat_final_l, dim3(1), dim3(kBlock), 0, s, a, l);
 }
 
 // ------------------------------------------------------------ band 2BFS --
@@ -1520,23 +1541,30 @@ void launch_bfs_finish(hipStream_t s, const BArena &a, int32_t sys, int32_t n)
 // attempt and the system takes the level kernels.
 
 // The system's words of dm are ORed into below: zero them first.
-__global__ void __launch_bounds__(kBlock) k_band_clear(BArena a, int32_t sys)
+// (128 words per 64-row slice)
+__global__ void __launch_bounds__(kBlock) k_band_clear_l(BArena a, BfsList L)
 {
-    const BSys &S = a.sys[sys];
-    const int64_t words = (int64_t)((S.n + 31) >> 5) * 64;
+    int j, blk;
+    if (!adm_block(L, kSlicesPerBlock, j, blk)) return;
+    const BSys &S = a.sys[L.sys[j]];
+    const int words = ((S.n + 31) >> 5) * 64;
     uint32_t *dw = a.dm + (size_t)(S.row0 >> 5) * 64;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < words; i += (int64_t)gridDim.x * kBlock)
-        dw[i] = 0u;
+    for (int t = 0; t < 2; ++t) {
+        const int i = (2 * blk + t) * kBlock + (int)threadIdx.x;
+        if (i < words) dw[i] = 0u;
+    }
 }
 
 // Wave per slice: for each offset d present, the slice's rows that have an
 // entry at d (a ballot) mark rows u + d of dm's word d, i.e. 64 bits placed
 // at row 64 j + d, across up to three words.
-__global__ void __launch_bounds__(kBlock) k_band_masks(BArena a, int32_t sys)
+__global__ void __launch_bounds__(kBlock) k_band_masks_l(BArena a, BfsList L)
 {
-    const BSys &S = a.sys[sys];
+    int lj, blk;
+    if (!adm_block(L, kSlicesPerBlock, lj, blk)) return;
+    const BSys &S = a.sys[L.sys[lj]];
     const int lane = threadIdx.x & 63;
-    const int j = blockIdx.x * kSlicesPerBlock + (threadIdx.x >> 6);
+    const int j = blk * kSlicesPerBlock + (threadIdx.x >> 6);
     if (j >= S.nslices) return;
     const int sl = S.slice0 + j;
     const int g = S.row0 + j * 64 + lane;
@@ -1713,11 +1741,12 @@ __global__ void __launch_bounds__(64) k_bfs_band(BArena a, BandList L)
     }
 }
 
-void launch_band_masks(hipStream_t s, const BArena &a, int32_t sys, int32_t nslices)
+void launch_band_masks(hipStream_t s, const BArena &a, const BfsList &l)
 {
-    hipLaunchKernelGGL(k_band_clear, dim3(rows_grid(nslices * 64)), dim3(kBlock), 0, s, a, sys);
-    hipLaunchKernelGGL(k_band_masks, dim3((nslices + kSlicesPerBlock - 1) / kSlicesPerBlock), dim3(kBlock), 0, s,
-                       a, sys);
+    if (l.cnt <= 0) return;
+    const int g = adm_grid(l, kSlicesPerBlock);
+    hipLaunchKernelGGL(k_band_clear_l, dim3(g), dim3(kBlock), 0, s, a, l);
+    hipLaunchKernelGGL(k_band_masks_l, dim3(g), dim3(kBlock), 0, s, a, l);
 }
 
 void launch_bfs_band(hipStream_t s, const BArena &a, const BandList &l)
@@ -1730,14 +1759,6 @@ void launch_bfs_band(hipStream_t s, const BArena &a, const BandList &l)
 }
 
 // ------------------------------------------------------- admission (host) --
-
-template <typename LIST>
-static int adm_grid(const LIST &l, int spb)
-{
-    int g = 0;
-    for (int j = 0; j < l.cnt; ++j) g += (l.nsl[j] + spb - 1) / spb;
-    return g;
-}
 
 void launch_admit_stage1(hipStream_t s, const BArena &a, const AdmitList &l)
 {
@@ -1778,9 +1799,9 @@ void launch_bfs_cancel(hipStream_t s, const BArena &a, int32_t sys)
     hipLaunchKernelGGL(k_bfs_cancel, dim3(1), dim3(64), 0, s, a, sys);
 }
 
-void launch_set_eps(hipStream_t s, const BArena &a, int32_t sys, double eps1, int32_t ci)
+void launch_set_eps(hipStream_t s, const BArena &a, const EpsList &l)
 {
-    hipLaunchKernelGGL(k_set_eps, dim3(1), dim3(64), 0, s, a, sys, eps1, ci);
+    if (l.cnt > 0) hipLaunchKernelGGL(k_set_eps, dim3(1), dim3(kBlock), 0, s, a, l);
 }
 
 }  // namespace batch
