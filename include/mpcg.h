@@ -121,7 +121,8 @@ typedef struct {
     int32_t knn_k;        /* neighbours; 0 = the model's k */
     int32_t tol_mode;     /* 0 relative to ||b|| (default), 1 absolute */
     int32_t max_restarts; /* FP64 restarts after a failed final check; default 5 */
-    int32_t graph_iters;  /* CG iterations enqueued between host polls; 0 = default (8) */
+    int32_t graph_iters;  /* CG iterations enqueued between host polls; 0 = default (8; 32 where
+                             one workgroup runs them in a launch) */
     int32_t precond;      /* 0 none (default); 1 Jacobi, M = diag(A), in both stages (the
                              preconditioned CG procedure of the subsection "Propagation of
                              Rounding Errors When Precondition is Applied"): a row without a
@@ -133,8 +134,10 @@ typedef struct {
                              (default; each FP32 x FP32 product is exact there), 1 accumulate in
                              FP32 -- the paper leaves the accumulation precision of the FP32 phase
                              open (Remark 3 only fixes the FP64 norms of v) */
-    int32_t spmv_variant; /* sparse product: 0 auto (the loaded tuning table, else SELL-64 when
-                             its padding fits, split in two launches for 32-bit columns);
+    int32_t spmv_variant; /* sparse product: 0 auto (diagonal storage for a symmetric matrix on
+                             few diagonals; the loaded tuning table, else SELL-64 when its
+                             padding fits, split in two launches for 32-bit columns; CG of a
+                             small system in one workgroup);
                              1 SELL-64 fused; 2 SELL-64 split (direction, then a one-vector
                              gather); 3 CSR stream.  Every variant runs each row's fma chain in
                              CSR order, so the products are the same bits */
@@ -282,7 +285,8 @@ mpcg_status mpcg_diameter_multi(mpcg_ctx *ctx, const mpcg_csr *A, const int32_t 
  * matrix's class (GPU architecture and compute units, 16- or 32-bit SELL
  * column offsets, round(log2(nnz / n)), nearest floor(log2(n))); else the
  * built-in defaults.  mpcg_options.spmv_variant 1-3 and bfs_mode 1-2 override
- * sell_split, the SELL/CSR choice and bfs_persist. */
+ * sell_split, the SELL/CSR choice and bfs_persist.  The sell_* fields have no
+ * effect on a matrix in diagonal storage or iterated in one workgroup. */
 typedef struct {
     int32_t sell_batch;          /* SELL-64 entries of a row whose loads are issued together: 4 or 8 */
     int32_t sell_whole_batch;    /* bit 0 FP32, bit 1 FP64 products: every lane loads its whole batch
@@ -298,12 +302,13 @@ typedef struct {
     int32_t batch_level_grid;    /* blocks of the multi-block level kernel, 1..65536 */
     int32_t bfs_dia;             /* 2BFS sweeps as bit-parallel levels over the diagonals when the
                                     pattern lies on at most 16 of them: 0 never, 1 when the pattern is
-                                    wider than |i - j| <= 8 and has at least 2^16 rows, 2 whenever it
-                                    qualifies */
-    int32_t bfs_dia_tiles;       /* with bfs_dia: 1 = several levels per launch (a block forms them on
-                                    its own words plus a halo that the levels consume: up to 16 levels
-                                    per tile where 8 or more fit, else 2 per launch), 0 = one launch
-                                    per level */
+                                    wider than |i - j| <= 8 and has at least 64 rows (2^16 with
+                                    bfs_dia_tiles 0), 2 whenever it qualifies */
+    int32_t bfs_dia_tiles;       /* with bfs_dia: 1 = several levels per launch (one block runs them
+                                    all while its LDS holds every row's bits; else a block forms them
+                                    on its own words plus a halo that the levels consume: up to 16
+                                    levels per tile where 8 or more fit, else 2 per launch), 0 = one
+                                    launch per level */
     int32_t sell_stream;         /* the SELL products read the matrix with nontemporal loads: -1 where
                                     that precision's copy exceeds the 256 MB Infinity Cache, 0 never,
                                     1 always */

@@ -22,8 +22,8 @@
 //
 // What bounds it: the bytes above plus the vectors (gathers of r and d hit
 // the L2).  One FP64 CG product on the 128^3 stencil needs 168 MB instead of
-// 255 MB (counted: 188 MB read and 50 MB written; neighbouring rows a plane of
-// the grid apart fall to other XCDs' L2s).
+// 255 MB (counted: 170 MB read and 50 MB written; rows a plane of the grid apart
+// are not always in the same XCD's L2 any more).
 
 #include "jacobi_common.hpp"
 

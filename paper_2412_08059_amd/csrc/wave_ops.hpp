@@ -7,9 +7,9 @@
 // of a value with itself are the partners' values), and DPP row rotations by
 // 8, 4, 2, 1 the nearer ones -- after the step at distance 2 k the values
 // repeat every 2 k lanes inside a row of 16, so the lane k places round the
-// row holds the partner's value.  Six ds_bpermute pairs take about 0.25 us
-// for a double, these about 0.07 us; every CG kernel does three such sums on
-// its critical path.
+// row holds the partner's value.  A ds_bpermute exchange goes through the
+// LDS pipe and is waited for, twice per step for a double; every CG kernel does
+// three such sums on its critical path.
 
 #pragma once
 
