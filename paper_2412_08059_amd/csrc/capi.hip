@@ -127,7 +127,7 @@ struct mpcg_ctx {
     mpcg_options opt{};
     char *ws = nullptr;
     size_t ws_bytes = 0;
-    DevState *hst = nullptr;   // pinned: [0],[1],[2] main channel, [3],[4],[5] side channel
+    DevState *hst = nullptr;   // pinned: [0],[1],[2] main channel, [3],[4],[5] side channel, [6] Plan::live
     hipEvent_t ev[2] = {nullptr, nullptr};
     hipEvent_t tm[8] = {};
     KnnModel model;
@@ -253,6 +253,7 @@ struct Plan {
     const int32_t *col = nullptr;
     const double *val = nullptr;
     DevState *st = nullptr;
+    int32_t *live = nullptr;   // host memory: a CG phase's launches clear it once the recurrence has stopped
     double *sp = nullptr;   // partials written by the product kernels (up to 3 per block)
     double *up = nullptr;   // partials written by the update kernel (2 per block with Jacobi)
     int pc = 0;             // Jacobi-preconditioned stages
@@ -325,6 +326,7 @@ mpcg_status ingest(mpcg_ctx *c, const mpcg_csr *A, const double *b, bool need_va
     p->col = A->col_idx;
     p->val = A->val;
     p->st = p->at<DevState>(p->L.state);
+    p->live = &c->hst[6].live;
     p->sp = p->at<double>(p->L.part);
     p->up = p->sp + 3 * kMaxGrid;
     p->pc = want_diag ? 1 : 0;
@@ -455,12 +457,14 @@ void run_cg_spmv(hipStream_t s, const Plan &p, const T *r, T *dA, T *dB, T *q, i
 {
     const T *src = p.pc ? zbuf<T>(p) : r;
     if (p.use_ds)
-        launch_ds_cg_spmv<T>(s, p.ds, p.sell.grid, src, dA, dB, q, p.up, p.nup, p.sp, it, it0, x, snap, p.pc, p.st);
+        launch_ds_cg_spmv<T>(s, p.ds, p.sell.grid, src, dA, dB, q, p.up, p.nup, p.sp, it, it0, x, snap, p.pc, p.st,
+                             p.live);
     else if (p.use_sell)
-        launch_sell_cg_spmv<T>(s, p.sell, src, dA, dB, q, p.up, p.nup, p.sp, it, it0, x, snap, p.pc, p.st);
+        launch_sell_cg_spmv<T>(s, p.sell, src, dA, dB, q, p.up, p.nup, p.sp, it, it0, x, snap, p.pc, p.st,
+                               p.live);
     else
         launch_cg_spmv<T>(s, csr_shape<T>(p), p.rp, p.col, csr_vals<T>(p), src, dA, dB, q, p.up, p.nup, p.sp,
-                          it, it0, x, snap, p.pc, p.st);
+                          it, it0, x, snap, p.pc, p.st, p.live);
 }
 
 template <typename T>
@@ -524,6 +528,8 @@ mpcg_status cg_loop(mpcg_ctx *c, const Plan &p, T *x, T *r, T *q, T *dA, T *dB, 
     const int G = p.use_wg ? poll_iters_wg(c) : poll_iters(c);
     const Chan &ch = c->main;
     T *snap = stop_flag ? snap_buf<T>(p) : nullptr;
+    // the stream holds no earlier phase's iterations: each phase ends with a read_state
+    __atomic_store_n(p.live, 1, __ATOMIC_RELEASE);
     int64_t k = 0;
     for (;;) {
         if (p.use_wg) {
@@ -536,11 +542,15 @@ mpcg_status cg_loop(mpcg_ctx *c, const Plan &p, T *x, T *r, T *q, T *dA, T *dB, 
             run_cg_update<T>(ch.s, p, r, q, it);
         }
         HIPCHK(hipGetLastError());
-        HIPCHK(hipMemcpyAsync(ch.poll[k & 1], p.st, sizeof(DevState), hipMemcpyDeviceToHost, ch.s));
+        // whether the recurrence still runs: the two launches an iteration say so
+        // themselves; of one workgroup's iterations the state is copied (a store
+        // to host memory in its loop cost 5% more than the copy)
+        if (p.use_wg)
+            HIPCHK(hipMemcpyAsync(ch.poll[k & 1], p.st, sizeof(DevState), hipMemcpyDeviceToHost, ch.s));
         HIPCHK(hipEventRecord(ch.ev[k & 1], ch.s));
         if (k > 0) {
             HIPCHK(hipEventSynchronize(ch.ev[(k - 1) & 1]));
-            if (!ch.poll[(k - 1) & 1]->live) break;
+            if (!(p.use_wg ? ch.poll[(k - 1) & 1]->live : __atomic_load_n(p.live, __ATOMIC_ACQUIRE))) break;
         }
         if (stop_flag && stop_flag->load()) break;
         ++k;
@@ -991,7 +1001,7 @@ mpcg_status mpcg_create(mpcg_ctx **out, const mpcg_options *opt, void *hip_strea
     if (hipGetDevice(&c->device) != hipSuccess || scratch_init(c->device) != hipSuccess ||
         hipGetDeviceProperties(&prop, c->device) != hipSuccess ||
         hipDeviceGetAttribute(&c->num_cu, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess ||
-        hipHostMalloc((void **)&c->hst, 6 * sizeof(DevState), hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc((void **)&c->hst, 7 * sizeof(DevState), hipHostMallocDefault) != hipSuccess ||
         hipStreamCreateWithFlags(&c->side_stream, hipStreamNonBlocking) != hipSuccess) {
         mpcg_destroy(c);
         return MPCG_EDEVICE;

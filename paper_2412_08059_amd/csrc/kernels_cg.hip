@@ -339,6 +339,7 @@ struct SpmvArgs {
     T *snap;           // x~ copies at the run-ahead crossings (FP32 only)
     double *part;      // this kernel's partials
     DevState *st;
+    int32_t *live;     // cleared in host memory when the recurrence has stopped
 };
 
 // A tile is R consecutive rows; a block walks a contiguous range of tiles.
@@ -365,14 +366,14 @@ __global__ void __launch_bounds__(kBlock) k_spmv(SpmvArgs<T> a)
     if (MODE == kModeCg) {
         __shared__ double sm_rho[kBlock / 64], sm_g[kBlock / 64];
         const int it = a.it;
-        const CgHead h = cg_head<T>(st, a.up, a.nup, a.pc, it, a.it0, sm_rho, sm_g);
+        const CgHead h = cg_head<T>(st, a.up, a.nup, a.pc, it, a.it0, sm_rho, sm_g, a.live);
         if (h.skip) return;
         f32acc = h.f32acc;
         dold = (it & 1) ? a.dB : a.dA;
         dnew = (it & 1) ? a.dA : a.dB;
         if (it != a.it0) {
             alpha_prev = (T)h.alph;
-            const bool stop = cg_head_decide(st, h, it);
+            const bool stop = cg_head_decide(st, h, it, a.live);
             const unsigned cross = a.snap ? spec_crossings(st, it, h.g) : 0u;
             if (stop || cross) {
                 // the iterate x_it of this block's rows, then its run-ahead copies
@@ -514,11 +515,11 @@ static SpmvArgs<T> spmv_args(const SpmvShape &sh, const int32_t *rp, const int32
 template <typename T>
 void launch_cg_spmv(hipStream_t s, const SpmvShape &sh, const int32_t *rp, const int32_t *col,
                     const T *val, const T *r, T *dA, T *dB, T *q, const double *up, int nup,
-                    double *part, int it, int it0, T *x, T *snap, int pc, DevState *st)
+                    double *part, int it, int it0, T *x, T *snap, int pc, DevState *st, int32_t *live)
 {
     SpmvArgs<T> a = spmv_args<T>(sh, rp, col, val);
     a.it = it; a.it0 = it0; a.x = x; a.snap = snap; a.pc = pc;
-    a.r = r; a.dA = dA; a.dB = dB; a.q = q; a.up = up; a.nup = nup; a.part = part; a.st = st;
+    a.r = r; a.dA = dA; a.dB = dB; a.q = q; a.up = up; a.nup = nup; a.part = part; a.st = st; a.live = live;
     hipLaunchKernelGGL((k_spmv<kModeCg, T>), dim3(sh.grid), dim3(kBlock), 0, s, a);
 }
 
@@ -717,11 +718,11 @@ void launch_diag(hipStream_t s, const int32_t *rp, const int32_t *col, const dou
 template void launch_cg_spmv<float>(hipStream_t, const SpmvShape &, const int32_t *, const int32_t *,
                                     const float *, const float *, float *, float *, float *,
                                     const double *, int, double *, int, int, float *, float *, int,
-                                    DevState *);
+                                    DevState *, int32_t *);
 template void launch_cg_spmv<double>(hipStream_t, const SpmvShape &, const int32_t *, const int32_t *,
                                      const double *, const double *, double *, double *, double *,
                                      const double *, int, double *, int, int, double *, double *, int,
-                                     DevState *);
+                                     DevState *, int32_t *);
 template void launch_cg_update<float>(hipStream_t, int32_t, float *, const float *, const double *, int,
                                       double *, int, int, const float *, float *, DevState *);
 template void launch_cg_update<double>(hipStream_t, int32_t, double *, const double *, const double *,

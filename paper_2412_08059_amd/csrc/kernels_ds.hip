@@ -404,6 +404,7 @@ struct DsArgs {
     const double *up;
     double *part;
     DevState *st;
+    int32_t *live;      // cleared in host memory when the recurrence has stopped
     // restart, residual, plain
     const float *x32;
     const double *x64in, *b, *dg;
@@ -583,14 +584,14 @@ __attribute__((amdgpu_num_sgpr(kSgprCap))) k_ds(DsArgs<T> a)
     if (MODE == kDsCg) {
         __shared__ double sm_rho[kBlock / 64], sm_g[kBlock / 64];
         const int it = a.it;
-        const CgHead h = cg_head<T>(st, a.up, a.nup, a.pc, it, a.it0, sm_rho, sm_g);
+        const CgHead h = cg_head<T>(st, a.up, a.nup, a.pc, it, a.it0, sm_rho, sm_g, a.live);
         if (h.skip) return;
         f32acc = h.f32acc;
         dold = (it & 1) ? a.dB : a.dA;
         dnew = (it & 1) ? a.dA : a.dB;
         if (it != a.it0) {
             alpha_prev = (T)h.alph;
-            const bool stop = cg_head_decide(st, h, it);
+            const bool stop = cg_head_decide(st, h, it, a.live);
             const unsigned cross = a.snap ? spec_crossings(st, it, h.g) : 0u;
             if (stop || cross) {
                 // the iterate x_it of this block's rows, then its run-ahead copies
@@ -791,11 +792,11 @@ template <int MODE, typename T> static void ds_launch(hipStream_t s, const DsMat
 
 template <typename T>
 void launch_ds_cg_spmv(hipStream_t s, const DsMat &m, int grid, const T *r, T *dA, T *dB, T *q, const double *up,
-                       int nup, double *part, int it, int it0, T *x, T *snap, int pc, DevState *st)
+                       int nup, double *part, int it, int it0, T *x, T *snap, int pc, DevState *st, int32_t *live)
 {
     DsArgs<T> a = ds_args<T>(m, grid);
     a.it = it; a.it0 = it0; a.r = r; a.dA = dA; a.dB = dB; a.q = q; a.up = up; a.nup = nup;
-    a.x = x; a.snap = snap; a.pc = pc; a.part = part; a.st = st;
+    a.x = x; a.snap = snap; a.pc = pc; a.part = part; a.st = st; a.live = live;
     ds_launch<kDsCg, T>(s, m, grid, a);
 }
 
@@ -836,9 +837,11 @@ template <typename T> void launch_ds_jacobi(hipStream_t s, const DsMat &m, const
 }
 
 template void launch_ds_cg_spmv<float>(hipStream_t, const DsMat &, int, const float *, float *, float *, float *,
-                                       const double *, int, double *, int, int, float *, float *, int, DevState *);
+                                       const double *, int, double *, int, int, float *, float *, int, DevState *,
+                                       int32_t *);
 template void launch_ds_cg_spmv<double>(hipStream_t, const DsMat &, int, const double *, double *, double *, double *,
-                                        const double *, int, double *, int, int, double *, double *, int, DevState *);
+                                        const double *, int, double *, int, int, double *, double *, int, DevState *,
+                                        int32_t *);
 template void launch_ds_plain<float>(hipStream_t, const DsMat &, int, const float *, float *);
 template void launch_ds_plain<double>(hipStream_t, const DsMat &, int, const double *, double *);
 template void launch_ds_jacobi<float>(hipStream_t, const DsMat &, const JacArgs<float> &);

@@ -337,6 +337,7 @@ struct SellArgs {
     double *z;
     double *part;
     DevState *st;
+    int32_t *live;       // cleared in host memory when the recurrence has stopped
 };
 
 // NT: the matrix (values, column offsets) is read with nontemporal loads.
@@ -382,14 +383,14 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(kSgprCa
     if (MODE == kSellCg || MODE == kSellDir) {
         __shared__ double sm_rho[kBlock / 64], sm_g[kBlock / 64];
         const int it = a.it;
-        const CgHead h = cg_head<T>(st, a.up, a.nup, a.pc, it, a.it0, sm_rho, sm_g);
+        const CgHead h = cg_head<T>(st, a.up, a.nup, a.pc, it, a.it0, sm_rho, sm_g, a.live);
         if (h.skip) return;
         f32acc = h.f32acc;
         dold = (it & 1) ? a.dB : a.dA;
         dnew = (it & 1) ? a.dA : a.dB;
         if (it != a.it0) {
             alpha_prev = (T)h.alph;
-            const bool stop = cg_head_decide(st, h, it);
+            const bool stop = cg_head_decide(st, h, it, a.live);
             const unsigned cross = a.snap ? spec_crossings(st, it, h.g) : 0u;
             if (stop || cross) {
                 // the iterate x_it of this block's rows, then its run-ahead copies
@@ -574,12 +575,12 @@ template <> const double *sell_vals<double>(const SellMat &m) { return m.v64; }
 template <typename T>
 void launch_sell_cg_spmv(hipStream_t s, const SellMat &m, const T *r, T *dA, T *dB, T *q,
                          const double *up, int nup, double *part, int it, int it0, T *x, T *snap, int pc,
-                         DevState *st)
+                         DevState *st, int32_t *live)
 {
     SellArgs<T> a = sell_args<T>(m, sell_vals<T>(m));
     a.it = it; a.it0 = it0; a.r = r; a.dA = dA; a.dB = dB; a.q = q; a.up = up; a.nup = nup;
     a.x = x; a.snap = snap; a.pc = pc;
-    a.part = part; a.st = st;
+    a.part = part; a.st = st; a.live = live;
     if (m.split) {
         sell_launch<kSellDir, T>(s, m, a);
         sell_launch<kSellCgD, T>(s, m, a);
@@ -618,10 +619,10 @@ void launch_sell_plain(hipStream_t s, const SellMat &m, const T *x, T *y)
 
 template void launch_sell_cg_spmv<float>(hipStream_t, const SellMat &, const float *, float *, float *,
                                          float *, const double *, int, double *, int, int, float *,
-                                         float *, int, DevState *);
+                                         float *, int, DevState *, int32_t *);
 template void launch_sell_cg_spmv<double>(hipStream_t, const SellMat &, const double *, double *,
                                           double *, double *, const double *, int, double *, int, int,
-                                          double *, double *, int, DevState *);
+                                          double *, double *, int, DevState *, int32_t *);
 template void launch_sell_plain<float>(hipStream_t, const SellMat &, const float *, float *);
 template void launch_sell_plain<double>(hipStream_t, const SellMat &, const double *, double *);
 

@@ -255,10 +255,12 @@ void launch_timing_state(hipStream_t s, DevState *st, double *part, int cnt);
 // crossing (FP32 only).
 // `r` is the vector the direction is built from: the residual, or z = M^-1 r
 // with Jacobi (pc = 1, the update partials then hold rho and r.r).
+// live: host memory, cleared by the launch in which the recurrence stops and by
+// every one after it.
 template <typename T>
 void launch_cg_spmv(hipStream_t s, const SpmvShape &sh, const int32_t *rp, const int32_t *col,
                     const T *val, const T *r, T *dA, T *dB, T *q, const double *up, int nup,
-                    double *part, int it, int it0, T *x, T *snap, int pc, DevState *st);
+                    double *part, int it, int it0, T *x, T *snap, int pc, DevState *st, int32_t *live);
 // Jacobi (dg != nullptr): also z = r / dg and partials of r.z (slot 0) and r.r
 // (slot nup + block).
 template <typename T>
@@ -285,7 +287,7 @@ void launch_spmv_plain(hipStream_t s, const SpmvShape &sh, const int32_t *rp, co
 template <typename T>
 void launch_sell_cg_spmv(hipStream_t s, const SellMat &m, const T *r, T *dA, T *dB, T *q,
                          const double *up, int nup, double *part, int it, int it0, T *x, T *snap, int pc,
-                         DevState *st);
+                         DevState *st, int32_t *live);
 void launch_sell_restart(hipStream_t s, const SellMat &m, const float *x32, double *x64,
                          const double *b, double *r, double *dA, double *dB, int it0, const double *dg,
                          double *z, double *part, DevState *st);
@@ -308,7 +310,7 @@ void launch_ds_ingest(hipStream_t s, const int32_t *rp, const int32_t *col, cons
                       float *p32, double *dg64, float *dg32, DevState *st);
 template <typename T>
 void launch_ds_cg_spmv(hipStream_t s, const DsMat &m, int grid, const T *r, T *dA, T *dB, T *q, const double *up,
-                       int nup, double *part, int it, int it0, T *x, T *snap, int pc, DevState *st);
+                       int nup, double *part, int it, int it0, T *x, T *snap, int pc, DevState *st, int32_t *live);
 void launch_ds_restart(hipStream_t s, const DsMat &m, int grid, const float *x32, double *x64, const double *b,
                        double *r, double *dA, double *dB, int it0, const double *dg, double *z, double *part,
                        DevState *st);

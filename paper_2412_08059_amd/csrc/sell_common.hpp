@@ -117,9 +117,18 @@ struct CgHead {
     int32_t maxit;
 };
 
+// live: a word in host memory that the host reads once a group of iterations
+// has run; the launch in which the recurrence stops clears it, and so does
+// every one after it (a copy of the device state for each group cost the
+// stream a launch and two gaps, 5 us).
+__device__ inline void host_stopped(int32_t *live)
+{
+    if (blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(live, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 template <typename T>
 __device__ inline CgHead cg_head(const DevState *st, const double *up, int nup, int pc, int it, int it0, double *sm,
-                                 double *sm2)
+                                 double *sm2, int32_t *live)
 {
     CgHead h;
     const int32_t stop = st->stop_it, xit = st->x_it;
@@ -133,6 +142,7 @@ __device__ inline CgHead cg_head(const DevState *st, const double *up, int nup, 
     h.rho = h.g = 0.0;
     h.xdone = xit == it;
     h.skip = stop < it;
+    if (h.skip) host_stopped(live);
     if (h.skip || it == it0) return h;
     h.rho = partials_total(h.f32acc, up, nup, sm);
     h.g = pc ? partials_total(h.f32acc, up + nup, nup, sm2) : h.rho;   // equal without a preconditioner
@@ -141,7 +151,7 @@ __device__ inline CgHead cg_head(const DevState *st, const double *up, int nup, 
 
 // The stop test of iteration it and what block 0 records of it; returns
 // whether the recurrence stops here.
-__device__ inline bool cg_head_decide(DevState *st, const CgHead &h, int it)
+__device__ inline bool cg_head_decide(DevState *st, const CgHead &h, int it, int32_t *live)
 {
     const bool conv = sqrt(h.g) <= h.thr;
     const bool cap = !conv && it >= h.maxit;
@@ -156,6 +166,7 @@ __device__ inline bool cg_head_decide(DevState *st, const CgHead &h, int it)
             st->reason = conv ? kConverged : kMaxit;
             st->stop_it = it;
             st->live = 0;
+            host_stopped(live);
         }
     }
     return conv || cap;
