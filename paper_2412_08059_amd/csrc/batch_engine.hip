@@ -22,6 +22,8 @@
 // the state it then restarts from is the one the sequential method stops in,
 // so its arithmetic does not depend on that pace.  While any system is being
 // admitted or waits for features, groups are shortened to a few ms.
+// While every listed system has at most kWgMaxSlices slices, a group is one
+// launch in which each advances in a workgroup of its own.
 
 #include "batch_internal.hpp"
 #include "knn.hpp"
@@ -780,7 +782,7 @@ void Engine::drop_graphs()
 }
 
 // One group of steps: a graph replay when the group is captured (once per
-// pair of grid sizes), else plain launches.
+// set of grid sizes and kernels), else plain launches.
 bool Engine::launch_group(int len)
 {
     if (list_max <= kWgMaxSlices) {   // small systems only: each advances in a workgroup of its own
