@@ -550,7 +550,14 @@ mpcg_status cg_loop(mpcg_ctx *c, const Plan &p, T *x, T *r, T *q, T *dA, T *dB, 
         HIPCHK(hipEventRecord(ch.ev[k & 1], ch.s));
         if (k > 0) {
             HIPCHK(hipEventSynchronize(ch.ev[(k - 1) & 1]));
-            if (!(p.use_wg ? ch.poll[(k - 1) & 1]->live : __atomic_load_n(p.live, __ATOMIC_ACQUIRE))) break;
+            if (!(p.use_wg ? ch.poll[(k - 1) & 1]->live : __atomic_load_n(p.live, __ATOMIC_ACQUIRE))) {
+                if (it_next) *it_next = it;
+                const mpcg_status rc = read_state(ch, p, out);
+                if (rc != MPCG_OK || !out->live) return rc;
+                // cleared by a launch that an earlier call left behind with an error
+                __atomic_store_n(p.live, 1, __ATOMIC_RELEASE);
+                k = -1;
+            }
         }
         if (stop_flag && stop_flag->load()) break;
         ++k;
