@@ -680,6 +680,9 @@ bool Engine::bfs_pump()
     }
     // transitions enqueued from the copy need a copy behind them
     bool enq = !b_inflight && bmirror_n > 0 ? process_bfs(bmirror, bmirror_n) : false;
+    // before the cancels: one that a listed transition followed would be undone
+    // on the device, and the slot reused under a sweep that still runs
+    flush_bfs();
     bool run = false;
     for (int32_t i = 0; i < (int32_t)slots.size(); ++i) {
         Slot &sl = slots[i];
