@@ -229,8 +229,7 @@ k_spmv_checked(const void *rp_in, int rp_is_i64, const int32_t *__restrict__ col
         const int rlo = (int)lo, rhi = (int)hi;
         T acc = T(0);
         int prev = -1;
-        for (int c0 = b0; c0 < b1; c0 += kChkEntries) {
-            const int cn = min(kChkEntries, b1 - c0);
+        for (int c0 = b0, cn; (cn = chunk_len(c0, b1, kChkEntries)) > 0; c0 += cn) {
             int c[kChkBatch];
             double v[kChkBatch];
             T g[kChkBatch];

@@ -129,6 +129,14 @@ struct Layout {
     int64_t n, nnz;
 };
 
+// Length of the next chunk of a walk over the entries at .. end - 1 (0 at the
+// end).  Entry indices go up to 2^31 - 2, so an index past the last entry need
+// not exist in 32 bits: a walk advances by the chunk's length, not by `most`.
+__host__ __device__ inline int32_t chunk_len(int32_t at, int32_t end, int32_t most)
+{
+    return end - at < most ? end - at : most;
+}
+
 // Launch shape of the CSR-stream kernels: tiles of R rows, `grid` blocks each
 // walking a contiguous range of tiles.
 struct SpmvShape {
