@@ -503,9 +503,9 @@ k_bfs_small(const int32_t *__restrict__ rp, const int32_t *__restrict__ col, int
             const int f = w >> lsh, l = w & (lanes - 1);
             const QEnt u = sq[c][f];
             if (u.b >= e0 && u.e <= e1) {   // the row's columns are in the window
-                for (int j = u.b + l; j < u.e; j += lanes) visit(w_col[j - e0]);
+                for (uint32_t j = u.b + l; j < (uint32_t)u.e; j += lanes) visit(w_col[j - e0]);
             } else {
-                for (int j = u.b + l; j < u.e; j += lanes) visit(col[j]);
+                for (uint32_t j = u.b + l; j < (uint32_t)u.e; j += lanes) visit(col[j]);   // past 2^31 no wrap
             }
         }
         __syncthreads();
@@ -668,7 +668,7 @@ k_bfs_level(const int32_t *__restrict__ rp, const int32_t *__restrict__ col, int
     bool first = true;
     for (int64_t bbase = bbase0; bbase < items; bbase += span, first = false) {
         const int64_t wbase = bbase + (threadIdx.x & ~63);
-        int j[kBfsItems], e[kBfsItems];
+        uint32_t j[kBfsItems], e[kBfsItems];   // j runs past e, which may be 2^31 - 1
 #pragma unroll
         for (int i = 0; i < kBfsItems; ++i) {
             const int64_t w = wbase + i * stride + lane;
@@ -819,7 +819,7 @@ k_bfs_persist(const int32_t *__restrict__ rp, const int32_t *__restrict__ col, i
         if (threadIdx.x == 0) s_min = kIntMax;
         for (int64_t bbase = (int64_t)blockIdx.x * kBlock; bbase < items; bbase += span) {   // block-uniform
             const int64_t wbase = bbase + (threadIdx.x & ~63);
-            int j[kBfsItems], e[kBfsItems];
+            uint32_t j[kBfsItems], e[kBfsItems];
 #pragma unroll
             for (int i = 0; i < kBfsItems; ++i) {
                 const int64_t w = wbase + i * stride + lane;
@@ -1226,10 +1226,10 @@ k_dia_offsets(const int32_t *__restrict__ rp, const int32_t *__restrict__ col, i
         const int64_t i = i0 + threadIdx.x;
         if (i >= n) continue;
         const int b = rp[i], e = rp[i + 1];
-        for (int k0 = b; k0 < e; k0 += kRow) {
+        for (int k0 = b, cn; (cn = chunk_len(k0, e, kRow)) > 0; k0 += cn) {
             int c[kRow];
 #pragma unroll
-            for (int j = 0; j < kRow; ++j) c[j] = k0 + j < e ? col[k0 + j] : (int)i;
+            for (int j = 0; j < kRow; ++j) c[j] = j < cn ? col[k0 + j] : (int)i;
 #pragma unroll
             for (int j = 0; j < kRow; ++j) {
                 if ((unsigned)c[j] >= (unsigned)n) continue;   // ignored, as by the queue kernels
@@ -1303,10 +1303,10 @@ k_dia_rowmasks(const int32_t *__restrict__ rp, const int32_t *__restrict__ col, 
         uint32_t has = 0u;
         if (i < n) {
             const int b = rp[i], e = rp[i + 1];
-            for (int k0 = b; k0 < e; k0 += kRow) {
+            for (int k0 = b, cn; (cn = chunk_len(k0, e, kRow)) > 0; k0 += cn) {
                 int c[kRow];
 #pragma unroll
-                for (int j = 0; j < kRow; ++j) c[j] = k0 + j < e ? col[k0 + j] : (int)i;
+                for (int j = 0; j < kRow; ++j) c[j] = j < cn ? col[k0 + j] : (int)i;
 #pragma unroll
                 for (int j = 0; j < kRow; ++j) {
                     if ((unsigned)c[j] >= (unsigned)n) continue;   // so every neighbour u + d is a row

@@ -415,8 +415,7 @@ __global__ void __launch_bounds__(kBlock) k_spmv(SpmvArgs<T> a)
         const int lo = a.rp[row0];
         const int hi = a.rp[row1];
         T acc = T(0);
-        for (int c0 = lo; c0 < hi; c0 += CHUNK) {
-            const int cn = min(CHUNK, hi - c0);
+        for (int c0 = lo, cn; (cn = chunk_len(c0, hi, CHUNK)) > 0; c0 += cn) {
             for (int j = tid; j < cn; j += kBlock) {
                 const int k = c0 + j;
                 const int c = a.col[k];

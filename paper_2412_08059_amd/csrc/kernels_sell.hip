@@ -122,8 +122,8 @@ k_ingest_entries(const int32_t *__restrict__ rp, const int32_t *__restrict__ col
         const int lo = __shfl(rpl, 0, 64);
         const int hi = rp[r0 + nrows];
         const int64_t base_off = fill ? off[s] : 0;
-        for (int kb = lo; kb < hi; kb += 64) {          // wave-uniform trip count
-            const int k = kb + lane;
+        for (int kb = lo, cn; (cn = chunk_len(kb, hi, 64)) > 0; kb += cn) {   // wave-uniform trip count
+            const int k = kb + min(lane, cn - 1);
             // row of entry k: largest m < nrows with rp[r0 + m] <= k
             int m = 0;
             for (int step = 32; step > 0; step >>= 1) {
@@ -132,7 +132,7 @@ k_ingest_entries(const int32_t *__restrict__ rp, const int32_t *__restrict__ col
                 if (cand < nrows && v <= k) m = cand;
             }
             const int rstart = __shfl(rpl, m, 64);
-            if (k < hi) {
+            if (lane < cn) {
                 const int row = r0 + m;
                 const int pos = k - rstart;
                 const int c = col[k];

@@ -49,7 +49,12 @@ def test_chunks_cover_the_entries_and_stay_among_them(walk, most, end, count):
     assert all(0 < cn <= most for _, cn in got)
 
 
-def test_kernel_walks_take_the_step():
-    """No walk of the entries adds a fixed chunk length to an entry index."""
-    text = open(os.path.join(ROOT, "paper_2412_08059_amd", "csrc", "kernels_sell.hip")).read()
-    assert "c0 += kChkEntries" not in text
+@pytest.mark.parametrize("source,fixed_steps", [
+    ("kernels_sell.hip", ["c0 += kChkEntries", "kb += 64"]),
+    ("kernels_cg.hip", ["c0 += CHUNK"]),
+    ("kernels_bfs.hip", ["k0 += kRow", "int j = u.b + l", " int j[kBfsItems]"]),
+])
+def test_kernel_walks_take_the_step(source, fixed_steps):
+    """No walk of the entries adds a fixed length to a signed 32-bit entry index."""
+    text = open(os.path.join(ROOT, "paper_2412_08059_amd", "csrc", source)).read()
+    assert [s for s in fixed_steps if s in text] == []
