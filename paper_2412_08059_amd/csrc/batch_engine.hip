@@ -170,9 +170,10 @@ struct Engine {
     bool list_dirty = true;
     int32_t list_blocks = 0, list_sys = 0;
     int32_t list_max = 0;               // slices of the largest listed system
+    int64_t list_partials = 0;          // partials that the blocks' heads would read (kHeadPartials)
     // step groups captured as graphs, by (product grid, per-system grid)
     hipStream_t cap = nullptr;
-    std::map<std::tuple<int32_t, int32_t, int32_t, int32_t>, hipGraphExec_t> graphs;   // (grids, steps, dir)
+    std::map<std::tuple<int32_t, int32_t, int32_t, int32_t, int32_t>, hipGraphExec_t> graphs;   // (grids, steps, dir, heads)
     double step_ms = 0.0;         // recent wall time per step (from the copies' arrival)
     double t_last_copy = 0.0;     // when the previous group's copy was processed
     int len_k[2] = {0, 0};        // steps of the group of each copy slot
@@ -747,9 +748,11 @@ bool Engine::rebuild_list()
         if (slots[i].used && slots[i].adm == 2 && !slots[i].retiring) ids.push_back(i);
     auto blocks = [](const Slot &sl) { return (sl.nslices + kSlicesPerBlock - 1) / kSlicesPerBlock; };
     int32_t most = 0;
+    int64_t partials = 0;
     for (int32_t i : ids) {
         total += blocks(slots[i]);
         most = std::max(most, slots[i].nslices);
+        partials += (int64_t)blocks(slots[i]) * slots[i].nslices;
     }
     nsys = (int32_t)ids.size();
     int32_t pre = 0;
@@ -774,6 +777,7 @@ bool Engine::rebuild_list()
     list_blocks = total;
     list_sys = nsys;
     list_max = most;
+    list_partials = partials;
     list_dirty = false;
     return true;
 }
@@ -794,9 +798,10 @@ bool Engine::launch_group(int len)
     }
     const int32_t gblk = coarse_grid(list_blocks);
     const int32_t gsys = coarse_grid(list_sys);
+    const bool heads = list_partials <= kHeadPartials;
     if (graphs_ok) {
         const bool dir = dir_needed();
-        const auto key = std::make_tuple(gblk, gsys, (int32_t)len, (int32_t)dir);
+        const auto key = std::make_tuple(gblk, gsys, (int32_t)len, (int32_t)dir, (int32_t)heads);
         auto it = graphs.find(key);
         if (it == graphs.end()) {
             if (graphs.size() >= 64) drop_graphs();
@@ -804,7 +809,7 @@ bool Engine::launch_group(int len)
             hipGraphExec_t ex = nullptr;
             bool ok = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal) == hipSuccess;
             if (ok) {
-                launch_steps(cap, a, len, gblk, gsys, dir);
+                launch_steps(cap, a, len, gblk, gsys, dir, heads);
                 ok = hipStreamEndCapture(cap, &g) == hipSuccess && g != nullptr;
             }
             ok = ok && hipGraphInstantiate(&ex, g, nullptr, nullptr, 0) == hipSuccess;
@@ -819,7 +824,7 @@ bool Engine::launch_group(int len)
         if (graphs_ok) return hipGraphLaunch(it->second, s) == hipSuccess;
     }
     const bool dir = dir_needed();
-    launch_steps(s, a, len, gblk, gsys, dir);
+    launch_steps(s, a, len, gblk, gsys, dir, heads);
     return hipGetLastError() == hipSuccess;
 }
 

@@ -16,6 +16,8 @@
 //   the updates' partials -> gamma, stop tests, beta, v ratios: at the head of
 //                 the next step's k_b_product, after a group's last step in
 //                 k_b_close
+//   k_b_decide, k_b_close: one block per system, both decisions of a step
+//                 while large systems are listed (kHeadPartials)
 //   k_b_wg        instead of these while every listed system has at most
 //                 4,096 rows: a workgroup per system, many steps a launch
 //   k_b_bfs_*     2BFS levels of the systems whose features are pending, on a
@@ -134,7 +136,7 @@ struct BArena {
     // the step's work list, rebuilt when a system joins or leaves it
     BSys *after;                           // the systems' states between a step's product and its update
     int2 *step_map;                        // [k] = (first slice, 4 slot + slices - 1) of the k-th listed block
-    int2 *step_of;                         // [k] = (first slice, slices) of that block's system
+    int2 *step_of;                         // [k] = (first slice, slices) of that block's system; slices < 0: it is idle
     int32_t *step_sys;                     // [k] = slot of the k-th listed system
     int32_t *step_cnt;                     // [0] = listed blocks, [1] = listed systems
     int32_t acc32;                         // dot_acc = 1: FP32-phase dot products accumulate in FP32
@@ -202,7 +204,17 @@ void launch_fill_slices(hipStream_t s, const BArena &a);   // every slice unowne
 // return at once).
 void launch_worklist(hipStream_t s, const BArena &a, const ListChunk &c);
 // dir: some listed system gathers a stored direction (k_b_dir first)
-void launch_steps(hipStream_t s, const BArena &a, int32_t steps, int32_t grid_blocks, int32_t grid_sys, bool dir);
+// heads: the blocks of a launch add their system's partials of the one before
+// and take its decision themselves; else a launch of one block per system does
+void launch_steps(hipStream_t s, const BArena &a, int32_t steps, int32_t grid_blocks, int32_t grid_sys, bool dir,
+                  bool heads);
+// heads while they read at most this many partials a launch: the sum over the
+// listed systems of blocks x slices (16 bytes a partial; one system of 360,000
+// rows).  Batches of 150 FP64 iterations, ms, heads and a launch per decision:
+// 1 x 100,000 rows (0.6 M partials) 2.3 and 2.8, 4 x 100,000 (2.4 M) 3.9 and 4.5
+// (5-point grid), 1 x 350,000 (7.5 M) 5.0 and 5.0, 16 x 100,000 (9.8 M) 10.65 and
+// 10.6, 1 x 500,000 (15 M) 6.7 and 5.6, 1 x 1 M (61 M) 15.5 and 8.9.
+constexpr int64_t kHeadPartials = 8000000;
 
 // The steps of a list whose systems have at most kWgMaxSlices slices each, one
 // workgroup per system and `steps` steps a launch (max_slices: the largest).

@@ -46,19 +46,26 @@ __device__ inline double block_sum_d(double v, double *sm)
 }
 
 // The thread's chain of a system's slice partials (component j): every kBlock-th
-// in order, kSumAhead loads in flight.
+// in order, kSumAhead loads in flight; in both precisions from the same loads.
 constexpr int kSumAhead = 8;
-template <typename A> __device__ inline A slice_sum(const BArena &a, int slice0, int cnt, int j)
+struct SliceSums {
+    double f64;
+    float f32;
+};
+__device__ inline SliceSums slice_sums(const BArena &a, int slice0, int cnt, int j)
 {
     const double *p = a.pslice + 2 * (size_t)slice0 + j;
-    A acc = A(0);
+    SliceSums acc{0.0, 0.0f};
     for (int i = threadIdx.x; i < cnt; i += kSumAhead * kBlock) {
         double v[kSumAhead];
 #pragma unroll
         for (int t = 0; t < kSumAhead; ++t) v[t] = i + t * kBlock < cnt ? p[2 * (size_t)(i + t * kBlock)] : 0.0;
 #pragma unroll
         for (int t = 0; t < kSumAhead; ++t)
-            if (i + t * kBlock < cnt) acc += (A)v[t];
+            if (i + t * kBlock < cnt) {
+                acc.f64 += v[t];
+                acc.f32 += (float)v[t];
+            }
     }
     return acc;
 }
@@ -66,7 +73,7 @@ template <typename A> __device__ inline A slice_sum(const BArena &a, int slice0,
 // Sum of component j of the slice partials of system S, fixed order.
 __device__ inline double sys_sum(const BArena &a, const BSys &S, int j, double *sm)
 {
-    return block_sum_d(slice_sum<double>(a, S.slice0, S.nslices, j), sm);
+    return block_sum_d(slice_sums(a, S.slice0, S.nslices, j).f64, sm);
 }
 
 // dot_acc = 1: the FP32 phase's sums in float (partials stored widened, exact).
@@ -74,7 +81,7 @@ __device__ inline float wave_sum_f(float v) { return wave_sum_all(v); }
 
 __device__ inline double sys_sum_f(const BArena &a, const BSys &S, int j, double *sm)
 {
-    float acc = slice_sum<float>(a, S.slice0, S.nslices, j);
+    float acc = slice_sums(a, S.slice0, S.nslices, j).f32;
     acc = wave_sum_f(acc);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     if (lane == 0) sm[w] = (double)acc;
@@ -712,9 +719,19 @@ __device__ inline double residual(const BArena &a, const StepSys &S, bool restar
 // and then state and partials are loaded together (a dependent load costs 0.8
 // us, the caches being cold at a launch's start).  A launch of one block per
 // system for each decision took 4.7 us.
+//
+// Every block reading all of its system's partials is quadratic in the system's
+// slices, so it pays for small ones only: beyond kHeadPartials (batch_internal.hpp)
+// a launch of one block per system takes each decision.
+//
+// A system that is held, done or free when a group of steps begins stays so to
+// its end (only launches between groups change that).  Its blocks say so in
+// their list entry in the group's first product, and return at once in the
+// launches after it.
 struct StepBlock {
     int32_t slice, cnt;      // first slice, slices
     int32_t slot, slice0, nslices;
+    bool idle;               // as of the last product without a sum at its head
 };
 
 __device__ inline bool step_block(const BArena &a, StepBlock &b)
@@ -727,7 +744,8 @@ __device__ inline bool step_block(const BArena &a, StepBlock &b)
     b.slot = m.y >> 2;
     b.cnt = (m.y & 3) + 1;
     b.slice0 = o.x;
-    b.nslices = o.y;
+    b.idle = o.y < 0;
+    b.nslices = b.idle ? -o.y : o.y;
     return (int)blockIdx.x < n;
 }
 
@@ -749,20 +767,18 @@ __device__ inline double step_load(const BArena &a, const StepBlock &b, const BS
     const int tid = threadIdx.x;
     uint32_t *l = reinterpret_cast<uint32_t *>(&S);
     const uint32_t word = tid < kSysWords ? reinterpret_cast<const uint32_t *>(from + b.slot)[tid] : 0u;
-    double part = 0.0;
-    float part32 = 0.0f;
-    if (sum) part = slice_sum<double>(a, b.slice0, b.nslices, j);
-    if (sum && a.acc32) part32 = slice_sum<float>(a, b.slice0, b.nslices, j);
+    SliceSums part{0.0, 0.0f};
+    if (sum) part = slice_sums(a, b.slice0, b.nslices, j);
     if (tid < kSysWords) l[tid] = word;
     if (!sum) {
         __syncthreads();
         return 0.0;
     }
-    part = wave_sum_all(part);
-    if (a.acc32) part32 = wave_sum_all(part32);
+    part.f64 = wave_sum_all(part.f64);
+    if (a.acc32) part.f32 = wave_sum_all(part.f32);
     if ((tid & 63) == 0) {
-        sm[tid >> 6] = part;
-        sm[kBlock / 64 + (tid >> 6)] = (double)part32;
+        sm[tid >> 6] = part.f64;
+        sm[kBlock / 64 + (tid >> 6)] = (double)part.f32;
     }
     __syncthreads();
     double v = 0.0;
@@ -797,8 +813,10 @@ k_b_product(BArena a, int32_t head)
     __shared__ BSys state;
     __shared__ double sm[2 * kBlock / 64];
     StepBlock b;
-    if (!step_block(a, b)) return;
+    if (!step_block(a, b) || (head && b.idle)) return;
     step_begin(a, b, head != 0, state, sm);
+    if (!head && threadIdx.x == 0)
+        a.step_of[blockIdx.x].y = step_active(state.mode) || state.snap_mask ? b.nslices : -b.nslices;
     if (b.slice == b.slice0 && threadIdx.x < kSysWords)
         reinterpret_cast<uint32_t *>(a.after + b.slot)[threadIdx.x] = reinterpret_cast<uint32_t *>(&state)[threadIdx.x];
     const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -843,22 +861,29 @@ __device__ inline double cg_update(const BArena &a, const StepSys &S, T *x, T *r
     return wave_dot((double)rv, (double)rv);
 }
 
-__global__ void __launch_bounds__(kBlock) k_b_update(BArena a)
+// The decision on the sum v of the product's partials (thread 0).
+__device__ inline void step_product_end(BSys &S, double v)
+{
+    S.snap_mask = 0;   // the product of this step took the copies
+    const int mode = S.mode;
+    if (step_active(mode)) step_product_done(S, mode, v);
+}
+
+// decided: k_b_decide has taken the decision.
+__global__ void __launch_bounds__(kBlock) k_b_update(BArena a, int32_t decided)
 {
     __shared__ BSys state;
     __shared__ double sm[2 * kBlock / 64];
     StepBlock b;
-    if (!step_block(a, b)) return;
-    const double v = step_load(a, b, a.after, state, true, 0, sm);
-    if (threadIdx.x == 0) {
-        state.snap_mask = 0;   // the product of this step took the copies
-        const int mode = state.mode;
-        if (step_active(mode)) step_product_done(state, mode, v);
-    }
-    __syncthreads();
+    if (!step_block(a, b) || b.idle) return;
+    const double v = step_load(a, b, decided ? a.sys : a.after, state, !decided, 0, sm);
     const int t = threadIdx.x;
-    if (b.slice == b.slice0 && t >= kStepFrom && t < kStepTo)
-        reinterpret_cast<uint32_t *>(a.sys + b.slot)[t] = reinterpret_cast<uint32_t *>(&state)[t];
+    if (!decided) {
+        if (t == 0) step_product_end(state, v);
+        __syncthreads();
+        if (b.slice == b.slice0 && t >= kStepFrom && t < kStepTo)
+            reinterpret_cast<uint32_t *>(a.sys + b.slot)[t] = reinterpret_cast<uint32_t *>(&state)[t];
+    }
     const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
     if (!state.upd || wv >= b.cnt) return;
     const StepSys S = step_sys_of(state, a.sys[b.slot]);
@@ -869,21 +894,46 @@ __global__ void __launch_bounds__(kBlock) k_b_update(BArena a)
     if (lane == 0) a.pslice[2 * (size_t)sl + 1] = p;
 }
 
-// Block per system, after a group's last step: the update's sum and decision,
-// so that the state is complete for the host's copy.
+// Block per system: a sum and its decision, the state left complete.  Listed
+// system of the block:
+__device__ inline bool step_system(const BArena &a, StepBlock &b)
+{
+    if ((int)blockIdx.x >= a.step_cnt[1]) return false;
+    b.slot = a.step_sys[blockIdx.x];
+    b.slice0 = a.sys[b.slot].slice0;
+    b.nslices = a.sys[b.slot].nslices;
+    return true;
+}
+__device__ inline void step_store(const BArena &a, const StepBlock &b, const BSys &S)
+{
+    const int t = threadIdx.x;
+    if (t >= kStepFrom && t < kStepTo)
+        reinterpret_cast<uint32_t *>(a.sys + b.slot)[t] = reinterpret_cast<const uint32_t *>(&S)[t];
+}
+
+// The product's, between it and an update that does not take it itself.
+__global__ void __launch_bounds__(kBlock) k_b_decide(BArena a)
+{
+    __shared__ BSys S;
+    __shared__ double sm[2 * kBlock / 64];
+    StepBlock b;
+    if (!step_system(a, b)) return;
+    const double v = step_load(a, b, a.sys, S, true, 0, sm);
+    if (threadIdx.x == 0) step_product_end(S, v);
+    __syncthreads();
+    step_store(a, b, S);
+}
+
+// The update's: after a group's last step, so that the state is complete for
+// the host's copy, and after every step whose next one does not take it.
 __global__ void __launch_bounds__(kBlock) k_b_close(BArena a)
 {
     __shared__ BSys S;
     __shared__ double sm[2 * kBlock / 64];
-    if ((int)blockIdx.x >= a.step_cnt[1]) return;
     StepBlock b;
-    b.slot = a.step_sys[blockIdx.x];
-    b.slice0 = a.sys[b.slot].slice0;
-    b.nslices = a.sys[b.slot].nslices;
+    if (!step_system(a, b)) return;
     step_begin(a, b, true, S, sm);
-    const int t = threadIdx.x;
-    if (t >= kStepFrom && t < kStepTo)
-        reinterpret_cast<uint32_t *>(a.sys + b.slot)[t] = reinterpret_cast<uint32_t *>(&S)[t];
+    step_store(a, b, S);
 }
 
 // ----------------------------------------------------------------- 2BFS --
@@ -1236,7 +1286,7 @@ __global__ void __launch_bounds__(kBlock) k_b_dir(BArena a, int32_t head)
     __shared__ BSys state;
     __shared__ double sm[2 * kBlock / 64];
     StepBlock b;
-    if (!step_block(a, b)) return;
+    if (!step_block(a, b) || (head && b.idle)) return;
     if (!a.sys[b.slot].split) return;
     step_begin(a, b, head != 0, state, sm);
     const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -1248,17 +1298,19 @@ __global__ void __launch_bounds__(kBlock) k_b_dir(BArena a, int32_t head)
     else if (mode == kCg64) dir_rows<double>(S, a.r64, a.dA64, a.dB64, row);
 }
 
-void launch_steps(hipStream_t s, const BArena &a, int32_t steps, int32_t grid_blocks, int32_t grid_sys, bool dir)
+void launch_steps(hipStream_t s, const BArena &a, int32_t steps, int32_t grid_blocks, int32_t grid_sys, bool dir,
+                  bool heads)
 {
     if (steps <= 0 || grid_blocks <= 0 || grid_sys <= 0) return;
     for (int32_t j = 0; j < steps; ++j) {
-        const int32_t head = j > 0;
+        const int32_t head = heads && j > 0;
         if (dir) hipLaunchKernelGGL(k_b_dir, dim3(grid_blocks), dim3(kBlock), 0, s, a, head);
         if (a.nt) hipLaunchKernelGGL(k_b_product<true>, dim3(grid_blocks), dim3(kBlock), 0, s, a, head);
         else hipLaunchKernelGGL(k_b_product<false>, dim3(grid_blocks), dim3(kBlock), 0, s, a, head);
-        hipLaunchKernelGGL(k_b_update, dim3(grid_blocks), dim3(kBlock), 0, s, a);
+        if (!heads) hipLaunchKernelGGL(k_b_decide, dim3(grid_sys), dim3(kBlock), 0, s, a);
+        hipLaunchKernelGGL(k_b_update, dim3(grid_blocks), dim3(kBlock), 0, s, a, heads ? 0 : 1);
+        if (!heads || j == steps - 1) hipLaunchKernelGGL(k_b_close, dim3(grid_sys), dim3(kBlock), 0, s, a);
     }
-    hipLaunchKernelGGL(k_b_close, dim3(grid_sys), dim3(kBlock), 0, s, a);
 }
 
 void launch_bfs_round(hipStream_t s, const BArena &a, int32_t hi_sys, int small_levels, int small_cap,
