@@ -316,7 +316,7 @@ struct SellArgs {
     const int64_t *off;
     int32_t n, nslices;
     int32_t it, it0;
-    WalkTab walk;
+    WalkNum walk;
     const T *r;
     T *dA, *dB, *q;
     const double *up;
@@ -563,7 +563,7 @@ static SellArgs<T> sell_args(const SellMat &m, const T *sval)
 {
     SellArgs<T> a{};
     a.rp = m.rp; a.scol = m.scol; a.sval = sval; a.off = m.off; a.n = m.n; a.nslices = m.nslices;
-    a.walk = walk_tab(m.nslices, m.grid);
+    a.walk = walk_num(m.nslices, m.grid);
     return a;
 }
 

@@ -152,6 +152,30 @@ struct WalkTab {
 };
 WalkTab walk_tab(int32_t nslices, int32_t grid);
 
+// The same ranges as a few numbers: floor(before * ngroups / grid), with before
+// blocks on the XCDs below, is before * q + floor(before * r / grid), and that
+// quotient (before and r below grid <= kMaxGrid, so 22 bits) is one multiply by
+// inv and at most one correction.
+struct WalkNum {
+    int32_t q, r;         // groups of slices: q grid + r
+    int32_t grid, per, rem;   // blocks: per on each XCD, one more on the first rem
+    uint32_t inv;         // floor((2^32 - 1) / grid)
+};
+inline WalkNum walk_num(int32_t nslices, int32_t grid)
+{
+    const int32_t ngroups = (int32_t)(((int64_t)nslices + kBlock / 64 - 1) / (kBlock / 64));
+    return {ngroups / grid, ngroups % grid, grid, grid / kNumXcd, grid % kNumXcd, 0xffffffffu / (uint32_t)grid};
+}
+__host__ __device__ inline int32_t walk_blocks(const WalkNum &t, int32_t xcd) { return t.per + (xcd < t.rem ? 1 : 0); }
+__host__ __device__ inline int32_t walk_first(const WalkNum &t, int32_t xcd)
+{
+    const int32_t before = xcd * t.per + (xcd < t.rem ? xcd : t.rem);
+    const uint32_t n = (uint32_t)before * (uint32_t)t.r;
+    uint32_t d = (uint32_t)(((uint64_t)n * t.inv) >> 32);
+    if (n - d * (uint32_t)t.grid >= (uint32_t)t.grid) ++d;
+    return before * t.q + (int32_t)d;
+}
+
 // SELL-64 copy of A (kernels_sell.hip): slices of 64 rows, entries of a slice
 // stored column-major, 16-bit column offsets when the bandwidth allows.
 struct SellMat {

@@ -183,15 +183,17 @@ __device__ inline void record_crossings(DevState *st, unsigned cross, int it, do
 }
 
 // Slice groups (kBlock / 64 slices, one per wave) of an XCD's contiguous
-// range are dealt round-robin to that XCD's blocks: at any moment the blocks
-// of one XCD work on a narrow window of consecutive rows, so the rows that a
-// stencil's neighbour planes gather are still in that XCD's L2.  The ranges
-// (in proportion to each XCD's blocks) come from the host with the launch: two
+// range (in proportion to its blocks) are dealt round-robin to that XCD's
+// blocks: at any moment the blocks of one XCD work on a narrow window of
+// consecutive rows, so the rows that a stencil's neighbour planes gather are
+// still in that XCD's L2.  The ranges come from the host with the launch: two
 // 64-bit divisions per wave are several hundred scalar instructions.
 struct SliceWalk {
     int g, g_end, step;   // group index, end, stride
 };
 
+// As a table: diagonal storage and the Jacobi iterations (FP64 CG product of the
+// 1 M band 19.0 us; 22.0 with the divisions, 21.4 with the numbers below).
 __device__ inline SliceWalk slice_walk(const WalkTab &t)
 {
     const int x = blockIdx.x % kNumXcd, i = blockIdx.x / kNumXcd;
@@ -199,6 +201,22 @@ __device__ inline SliceWalk slice_walk(const WalkTab &t)
     w.g = t.first[x] + i;
     w.g_end = t.first[x + 1];
     w.step = t.blocks[x];
+    return w;
+}
+
+// As numbers: the SELL products, which lose by reading the table at the block's
+// index, however early.  CG products, us with the table, read first, and with
+// the numbers: FP64 7-point 128^3 43.8, 42.7, 41.1; 19-point 100^3 45.7, 44.1,
+// 42.5; 1 M rows of half-width 9 45.9, 44.0, 42.3; 5-point 1001^2 20.9, 20.2,
+// 19.5; FP32 of these 24.6 to 13.5, 24.1 to 13.1, 23.4 to 12.7.  (One loses: the
+// unsplit product of a random graph of 1 M rows, 420 and 431.)
+__device__ inline SliceWalk slice_walk(const WalkNum &t)
+{
+    const int x = blockIdx.x % kNumXcd, i = blockIdx.x / kNumXcd;
+    SliceWalk w;
+    w.g = walk_first(t, x) + i;
+    w.g_end = walk_first(t, x + 1);
+    w.step = walk_blocks(t, x);
     return w;
 }
 
