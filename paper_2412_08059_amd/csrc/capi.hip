@@ -266,6 +266,7 @@ struct Plan {
     bool use_sell = false, use_ds = false;   // at most one; neither: CSR
     bool use_wg = false;                     // CG iterations in one workgroup
     int32_t max_row = 0;                     // longest row
+    bool many = false;                       // a sample of its rows holds more than kDsMax distances
     int nup = 1;
     mpcg_tuning tune{};   // scheduling parameters resolved for this matrix
     char *ws = nullptr;
@@ -381,6 +382,7 @@ mpcg_status ingest(mpcg_ctx *c, const mpcg_csr *A, const double *b, bool need_va
     p->sh32 = spmv_shape(A->n, A->nnz, 4, c->num_cu);
     // small systems: unpreconditioned, FP64-accumulated dots, no explicit variant
     p->max_row = s.max_row;
+    p->many = s.ds_many != 0;
     p->use_wg = (p->use_ds || p->use_sell) && wg_fits(A->n, s.max_row) && !want_diag && c->opt.dot_acc == 0 &&
                 c->opt.spmv_variant == 0;
     p->nup = vec_grid(A->n);
@@ -676,6 +678,11 @@ mpcg_status dia_prepare(const Chan &ch, const Plan &p, BfsBufs *bb)
     if (mode == 0 || p.n >= (1 << 30) - 64 ||
         (mode == 1 && (p.band <= 8 || p.n < (small ? kDiaBlockMinRows : 1 << 16))))
         return MPCG_OK;
+    // Looking for the diagonals of a pattern that has none takes 0.1 ms, as long
+    // as a small graph's whole sweep (us, with and without, one BFS of random
+    // graphs: 1,000 rows 270 and 150, 20,000 rows 315 and 190): not where the
+    // ingest's sample has already seen too many distances.
+    if (mode == 1 && p.n < (1 << 16) && p.many) return MPCG_OK;
     DiaOffs &o = bb->doff;
     o.nd = 0;
     if (p.use_ds) {   // diagonal storage knows the distances

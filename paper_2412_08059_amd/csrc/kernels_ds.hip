@@ -46,7 +46,7 @@ struct DsSample {
     int32_t far[kDsMax], misfit;
 };
 __device__ inline void ds_sample(int lo, int hi, int64_t i, const int32_t *col, int32_t n, int64_t nnz, int64_t cap,
-                                 DevState *st, DsSample *sm)
+                                 int ds, DevState *st, DsSample *sm)
 {
     // (lo, hi): the sampled row's entries, none for a thread without a row
     const int j = threadIdx.x % kDsRowMax;
@@ -71,7 +71,11 @@ __device__ inline void ds_sample(int lo, int hi, int64_t i, const int32_t *col, 
     int nh = nnear, nfar = 0;
     while (nfar < kDsMax && sm->far[nfar]) ++nfar;
     nh += nfar;
-    if (sm->misfit || nh == 0 || nh > kDsMax) return;
+    if (sm->misfit || nh > kDsMax) {
+        st->ds_many = 1;
+        return;
+    }
+    if (!ds || nh == 0) return;
     // Worth it when at least two thirds of the diagonals' places hold an
     // entry: each place costs a gather whether or not it does.
     if ((int64_t)(2 * nh + 1) * n * 2 > 3 * nnz || (int64_t)(nh + 1) * ds_stride(n) > cap) return;
@@ -91,9 +95,9 @@ __device__ inline void ds_sample(int lo, int hi, int64_t i, const int32_t *col, 
 }
 
 // One block after k_ingest_rows: clears the device state, folds the blocks'
-// statistics into it, samples the distances if ds (and the row pointers are
-// usable), and unless diagonal storage takes the matrix forms the SELL slice
-// offsets (exclusive scan of the padded slice sizes).
+// statistics into it, samples the distances (if the row pointers are usable;
+// for diagonal storage if ds), and unless diagonal storage takes the matrix
+// forms the SELL slice offsets (exclusive scan of the padded slice sizes).
 __global__ void __launch_bounds__(1024)
 k_ingest_fold(const int32_t *blk, int32_t nblk, const int32_t *rp, const int32_t *col, int32_t n, int64_t nnz,
               const int64_t *wid, int64_t *off, int64_t cap, int ds, DevState *st)
@@ -108,7 +112,7 @@ k_ingest_fold(const int32_t *blk, int32_t nblk, const int32_t *rp, const int32_t
     const int64_t step = ((int64_t)n + kDsSample - 1) / kDsSample;
     const int r = t / kDsRowMax;
     const int64_t row = (int64_t)r * step + (r * 2654435761u >> 7) % (uint64_t)step;
-    const bool has = ds && r < kDsSample && row < n;
+    const bool has = r < kDsSample && row < n;
     const int rlo = has ? rp[row] : 0, rhi = has ? rp[row + 1] : 0;
     int e = 0, l = 0, bd = 0;
     for (int i = t; i < nblk; i += 1024) {
@@ -139,7 +143,7 @@ k_ingest_fold(const int32_t *blk, int32_t nblk, const int32_t *rp, const int32_t
         st->max_row = l;
         st->max_band = bd;
     }
-    if (ds && !(e & kErrRowPtr)) ds_sample(rlo, rhi, row, col, n, nnz, cap, st, &smp);   // ds_cand is 0 otherwise
+    if (!(e & kErrRowPtr)) ds_sample(rlo, rhi, row, col, n, nnz, cap, ds, st, &smp);   // ds_cand is 0 otherwise
     if (t == 0) cand = st->ds_cand;
     __syncthreads();
     if (cand) return;

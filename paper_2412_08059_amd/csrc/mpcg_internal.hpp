@@ -110,6 +110,7 @@ struct alignas(256) DevState {
     // Diagonal storage (kernels_ds.hip): the sampled distances, ascending, and
     // whether the entries' pass found others or an unsymmetric pair.
     int32_t ds_cand, ds_miss, ds_nh;
+    int32_t ds_many;      // the sampled rows hold more than kDsMax distances
     int32_t ds_d[8];
     int64_t sell_total;   // padded SELL entries (if the offsets were formed)
 };
@@ -246,8 +247,8 @@ __device__ inline unsigned spec_crossings(DevState *st, int it, double g)
 // when its padded size fits in `cap` entries (see kernels_sell.hip).
 // launch_ingest_rows: row pointers, b, row lengths, slice widths, statistics
 // per block.  launch_ingest_fold, after it: clears st, the statistics into it,
-// with ds the sampled distances, and unless st->ds_cand says that the diagonal
-// storage takes the matrix the slice offsets.  launch_ingest_sell, after that:
+// whether a sample of rows holds few distances, with ds these, and unless
+// st->ds_cand says that the diagonal storage takes the matrix the slice offsets.  launch_ingest_sell, after that:
 // the entries (nothing while st->ds_cand).
 void launch_ingest_rows(hipStream_t s, const void *rp_in, int rp_is_i64, int32_t *rp32_out, const int32_t *col,
                         const double *b, int32_t n, int64_t nnz, int64_t *wid, int32_t *blk);

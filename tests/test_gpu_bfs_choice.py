@@ -1,0 +1,98 @@
+"""The 2BFS path that a matrix gets by default: the integers of the oracle's BFS
+at the edges of the rule, and no slower than the better of the two paths that
+the tuning can force."""
+
+import time
+
+import numpy as np
+import pytest
+import scipy.sparse as sp
+
+import oracle
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _offsets(n, offs, keep=None):
+    """Symmetric pattern on the distances offs (keep: share of the pairs kept)."""
+    rng = np.random.default_rng(n)
+    i = np.concatenate([np.arange(n - d) for d in offs])
+    j = np.concatenate([np.arange(d, n) for d in offs])
+    if keep is not None:
+        m = rng.random(len(i)) < keep
+        i, j = i[m], j[m]
+    a = sp.coo_matrix((-np.ones(len(i)), (i, j)), shape=(n, n))
+    a = a + a.T
+    return W.CSR.from_scipy((a + sp.diags(np.asarray(-a.sum(axis=1)).ravel() + 0.1)).tocsr())
+
+
+def _grid(w, length):
+    n = w * length
+    i = np.arange(n)
+    right, up = i[i % w != w - 1], i[: n - w]
+    r, c = np.concatenate([right, up]), np.concatenate([right + 1, up + w])
+    a = sp.coo_matrix((-np.ones(len(r)), (r, c)), shape=(n, n))
+    a = a + a.T
+    return W.CSR.from_scipy((a + sp.diags(np.asarray(-a.sum(axis=1)).ravel() + 0.1)).tocsr())
+
+
+@pytest.mark.parametrize("n", [64, 1000, 65535, 65536])
+@pytest.mark.parametrize("name,offs,keep", [
+    ("eight_distances", [1, 2, 3, 4, 5, 6, 7, 31], None), ("nine_distances", [1, 2, 3, 4, 5, 6, 7, 8, 31], None),
+    ("far", [1, 33, 35, 37, 39, 41, 43, 45, 47, 49], 0.9), ("sparse", [1, 40], 0.6),
+])
+def test_bfs_is_the_oracles(n, name, offs, keep):
+    import torch
+    from paper_2412_08059_amd import DeviceCSR, Solver
+    a = _offsets(n, offs, keep)
+    s = Solver(a.n, a.nnz)
+    try:
+        dev = DeviceCSR.from_host(a)
+        for src in (0, n // 2, n - 1):
+            st, dist, ecc, far = s.bfs(dev, src)
+            want = oracle.bfs(a, src)[0]
+            assert st == 0
+            assert np.array_equal(dist.cpu().numpy(), want)
+            assert (ecc, far) == (want.max(), int(np.argmax(want)))   # the smallest vertex at that distance
+        st, f = s.features(dev, torch.ones(n, dtype=torch.float64, device="cuda"))
+        assert st == 0
+        assert (f.pdiam, f.bfs_t, f.bfs_u, f.n_components) == oracle.pseudo_diameter(a)
+    finally:
+        s.close()
+
+
+GRAPHS = {
+    "random_1000": lambda: W.er_laplacian(1000, 16, seed=1),
+    "random_20000": lambda: W.er_laplacian(20000, 16, seed=2),
+    "grid_100": lambda: W.poisson2d(100),
+}
+
+
+@pytest.mark.parametrize("name", sorted(GRAPHS))
+def test_default_is_the_faster_path(name):
+    """Least of 30 calls each, forced paths and default in turn; the default may
+    take a quarter more than the better one (calls of a fixed kind differ by
+    under a tenth)."""
+    import torch
+    from paper_2412_08059_amd import DeviceCSR, Solver
+    a = GRAPHS[name]()
+    dev = DeviceCSR.from_host(a)
+    band = int(np.abs(np.repeat(np.arange(a.n), np.diff(a.row_ptr)) - a.col).max())
+    solvers = {}
+    for key, dia in (("default", None), ("queue", 0), ("diagonals", 2)):
+        s = solvers[key] = Solver(a.n, a.nnz)
+        if dia is not None:
+            s.set_tuning({**s.tuning_for(a.n, a.nnz, band), "bfs_dia": dia})
+    best = dict.fromkeys(solvers, np.inf)
+    for _ in range(30):
+        for key, s in solvers.items():
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            st, _, _, _ = s.bfs(dev, 0)
+            best[key] = min(best[key], time.perf_counter() - t0)
+            assert st == 0
+    for s in solvers.values():
+        s.close()
+    print(f"  {name}: " + ", ".join(f"{k} {1e6 * v:.0f} us" for k, v in best.items()), flush=True)
+    assert best["default"] <= 1.25 * min(best["queue"], best["diagonals"])
