@@ -346,7 +346,7 @@ mpcg_status ingest(mpcg_ctx *c, const mpcg_csr *A, const double *b, bool need_va
     const bool try_ds = want_copy && c->opt.spmv_variant == 0 && A->nnz <= (2 * kDsMax + 1) * A->n;
     int32_t *blk = p->at<int32_t>(p->L.ingest_blk);
     launch_ingest_rows(c->stream, A->row_ptr, A->row_ptr_is_i64 ? 1 : 0, rp32, A->col_idx, b, p->n, A->nnz, wid, blk);
-    launch_ingest_fold(c->stream, blk, p->rp, A->col_idx, p->n, A->nnz, wid, soff, p->L.sell_cap, try_ds, p->st);
+    launch_ingest_fold(c->stream, blk, p->rp, A->col_idx, A->val, p->n, A->nnz, wid, soff, p->L.sell_cap, try_ds, p->st);
     if (try_ds)
         launch_ds_ingest(c->stream, p->rp, A->col_idx, A->val, p->n, v64, v32, want_diag ? p->dg64 : nullptr,
                          want_diag ? p->dg32 : nullptr, p->st);
@@ -365,7 +365,7 @@ mpcg_status ingest(mpcg_ctx *c, const mpcg_csr *A, const double *b, bool need_va
     mpcg_status rc = verdict();
     if (rc != MPCG_OK) return rc;
     if (c->hst[1].ds_cand && c->hst[1].ds_miss) {   // other diagonals, not symmetric, or malformed
-        launch_ingest_fold(c->stream, blk, p->rp, A->col_idx, p->n, A->nnz, wid, soff, p->L.sell_cap, 0, p->st);
+        launch_ingest_fold(c->stream, blk, p->rp, A->col_idx, A->val, p->n, A->nnz, wid, soff, p->L.sell_cap, 0, p->st);
         general();
         rc = verdict();
         if (rc != MPCG_OK) return rc;

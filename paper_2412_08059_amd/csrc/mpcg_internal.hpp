@@ -252,8 +252,8 @@ __device__ inline unsigned spec_crossings(DevState *st, int it, double g)
 // the entries (nothing while st->ds_cand).
 void launch_ingest_rows(hipStream_t s, const void *rp_in, int rp_is_i64, int32_t *rp32_out, const int32_t *col,
                         const double *b, int32_t n, int64_t nnz, int64_t *wid, int32_t *blk);
-void launch_ingest_fold(hipStream_t s, const int32_t *blk, const int32_t *rp, const int32_t *col, int32_t n,
-                        int64_t nnz, const int64_t *wid, int64_t *off, int64_t cap, int ds, DevState *st);
+void launch_ingest_fold(hipStream_t s, const int32_t *blk, const int32_t *rp, const int32_t *col, const double *val,
+                        int32_t n, int64_t nnz, const int64_t *wid, int64_t *off, int64_t cap, int ds, DevState *st);
 void launch_ingest_sell(hipStream_t s, const int32_t *rp32, const int32_t *col, const double *val, int32_t n,
                         const int64_t *off, int64_t cap, int allow_fill, void *scol, double *sv64, float *sv32,
                         DevState *st);
