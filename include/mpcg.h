@@ -303,7 +303,8 @@ typedef struct {
     int32_t bfs_dia;             /* 2BFS sweeps as bit-parallel levels over the diagonals when the
                                     pattern lies on at most 16 of them: 0 never, 1 when the pattern is
                                     wider than |i - j| <= 8 and has at least 64 rows (2^16 with
-                                    bfs_dia_tiles 0), 2 whenever it qualifies */
+                                    bfs_dia_tiles 0), and above 65,536 rows wider than |i - j| <= 22;
+                                    2 whenever it qualifies */
     int32_t bfs_dia_tiles;       /* with bfs_dia: 1 = several levels per launch (one block runs them
                                     all while its LDS holds every row's bits; else a block forms them
                                     on its own words plus a halo that the levels consume: up to 16

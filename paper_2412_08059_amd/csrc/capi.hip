@@ -244,6 +244,17 @@ namespace {
 // 683 and 1,035 / 684)
 constexpr int64_t kSegMinRows = 6144;
 constexpr int32_t kDiaBlockMinRows = 64;
+// Long thin graphs stay with the queue kernels: a grid w rows wide has frontiers
+// of w vertices within w^2 indices, and while these and a margin of w on both
+// sides fit a quarter of the one-workgroup kernel's window (2,048 rows) a level
+// takes it 0.9 us.  Up to kThinRows rows (two words a thread) one block's
+// bit-parallel levels take 0.5 to 0.7, above them those or the tiles' 1.1 to 1.2.
+// Features, ms, queue and bits: 9 wide, 60,000 rows 12.1 and 9.0, 70,000 13.9 and
+// 18.1, 1 M 195 and 244; 22 wide, 400,000 33.5 and 40.8; 23 wide (beyond the window)
+// 53.5 and 39.1; 24 wide,
+// 70,000 8.9 and 7.0, 1 M 129 and 93.
+constexpr int32_t kThinBand = 22;
+constexpr int64_t kThinRows = 65536;
 
 struct Plan {
     Layout L;
@@ -683,6 +694,7 @@ mpcg_status dia_prepare(const Chan &ch, const Plan &p, BfsBufs *bb)
     // graphs: 1,000 rows 270 and 150, 20,000 rows 315 and 190): not where the
     // ingest's sample has already seen too many distances.
     if (mode == 1 && p.n < (1 << 16) && p.many) return MPCG_OK;
+    if (mode == 1 && p.band <= kThinBand && p.n > kThinRows) return MPCG_OK;
     DiaOffs &o = bb->doff;
     o.nd = 0;
     if (p.use_ds) {   // diagonal storage knows the distances

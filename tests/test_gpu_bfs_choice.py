@@ -66,14 +66,20 @@ GRAPHS = {
     "random_1000": lambda: W.er_laplacian(1000, 16, seed=1),
     "random_20000": lambda: W.er_laplacian(20000, 16, seed=2),
     "grid_100": lambda: W.poisson2d(100),
+    "thin_9x7000": lambda: _grid(9, 7000),        # one block's bits
+    "thin_9x9000": lambda: _grid(9, 9000),        # the queue kernel's window
+    "thin_20x15000": lambda: _grid(20, 15000),
+    "thin_24x12500": lambda: _grid(24, 12500),    # tiles
+    "thin_10x60000": lambda: _grid(10, 60000),
 }
 
 
 @pytest.mark.parametrize("name", sorted(GRAPHS))
 def test_default_is_the_faster_path(name):
-    """Least of 30 calls each, forced paths and default in turn; the default may
-    take a quarter more than the better one (calls of a fixed kind differ by
-    under a tenth)."""
+    """Least of 30 calls each (4 of the long ones), forced paths and default in
+    turn; the default may take a quarter more than the better one, on the thin
+    grids an eighth (calls of a fixed kind differ by under a tenth, long ones
+    by under a hundredth)."""
     import torch
     from paper_2412_08059_amd import DeviceCSR, Solver
     a = GRAPHS[name]()
@@ -85,7 +91,7 @@ def test_default_is_the_faster_path(name):
         if dia is not None:
             s.set_tuning({**s.tuning_for(a.n, a.nnz, band), "bfs_dia": dia})
     best = dict.fromkeys(solvers, np.inf)
-    for _ in range(30):
+    for _ in range(4 if name.startswith("thin") else 30):
         for key, s in solvers.items():
             torch.cuda.synchronize()
             t0 = time.perf_counter()
@@ -95,4 +101,4 @@ def test_default_is_the_faster_path(name):
     for s in solvers.values():
         s.close()
     print(f"  {name}: " + ", ".join(f"{k} {1e6 * v:.0f} us" for k, v in best.items()), flush=True)
-    assert best["default"] <= 1.25 * min(best["queue"], best["diagonals"])
+    assert best["default"] <= (1.125 if name.startswith("thin") else 1.25) * min(best["queue"], best["diagonals"])
