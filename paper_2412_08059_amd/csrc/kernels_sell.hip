@@ -193,6 +193,17 @@ void launch_ingest_sell(hipStream_t s, const int32_t *rp32, const int32_t *col, 
 // A chunk is one batch of loads: its LDS lets 24 waves share a CU.
 constexpr int kChkBatch = 5;                    // loads of a lane issued together
 constexpr int kChkEntries = 64 * kChkBatch;
+// Long rows of like length in a matrix that leaves most of the chip idle: a
+// chunk of 320 entries holds only a few rows, whose lanes run long chains while
+// the others wait; there each lane loads its own row's entries instead, eight
+// at a time.  The loads are not coalesced, so with more slices than waves on
+// the chip the chunks win.  FP64 calls, us, chunks and lanes (checks, copy and
+// product before the checked pass): 2,000 rows of 146 entries 264, 67 (189), of
+// 788 2,419, 217 (1,083); 20,000 of 49 63, 48 (124), of 299 798, 202 (529); 65,536
+// of 49 66, 68 (129), of 97 121, 98 (234); 131,072 of 97 137, 193 (684).
+constexpr int kChkLong = 48;                    // entries of the longest row
+constexpr int kChkLongSlices = 1024;            // slices: a wave on each SIMD
+constexpr int kChkLongBatch = 8;
 
 template <typename T>
 __global__ void __launch_bounds__(kBlock)
@@ -229,6 +240,40 @@ k_spmv_checked(const void *rp_in, int rp_is_i64, const int32_t *__restrict__ col
         const int rlo = (int)lo, rhi = (int)hi;
         T acc = T(0);
         int prev = -1;
+        const int len = rhi - rlo, most = wave_fold(len, [](int p, int q) { return p > q ? p : q; });
+        // unlike lengths: a lane's walk of the longest takes longer than the chunks
+        if (most >= kChkLong && nslices <= kChkLongSlices && (b1 - b0) / 8 >= most) {
+            for (int k0 = 0; k0 < most; k0 += kChkLongBatch) {
+                int c[kChkLongBatch];
+                double v[kChkLongBatch];
+                T g[kChkLongBatch];
+#pragma unroll
+                for (int j = 0; j < kChkLongBatch; ++j) {
+                    c[j] = 0;
+                    v[j] = 0.0;
+                    if (k0 + j < len) {
+                        c[j] = col[rlo + k0 + j];
+                        v[j] = val[rlo + k0 + j];
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < kChkLongBatch; ++j) {
+                    const bool in = c[j] >= 0 && c[j] < n;
+                    if (!in) err |= kErrCol;
+                    if (!isfinite(v[j])) err |= kErrNonFiniteA;
+                    g[j] = x[in ? c[j] : 0];
+                }
+#pragma unroll
+                for (int j = 0; j < kChkLongBatch; ++j)
+                    if (k0 + j < len) {
+                        if (c[j] <= prev) err |= kErrUnsorted;
+                        prev = c[j];
+                        acc = fma_t<T>((T)v[j], g[j], acc);
+                    }
+            }
+            if (row < n) y[row] = acc;
+            continue;
+        }
         for (int c0 = b0, cn; (cn = chunk_len(c0, b1, kChkEntries)) > 0; c0 += cn) {
             int c[kChkBatch];
             double v[kChkBatch];
