@@ -22,8 +22,9 @@
 // the state it then restarts from is the one the sequential method stops in,
 // so its arithmetic does not depend on that pace.  While any system is being
 // admitted or waits for features, groups are shortened to a few ms.
-// While every listed system has at most kWgMaxSlices slices, a group is one
-// launch in which each advances in a workgroup of its own.
+// While every listed system has at most kWgMaxSlices slices (and not too many
+// entries, wg_max_entries), a group is one launch in which each advances in a
+// workgroup of its own.
 
 #include "batch_internal.hpp"
 #include "knn.hpp"
@@ -170,6 +171,7 @@ struct Engine {
     bool list_dirty = true;
     int32_t list_blocks = 0, list_sys = 0;
     int32_t list_max = 0;               // slices of the largest listed system
+    int64_t list_entries = 0;           // most entries of a listed system
     int64_t list_partials = 0;          // partials that the blocks' heads would read (kHeadPartials)
     // step groups captured as graphs, by (product grid, per-system grid)
     hipStream_t cap = nullptr;
@@ -204,6 +206,7 @@ struct Engine {
     bool step_once();
     bool rebuild_list();
     bool launch_group(int len);
+    bool wg_form() const;
     bool dir_needed() const;
     bool band_pump();
     void process_band(const BSys *m, int32_t cnt);
@@ -748,10 +751,11 @@ bool Engine::rebuild_list()
         if (slots[i].used && slots[i].adm == 2 && !slots[i].retiring) ids.push_back(i);
     auto blocks = [](const Slot &sl) { return (sl.nslices + kSlicesPerBlock - 1) / kSlicesPerBlock; };
     int32_t most = 0;
-    int64_t partials = 0;
+    int64_t partials = 0, entries = 0;
     for (int32_t i : ids) {
         total += blocks(slots[i]);
         most = std::max(most, slots[i].nslices);
+        entries = std::max(entries, slots[i].padded);
         partials += (int64_t)blocks(slots[i]) * slots[i].nslices;
     }
     nsys = (int32_t)ids.size();
@@ -777,6 +781,7 @@ bool Engine::rebuild_list()
     list_blocks = total;
     list_sys = nsys;
     list_max = most;
+    list_entries = entries;
     list_partials = partials;
     list_dirty = false;
     return true;
@@ -788,11 +793,17 @@ void Engine::drop_graphs()
     graphs.clear();
 }
 
+// Small systems only: each advances in a workgroup of its own.
+bool Engine::wg_form() const
+{
+    return list_max <= kWgMaxSlices && list_entries <= wg_max_entries(list_sys, list_max);
+}
+
 // One group of steps: a graph replay when the group is captured (once per
 // set of grid sizes and kernels), else plain launches.
 bool Engine::launch_group(int len)
 {
-    if (list_max <= kWgMaxSlices) {   // small systems only: each advances in a workgroup of its own
+    if (wg_form()) {
         launch_wg_steps(s, a, list_sys, list_max, kWgSteps);
         return hipGetLastError() == hipSuccess;
     }
@@ -893,7 +904,7 @@ bool Engine::step_once()
     const int k = (int)(group & 1);
     if (list_dirty && !rebuild_list()) return false;
     const int len = group_len();
-    len_k[k] = any_live && list_sys > 0 && list_max > kWgMaxSlices ? len : 0;   // one-workgroup steps are not timed
+    len_k[k] = any_live && list_sys > 0 && !wg_form() ? len : 0;   // one-workgroup steps are not timed
     if (any_live && list_sys > 0 && !launch_group(len)) return false;
     if (hipGetLastError() != hipSuccess) return false;
     mirror_n[k] = hi_sys;

@@ -218,11 +218,24 @@ constexpr int64_t kHeadPartials = 8000000;
 
 // The steps of a list whose systems have at most kWgMaxSlices slices each, one
 // workgroup per system and `steps` steps a launch (max_slices: the largest).
-// Beside a larger system the small ones ride in its steps instead, where they
-// cost little; a launch lasts 0.1 to 0.3 ms, the latency the host sees.
+// Beside a larger system the small ones ride in its steps instead (512 trees of
+// 1,000 rows 5.7 ms, with a 65^2 grid 12.3); a launch lasts 0.1 to 0.3 ms, the
+// latency the host sees.
 constexpr int kWgMaxSlices = 64;
 constexpr int kWgSteps = 64;
 void launch_wg_steps(hipStream_t s, const BArena &a, int32_t nsys, int32_t max_slices, int32_t steps);
+// One workgroup reads its matrix alone, so the most entries (padded) that a
+// listed system may have there depend on the rows per thread; with more systems
+// the launches over all slices have more to do as well.  200 FP64 iterations, ms,
+// launches and workgroups: 1 system of 4,096 rows and 69 k entries 2.8 and 2.8,
+// 102 k 3.4 and 3.9, 413 k 3.9 and 8.9; of 2,000 rows and 204 k 2.8 and 2.8, 402 k 2.8
+// and 3.9; of 1,000 rows and 377 k 2.8 and 2.8; 64 systems of 3,000 rows and 303 k 6.3
+// and 6.2, of 4,096 rows and 413 k 11.8 and 12.9, of 2,000 rows and 402 k 5.1 and 5.7.
+inline int64_t wg_max_entries(int32_t nsys, int32_t max_slices)
+{
+    const int64_t base = max_slices <= 16 ? 400000 : max_slices <= 32 ? 200000 : 80000;
+    return base + 2000 * (int64_t)nsys;
+}
 
 // ---- 2BFS (BFS stream) ----
 // Kernels on the BFS stream write only the BFS fields of a system's state
