@@ -74,7 +74,8 @@ def format_bytes(kind: str, a) -> float:
     SELL-64: every padded entry's value and stored column (16-bit offsets when
     the band allows, else 32-bit), the row pointers the slices read their
     lengths from and the slice offsets; padded entries: 64 x the longest row of
-    each 64-row slice."""
+    each 64-row slice.  The plain product (mpcg_spmv) passes over the CSR arrays
+    themselves, FP64 values in either precision."""
     import numpy as np
     s = 8 if kind.endswith("64") else 4
     n = a.n
@@ -96,7 +97,7 @@ def format_bytes(kind: str, a) -> float:
         return 3 * s * n
     if kind.startswith("jacobi"):
         return mat + (3 if diagonals else 4) * s * n
-    return mat + 2 * s * n
+    return 12 * a.nnz + 4 * (n + 1) + 2 * s * n
 
 
 def _host_info():

@@ -352,7 +352,8 @@ mpcg_status mpcg_last_kernel_ms(const mpcg_ctx *ctx, double *ms);
 #define MPCG_KERNEL_CG_SPMV_F32 1   /* the same on float32(A), FP32 vectors */
 #define MPCG_KERNEL_UPDATE_F64 2    /* alpha, r -= alpha q, r.r; FP64 */
 #define MPCG_KERNEL_UPDATE_F32 3
-#define MPCG_KERNEL_SPMV_F64 4      /* plain y = A x (mpcg_spmv) */
+#define MPCG_KERNEL_SPMV_F64 4      /* plain y = A x (mpcg_spmv; with spmv_variant 0 its checked pass over
+                                       the CSR arrays, without the copy of the result to y) */
 #define MPCG_KERNEL_SPMV_F32 5
 #define MPCG_KERNEL_JACOBI_F64 6    /* one Jacobi iteration of mpcg_solve_jacobi (residual + update), FP64 */
 #define MPCG_KERNEL_JACOBI_F32 7

@@ -520,9 +520,15 @@ void run_resid(hipStream_t s, const Plan &p, const double *x, const double *b)
 template <typename T>
 void run_plain(hipStream_t s, const Plan &p, const T *x, T *y)
 {
-    if (p.use_ds) launch_ds_plain<T>(s, p.ds, p.sell.grid, x, y);
-    else if (p.use_sell) launch_sell_plain<T>(s, p.sell, x, y);
+    if (p.use_sell) launch_sell_plain<T>(s, p.sell, x, y);
     else launch_spmv_plain<T>(s, csr_shape<T>(p), p.rp, p.col, csr_vals<T>(p), x, y);
+}
+
+// The checked product of mpcg_spmv, spmv_variant 0.
+template <typename T>
+void run_checked(hipStream_t s, const mpcg_csr &A, const T *x, T *y, DevState *st)
+{
+    launch_spmv_checked<T>(s, A.row_ptr, A.row_ptr_is_i64 ? 1 : 0, A.col_idx, A.val, (int32_t)A.n, A.nnz, x, y, st);
 }
 
 int poll_iters(const mpcg_ctx *c) { return c->opt.graph_iters > 0 ? c->opt.graph_iters : 8; }
@@ -1437,14 +1443,15 @@ mpcg_status mpcg_spmv(mpcg_ctx *c, const mpcg_csr *A, int32_t precision, const v
         DevState *st = reinterpret_cast<DevState *>(c->ws + L.state);
         HIPCHK(hipMemsetAsync(st, 0, sizeof(DevState), c->stream));
         HIPCHK(hipEventRecord(c->tm[5], c->stream));
-        if (precision == 64)
-            launch_spmv_checked<double>(c->stream, A->row_ptr, A->row_ptr_is_i64 ? 1 : 0, A->col_idx, A->val,
-                                        (int32_t)A->n, A->nnz, static_cast<const double *>(x),
-                                        reinterpret_cast<double *>(c->ws + L.q64), static_cast<double *>(y), st);
-        else
-            launch_spmv_checked<float>(c->stream, A->row_ptr, A->row_ptr_is_i64 ? 1 : 0, A->col_idx, A->val,
-                                       (int32_t)A->n, A->nnz, static_cast<const float *>(x),
-                                       reinterpret_cast<float *>(c->ws + L.q32), static_cast<float *>(y), st);
+        double *s64 = reinterpret_cast<double *>(c->ws + L.q64);
+        float *s32 = reinterpret_cast<float *>(c->ws + L.q32);
+        if (precision == 64) {
+            run_checked<double>(c->stream, *A, static_cast<const double *>(x), s64, st);
+            launch_spmv_commit<double>(c->stream, s64, static_cast<double *>(y), (int32_t)A->n, st);
+        } else {
+            run_checked<float>(c->stream, *A, static_cast<const float *>(x), s32, st);
+            launch_spmv_commit<float>(c->stream, s32, static_cast<float *>(y), (int32_t)A->n, st);
+        }
         HIPCHK(hipGetLastError());
         HIPCHK(hipEventRecord(c->tm[6], c->stream));
         HIPCHK(hipMemcpyAsync(&c->hst[2].ing_err, &st->ing_err, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
@@ -1627,8 +1634,10 @@ mpcg_status mpcg_time_kernel(mpcg_ctx *c, const mpcg_csr *A, int32_t kernel, int
     if (!c || !A || !ms || reps < 1 || kernel < 0 || kernel > 7) return MPCG_EINVAL;
     const bool f32 = (kernel & 1) != 0;
     const bool jac = kernel >= MPCG_KERNEL_JACOBI_F64;
+    // the product that mpcg_spmv runs
+    const bool checked = c->opt.spmv_variant == 0 && (kernel == MPCG_KERNEL_SPMV_F64 || kernel == MPCG_KERNEL_SPMV_F32);
     Plan p;
-    mpcg_status rc = ingest(c, A, nullptr, f32, &p, jac);
+    mpcg_status rc = ingest(c, A, nullptr, f32, &p, jac, !checked);
     if (rc != MPCG_OK) return rc;
     float *x32 = p.at<float>(p.L.x32), *r32 = p.at<float>(p.L.r32), *q32 = p.at<float>(p.L.q32);
     float *dA32 = p.at<float>(p.L.dA32), *dB32 = p.at<float>(p.L.dB32);
@@ -1665,7 +1674,8 @@ mpcg_status mpcg_time_kernel(mpcg_ctx *c, const mpcg_csr *A, int32_t kernel, int
             run_cg_update<float>(c->stream, p, r32, q32, 1);
             break;
         case MPCG_KERNEL_SPMV_F64:
-            run_plain<double>(c->stream, p, r64, q64);
+            if (checked) run_checked<double>(c->stream, *A, r64, q64, p.st);
+            else run_plain<double>(c->stream, p, r64, q64);
             break;
         case MPCG_KERNEL_JACOBI_F64:   // threshold 0 and no cap: every launch runs
             launch_jacobi_iter<double>(c->stream, jac_mat(p), csr_vals<double>(p), r64, p.dg64, x64, dA64, 1,
@@ -1676,7 +1686,8 @@ mpcg_status mpcg_time_kernel(mpcg_ctx *c, const mpcg_csr *A, int32_t kernel, int
                                       0x7fff0000, 0.0, 1, p.sp, p.st);
             break;
         default:
-            run_plain<float>(c->stream, p, r32, q32);
+            if (checked) run_checked<float>(c->stream, *A, r32, q32, p.st);
+            else run_plain<float>(c->stream, p, r32, q32);
             break;
         }
     };

@@ -414,7 +414,7 @@ void launch_ds_ingest(hipStream_t s, const int32_t *rp, const int32_t *col, cons
 
 // -------------------------------------------------------------- products --
 
-enum DsMode { kDsCg = 0, kDsRestart = 1, kDsResid = 2, kDsPlain = 3 };
+enum DsMode { kDsCg = 0, kDsRestart = 1, kDsResid = 2 };
 
 template <typename T>
 struct DsArgs {
@@ -430,12 +430,10 @@ struct DsArgs {
     double *part;
     DevState *st;
     int32_t *live;      // cleared in host memory when the recurrence has stopped
-    // restart, residual, plain
+    // restart, residual
     const float *x32;
     const double *x64in, *b, *dg;
     double *x64out, *rout, *dz, *z;
-    const T *xin;
-    T *yout;
 };
 
 // A vector or plane element at a byte offset below 2^32 (ds_sample keeps the
@@ -671,8 +669,6 @@ __attribute__((amdgpu_num_sgpr(kSgprCap))) k_ds(DsArgs<T> a)
             if (MODE == kDsCg)
                 acc = ds_sum<NH, NEAR, false, T>(a.p, a.S, a.d, a.n, rb, lane, lu,
                                            [&](uint32_t c) { return fma_t<T>(beta, ds_at(dold, c), ds_at(a.r, c)); });
-            else if (MODE == kDsPlain)
-                acc = ds_sum<NH, NEAR, false, T>(a.p, a.S, a.d, a.n, rb, lane, lu, [&](uint32_t c) { return ds_at(a.xin, c); });
             else if (a.x32)
                 acc = ds_sum<NH, NEAR, false, T>(a.p, a.S, a.d, a.n, rb, lane, lu,
                                            [&](uint32_t c) { return (T)ds_at(a.x32, c / 2); });
@@ -680,9 +676,7 @@ __attribute__((amdgpu_num_sgpr(kSgprCap))) k_ds(DsArgs<T> a)
                 acc = ds_sum<NH, NEAR, false, T>(a.p, a.S, a.d, a.n, rb, lane, lu,
                                            [&](uint32_t c) { return (T)ds_at(a.x64in, c); });
             if (!has) continue;
-            if (MODE == kDsPlain) {
-                a.yout[row] = acc;
-            } else if (MODE == kDsCg) {
+            if (MODE == kDsCg) {
                 const T dof = dold[row];
                 if (x_pending) a.x[row] = fma_t<T>(alpha_prev, dof, a.x[row]);
                 const T dn = fma_t<T>(beta, dof, a.r[row]);
@@ -709,7 +703,6 @@ __attribute__((amdgpu_num_sgpr(kSgprCap))) k_ds(DsArgs<T> a)
             }
         }
     }
-    if (MODE == kDsPlain) return;
     if (f32acc) {
         const float bs = sell_block_sum_f(sf, sm);
         if (tid == 0) a.part[blockIdx.x] = (double)bs;
@@ -843,13 +836,6 @@ void launch_ds_resid(hipStream_t s, const DsMat &m, int grid, const double *x64,
     ds_launch<kDsResid, double>(s, m, grid, a);
 }
 
-template <typename T> void launch_ds_plain(hipStream_t s, const DsMat &m, int grid, const T *x, T *y)
-{
-    DsArgs<T> a = ds_args<T>(m, grid);
-    a.xin = x; a.yout = y;
-    ds_launch<kDsPlain, T>(s, m, grid, a);
-}
-
 template <typename T> void launch_ds_jacobi(hipStream_t s, const DsMat &m, const JacArgs<T> &a)
 {
     DsPlanes<T> p{};
@@ -867,8 +853,6 @@ template void launch_ds_cg_spmv<float>(hipStream_t, const DsMat &, int, const fl
 template void launch_ds_cg_spmv<double>(hipStream_t, const DsMat &, int, const double *, double *, double *, double *,
                                         const double *, int, double *, int, int, double *, double *, int, DevState *,
                                         int32_t *);
-template void launch_ds_plain<float>(hipStream_t, const DsMat &, int, const float *, float *);
-template void launch_ds_plain<double>(hipStream_t, const DsMat &, int, const double *, double *);
 template void launch_ds_jacobi<float>(hipStream_t, const DsMat &, const JacArgs<float> &);
 template void launch_ds_jacobi<double>(hipStream_t, const DsMat &, const JacArgs<double> &);
 

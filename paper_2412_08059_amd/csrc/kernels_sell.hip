@@ -332,17 +332,24 @@ __global__ void __launch_bounds__(kBlock) k_commit(const T *__restrict__ from, T
 
 template <typename T>
 void launch_spmv_checked(hipStream_t s, const void *rp, int rp_is_i64, const int32_t *col, const double *val, int32_t n,
-                         int64_t nnz, const T *x, T *scratch, T *y, DevState *st)
+                         int64_t nnz, const T *x, T *scratch, DevState *st)
 {
     const int ngroups = ((n + 63) / 64 + kBlock / 64 - 1) / (kBlock / 64);
     hipLaunchKernelGGL((k_spmv_checked<T>), dim3(ngroups), dim3(kBlock), 0, s, rp, rp_is_i64, col, val, n, nnz, x, scratch, st);
+}
+
+template <typename T> void launch_spmv_commit(hipStream_t s, const T *scratch, T *y, int32_t n, const DevState *st)
+{
+    const int ngroups = ((n + 63) / 64 + kBlock / 64 - 1) / (kBlock / 64);
     hipLaunchKernelGGL((k_commit<T>), dim3(ngroups < 4096 ? ngroups : 4096), dim3(kBlock), 0, s, scratch, y, n, st);
 }
 
 template void launch_spmv_checked<float>(hipStream_t, const void *, int, const int32_t *, const double *, int32_t,
-                                         int64_t, const float *, float *, float *, DevState *);
+                                         int64_t, const float *, float *, DevState *);
 template void launch_spmv_checked<double>(hipStream_t, const void *, int, const int32_t *, const double *, int32_t,
-                                          int64_t, const double *, double *, double *, DevState *);
+                                          int64_t, const double *, double *, DevState *);
+template void launch_spmv_commit<float>(hipStream_t, const float *, float *, int32_t, const DevState *);
+template void launch_spmv_commit<double>(hipStream_t, const double *, double *, int32_t, const DevState *);
 
 // -------------------------------------------------------------- kernels --
 

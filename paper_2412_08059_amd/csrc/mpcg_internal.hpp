@@ -329,11 +329,12 @@ void launch_sell_resid(hipStream_t s, const SellMat &m, const double *x64, const
 template <typename T>
 void launch_sell_plain(hipStream_t s, const SellMat &m, const T *x, T *y);
 
-// y = A x in one pass over the CSR arrays, checks included (mpcg_spmv): errors
-// into st->ing_err, y written only if there are none.
+// A x in one pass over the CSR arrays, checks included (mpcg_spmv), into
+// scratch; errors into st->ing_err.  launch_spmv_commit: y, if there are none.
 template <typename T>
 void launch_spmv_checked(hipStream_t s, const void *rp, int rp_is_i64, const int32_t *col, const double *val, int32_t n,
-                         int64_t nnz, const T *x, T *scratch, T *y, DevState *st);
+                         int64_t nnz, const T *x, T *scratch, DevState *st);
+template <typename T> void launch_spmv_commit(hipStream_t s, const T *scratch, T *y, int32_t n, const DevState *st);
 
 // ----- diagonal storage (kernels_ds.hip) -----
 // After launch_ingest_fold: planes (and diag(A) if dg64) filled and the
@@ -349,7 +350,6 @@ void launch_ds_restart(hipStream_t s, const DsMat &m, int grid, const float *x32
                        DevState *st);
 void launch_ds_resid(hipStream_t s, const DsMat &m, int grid, const double *x64, const double *b, double *part,
                      DevState *st);
-template <typename T> void launch_ds_plain(hipStream_t s, const DsMat &m, int grid, const T *x, T *y);
 
 // ----- small systems (kernels_wg.hip) -----
 // `iters` CG iterations from iteration it (phase started at it0) in one
