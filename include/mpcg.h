@@ -341,7 +341,7 @@ mpcg_status mpcg_load_tuning(mpcg_ctx *ctx, const char *path);
  * largest |i - j| = band (HOST output). */
 mpcg_status mpcg_get_tuning(const mpcg_ctx *ctx, int64_t n, int64_t nnz, int64_t band, mpcg_tuning *out);
 
-/* Time of the most recent mpcg_spmv kernel launch in milliseconds (HIP events
+/* Time of the most recent mpcg_spmv's product kernel in milliseconds (HIP events
  * on the context stream), 0 if none. */
 mpcg_status mpcg_last_kernel_ms(const mpcg_ctx *ctx, double *ms);
 

@@ -1445,15 +1445,12 @@ mpcg_status mpcg_spmv(mpcg_ctx *c, const mpcg_csr *A, int32_t precision, const v
         HIPCHK(hipEventRecord(c->tm[5], c->stream));
         double *s64 = reinterpret_cast<double *>(c->ws + L.q64);
         float *s32 = reinterpret_cast<float *>(c->ws + L.q32);
-        if (precision == 64) {
-            run_checked<double>(c->stream, *A, static_cast<const double *>(x), s64, st);
-            launch_spmv_commit<double>(c->stream, s64, static_cast<double *>(y), (int32_t)A->n, st);
-        } else {
-            run_checked<float>(c->stream, *A, static_cast<const float *>(x), s32, st);
-            launch_spmv_commit<float>(c->stream, s32, static_cast<float *>(y), (int32_t)A->n, st);
-        }
+        if (precision == 64) run_checked<double>(c->stream, *A, static_cast<const double *>(x), s64, st);
+        else run_checked<float>(c->stream, *A, static_cast<const float *>(x), s32, st);
+        HIPCHK(hipEventRecord(c->tm[6], c->stream));   // mpcg_last_kernel_ms: the product
+        if (precision == 64) launch_spmv_commit<double>(c->stream, s64, static_cast<double *>(y), (int32_t)A->n, st);
+        else launch_spmv_commit<float>(c->stream, s32, static_cast<float *>(y), (int32_t)A->n, st);
         HIPCHK(hipGetLastError());
-        HIPCHK(hipEventRecord(c->tm[6], c->stream));
         HIPCHK(hipMemcpyAsync(&c->hst[2].ing_err, &st->ing_err, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
         HIPCHK(hipStreamSynchronize(c->stream));
         const mpcg_status rc1 = ingest_status(c->hst[2].ing_err);

@@ -10,6 +10,13 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
+def _diagonal(n):
+    import torch
+    from paper_2412_08059_amd import DeviceCSR
+    i = torch.arange(n + 1, dtype=torch.int32, device="cuda")
+    return DeviceCSR(i, i[:n].clone(), torch.ones(n, dtype=torch.float64, device="cuda"), n)
+
+
 def _tridiagonal(n):
     import torch
     from paper_2412_08059_amd import DeviceCSR
@@ -42,3 +49,22 @@ def test_timing_hook_times_what_spmv_runs():
     s.close()
     print(f"  call {1e3 * call:.0f} us, hook {1e3 * hook:.0f} us", flush=True)
     assert 0.6 * call <= hook <= call
+
+
+def test_last_kernel_is_the_product_alone():
+    """On a diagonal matrix the product moves 32 bytes a row and the copy of the
+    result to y 16: both together take half as much again as the product."""
+    import torch
+    from paper_2412_08059_amd import Solver, capi
+    a = _diagonal(32_000_000)
+    x = torch.ones(a.n, dtype=torch.float64, device="cuda")
+    s = Solver(a.n, a.nnz)
+    last = np.inf
+    for _ in range(6):
+        st, _ = s.spmv(a, x, 64)
+        assert st == 0
+        last = min(last, capi.mpcg_last_kernel_ms(s.ctx))
+    hook = min(capi.mpcg_time_kernel(s.ctx, a.desc, capi.MPCG_KERNEL_SPMV_F64, 10) for _ in range(3))
+    s.close()
+    print(f"  last kernel {1e3 * last:.0f} us, hook {1e3 * hook:.0f} us", flush=True)
+    assert last <= 1.2 * hook
