@@ -139,10 +139,28 @@ def _matrices(quick: bool):
     return mats
 
 
-def _time_kernels(capi, ctx, desc, reps):
-    t64 = capi.mpcg_time_kernel(ctx, desc, capi.MPCG_KERNEL_CG_SPMV_F64, reps)
-    t32 = capi.mpcg_time_kernel(ctx, desc, capi.MPCG_KERNEL_CG_SPMV_F32, reps)
-    return t32, t64
+def sell_variant(sell_split: int) -> int:
+    """The mpcg_options.spmv_variant that runs a candidate's SELL-64 products.
+    Variant 0 would time diagonal storage on grids and bands, where the SELL
+    fields have no effect; the class's other matrices are on SELL-64."""
+    return 2 if sell_split == 1 else 1
+
+
+def _time_sell(cands, a, A, reps):
+    """{candidate: FP32 + FP64 CG product, ms}."""
+    from paper_2412_08059_amd import Solver, capi
+    out = {}
+    for variant in (1, 2):
+        mine = [c for c in cands if sell_variant(c[2]) == variant]
+        if not mine:
+            continue
+        sv = Solver(a.n, a.nnz, tuning=None, spmv_variant=variant)
+        for cand in mine:
+            capi.mpcg_set_tuning(sv.ctx, dict(zip(("sell_batch", "sell_whole_batch", "sell_split"), cand)))
+            out[cand] = (capi.mpcg_time_kernel(sv.ctx, A.desc, capi.MPCG_KERNEL_CG_SPMV_F64, reps)
+                         + capi.mpcg_time_kernel(sv.ctx, A.desc, capi.MPCG_KERNEL_CG_SPMV_F32, reps))
+        sv.close()
+    return out
 
 
 def tune_solve(quick: bool = False, log=print):
@@ -166,11 +184,7 @@ def tune_solve(quick: bool = False, log=print):
         B = torch.from_numpy(b).cuda()
         X = torch.empty(a.n, dtype=torch.float64, device="cuda")
         reps = 5 if quick else 15
-        sell = {}
-        for cand in sell_candidates(key[2]):
-            capi.mpcg_set_tuning(sv.ctx, dict(zip(("sell_batch", "sell_whole_batch", "sell_split"), cand)))
-            t32, t64 = _time_kernels(capi, sv.ctx, A.desc, reps)
-            sell[cand] = t32 + t64
+        sell = _time_sell(sell_candidates(key[2]), a, A, reps)
         best_sell = choose_min(sell)
         # nontemporal matrix loads stay with the size rule (-1): a class spans
         # sizes on both sides of the Infinity Cache
