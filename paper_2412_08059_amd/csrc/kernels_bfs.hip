@@ -156,6 +156,31 @@ __device__ inline int wave_sum_i(int v)
     return wave_fold(v, [](int x, int y) { return x + y; });
 }
 
+// Its wave reductions go through the LDS pipe: with the exchanges of wave_ops.hpp
+// the kernel's levels are slower (features of a 1 M band of half-width 16 163 and
+// 168 ms, of 20,000 rows and half-width 9 4.41 and 4.51).
+__device__ inline int small_max_i(int v)
+{
+    for (int off = 32; off > 0; off >>= 1) {
+        const int o = __shfl_xor(v, off, 64);
+        v = v > o ? v : o;
+    }
+    return v;
+}
+__device__ inline int small_min_i(int v)
+{
+    for (int off = 32; off > 0; off >>= 1) {
+        const int o = __shfl_xor(v, off, 64);
+        v = v < o ? v : o;
+    }
+    return v;
+}
+__device__ inline int small_sum_i(int v)
+{
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
 __global__ void __launch_bounds__(kBfsSmallThreads)
 k_bfs_small(const int32_t *__restrict__ rp, const int32_t *__restrict__ col, int32_t *dist,
             QEnt *q0, QEnt *q1, int32_t n, int32_t lanes, int32_t small_max, int32_t band, int32_t k,
@@ -320,8 +345,8 @@ k_bfs_small(const int32_t *__restrict__ rp, const int32_t *__restrict__ col, int
             }
             F = b_f[lane];
             V = b_v[lane];
-            pf0 = wave_sum_i(__popc(F));
-            pv0 = wave_sum_i(__popc(V));
+            pf0 = small_sum_i(__popc(F));
+            pv0 = small_sum_i(__popc(V));
             // rows within band of an edge of the window that is not an edge of the graph
             const int lo_end = w0 > 0 ? band : 0;                 // rows [0, lo_end)
             const int hi_beg = w0 + nw < n ? nw - band : nw;      // rows [hi_beg, nw)
@@ -410,11 +435,11 @@ k_bfs_small(const int32_t *__restrict__ rp, const int32_t *__restrict__ col, int
         if (wv == 0) {
             const int lane = ln;
             code = b_code;
-            const int pf = wave_sum_i(__popc(F));
-            const int pv = wave_sum_i(__popc(V));
-            const int fmin = wave_min_i(F ? lane * 32 + __ffs((int)F) - 1 : kIntMax);
-            const int fmax = wave_max_i(F ? lane * 32 + 31 - __clz((int)F) : -1);
-            const int pmx = wave_max_i(Fp ? lane * 32 + 31 - __clz((int)Fp) : -1);
+            const int pf = small_sum_i(__popc(F));
+            const int pv = small_sum_i(__popc(V));
+            const int fmin = small_min_i(F ? lane * 32 + __ffs((int)F) - 1 : kIntMax);
+            const int fmax = small_max_i(F ? lane * 32 + 31 - __clz((int)F) : -1);
+            const int pmx = small_max_i(Fp ? lane * 32 + 31 - __clz((int)Fp) : -1);
             b_f[lane] = F;
             if (lane == 0) {
                 b_level = lev;
@@ -503,9 +528,9 @@ k_bfs_small(const int32_t *__restrict__ rp, const int32_t *__restrict__ col, int
             const int f = w >> lsh, l = w & (lanes - 1);
             const QEnt u = sq[c][f];
             if (u.b >= e0 && u.e <= e1) {   // the row's columns are in the window
-                for (uint32_t j = u.b + l; j < (uint32_t)u.e; j += lanes) visit(w_col[j - e0]);
+                for (int j = l, c = u.e - u.b; j < c; j += lanes) visit(w_col[u.b - e0 + j]);
             } else {
-                for (uint32_t j = u.b + l; j < (uint32_t)u.e; j += lanes) visit(col[j]);   // past 2^31 no wrap
+                for (int j = l, c = u.e - u.b; j < c; j += lanes) visit(col[u.b + j]);
             }
         }
         __syncthreads();
