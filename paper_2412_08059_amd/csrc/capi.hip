@@ -250,9 +250,8 @@ constexpr int32_t kDiaBlockMinRows = 64;
 // takes it 0.9 us.  Up to kThinRows rows (two words a thread) one block's
 // bit-parallel levels take 0.5 to 0.7, above them those or the tiles' 1.1 to 1.2.
 // Features, ms, queue and bits: 9 wide, 60,000 rows 12.1 and 9.0, 70,000 13.9 and
-// 18.1, 1 M 195 and 244; 22 wide, 400,000 33.5 and 40.8; 23 wide (beyond the window)
-// 53.5 and 39.1; 24 wide,
-// 70,000 8.9 and 7.0, 1 M 129 and 93.
+// 18.1, 1 M 195 and 244; 22 wide, 400,000 33.5 and 40.8; 23 wide (beyond the
+// window), 400,000 53.5 and 39.1; 24 wide, 70,000 8.9 and 7.0, 1 M 129 and 93.
 constexpr int32_t kThinBand = 22;
 constexpr int64_t kThinRows = 65536;
 
@@ -943,9 +942,10 @@ mpcg_status pseudo_diameter(const mpcg_ctx *c, const Chan &ch, const Plan &p, mp
 // product grid fills every CU (8 blocks of 256 threads each), one block per CU
 // fewer.  A phase keeps the plan it may have started with beside the 2BFS to
 // its end: the grid fixes which rows share a partial sum, so Algorithm II's
-// bits then do not depend on when the 2BFS ends.  (With diagonal storage the
-// smaller grid is no slower alone either: 1M band FP64 product 25.5 us at
-// 1,792 blocks and 26.0 at 2,048, 128^3 35.6 and 35.3.)
+// bits then do not depend on when the 2BFS ends.  Alone, the smaller grid takes
+// 1 to 4 % longer (FP64 product, us at 1,792 and 2,048 blocks: 128^3 33.2 and
+// 32.3, 1 M band 19.6 and 19.3; SELL-64 128^3 42.8 and 41.2, random graph of 1 M
+// rows 183.7 and 181.3; FP32 the same).
 Plan shared_plan(const mpcg_ctx *c, const Plan &p)
 {
     Plan q = p;

@@ -1,8 +1,9 @@
 // Steps of small systems, one workgroup per system (gfx950).
 //
-// A step of the batch is four launches over all listed slices; with systems of
+// A step of the batch is two launches over all listed slices; with systems of
 // a few thousand rows each launch is mostly latency (gaps, and chains of work
-// list, state, slice and matrix loads).  While no listed system is larger, a
+// list, state, slice and matrix loads).  While no listed system is larger (or
+// has more entries than one workgroup reads in that time, wg_max_entries), a
 // workgroup takes its system through up to `steps` steps instead: the state in
 // LDS, x, r and d of its rows and their first E entries in registers, d (or
 // the x of a residual) also in LDS for the gathers, entries past E read where
@@ -15,11 +16,11 @@
 //
 // What bounds it: the five barriers of a step and the scalars one lane forms
 // between them (512 systems of 1,000 rows, two workgroups a CU: 2.7 us a step
-// for all of them, where the four launches took 23 us).  Batches, ms before
-// and after: 512 trees of 1,000 rows 20.9 -> 4.6, 100 of 300 .. 1,000 rows
-// (FP64) 8.6 -> 1.9, 64 mixed systems of 1,000 .. 2,000 rows 9.1 -> 2.9, of
-// 1,000 .. 4,000 rows with features 15.8 -> 10.2 (what is left there is the
-// 2BFS).  Half or twice the entries in registers: within 1%.
+// for all of them).  Batches, ms, two launches a step and this: 512 trees of
+// 1,000 rows 20.7 and 5.6, 100 of 300 .. 1,000 rows (FP64) 6.9 and 2.4, 64 mixed
+// systems of 1,000 .. 2,000 rows 10.7 and 5.1, of 1,000 .. 4,000 rows with
+// features 21.3 and 16.7 (what is left there is the 2BFS).  Half or twice the
+// entries in registers: within 1%.
 
 #include "batch_step.hpp"
 

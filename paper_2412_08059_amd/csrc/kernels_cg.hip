@@ -3,20 +3,21 @@
 // reduction that finalises the CG scalars on the device.
 //
 // One CG iteration i is two launches:
-//   k_cg_spmv    gamma_i = r_i.r_i from the update partials of iteration i-1,
-//                stop test, beta_i = gamma_i / gamma_{i-1}, decay ratio for v
-//                (eq. 13); d_i = r_i + beta_i d_{i-1} (own rows written,
+//   product      (k_spmv here; k_sell, k_ds) gamma_i = r_i.r_i from the update
+//                partials of iteration i-1, stop test, beta_i = gamma_i /
+//                gamma_{i-1}, decay ratio for v (eq. 13); x += alpha_{i-1}
+//                d_{i-1}; d_i = r_i + beta_i d_{i-1} (own rows written,
 //                gathered columns recomputed on the fly), q = A d_i, partials
 //                of d_i.q.
 //   k_cg_update  delta_i from those partials, breakdown test,
 //                alpha_i = gamma_i / delta_i (rounded to the working
-//                precision), x += alpha d_i, r -= alpha q, partials of r.r.
+//                precision), r -= alpha q, partials of r.r.
 // Every block of a kernel finishes the previous kernel's reduction itself
 // (same partials, same order, same bits), so blocks of one grid never wait
 // for each other and no cross-block memory fence is needed; block 0 records
 // the scalars in the device state for the host.
 // These are the steps of the CG procedure in the paper's "Conjugate Gradient
-// Method" section with the direction update moved to the start of the next
+// Method" section with the updates of x and of the direction moved to the next
 // product; the arithmetic of each element is unchanged.
 
 #include "mpcg_internal.hpp"

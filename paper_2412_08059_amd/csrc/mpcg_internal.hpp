@@ -37,8 +37,10 @@ constexpr int64_t kInfinityCacheBytes = 256ll << 20;   // MI355X last-level (Inf
 constexpr int kNumXcd = 8;            // MI355X: blocks are dispatched round-robin over 8 XCDs
 constexpr int kMaxGrid = 2048;        // largest grid of a kernel that writes reduction partials
 constexpr int kUpdateGrid = 1024;     // blocks of a CG update launch: fewer partials for the next product
-constexpr int kSegBand = 8;           // widest band of the segmented BFS (kernels_bseg.hip)
-constexpr int kDsMax = 8;             // distances |i - j| > 0 that diagonal storage handles
+constexpr int kSegBand = 8;           // widest band of the segmented BFS (kernels_bseg.hip; 16 boundary rows
+                                      // a segment are its lane layout: wider ones are not tried)
+constexpr int kDsMax = 8;             // distances |i - j| > 0 that diagonal storage handles (nine and more, a
+                                      // 19- or 27-point stencil, are not measured)
 constexpr int kSgprCap = 80;          // scalar registers with which eight waves fit on a SIMD
 constexpr int kSpmvBlocksPerCu = 5;   // 32 KB of LDS per block, 160 KB per CU
 
