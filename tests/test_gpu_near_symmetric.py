@@ -67,3 +67,30 @@ def test_one_ingest(name, gen):
         s.close()
     print(f"  {name}: {1e3 * best[0]:.3f} ms, SELL-64 {1e3 * best[1]:.3f} ms", flush=True)
     assert best[0] <= 1.25 * best[1]
+
+
+@pytest.mark.parametrize("links", [14, 15, 16, 40])
+@pytest.mark.parametrize("n,hub", [(100, 50), (5000, 0), (5000, 2501), (70000, 69999)])
+def test_one_long_row(n, hub, links):
+    """A path with one vertex linked to `links` more, its row as long as eight
+    distances allow (17 entries) or longer: SELL-64's bits."""
+    import scipy.sparse as sp
+    import torch
+    from paper_2412_08059_amd import DeviceCSR, Solver
+    far = [v for v in (np.arange(1, links + 1) * (n // (links + 2))).tolist() if abs(v - hub) > 1]
+    i = np.concatenate([np.arange(n - 1), np.full(len(far), hub)])
+    j = np.concatenate([np.arange(1, n), far])
+    w = sp.coo_matrix((-np.random.default_rng(links).uniform(0.5, 1.0, len(i)), (i, j)), shape=(n, n)).tocsr()
+    w = w + w.T
+    m = (w + sp.diags(1e-2 - np.asarray(w.sum(axis=1)).ravel())).tocsr()
+    m.sort_indices()
+    a = W.CSR(n, m.indptr.astype(np.int64), m.indices.astype(np.int32), m.data, "hub")
+    dev = DeviceCSR.from_host(a)
+    b = torch.from_numpy(W.rhs(a, seed=5)[1]).cuda()
+    got = []
+    for variant in (0, 1):
+        s = Solver(a.n, a.nnz, spmv_variant=variant, maxit1=50, maxit2=50, max_restarts=1)
+        st, x, stats = s.solve(dev, b, 1e-4, 1e-9)
+        got.append((st, stats.n1, stats.n2, stats.flags, x.cpu().numpy().view(np.int64)))
+        s.close()
+    assert got[0][:4] == got[1][:4] and np.array_equal(got[0][4], got[1][4])
