@@ -189,7 +189,7 @@ Layout plan_layout(int64_t n, int64_t nnz)
     L.sell_col = take(sizeof(int32_t) * (size_t)L.sell_cap);
     L.sell_v64 = take(sizeof(double) * (size_t)L.sell_cap);
     L.sell_v32 = take(sizeof(float) * (size_t)L.sell_cap);
-    L.ingest_blk = take(sizeof(int32_t) * 3 * ((N + kBlock - 1) / kBlock + 1));
+    L.ingest_blk = take(sizeof(int32_t) * 3 * ((N + kBlock - 1) / kBlock + 1));   // and kDsMirrorBlocks <= 3 flags
     L.snap32 = take(sizeof(float) * kNumEps * N);
     L.z32 = take(sizeof(float) * N);
     L.z64 = take(sizeof(double) * N);
@@ -355,8 +355,9 @@ mpcg_status ingest(mpcg_ctx *c, const mpcg_csr *A, const double *b, bool need_va
     // arrays; what its passes find unfit (or an explicit variant) goes to SELL
     const bool try_ds = want_copy && c->opt.spmv_variant == 0 && A->nnz <= (2 * kDsMax + 1) * A->n;
     int32_t *blk = p->at<int32_t>(p->L.ingest_blk);
-    launch_ingest_rows(c->stream, A->row_ptr, A->row_ptr_is_i64 ? 1 : 0, rp32, A->col_idx, b, p->n, A->nnz, wid, blk);
-    launch_ingest_fold(c->stream, blk, p->rp, A->col_idx, A->val, p->n, A->nnz, wid, soff, p->L.sell_cap, try_ds, p->st);
+    launch_ingest_rows(c->stream, A->row_ptr, A->row_ptr_is_i64 ? 1 : 0, rp32, A->col_idx, A->val, b, p->n, A->nnz,
+                       try_ds, wid, blk);
+    launch_ingest_fold(c->stream, blk, p->rp, A->col_idx, p->n, A->nnz, wid, soff, p->L.sell_cap, try_ds, p->st);
     if (try_ds)
         launch_ds_ingest(c->stream, p->rp, A->col_idx, A->val, p->n, v64, v32, want_diag ? p->dg64 : nullptr,
                          want_diag ? p->dg32 : nullptr, p->st);
@@ -375,7 +376,7 @@ mpcg_status ingest(mpcg_ctx *c, const mpcg_csr *A, const double *b, bool need_va
     mpcg_status rc = verdict();
     if (rc != MPCG_OK) return rc;
     if (c->hst[1].ds_cand && c->hst[1].ds_miss) {   // other diagonals, not symmetric, or malformed
-        launch_ingest_fold(c->stream, blk, p->rp, A->col_idx, A->val, p->n, A->nnz, wid, soff, p->L.sell_cap, 0, p->st);
+        launch_ingest_fold(c->stream, blk, p->rp, A->col_idx, p->n, A->nnz, wid, soff, p->L.sell_cap, 0, p->st);
         general();
         rc = verdict();
         if (rc != MPCG_OK) return rc;

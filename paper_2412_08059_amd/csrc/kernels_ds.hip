@@ -36,35 +36,19 @@ namespace mpcg {
 
 // Sampled offsets (one block): the distances |i - j| > 0 of kDsSample rows
 // spread over the matrix, a thread per entry.  Up to 63 they are bits of a
-// mask, beyond that slots claimed by compare-and-swap.  With ds each sampled
-// entry is also looked up in its column's row: a matrix that is symmetric only
-// to rounding is then not a candidate.  Other distances than the sampled ones,
-// or an unequal pair outside the sample, are found out by k_ds_rows, which costs
-// a second ingest but no result (7-point stencil, 49^3 rows 0.08 ms, 128^3 0.27;
-// the look-ups take 3 us).
-constexpr int kDsRowMax = 2 * kDsMax + 1;          // entries of the longest row that can match
-constexpr int kDsSample = 1024 / kDsRowMax;        // rows
+// mask, beyond that slots claimed by compare-and-swap.  The upper entries' mirror
+// images have been looked up by blocks of k_ingest_rows (the dependent loads took
+// 6 us here, of a 2M-row band's 0.37 ms): a matrix that is symmetric only to
+// rounding is then not a candidate.  Other distances than the sampled ones, or an
+// unequal pair outside the sample, are found out by k_ds_rows, which costs a
+// second ingest but no result (7-point stencil, 49^3 rows 0.08 ms, 128^3 0.27).
 struct DsSample {
     unsigned long long near;      // bit d: distance d
-    int32_t far[kDsMax], misfit, unequal;
+    int32_t far[kDsMax], misfit;
 };
 
-// Whether entry k in row i, column c, has its mirror image, bit for bit.
-__device__ inline bool ds_mirrored(const int32_t *rp, const int32_t *col, const double *val, int32_t i, int32_t c, int k)
-{
-    const int lo = rp[c], len = rp[c + 1] - lo;
-    int32_t cc[kDsRowMax];
-#pragma unroll
-    for (int t = 0; t < kDsRowMax; ++t) cc[t] = t < len ? col[lo + t] : -1;
-    int at = -1;
-#pragma unroll
-    for (int t = 0; t < kDsRowMax; ++t)
-        if (cc[t] == i) at = t;
-    return at >= 0 && __double_as_longlong(val[lo + at]) == __double_as_longlong(val[k]);
-}
-
-__device__ inline void ds_sample(int lo, int hi, int64_t i, const int32_t *rp, const int32_t *col, const double *val,
-                                 int32_t n, int64_t nnz, int64_t cap, int ds, DevState *st, DsSample *sm)
+__device__ inline void ds_sample(int lo, int hi, int64_t i, const int32_t *col, int32_t n, int64_t nnz, int64_t cap,
+                                 int ds, DevState *st, DsSample *sm)
 {
     // (lo, hi): the sampled row's entries, none for a thread without a row
     const int j = threadIdx.x % kDsRowMax;
@@ -73,7 +57,6 @@ __device__ inline void ds_sample(int lo, int hi, int64_t i, const int32_t *rp, c
         const int32_t c = col[lo + j];
         const int64_t diff = (int64_t)c - i;
         const int64_t d = diff < 0 ? -diff : diff;
-        if (ds && d > 0 && c >= 0 && c < n && !ds_mirrored(rp, col, val, (int32_t)i, c, lo + j)) sm->unequal = 1;
         if (d > 0 && d < 64) {
             atomicOr(&sm->near, 1ull << d);
         } else if (d >= 64 && d < n) {   // a column out of range is found by the entries' pass
@@ -96,7 +79,7 @@ __device__ inline void ds_sample(int lo, int hi, int64_t i, const int32_t *rp, c
         st->ds_many = 1;
         return;
     }
-    if (!ds || sm->unequal || nh == 0) return;
+    if (!ds || nh == 0) return;
     // Worth it when at least two thirds of the diagonals' places hold an
     // entry: each place costs a gather whether or not it does.
     if ((int64_t)(2 * nh + 1) * n * 2 > 3 * nnz || (int64_t)(nh + 1) * ds_stride(n) > cap) return;
@@ -120,8 +103,8 @@ __device__ inline void ds_sample(int lo, int hi, int64_t i, const int32_t *rp, c
 // for diagonal storage if ds), and unless diagonal storage takes the matrix
 // forms the SELL slice offsets (exclusive scan of the padded slice sizes).
 __global__ void __launch_bounds__(1024)
-k_ingest_fold(const int32_t *blk, int32_t nblk, const int32_t *rp, const int32_t *col, const double *val, int32_t n,
-              int64_t nnz, const int64_t *wid, int64_t *off, int64_t cap, int ds, DevState *st)
+k_ingest_fold(const int32_t *blk, int32_t nblk, const int32_t *rp, const int32_t *col, int32_t n, int64_t nnz,
+              const int64_t *wid, int64_t *off, int64_t cap, int ds, DevState *st)
 {
     __shared__ int32_t fold[3][1024 / 64];
     __shared__ int64_t part[1024 / 64];
@@ -130,11 +113,12 @@ k_ingest_fold(const int32_t *blk, int32_t nblk, const int32_t *rp, const int32_t
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     for (int i = t; i < (int)(sizeof(DevState) / sizeof(int32_t)); i += 1024) reinterpret_cast<int32_t *>(st)[i] = 0;
     // the sampled row's pointers, loaded beside the statistics
-    const int64_t step = ((int64_t)n + kDsSample - 1) / kDsSample;
     const int r = t / kDsRowMax;
-    const int64_t row = (int64_t)r * step + (r * 2654435761u >> 7) % (uint64_t)step;
+    const int64_t row = ds_sample_row(r, n);
     const bool has = r < kDsSample && row < n;
     const int rlo = has ? rp[row] : 0, rhi = has ? rp[row + 1] : 0;
+    int unequal = 0;   // with ds: some sampled entry has no equal mirror image
+    for (int k = 0; k < kDsMirrorBlocks; ++k) unequal |= blk[3 * nblk + k];
     int e = 0, l = 0, bd = 0;
     for (int i = t; i < nblk; i += 1024) {
         e |= blk[3 * i];
@@ -152,7 +136,7 @@ k_ingest_fold(const int32_t *blk, int32_t nblk, const int32_t *rp, const int32_t
     }
     if (t == 0) smp.near = 0;
     if (t < kDsMax) smp.far[t] = 0;
-    if (t == kDsMax) smp.misfit = smp.unequal = 0;
+    if (t == kDsMax) smp.misfit = 0;
     __syncthreads();
     for (int k = 0; k < 1024 / 64; ++k) {
         e |= fold[0][k];
@@ -165,9 +149,9 @@ k_ingest_fold(const int32_t *blk, int32_t nblk, const int32_t *rp, const int32_t
         st->max_band = bd;
     }
     // a row with more entries than kDsMax distances can give is not diagonal
-    // storage's, sampled or not (nor looked up: 1M-row random graph 50 -> 35 us)
-    if (l > kDsRowMax) ds = 0;
-    if (!(e & kErrRowPtr)) ds_sample(rlo, rhi, row, rp, col, val, n, nnz, cap, ds, st, &smp);   // else ds_cand is 0
+    // storage's, sampled or not
+    if (l > kDsRowMax || unequal) ds = 0;
+    if (!(e & kErrRowPtr)) ds_sample(rlo, rhi, row, col, n, nnz, cap, ds, st, &smp);   // else ds_cand is 0
     if (t == 0) cand = st->ds_cand;
     __syncthreads();
     if (cand) return;
@@ -195,10 +179,10 @@ k_ingest_fold(const int32_t *blk, int32_t nblk, const int32_t *rp, const int32_t
     }
 }
 
-void launch_ingest_fold(hipStream_t s, const int32_t *blk, const int32_t *rp, const int32_t *col, const double *val,
-                        int32_t n, int64_t nnz, const int64_t *wid, int64_t *off, int64_t cap, int ds, DevState *st)
+void launch_ingest_fold(hipStream_t s, const int32_t *blk, const int32_t *rp, const int32_t *col, int32_t n, int64_t nnz,
+                        const int64_t *wid, int64_t *off, int64_t cap, int ds, DevState *st)
 {
-    hipLaunchKernelGGL(k_ingest_fold, dim3(1), dim3(1024), 0, s, blk, (n + kBlock - 1) / kBlock, rp, col, val, n, nnz,
+    hipLaunchKernelGGL(k_ingest_fold, dim3(1), dim3(1024), 0, s, blk, (n + kBlock - 1) / kBlock, rp, col, n, nnz,
                        wid, off, cap, ds, st);
 }
 

@@ -28,33 +28,82 @@ namespace mpcg {
 // passes come before the last, see kernels_ds.hip):
 //   k_ingest_rows     thread per row: row-pointer checks (and int64 -> int32
 //                     conversion), b finite, row length, bandwidth from the
-//                     first and last column of the row, slice width;
+//                     first and last column of the row, slice width; with ds
+//                     its first blocks look the mirror images of the sampled
+//                     rows' upper entries up, beside the others;
 //   k_ingest_fold     one block: the blocks' statistics into the device state,
 //                     padded slice offsets (kernels_ds.hip);
 //   k_ingest_entries  wave per slice, entries read in coalesced 64-wide
 //                     strides: column range, strictly increasing columns,
 //                     finite values, and the SELL-64 copy when it fits.
 
+// Row i's entries; false where they are not a range of the arrays.
+__device__ inline bool row_range(const void *rp_in, int rp_is_i64, int64_t i, int64_t nnz, int64_t &lo, int64_t &hi)
+{
+    if (rp_is_i64) {
+        lo = ((const int64_t *)rp_in)[i];
+        hi = ((const int64_t *)rp_in)[i + 1];
+    } else {
+        lo = ((const int32_t *)rp_in)[i];
+        hi = ((const int32_t *)rp_in)[i + 1];
+    }
+    return lo >= 0 && hi >= lo && hi <= nnz;
+}
+
+// A thread per place of the sampled rows' upper entries (at most kDsMax in
+// diagonal storage, the last of the row): whether some entry's mirror image is
+// not among the first kDsMax of its column's row, bit for bit.  Nothing is
+// checked yet, so neither a row's range nor its columns are taken on trust.
+__device__ inline int unequal_pair(const void *rp_in, int rp_is_i64, const int32_t *col, const double *val, int32_t n,
+                                   int64_t nnz, int k)
+{
+    const int r = k / kDsMax, j = k % kDsMax;
+    int64_t lo, hi, clo, chi;
+    if (r >= kDsSample) return 0;
+    const int64_t row = ds_sample_row(r, n);
+    if (row >= n || !row_range(rp_in, rp_is_i64, row, nnz, lo, hi) || lo + j >= hi) return 0;
+    const int32_t c = col[hi - 1 - j];
+    const double v = val[hi - 1 - j];
+    if (c <= row || c >= n || !row_range(rp_in, rp_is_i64, c, nnz, clo, chi)) return 0;
+    int32_t cc[kDsMax];
+    double cv[kDsMax];
+#pragma unroll
+    for (int t = 0; t < kDsMax; ++t) {
+        cc[t] = -1;
+        cv[t] = 0.0;
+        if (clo + t < chi) {
+            cc[t] = col[clo + t];
+            cv[t] = val[clo + t];
+        }
+    }
+    int equal = 0;
+#pragma unroll
+    for (int t = 0; t < kDsMax; ++t)
+        equal |= cc[t] == (int32_t)row && __double_as_longlong(cv[t]) == __double_as_longlong(v);
+    return !equal;
+}
+
 __global__ void __launch_bounds__(kBlock)
-k_ingest_rows(const void *rp_in, int rp_is_i64, const int32_t *__restrict__ col,
-              const double *__restrict__ b, int32_t n, int64_t nnz, int32_t nslices,
+k_ingest_rows(const void *rp_in, int rp_is_i64, const int32_t *__restrict__ col, const double *__restrict__ val,
+              const double *__restrict__ b, int32_t n, int64_t nnz, int32_t nslices, int32_t nblk,
               int32_t *__restrict__ rp32_out, int64_t *__restrict__ wid, int32_t *__restrict__ blk)
 {
     __shared__ int sm[3][kBlock / 64];
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int nmir = (int)gridDim.x - nblk, k = (int)blockIdx.x;   // these first: their loads depend on each other
+    if (k < nmir) {
+        const int any = __syncthreads_or(unequal_pair(rp_in, rp_is_i64, col, val, n, nnz, k * kBlock + (int)threadIdx.x));
+        if (threadIdx.x == 0) blk[3 * nblk + k] = any;
+        return;
+    }
+    const int rb = k - nmir;
+    const int64_t i = (int64_t)rb * kBlock + threadIdx.x;
     int err = 0, len = 0, band = 0;
     if (i < n) {
         int64_t lo, hi;
-        if (rp_is_i64) {
-            lo = ((const int64_t *)rp_in)[i];
-            hi = ((const int64_t *)rp_in)[i + 1];
-        } else {
-            lo = ((const int32_t *)rp_in)[i];
-            hi = ((const int32_t *)rp_in)[i + 1];
-        }
+        const bool ok = row_range(rp_in, rp_is_i64, i, nnz, lo, hi);
         if (i == 0 && lo != 0) err |= kErrRowPtr;
         if (i == n - 1 && hi != nnz) err |= kErrRowPtr;
-        if (lo < 0 || hi < lo || hi > nnz) {
+        if (!ok) {
             err |= kErrRowPtr;
         } else if (hi > lo) {
             len = (int)(hi - lo);
@@ -95,9 +144,9 @@ k_ingest_rows(const void *rp_in, int rp_is_i64, const int32_t *__restrict__ col,
             l = l > sm[1][j] ? l : sm[1][j];
             bd = bd > sm[2][j] ? bd : sm[2][j];
         }
-        blk[3 * blockIdx.x] = e;
-        blk[3 * blockIdx.x + 1] = l;
-        blk[3 * blockIdx.x + 2] = bd;
+        blk[3 * rb] = e;
+        blk[3 * rb + 1] = l;
+        blk[3 * rb + 2] = bd;
     }
 }
 
@@ -155,11 +204,12 @@ k_ingest_entries(const int32_t *__restrict__ rp, const int32_t *__restrict__ col
 }
 
 void launch_ingest_rows(hipStream_t s, const void *rp_in, int rp_is_i64, int32_t *rp32_out, const int32_t *col,
-                        const double *b, int32_t n, int64_t nnz, int64_t *wid, int32_t *blk)
+                        const double *val, const double *b, int32_t n, int64_t nnz, int ds, int64_t *wid, int32_t *blk)
 {
+    static_assert(kDsSample * kDsMax <= kDsMirrorBlocks * kBlock && kDsMirrorBlocks <= 3, "places and flags");
     const int nblk = (n + kBlock - 1) / kBlock;
-    hipLaunchKernelGGL(k_ingest_rows, dim3(nblk), dim3(kBlock), 0, s, rp_in, rp_is_i64, col, b, n, nnz,
-                       (n + 63) / 64, rp32_out, wid, blk);
+    hipLaunchKernelGGL(k_ingest_rows, dim3(nblk + (ds ? kDsMirrorBlocks : 0)), dim3(kBlock), 0, s, rp_in, rp_is_i64, col,
+                       val, b, n, nnz, (n + 63) / 64, nblk, rp32_out, wid, blk);
 }
 
 void launch_ingest_sell(hipStream_t s, const int32_t *rp32, const int32_t *col, const double *val, int32_t n,

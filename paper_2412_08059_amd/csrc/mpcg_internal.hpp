@@ -41,6 +41,11 @@ constexpr int kSegBand = 8;           // widest band of the segmented BFS (kerne
                                       // a segment are its lane layout: wider ones are not tried)
 constexpr int kDsMax = 8;             // distances |i - j| > 0 that diagonal storage handles (nine and more, a
                                       // 19- or 27-point stencil, are not measured)
+// Rows that ingest samples for diagonal storage (kernels_ds.hip): row r of them is
+// ds_sample_row(r, n); and the blocks that look their entries' mirror images up.
+constexpr int kDsRowMax = 2 * kDsMax + 1;          // entries of the longest row that can match
+constexpr int kDsSample = 1024 / kDsRowMax;
+constexpr int kDsMirrorBlocks = 2;
 constexpr int kSgprCap = 80;          // scalar registers with which eight waves fit on a SIMD
 constexpr int kSpmvBlocksPerCu = 5;   // 32 KB of LDS per block, 160 KB per CU
 
@@ -248,14 +253,15 @@ __device__ inline unsigned spec_crossings(DevState *st, int it, double g)
 // Validate A (and b), convert int64 row pointers, and build the SELL-64 copy
 // when its padded size fits in `cap` entries (see kernels_sell.hip).
 // launch_ingest_rows: row pointers, b, row lengths, slice widths, statistics
-// per block.  launch_ingest_fold, after it: clears st, the statistics into it,
+// per block (blk: 3 for each 256 rows, then with ds kDsMirrorBlocks flags of unequal
+// pairs).  launch_ingest_fold, after it: clears st, the statistics into it,
 // whether a sample of rows holds few distances, with ds these, and unless
 // st->ds_cand says that the diagonal storage takes the matrix the slice offsets.  launch_ingest_sell, after that:
 // the entries (nothing while st->ds_cand).
 void launch_ingest_rows(hipStream_t s, const void *rp_in, int rp_is_i64, int32_t *rp32_out, const int32_t *col,
-                        const double *b, int32_t n, int64_t nnz, int64_t *wid, int32_t *blk);
-void launch_ingest_fold(hipStream_t s, const int32_t *blk, const int32_t *rp, const int32_t *col, const double *val,
-                        int32_t n, int64_t nnz, const int64_t *wid, int64_t *off, int64_t cap, int ds, DevState *st);
+                        const double *val, const double *b, int32_t n, int64_t nnz, int ds, int64_t *wid, int32_t *blk);
+void launch_ingest_fold(hipStream_t s, const int32_t *blk, const int32_t *rp, const int32_t *col, int32_t n, int64_t nnz,
+                        const int64_t *wid, int64_t *off, int64_t cap, int ds, DevState *st);
 void launch_ingest_sell(hipStream_t s, const int32_t *rp32, const int32_t *col, const double *val, int32_t n,
                         const int64_t *off, int64_t cap, int allow_fill, void *scol, double *sv64, float *sv32,
                         DevState *st);

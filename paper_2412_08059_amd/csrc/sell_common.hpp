@@ -11,6 +11,13 @@
 
 namespace mpcg {
 
+// Row r of ingest's sample, one in each kDsSample-th of the rows (may be >= n).
+__device__ inline int64_t ds_sample_row(int r, int32_t n)
+{
+    const int64_t step = ((int64_t)n + kDsSample - 1) / kDsSample;
+    return (int64_t)r * step + (r * 2654435761u >> 7) % (uint64_t)step;
+}
+
 template <typename T> __device__ inline T fma_t(T a, T b, T c);
 template <> __device__ inline float fma_t<float>(float a, float b, float c) { return fmaf(a, b, c); }
 template <> __device__ inline double fma_t<double>(double a, double b, double c) { return fma(a, b, c); }
